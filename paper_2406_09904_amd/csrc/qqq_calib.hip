@@ -1,5 +1,5 @@
-// Offline (calibration-time) stage of QQQ on one layer: adaptive smoothing (Sec. 3.1, Eq. 1-2) and
-// Hessian-based quantisation compensation (Sec. 3.2, Eq. 3-4).  Entry points of include/qqq_calib.h.
+// Offline (calibration-time) stage of QQQ on one layer: adaptive smoothing (Sec. 3.1, Eq. 1-2) and the
+// Hessian of Sec. 3.2 (its compensation sweep is in qqq_compensate.hip).  Entry points of include/qqq_calib.h.
 //
 // Everything that decides an integer code is done in a fixed precision and operation order (stated at
 // each kernel) so that the result can be checked bit for bit; floating-point contraction is off in
@@ -222,144 +222,6 @@ __global__ __launch_bounds__(256) void hessian_kernel(const _Float16* x, int64_t
     }
 }
 
-// ------------------------------------------------------------------ Sec. 3.2: compensation
-
-// working copy: Hw = H with dead channels (H_ii == 0) set to 1 on the diagonal; W64 = fp64(W) with
-// dead channels zeroed; dsum accumulates the diagonal (after the dead-channel rule) for the damping
-__global__ __launch_bounds__(256) void gptq_prepare_kernel(const double* H, const _Float16* w, int64_t N, int64_t K,
-                                                           double* Hw, double* W64, double* dsum) {
-  const int64_t stride = (int64_t)gridDim.x * 256;
-  const int64_t tid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  for (int64_t e = tid; e < K * K; e += stride) {
-    const int64_t i = e / K, j = e - i * K;
-    double v = H[e];
-    if (i == j && v == 0.0) v = 1.0;
-    Hw[e] = v;
-  }
-  for (int64_t e = tid; e < N * K; e += stride) {
-    const int64_t k = e % K;
-    W64[e] = (H[k * K + k] == 0.0) ? 0.0 : (double)(float)w[e];
-  }
-  double part = 0.0;
-  for (int64_t i = tid; i < K; i += stride) {
-    const double d = H[i * K + i];
-    part += (d == 0.0) ? 1.0 : d;
-  }
-  if (part != 0.0) atomicAdd(dsum, part);
-}
-
-__global__ __launch_bounds__(256) void gptq_damp_kernel(double* Hw, int64_t K, const double* dsum, double percdamp) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < K) Hw[i * K + i] += percdamp * (dsum[0] / (double)K);
-}
-
-// In-place inverse of the damped Hessian (symmetric positive definite: no pivoting) by K
-// Gauss-Jordan sweeps.  Sweep p, first kernel: row[j] = A[p,j] / d (row[p] = 1 / d), col[r] = A[r,p]
-// (col[p] = 0), d = A[p,p]; second kernel: A[r,j] = (j == p ? 0 : A[r,j]) - col[r] * row[j] for r != p,
-// A[p,j] = row[j].
-__global__ __launch_bounds__(256) void gj_pivot_kernel(const double* A, int64_t K, int64_t p, double* row, double* col) {
-  const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (j >= K) return;
-  const double d = A[p * K + p];
-  row[j] = (j == p) ? 1.0 / d : A[p * K + j] / d;
-  col[j] = (j == p) ? 0.0 : A[j * K + p];
-}
-
-__global__ __launch_bounds__(256) void gj_update_kernel(double* A, int64_t K, int64_t p, const double* row,
-                                                        const double* col) {
-  const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t r = blockIdx.y;
-  if (j >= K) return;
-  if (r == p) {
-    A[r * K + j] = row[j];
-  } else {
-    const double base = (j == p) ? 0.0 : A[r * K + j];
-    A[r * K + j] = base - col[r] * row[j];
-  }
-}
-
-// Channel i of Eq. 4 for every output channel n: code, error, and the move of the channels still in F.
-//   q = clamp(rne(fp32(w / s)), -7, 7), s == 0 gives 0;  err = (w - q * s) / Hinv[i,i];
-//   W[n, j] -= err * Hinv[i, j] for j > i  (product rounded, then the difference rounded: no FMA)
-// grid: x = chunks of 256 trailing channels, y = output channel n
-__global__ __launch_bounds__(256) void gptq_column_kernel(double* W64, const double* Hinv, const uint16_t* s_w,
-                                                          int64_t N, int64_t K, int64_t i, uint32_t* w_nat) {
-  const int64_t n = blockIdx.y;
-  const double w = W64[n * K + i];
-  const double s = (double)half_bits_to_float(s_w[n]);
-  double q = 0.0;
-  if (s != 0.0) {
-    q = (double)__builtin_rintf((float)(w / s));
-    q = q > 7.0 ? 7.0 : (q < -7.0 ? -7.0 : q);
-  }
-  const double err = (w - q * s) / Hinv[i * K + i];
-  const int64_t j = i + 1 + (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (j < K) W64[n * K + j] = W64[n * K + j] - err * Hinv[i * K + j];
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    uint32_t* word = &w_nat[n * (K / 8) + i / 8];
-    const int sh = 4 * (int)(i % 8);
-    *word = (*word & ~(0xFu << sh)) | (((uint32_t)(int)q & 0xFu) << sh);
-  }
-}
-
-// channel i leaves F: Hinv[a,b] -= Hinv[a,i] * Hinv[i,b] / Hinv[i,i] for a, b > i (row i and column i
-// themselves are not written, so every workgroup reads the same old values)
-__global__ __launch_bounds__(256) void gptq_eliminate_kernel(double* Hinv, int64_t K, int64_t i) {
-  const int64_t b = i + 1 + (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t a = i + 1 + blockIdx.y;
-  if (b >= K || a >= K) return;
-  const double d = Hinv[i * K + i];
-  const double t = (Hinv[a * K + i] * Hinv[i * K + b]) / d;
-  Hinv[a * K + b] = Hinv[a * K + b] - t;
-}
-
-// Per-group weights (Sec. 3.3.2: groups of 128 input channels): when the sweep reaches a group's first
-// channel, the group's scale comes from the weights as they stand then, s = fp16(fp32(max |w|) / 7).
-// One thread per output channel.
-__global__ __launch_bounds__(256) void gptq_group_scale_kernel(const double* W64, int64_t N, int64_t K, int64_t i0,
-                                                               int group, uint16_t* s_row) {
-  const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (n >= N) return;
-  double amax = 0.0;
-  for (int k = 0; k < group; ++k) amax = fmax(amax, fabs(W64[n * K + i0 + k]));
-  s_row[n] = __builtin_bit_cast(uint16_t, (_Float16)((float)amax / 7.0f));
-}
-
-// After the sweep, what the front-end derives from codes and group scales (Sec. 3.3.2, Fig. 5 offline):
-// s_Wc[n] = fp16(max_k |code * s_Wg| / 127) with the product in fp32, s*_Wg = fp16(s_Wg / s_Wc) capped at
-// 18.203125 (0 where s_Wc is 0), integer form clamp(rne(s*_Wg), 1, 18).  One thread per output channel.
-__global__ __launch_bounds__(256) void gptq_group_finish_kernel(const uint32_t* w_nat, const uint16_t* s_wg, int64_t N,
-                                                                int64_t K, int group, uint16_t* s_wc, uint16_t* s_star,
-                                                                int8_t* s_int) {
-  const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (n >= N) return;
-  const int64_t G = K / group;
-  float dmax = 0.0f;
-  for (int64_t g = 0; g < G; ++g) {
-    int cmax = 0;
-    for (int j = 0; j < group / 8; ++j) {
-      const uint32_t word = w_nat[n * (K / 8) + g * (group / 8) + j];
-      for (int q = 0; q < 8; ++q) {
-        const int code = ((int)(word << (28 - 4 * q))) >> 28;  // sign-extended nibble
-        cmax = max(cmax, code < 0 ? -code : code);
-      }
-    }
-    dmax = fmaxf(dmax, (float)cmax * half_bits_to_float(s_wg[g * N + n]));
-  }
-  const uint16_t wcb = __builtin_bit_cast(uint16_t, (_Float16)(dmax / 127.0f));
-  s_wc[n] = wcb;
-  const float wc = half_bits_to_float(wcb);
-  for (int64_t g = 0; g < G; ++g) {
-    uint16_t star = 0;
-    if (wc != 0.0f) {
-      const _Float16 h = (_Float16)(half_bits_to_float(s_wg[g * N + n]) / wc);
-      star = __builtin_bit_cast(uint16_t, (float)h > 18.203125f ? (_Float16)18.203125f : h);
-    }
-    s_star[g * N + n] = star;
-    if (s_int) s_int[g * N + n] = (int8_t)fminf(fmaxf(__builtin_rintf(half_bits_to_float(star)), 1.0f), 18.0f);
-  }
-}
-
 static bool calib_shape_ok(int64_t M, int64_t N, int64_t K) {
   return M >= 1 && M <= 0x7FFFFFFF && N >= 16 && N % 16 == 0 && N <= 0x7FFFFFF0 && K >= 128 && K % 128 == 0 &&
          K <= 131072;
@@ -542,103 +404,6 @@ int qqq_hessian(const void* x_fp16, int64_t M, int64_t K, double* H, void* strea
   const unsigned t = (unsigned)((K + 63) / 64);
   hipLaunchKernelGGL(hessian_kernel, dim3(t, t), dim3(256), 0, (hipStream_t)stream, (const _Float16*)x_fp16, M, K, H);
   return check_launch("hessian");
-}
-
-size_t qqq_gptq_workspace_bytes(int64_t N, int64_t K) {
-  if (N < 1 || N > 65535 || K < 8 || K % 8 != 0 || K > 16384) return 0;
-  return align256c((size_t)K * K * 8) + align256c((size_t)N * K * 8) + 2 * align256c((size_t)K * 8) + 256;
-}
-
-// what both sweeps share: argument checks, the working copies, damping and the inverse Hessian
-struct GptqWork { double *Hinv, *W64; };
-static int gptq_begin(const char* who, const void* w_fp16, const double* H, int64_t N, int64_t K, double percdamp,
-                      const uint32_t* w_nat, void* workspace, size_t workspace_bytes, hipStream_t st, GptqWork* out) {
-  if (N < 1 || N > 65535 || K < 8 || K % 8 != 0 || K > 16384 || !(percdamp >= 0.0) || percdamp > 1e6)
-    return set_error(QQQ_ERR_SHAPE, "%s: unsupported N=%lld K=%lld percdamp=%g (need N <= 65535, K%%8==0, K <= 16384, "
-                     "percdamp >= 0)", who, (long long)N, (long long)K, percdamp);
-  if (!w_fp16 || !H || !w_nat || !workspace) return set_error(QQQ_ERR_NULL, "%s: null pointer argument", who);
-  if (!aligned16c(w_fp16) || !aligned16c(workspace) || (reinterpret_cast<uintptr_t>(H) & 7u) ||
-      (reinterpret_cast<uintptr_t>(w_nat) & 3u))
-    return set_error(QQQ_ERR_SHAPE, "%s: w_fp16 and workspace must be 16-byte, H 8-byte, w_nat 4-byte aligned", who);
-  const size_t need = qqq_gptq_workspace_bytes(N, K);
-  if (workspace_bytes < need)
-    return set_error(QQQ_ERR_WORKSPACE, "%s: workspace %zu bytes < %zu needed", who, workspace_bytes, need);
-  char* base = (char*)workspace;
-  double* Hinv = (double*)base;
-  double* W64 = (double*)(base + align256c((size_t)K * K * 8));
-  double* row = (double*)((char*)W64 + align256c((size_t)N * K * 8));
-  double* col = (double*)((char*)row + align256c((size_t)K * 8));
-  double* dsum = (double*)((char*)col + align256c((size_t)K * 8));
-  int rc;
-  if ((rc = fill_u32(dsum, 2, 0u, st)) != QQQ_OK) return rc;
-  hipLaunchKernelGGL(gptq_prepare_kernel, dim3(2048), dim3(256), 0, st, H, (const _Float16*)w_fp16, N, K, Hinv, W64, dsum);
-  if ((rc = check_launch("gptq_prepare")) != QQQ_OK) return rc;
-  const unsigned kb = (unsigned)((K + 255) / 256);
-  hipLaunchKernelGGL(gptq_damp_kernel, dim3(kb), dim3(256), 0, st, Hinv, K, dsum, percdamp);
-  if ((rc = check_launch("gptq_damp")) != QQQ_OK) return rc;
-  for (int64_t p = 0; p < K; ++p) {  // H^-1 in place
-    hipLaunchKernelGGL(gj_pivot_kernel, dim3(kb), dim3(256), 0, st, Hinv, K, p, row, col);
-    hipLaunchKernelGGL(gj_update_kernel, dim3(kb, (unsigned)K), dim3(256), 0, st, Hinv, K, p, row, col);
-  }
-  if ((rc = check_launch("gptq inverse")) != QQQ_OK) return rc;
-  out->Hinv = Hinv;
-  out->W64 = W64;
-  return QQQ_OK;
-}
-
-// channel i of Eq. 4 with the scales at `scales` [N], then channel i leaves F
-static void gptq_step(const GptqWork& wk, const uint16_t* scales, int64_t N, int64_t K, int64_t i, uint32_t* w_nat,
-                      hipStream_t st) {
-  const int64_t trail = K - i - 1;
-  const unsigned tb = (unsigned)(trail > 0 ? (trail + 255) / 256 : 1);
-  hipLaunchKernelGGL(gptq_column_kernel, dim3(tb, (unsigned)N), dim3(256), 0, st, wk.W64, wk.Hinv, scales, N, K, i,
-                     w_nat);
-  if (trail > 0)
-    hipLaunchKernelGGL(gptq_eliminate_kernel, dim3(tb, (unsigned)trail), dim3(256), 0, st, wk.Hinv, K, i);
-}
-
-int qqq_gptq_quantize_w4_perchannel(const void* w_fp16, const double* H, int64_t N, int64_t K, double percdamp,
-                                    uint32_t* w_nat, void* s_w_fp16, void* workspace, size_t workspace_bytes,
-                                    void* stream) {
-  if (!s_w_fp16) return set_error(QQQ_ERR_NULL, "gptq: null pointer argument");
-  if (reinterpret_cast<uintptr_t>(s_w_fp16) & 1u) return set_error(QQQ_ERR_SHAPE, "gptq: s_w must be 2-byte aligned");
-  hipStream_t st = (hipStream_t)stream;
-  GptqWork wk;
-  int rc = gptq_begin("gptq", w_fp16, H, N, K, percdamp, w_nat, workspace, workspace_bytes, st, &wk);
-  if (rc != QQQ_OK) return rc;
-  // scales from the original weights (and round-to-nearest codes, overwritten channel by channel below)
-  rc = launch_quant_weight(w_fp16, N, K, K, false, w_nat, (uint16_t*)s_w_fp16, nullptr, nullptr, nullptr, st);
-  if (rc != QQQ_OK) return rc;
-  for (int64_t i = 0; i < K; ++i) gptq_step(wk, (const uint16_t*)s_w_fp16, N, K, i, w_nat, st);  // Eq. 4, channel by channel
-  return check_launch("gptq column");
-}
-
-int qqq_gptq_quantize_w4_pergroup(const void* w_fp16, const double* H, int64_t N, int64_t K, int group, double percdamp,
-                                  uint32_t* w_nat, void* s_wg_fp16, void* s_star_fp16, int8_t* s_int, void* s_wc_fp16,
-                                  void* workspace, size_t workspace_bytes, void* stream) {
-  if (group != QQQ_GROUP) return set_error(QQQ_ERR_SHAPE, "gptq_pergroup: group must be 128, got %d", group);
-  if (K % QQQ_GROUP != 0) return set_error(QQQ_ERR_SHAPE, "gptq_pergroup: K=%lld must be a multiple of 128", (long long)K);
-  if (!s_wg_fp16 || !s_star_fp16 || !s_wc_fp16) return set_error(QQQ_ERR_NULL, "gptq_pergroup: null pointer argument");
-  if ((reinterpret_cast<uintptr_t>(s_wg_fp16) | reinterpret_cast<uintptr_t>(s_star_fp16) |
-       reinterpret_cast<uintptr_t>(s_wc_fp16)) & 1u)
-    return set_error(QQQ_ERR_SHAPE, "gptq_pergroup: scale tables must be 2-byte aligned");
-  hipStream_t st = (hipStream_t)stream;
-  GptqWork wk;
-  int rc = gptq_begin("gptq_pergroup", w_fp16, H, N, K, percdamp, w_nat, workspace, workspace_bytes, st, &wk);
-  if (rc != QQQ_OK) return rc;
-  if ((rc = fill_u32(w_nat, (size_t)N * (size_t)(K / 8), 0u, st)) != QQQ_OK) return rc;
-  uint16_t* s_wg = (uint16_t*)s_wg_fp16;
-  const unsigned nb = (unsigned)((N + 255) / 256);
-  for (int64_t i = 0; i < K; ++i) {
-    uint16_t* s_row = s_wg + (i / QQQ_GROUP) * N;
-    if (i % QQQ_GROUP == 0)  // the sweep enters a group: its scale from the weights as they stand now
-      hipLaunchKernelGGL(gptq_group_scale_kernel, dim3(nb), dim3(256), 0, st, wk.W64, N, K, i, QQQ_GROUP, s_row);
-    gptq_step(wk, s_row, N, K, i, w_nat, st);
-  }
-  if ((rc = check_launch("gptq_pergroup column")) != QQQ_OK) return rc;
-  hipLaunchKernelGGL(gptq_group_finish_kernel, dim3(nb), dim3(256), 0, st, w_nat, s_wg, N, K, QQQ_GROUP,
-                     (uint16_t*)s_wc_fp16, (uint16_t*)s_star_fp16, s_int);
-  return check_launch("gptq_pergroup finish");
 }
 
 }  // extern "C"

@@ -1,0 +1,525 @@
+// Hessian-based quantisation compensation (Sec. 3.2, Eq. 3-4) on one layer: entry points
+// qqq_gptq_quantize_w4_perchannel / _pergroup of include/qqq_calib.h.
+//
+// Eq. 4 needs, for each channel i, row i of the inverse Hessian of the channels not yet quantised.  Those
+// rows never have to be formed.  With H = R D R^T, R unit upper triangular and D diagonal (the Cholesky
+// factorisation taken from the last channel to the first), row i of [H_F^-1] over its diagonal entry
+// is row i of R^-1, so the running weight of channel j obeys
+//     w_j = W_j + sum_{i < j} (W_i - Q_i) R[i,j]
+// when its turn comes, W the original weights and Q the dequantised codes: the moves of Eq. 4, summed.  One factorisation of
+// K^3/3 multiply-adds and a triangular product of N K^2 / 2 replace an explicit inverse and a rank-1
+// update of both matrices per channel, and W_i - Q_i is exact in fp64 (fp16 minus int4 x fp16).
+//
+// Both parts are blocked so that almost all of their arithmetic is fp64 MFMA (f64_update_kernel):
+//   factorisation  per 64 channels, from the last: factor_panel_kernel, then the update of the channels before
+//   sweep          per 128 channels, from the first: sweep_kernel, then the update of the channels after
+// What is left serial is one dependent step per channel, in registers.
+// Bound: K = N = 4096 holds 2.3e10 + 6.9e10 fp64 operations, 1.3 ms at the 70 TFLOP/s a large fp64 product
+// reaches here.  Measured, K = N = 4096: 8.9 ms (an inverse by K rank-1 sweeps and a rank-1 update of both matrices
+// per channel: 360 ms); K = 2048, N = 5632 with group scales: 4.1 ms (81 ms).
+#include "qqq_calib.h"
+#include "qqq_internal.h"
+
+namespace qqq {
+
+namespace {
+
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+constexpr int kFB = 64;    // channels per factorisation block
+constexpr int kSB = 128;   // channels per sweep block (= a group of the per-group quantiser)
+static_assert(kSB == QQQ_GROUP, "a sweep block is one group");
+
+bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
+size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
+
+int check_launch(const char* what) {
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return set_error(QQQ_ERR_HIP, "%s launch: %s", what, hipGetErrorString(e));
+  return QQQ_OK;
+}
+
+// one 64-bit value of lane SRC of every four lanes, in all four (no LDS, no scalar registers)
+template <int SRC>
+__device__ __forceinline__ double quad_broadcast(double x) {
+  constexpr int sel = SRC * 0x55;  // quad_perm [SRC, SRC, SRC, SRC]
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, sel, 0xF, 0xF, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), sel, 0xF, 0xF, true);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+template <int XOR>  // value of lane ^ XOR within four lanes
+__device__ __forceinline__ uint32_t quad_swap(uint32_t x) {
+  constexpr int sel = XOR == 1 ? 0xB1 : 0x4E;
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, sel, 0xF, 0xF, true);
+}
+
+// keep[i] = 0 for a channel that never fired (H_ii == 0: its weight counts as 0), else 1;
+// damp[0] = percdamp * mean of the diagonal, a never-firing channel counting 1
+__global__ __launch_bounds__(1024) void diagonal_kernel(const double* H, int64_t K, double percdamp, double* keep,
+                                                        double* damp) {
+  __shared__ double part[1024];
+  double sum = 0.0;
+  for (int64_t i = threadIdx.x; i < K; i += 1024) {
+    const double d = H[i * K + i];
+    keep[i] = d == 0.0 ? 0.0 : 1.0;
+    sum += d == 0.0 ? 1.0 : d;
+  }
+  part[threadIdx.x] = sum;
+  __syncthreads();
+  for (int w = 512; w > 0; w >>= 1) {
+    if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) damp[0] = percdamp * (part[0] / (double)K);
+}
+
+// Working copies: the upper triangle of the damped Hessian (the factorisation reads nothing below the
+// diagonal) and the running weights in fp64.  K % 8 == 0.  grid.y: rows of H, then rows of W.
+__global__ __launch_bounds__(256) void prepare_kernel(const double* H, const _Float16* w, const double* keep,
+                                                      const double* damp, int64_t N, int64_t K, double* A, double* W64) {
+  for (int64_t r = blockIdx.x; r < K + N; r += gridDim.x) {
+    if (r < K) {
+      for (int64_t j = (r & ~(int64_t)1) + 2 * threadIdx.x; j < K; j += 512) {
+        const int64_t at = r * K + j;
+        double h0 = H[at], h1 = H[at + 1];  // (H is 8-byte aligned)
+        if (j == r) h0 = (h0 == 0.0 ? 1.0 : h0) + damp[0];
+        if (j + 1 == r) h1 = (h1 == 0.0 ? 1.0 : h1) + damp[0];
+        *reinterpret_cast<double2*>(A + at) = make_double2(h0, h1);
+      }
+    } else {
+      const int64_t at0 = (r - K) * K;
+      for (int64_t k = 2 * threadIdx.x; k < K; k += 512) {
+        const uint32_t two = *reinterpret_cast<const uint32_t*>(w + at0 + k);
+        const double w0 = keep[k] != 0.0 ? (double)half_bits_to_float(two & 0xFFFFu) : 0.0;
+        const double w1 = keep[k + 1] != 0.0 ? (double)half_bits_to_float(two >> 16) : 0.0;
+        *reinterpret_cast<double2*>(W64 + at0 + k) = make_double2(w0, w1);
+      }
+    }
+  }
+}
+
+// C += (or -=) A B in fp64: C [M,N], A [M,kd], B [kd,N], all row-major and 16-byte aligned, N and kd even.
+// 64 x 64 tile per workgroup, a wave per 32 x 32 quarter, 32 of kd at a time through LDS with the next
+// 32 already requested.  v_mfma_f64_16x16x4_f64 (64 clocks): lane l holds row (column) l % 16 and k = l / 16
+// of the operands, register v of the result is row 4 v + l / 16, column l % 16.  Row strides of the LDS tiles
+// (34 and 80 doubles) put the 32 lanes of half a wave on all 64 banks.  The matrix pipe is the limit: each
+// fragment read feeds two MFMAs.
+// UPPER: only the tiles that reach the diagonal or lie above it (a symmetric C kept as its upper triangle).
+template <bool UPPER, bool SUB>
+__global__ __launch_bounds__(256) void f64_update_kernel(const double* A, int64_t lda, const double* B, int64_t ldb,
+                                                         double* C, int64_t ldc, int M, int N, int kd) {
+  constexpr int kAs = 34, kBs = 80;
+  __shared__ __attribute__((aligned(16))) double sa[64 * kAs];
+  __shared__ __attribute__((aligned(16))) double sb[32 * kBs];
+  const int tn = blockIdx.x, tm = blockIdx.y;
+  if (UPPER && tn < tm) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int m0 = tm * 64, n0 = tn * 64;
+  const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
+  const int l16 = lane & 15, q = lane >> 4;
+
+  double2 ra[4], rb[4];
+  const double2 zero = make_double2(0.0, 0.0);
+  auto fetch = [&](int k0) {  // out-of-range elements feed zeros
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int e = tid + 256 * j;
+      const int row = e >> 4, ka = k0 + 2 * (e & 15);
+      ra[j] = (m0 + row < M && ka < kd) ? *reinterpret_cast<const double2*>(A + (int64_t)(m0 + row) * lda + ka) : zero;
+      const int k = k0 + (e >> 5), col = n0 + 2 * (e & 31);
+      rb[j] = (k < kd && col < N) ? *reinterpret_cast<const double2*>(B + (int64_t)k * ldb + col) : zero;
+    }
+  };
+  fetch(0);
+  v4d acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int row = m0 + wr + 16 * i + 4 * v + q, col = n0 + wc + 16 * j + l16;
+        acc[i][j][v] = (row < M && col < N) ? C[(int64_t)row * ldc + col] : 0.0;
+      }
+  for (int k0 = 0; k0 < kd; k0 += 32) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int e = tid + 256 * j;
+      const double2 a = SUB ? make_double2(-ra[j].x, -ra[j].y) : ra[j];
+      *reinterpret_cast<double2*>(&sa[(e >> 4) * kAs + 2 * (e & 15)]) = a;
+      *reinterpret_cast<double2*>(&sb[(e >> 5) * kBs + 2 * (e & 31)]) = rb[j];
+    }
+    __syncthreads();
+    if (k0 + 32 < kd) fetch(k0 + 32);
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      double a[2], b[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        a[i] = sa[(wr + 16 * i + l16) * kAs + 4 * s + q];
+        b[i] = sb[(4 * s + q) * kBs + wc + 16 * i + l16];
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int row = m0 + wr + 16 * i + 4 * v + q, col = n0 + wc + 16 * j + l16;
+        if (row < M && col < N) C[(int64_t)row * ldc + col] = acc[i][j][v];
+      }
+}
+
+// One block [c0, c0 + 64) of H = R D R^T, the channels after it already eliminated from A.
+// Every workgroup factors the 64 x 64 diagonal block for itself (64 dependent steps: column j's pivot
+// d_j, R[i,j] = A[i,j] / d_j for i < j, A[i,k] -= R[i,j] A[k,j] for k < j) and then solves for its own 64 of
+// the c0 rows above: y_j = a_j - sum_{k > j} y_k R[j,k], x_j = y_j / d_j, i.e. R = x and R D = y there.
+// Written: x in place (A[row, c0 + j]) and y transposed into the unused lower triangle (A[c0 + j, row]),
+// which is the row-major operand the update of the rows above wants; the diagonal block's R goes
+// transposed below the diagonal (its upper half is still being read by other workgroups).
+// Lane = row of the block, wave w = its columns w mod 4, so a step needs one barrier: the column's owner
+// publishes it, everyone divides and updates.
+__global__ __launch_bounds__(256) void factor_panel_kernel(double* A, int64_t K, int c0) {
+  __shared__ double colbuf[2][64];
+  __shared__ double rt[64][66];  // rt[j][i] = R[c0 + i, c0 + j] for i < j, else 0
+  __shared__ double rcp[64];     // 1 / d_j
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int nb = min(64, (int)K - c0);
+  // ---- the rows this workgroup solves: four lanes per row, lane's columns 4 r + (tid & 3)
+  const int64_t row = (int64_t)blockIdx.x * 64 + (tid >> 2);
+  const int ql = tid & 3;
+  const bool live = row < c0;
+  double y[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) y[r] = (live && 4 * r + ql < nb) ? A[row * K + c0 + 4 * r + ql] : 0.0;
+
+  {  // ---- the diagonal block; channels past K are identity
+    double a[16];  // element (lane, 4 r + wave), valid for lane <= column
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int j = 4 * r + wave;
+      a[r] = (lane < nb && j < nb && lane <= j) ? A[(int64_t)(c0 + lane) * K + c0 + j] : (lane == j ? 1.0 : 0.0);
+    }
+#pragma unroll
+    for (int j = 63; j >= 0; --j) {
+      double* col = colbuf[j & 1];
+      if (wave == (j & 3)) col[lane] = a[j >> 2];
+      __syncthreads();
+      const double rd = 1.0 / col[j];
+      const double x = lane < j ? col[lane] * rd : 0.0;
+      if (wave == (j & 3)) {
+        rt[j][lane] = x;
+        if (lane == 0) rcp[j] = rd;
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (4 * r < j) {  // (columns at or past j, and rows at or past j, are finished or zero: x is 0 there)
+          const int k = 4 * r + wave;
+          const double m = k < j ? col[k] : 0.0;
+          a[r] = __builtin_fma(-x, m, a[r]);
+        }
+    }
+  }
+  __syncthreads();
+  if (blockIdx.x == 0) {
+    for (int e = tid; e < 64 * 64; e += 256) {
+      const int j = e >> 6, i = e & 63;
+      if (i < j && j < nb) A[(int64_t)(c0 + j) * K + c0 + i] = rt[j][i];
+    }
+  }
+  // ---- the solve, column by column from the last; rt is zero at and past the diagonal
+#define QQQ_SOLVE(J, O)                                                                      \
+  {                                                                                          \
+    const double yj = quad_broadcast<O>(y[(J) >> 2]);                                        \
+    _Pragma("unroll") for (int r = 0; r <= ((J) >> 2); ++r)                                  \
+        y[r] = __builtin_fma(-yj, rt[J][4 * r + ql], y[r]);                                  \
+  }
+#pragma unroll
+  for (int r4 = 15; r4 >= 0; --r4) {
+    QQQ_SOLVE(4 * r4 + 3, 3)
+    QQQ_SOLVE(4 * r4 + 2, 2)
+    QQQ_SOLVE(4 * r4 + 1, 1)
+    QQQ_SOLVE(4 * r4 + 0, 0)
+  }
+#undef QQQ_SOLVE
+  if (!live) return;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int j = 4 * r + ql;
+    if (j < nb) {
+      A[row * K + c0 + j] = y[r] * rcp[j];
+      A[(int64_t)(c0 + j) * K + row] = y[r];
+    }
+  }
+}
+
+// Channels [c0, c0 + 128) of every output channel, one after the other: code of the running weight, then the
+// move of the later channels of the block,
+//   q = clamp(rne(fp32(w / s)), -7, 7), s == 0 gives 0;  w_j += (W_i - q s) R[i,j] for j > i.
+// Four lanes per output channel, lane's channels 4 r + (lane % 4) in registers; a step is the quotient, its
+// rounding and one multiply-add per later channel the lane holds, the broadcast of W_i - q s inside the
+// four lanes being a data-parallel move.  R's block sits in LDS as rows of what a step still needs (row i from
+// channel 4 (i / 4) on, zeros up to the diagonal).  Bound by the chain of dependent fp64 operations
+// (about 12 per channel), so workgroups are kept at 32 output channels to spread them over the chip.
+// The quotient: w * (1/s) corrected by its exact remainder, which is the correctly rounded w / s.
+// GROUP: the scale is taken here, s = fp16(fp32(max |w|) / 7) over the block as Eq. 4 leaves its weights when the
+// sweep enters it.  What has been added up so far for channel j, P_j = sum over i < c0 of (W_i - Q_i) R[i,j], is
+// its move once the block's earlier channels have had theirs; with none of them quantised yet, the move z of
+// all channels solves z R = P over the block's triangle (z = P for its first channel).
+// W64's block is overwritten with W_i - q s, the left operand of the update of the channels after.
+template <bool GROUP>
+__global__ __launch_bounds__(128) void sweep_kernel(const _Float16* w, const double* A, const double* keep, int64_t N,
+                                                    int64_t K, int c0, uint16_t* scales, double* W64, uint32_t* w_nat) {
+  constexpr int kRows = 16 * (32 * 33 / 2);  // doubles: the sum over i of 128 - 4 (i / 4)
+  __shared__ __attribute__((aligned(16))) double rl[kRows];
+  const int tid = threadIdx.x, ql = tid & 3;
+  const int nb = min(kSB, (int)K - c0);
+  const int64_t row = (int64_t)blockIdx.x * 32 + (tid >> 2);
+  const int64_t n = row < N ? row : N - 1;  // (rows past N repeat the last one and store nothing)
+  const int64_t at = n * K + c0 + ql;
+
+  double acc[32];
+  float wo[32];
+#pragma unroll
+  for (int r = 0; r < 32; ++r) {
+    const bool in = 4 * r + ql < nb;
+    acc[r] = in ? W64[at + 4 * r] : 0.0;
+    wo[r] = (in && keep[c0 + 4 * r + ql] != 0.0) ? (float)w[at + 4 * r] : 0.0f;
+  }
+  // R: strictly upper part; where i and j share a factorisation block it lies transposed below the diagonal
+  for (int e = tid; e < 32 * 4 * 128; e += 128) {
+    const int i = e >> 7, j = e & 127;
+    const int r4 = i >> 2;
+    if (j < 4 * r4) continue;
+    double v = 0.0;
+    if (j > i && j < nb)
+      v = (i / kFB == j / kFB) ? A[(int64_t)(c0 + j) * K + c0 + i] : A[(int64_t)(c0 + i) * K + c0 + j];
+    const int base = 16 * (32 * r4 - r4 * (r4 - 1) / 2) + (i & 3) * (128 - 4 * r4);
+    rl[base + j - 4 * r4] = v;
+  }
+  __syncthreads();
+  // row i = 4 r + O of R from channel 4 r on, this lane's channels
+  auto r_row = [&](int r, int o) { return rl + 16 * (32 * r - r * (r - 1) / 2) + o * (128 - 4 * r) + ql; };
+
+  double s;
+  if constexpr (GROUP) {
+    double z[32];
+#pragma unroll
+    for (int r = 0; r < 32; ++r) z[r] = acc[r] - (double)wo[r];
+#define QQQ_SOLVE(O)                                                                                       \
+  {                                                                                                        \
+    const double d = quad_broadcast<O>(z[r]);                                                              \
+    const double* ri = r_row(r, O);                                                                        \
+    _Pragma("unroll") for (int k = r; k < 32; ++k) z[k] = __builtin_fma(-d, ri[4 * (k - r)], z[k]);        \
+  }
+#pragma unroll
+    for (int r = 0; r < 32; ++r) {
+      QQQ_SOLVE(0)
+      QQQ_SOLVE(1)
+      QQQ_SOLVE(2)
+      QQQ_SOLVE(3)
+    }
+#undef QQQ_SOLVE
+    double amax = 0.0;
+#pragma unroll
+    for (int r = 0; r < 32; ++r) amax = fmax(amax, fabs((double)wo[r] + z[r]));
+    float m = (float)amax;  // rounding is monotonic: the maximum may be rounded before it is complete
+    m = fmaxf(m, __builtin_bit_cast(float, quad_swap<1>(__builtin_bit_cast(uint32_t, m))));
+    m = fmaxf(m, __builtin_bit_cast(float, quad_swap<2>(__builtin_bit_cast(uint32_t, m))));
+    const uint16_t sb = __builtin_bit_cast(uint16_t, (_Float16)(m / 7.0f));
+    if (ql == 0 && row < N) scales[n] = sb;
+    s = (double)half_bits_to_float(sb);
+  } else {
+    s = (double)half_bits_to_float(scales[n]);
+  }
+  const double rs = s == 0.0 ? 0.0 : 1.0 / s;  // 0 makes every quotient, and so every code, 0
+
+  uint32_t words[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) words[r] = 0;
+#define QQQ_STEP(O)                                                                                        \
+  {                                                                                                        \
+    const double v = acc[r];                                                                               \
+    const double q0 = v * rs;                                                                              \
+    const double quo = __builtin_fma(__builtin_fma(-q0, s, v), rs, q0);                                    \
+    const float code = __builtin_amdgcn_fmed3f(__builtin_rintf((float)quo), -7.0f, 7.0f);                  \
+    const double diff = __builtin_fma(-(double)code, s, (double)wo[r]);                                    \
+    const double d = quad_broadcast<O>(diff);                                                              \
+    if (ql == O) {                                                                                         \
+      own_code = (int)code;                                                                                \
+      acc[r] = diff;                                                                                       \
+    }                                                                                                      \
+    const double* ri = r_row(r, O);                                                                        \
+    _Pragma("unroll") for (int k = r; k < 32; ++k) acc[k] = __builtin_fma(d, ri[4 * (k - r)], acc[k]);     \
+  }
+#pragma unroll
+  for (int r = 0; r < 32; ++r) {
+    int own_code = 0;
+    QQQ_STEP(0)
+    QQQ_STEP(1)
+    QQQ_STEP(2)
+    QQQ_STEP(3)
+    words[r >> 1] |= ((uint32_t)own_code & 0xFu) << (4 * ql + 16 * (r & 1));
+  }
+#undef QQQ_STEP
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {  // every lane's nibbles of every word
+    words[r] |= quad_swap<1>(words[r]);
+    words[r] |= quad_swap<2>(words[r]);
+  }
+  if (row >= N) return;
+#pragma unroll
+  for (int r = 0; r < 16; ++r)
+    if ((r >> 2) == ql && 8 * r < nb) w_nat[n * (K / 8) + c0 / 8 + r] = words[r];
+  if (c0 + kSB < K) {
+#pragma unroll
+    for (int r = 0; r < 32; ++r) W64[at + 4 * r] = acc[r];
+  }
+}
+
+// After a per-group sweep, what the front-end derives from codes and group scales (Sec. 3.3.2, Fig. 5 offline):
+// s_Wc[n] = fp16(max_k |code * s_Wg| / 127) with the product in fp32, s*_Wg = fp16(s_Wg / s_Wc) capped at
+// 18.203125 (0 where s_Wc is 0), integer form clamp(rne(s*_Wg), 1, 18).  One thread per output channel.
+__global__ __launch_bounds__(256) void group_finish_kernel(const uint32_t* w_nat, const uint16_t* s_wg, int64_t N,
+                                                           int64_t K, int group, uint16_t* s_wc, uint16_t* s_star,
+                                                           int8_t* s_int) {
+  const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (n >= N) return;
+  const int64_t G = K / group;
+  float dmax = 0.0f;
+  for (int64_t g = 0; g < G; ++g) {
+    int cmax = 0;
+    for (int j = 0; j < group / 8; ++j) {
+      const uint32_t word = w_nat[n * (K / 8) + g * (group / 8) + j];
+      for (int q = 0; q < 8; ++q) {
+        const int code = ((int)(word << (28 - 4 * q))) >> 28;  // sign-extended nibble
+        cmax = max(cmax, code < 0 ? -code : code);
+      }
+    }
+    dmax = fmaxf(dmax, (float)cmax * half_bits_to_float(s_wg[g * N + n]));
+  }
+  const uint16_t wcb = __builtin_bit_cast(uint16_t, (_Float16)(dmax / 127.0f));
+  s_wc[n] = wcb;
+  const float wc = half_bits_to_float(wcb);
+  for (int64_t g = 0; g < G; ++g) {
+    uint16_t star = 0;
+    if (wc != 0.0f) {
+      const _Float16 h = (_Float16)(half_bits_to_float(s_wg[g * N + n]) / wc);
+      star = __builtin_bit_cast(uint16_t, (float)h > 18.203125f ? (_Float16)18.203125f : h);
+    }
+    s_star[g * N + n] = star;
+    if (s_int) s_int[g * N + n] = (int8_t)fminf(fmaxf(__builtin_rintf(half_bits_to_float(star)), 1.0f), 18.0f);
+  }
+}
+
+// what both sweeps share: argument checks, the working copies, damping and the factorisation
+struct Work { double *A, *W64, *keep; };
+int begin(const char* who, const void* w_fp16, const double* H, int64_t N, int64_t K, double percdamp,
+          const uint32_t* w_nat, void* workspace, size_t workspace_bytes, hipStream_t st, Work* out) {
+  if (N < 1 || N > 65535 || K < 8 || K % 8 != 0 || K > 16384 || !(percdamp >= 0.0) || percdamp > 1e6)
+    return set_error(QQQ_ERR_SHAPE, "%s: unsupported N=%lld K=%lld percdamp=%g (need N <= 65535, K%%8==0, K <= 16384, "
+                     "percdamp >= 0)", who, (long long)N, (long long)K, percdamp);
+  if (!w_fp16 || !H || !w_nat || !workspace) return set_error(QQQ_ERR_NULL, "%s: null pointer argument", who);
+  if (!aligned16(w_fp16) || !aligned16(workspace) || (reinterpret_cast<uintptr_t>(H) & 7u) ||
+      (reinterpret_cast<uintptr_t>(w_nat) & 3u))
+    return set_error(QQQ_ERR_SHAPE, "%s: w_fp16 and workspace must be 16-byte, H 8-byte, w_nat 4-byte aligned", who);
+  const size_t need = qqq_gptq_workspace_bytes(N, K);
+  if (workspace_bytes < need)
+    return set_error(QQQ_ERR_WORKSPACE, "%s: workspace %zu bytes < %zu needed", who, workspace_bytes, need);
+  char* base = (char*)workspace;
+  double* A = (double*)base;
+  double* W64 = (double*)(base + align256((size_t)K * K * 8));
+  double* keep = (double*)((char*)W64 + align256((size_t)N * K * 8));
+  double* damp = (double*)((char*)keep + align256((size_t)K * 8));
+  int rc;
+  hipLaunchKernelGGL(diagonal_kernel, dim3(1), dim3(1024), 0, st, H, K, percdamp, keep, damp);
+  if ((rc = check_launch("gptq diagonal")) != QQQ_OK) return rc;
+  hipLaunchKernelGGL(prepare_kernel, dim3((unsigned)(K + N < 4096 ? K + N : 4096)), dim3(256), 0, st, H,
+                     (const _Float16*)w_fp16, keep, damp, N, K, A, W64);
+  if ((rc = check_launch("gptq prepare")) != QQQ_OK) return rc;
+  for (int64_t c0 = (K - 1) / kFB * kFB; c0 >= 0; c0 -= kFB) {
+    const unsigned tiles = (unsigned)(c0 / kFB);
+    hipLaunchKernelGGL(factor_panel_kernel, dim3(tiles ? tiles : 1), dim3(256), 0, st, A, K, (int)c0);
+    if (tiles)
+      hipLaunchKernelGGL((f64_update_kernel<true, true>), dim3(tiles, tiles), dim3(256), 0, st, A + c0, K, A + c0 * K,
+                         K, A, K, (int)c0, (int)c0, (int)(K - c0 < kFB ? K - c0 : kFB));
+  }
+  if ((rc = check_launch("gptq factorisation")) != QQQ_OK) return rc;
+  out->A = A;
+  out->W64 = W64;
+  out->keep = keep;
+  return QQQ_OK;
+}
+
+// Eq. 4 over all channels; scales: [N], or [K/128, N] (written) with group scales
+template <bool GROUP>
+int sweep(const Work& wk, const void* w_fp16, int64_t N, int64_t K, uint16_t* scales, uint32_t* w_nat, hipStream_t st) {
+  for (int64_t c0 = 0; c0 < K; c0 += kSB) {
+    hipLaunchKernelGGL((sweep_kernel<GROUP>), dim3((unsigned)((N + 31) / 32)), dim3(128), 0, st, (const _Float16*)w_fp16,
+                       wk.A, wk.keep, N, K, (int)c0, GROUP ? scales + c0 / kSB * N : scales, wk.W64, w_nat);
+    const int64_t rest = K - c0 - kSB;
+    if (rest > 0)
+      hipLaunchKernelGGL((f64_update_kernel<false, false>), dim3((unsigned)((rest + 63) / 64), (unsigned)((N + 63) / 64)),
+                         dim3(256), 0, st, wk.W64 + c0, K, wk.A + c0 * K + c0 + kSB, K, wk.W64 + c0 + kSB, K, (int)N,
+                         (int)rest, kSB);
+  }
+  return check_launch("gptq sweep");
+}
+
+}  // namespace
+
+}  // namespace qqq
+
+using namespace qqq;
+
+extern "C" {
+
+size_t qqq_gptq_workspace_bytes(int64_t N, int64_t K) {
+  if (N < 1 || N > 65535 || K < 8 || K % 8 != 0 || K > 16384) return 0;
+  return align256((size_t)K * K * 8) + align256((size_t)N * K * 8) + 2 * align256((size_t)K * 8) + 256;
+}
+
+int qqq_gptq_quantize_w4_perchannel(const void* w_fp16, const double* H, int64_t N, int64_t K, double percdamp,
+                                    uint32_t* w_nat, void* s_w_fp16, void* workspace, size_t workspace_bytes,
+                                    void* stream) {
+  if (!s_w_fp16) return set_error(QQQ_ERR_NULL, "gptq: null pointer argument");
+  if (reinterpret_cast<uintptr_t>(s_w_fp16) & 1u) return set_error(QQQ_ERR_SHAPE, "gptq: s_w must be 2-byte aligned");
+  hipStream_t st = (hipStream_t)stream;
+  Work wk;
+  int rc = begin("gptq", w_fp16, H, N, K, percdamp, w_nat, workspace, workspace_bytes, st, &wk);
+  if (rc != QQQ_OK) return rc;
+  // scales from the original weights (and round-to-nearest codes, overwritten block by block below)
+  rc = launch_quant_weight(w_fp16, N, K, K, false, w_nat, (uint16_t*)s_w_fp16, nullptr, nullptr, nullptr, st);
+  if (rc != QQQ_OK) return rc;
+  return sweep<false>(wk, w_fp16, N, K, (uint16_t*)s_w_fp16, w_nat, st);
+}
+
+int qqq_gptq_quantize_w4_pergroup(const void* w_fp16, const double* H, int64_t N, int64_t K, int group, double percdamp,
+                                  uint32_t* w_nat, void* s_wg_fp16, void* s_star_fp16, int8_t* s_int, void* s_wc_fp16,
+                                  void* workspace, size_t workspace_bytes, void* stream) {
+  if (group != QQQ_GROUP) return set_error(QQQ_ERR_SHAPE, "gptq_pergroup: group must be 128, got %d", group);
+  if (K % QQQ_GROUP != 0) return set_error(QQQ_ERR_SHAPE, "gptq_pergroup: K=%lld must be a multiple of 128", (long long)K);
+  if (!s_wg_fp16 || !s_star_fp16 || !s_wc_fp16) return set_error(QQQ_ERR_NULL, "gptq_pergroup: null pointer argument");
+  if ((reinterpret_cast<uintptr_t>(s_wg_fp16) | reinterpret_cast<uintptr_t>(s_star_fp16) |
+       reinterpret_cast<uintptr_t>(s_wc_fp16)) & 1u)
+    return set_error(QQQ_ERR_SHAPE, "gptq_pergroup: scale tables must be 2-byte aligned");
+  hipStream_t st = (hipStream_t)stream;
+  Work wk;
+  int rc = begin("gptq_pergroup", w_fp16, H, N, K, percdamp, w_nat, workspace, workspace_bytes, st, &wk);
+  if (rc != QQQ_OK) return rc;
+  uint16_t* s_wg = (uint16_t*)s_wg_fp16;
+  if ((rc = sweep<true>(wk, w_fp16, N, K, s_wg, w_nat, st)) != QQQ_OK) return rc;
+  hipLaunchKernelGGL(group_finish_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st, w_nat, s_wg, N, K,
+                     QQQ_GROUP, (uint16_t*)s_wc_fp16, (uint16_t*)s_star_fp16, s_int);
+  return check_launch("gptq_pergroup finish");
+}
+
+}  // extern "C"
