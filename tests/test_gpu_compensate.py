@@ -40,6 +40,18 @@ def test_per_channel_sweep_at_block_edges(K, N):
     assert np.array_equal(orc.w8_perchannel(w_nat.cpu().numpy().view(np.uint32), K), codes)
 
 
+@pytest.mark.parametrize("M,K,shift", [(1, 1, 0), (3, 31, 0), (65, 72, 0), (64, 72, 4), (33, 2056, 0), (31, 2051, 0)])
+def test_hessian_tiles(M, K, shift):
+    """32- and 64-wide tiles, whole and element-wise rows (odd K, or a base that is not 16-byte aligned), ragged edges.
+    Every product of two fp16 is exact in fp64 and these sums stay below 53 bits: equal bit for bit, both halves."""
+    x = synth.activations_fp16(M, K, 600 + M + K, "normal", 0.02, 10.0)
+    buf = torch.zeros(M * K + 8, dtype=torch.float16, device="cuda")
+    d_x = buf[shift:shift + M * K].view(M, K)
+    d_x.copy_(torch.from_numpy(x))
+    H = qqq.qqq_hessian(d_x).cpu().numpy()
+    assert np.array_equal(H, cal.hessian(x.view(np.uint16)))
+
+
 @pytest.mark.parametrize("K,N", [(128, 1), (256, 33), (640, 97)])
 def test_per_group_sweep_at_block_edges(K, N):
     x, w = layer(2 * K + 10, K, N, 500 + K + N)
