@@ -112,7 +112,7 @@ static const struct DispatchModel {
   double margin_split = 0.88, margin_leave_large_tile = 0.95;
   int min_ksteps_per_split = 4;
   double decode_base_us = 5.0;
-  double decode_c64_lo[2] = {0.038, 0.0015}, decode_c64_hi[2] = {0.045, 0.0017};  // 64- and 128-channel groups: M <= 32, M > 32
+  double decode_c64_lo[2] = {0.038, 0.0015}, decode_c64_hi[2] = {0.044, 0.0011};  // 64- and 128-channel groups: M <= 32, M > 32
   double decode_c32_lo[2] = {0.06, 0.0008}, decode_c32_hi[2] = {0.093, 0.0007};   // 32-channel groups
   double decode_c16_lo[2] = {0.04, 0.0031}, decode_c16_hi[2] = {0.12, 0.0023};    // 16-channel groups
   double prefill_wins_by = 0.92;             // the prefill path must be this much cheaper at 17..64 rows

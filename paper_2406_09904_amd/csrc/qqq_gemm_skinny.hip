@@ -583,7 +583,17 @@ static int launch_mode(const GemmParams& p, hipStream_t st) {
     if (nt >= 2) return launch_w<MODE, 2, 2, 1>(p, w, S, st);
     return launch_w<MODE, 1, 2, 2>(p, w, S, st);
   }
-  if (nt >= 4) return launch_w<MODE, 4, 4, 1>(p, 4, S, st);  // 16 tiles of accumulators: 4 waves fit LDS and registers
+  // Three or four row tiles: 64 channels leave 12 or 16 accumulator tiles a wave.  Eight waves (two per SIMD) cover each
+  // other's loads (us: 64 rows on 5120 x 13824 with group scales 16.0 with four waves, 14.8 with eight; on 8192 x 28672
+  // 41.4, 36.9); with three row tiles four waves need few enough registers for two workgroups to share a CU, and
+  // where there is more than one per CU that is ahead (37 rows on 5120 x 13824 13.3, 12.4; 48 rows on 8192 x 28672 30.4,
+  // 31.8; 40 rows on 4096 x 20480 16.8, 19.0).
+  if (mt == 3) {  // a row tile less than four: 37 rows on 5120 x 13824 15.7 us with four, 13.3 with three
+    if (nt >= 4) return launch_w<MODE, 4, 3, 1>(p, g_tune_w > 0 ? g_tune_w : (int64_t)p.N / 64 * S <= num_cus() ? 8 : 4, S, st);
+    if (nt >= 2) return launch_w<MODE, 2, 3, 1>(p, w, S, st);
+    return launch_w<MODE, 1, 3, 1>(p, w, S, st);
+  }
+  if (nt >= 4) return launch_w<MODE, 4, 4, 1>(p, g_tune_w > 0 ? g_tune_w : 8, S, st);
   if (nt >= 2) return launch_w<MODE, 2, 4, 1>(p, w, S, st);
   return launch_w<MODE, 1, 4, 1>(p, w, S, st);
 }
