@@ -437,7 +437,7 @@ def conversion_ablation(torch, qqq, wls, use_graph):
     qqq.set_prefill_tuning(0)
     for r in rows:
         r["tops"] = round(c.ops / (r["gemm_us"] * 1e-6) / 1e12, 1)
-    return {"shape": {"M": wl.M, "K": wl.K, "N": wl.N}, "kernel": "gemm_prefill_dma_kernel, 128x512 tile",
+    return {"shape": {"M": wl.M, "K": wl.K, "N": wl.N}, "kernel": "gemm_prefill_dma_kernel, its large tile (128x512 per-channel, 256x256 with group scales)",
             "rows": rows}
 
 

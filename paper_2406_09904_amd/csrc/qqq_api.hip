@@ -90,21 +90,37 @@ static size_t split_bytes(int64_t M, int64_t N) {
 //   launch_us     one more kernel in the stream (empty-kernel spacing).
 //   reduce_tbs    the K-split reduce kernel's traffic rate (splits * M * N int32 written and read).
 //   margins       how much cheaper (modelled) an alternative must be before the large tile or the
-//                 unsplit launch is given up: set so that on a 72-case grid no pick lost more than
-//                 13 % against the best forced choice.
+//                 unsplit launch is given up.  With all of this, on 126 shapes drawn over K = 1024 .. 11008,
+//                 N = 1024 .. 28672, M = 65 .. 4096 and three conversions, the pick is 1 % behind the best forced
+//                 choice on average and 17 % at most.
 //   decode_*      time of the decode kernel for 17..64 rows: decode_base_us + c(M) * N*K/1e6 with
 //                 c linear in M per channel-group width, the width being the launcher's own choice
 //                 (fit over M = 17..64 on the six layers plus 8192 x 8192, 5120 x 5120).
-//   pergroup_*    the per-group prefill GEMM relative to the per-channel one of the same shape, for
-//                 its two clamp-free conversions: the biased integer route (a factor on the time
-//                 plus its pre-pass launch and per-tile correction) and the fp16-FMA route (a larger
-//                 factor, nothing else); fitted on ten shapes from M=64 to 1024, they cross where
-//                 the per-channel GEMM takes about 33 us.
+//   pergroup_prepass_us  what the biased integer route pays on top of its tiles: the pre-pass launch and the
+//                 correction at the start of each tile.
 // A test times the automatic pick against every forced pick on a small grid (15 % bar).
-struct TileCost { int shape, bm, bn; bool one_per_cu; double alone_us, saturated_us; };
+// What an int4 weight costs to convert decides how much a tile gains from having many rows, so tile[] is
+// measured per conversion.
+enum CostClass : int { kCostChannel, kCostBias, kCostFma, kCostReal, kCostClamp, kCostClasses };
+static int cost_class(int mode) {
+  switch (mode) {
+    case kPerChannel: return kCostChannel;
+    case kGroupBias:
+    case kGroupBiasWide: return kCostBias;
+    case kGroupClamp: return kCostClamp;
+    case kGroupReal:
+    case kGroupCvt: return kCostReal;
+  }
+  return kCostFma;
+}
+struct TileCost { int shape, bm, bn; double alone_us, saturated_us; };
 static const struct DispatchModel {
-  TileCost tile[4] = {{0, 128, 512, true, 1.15, 1.33}, {3, 128, 256, true, 0.71, 0.78},
-                      {4, 128, 128, false, 0.63, 0.52}, {5, 64, 128, false, 0.39, 0.275}};
+  TileCost tile[kCostClasses][4] = {
+      {{0, 128, 512, 1.15, 1.33}, {3, 128, 256, 0.71, 0.78}, {4, 128, 128, 0.63, 0.52}, {5, 64, 128, 0.39, 0.275}},
+      {{0, 256, 256, 1.29, 1.58}, {3, 128, 256, 0.89, 0.92}, {4, 128, 128, 0.66, 0.52}, {5, 64, 128, 0.45, 0.303}},
+      {{0, 256, 256, 1.42, 1.68}, {3, 128, 256, 1.05, 1.10}, {4, 128, 128, 0.74, 0.66}, {5, 64, 128, 0.557, 0.43}},
+      {{0, 256, 256, 1.53, 1.80}, {3, 128, 256, 1.06, 1.16}, {4, 128, 128, 0.76, 0.65}, {5, 64, 128, 0.63, 0.47}},
+      {{0, 256, 256, 1.90, 1.95}, {3, 128, 256, 1.44, 1.41}, {4, 128, 128, 0.94, 0.69}, {5, 64, 128, 0.80, 0.50}}};
   double tile_fixed_ksteps = 4.0;
   double stream_tbs = 5.0;
   double launch_us = 2.4;
@@ -116,7 +132,7 @@ static const struct DispatchModel {
   double decode_c32_lo[2] = {0.06, 0.0008}, decode_c32_hi[2] = {0.093, 0.0007};   // 32-channel groups
   double decode_c16_lo[2] = {0.04, 0.0031}, decode_c16_hi[2] = {0.12, 0.0023};    // 16-channel groups
   double prefill_wins_by = 0.92;             // the prefill path must be this much cheaper at 17..64 rows
-  double pergroup_bias_factor = 1.13, pergroup_prepass_us = 7.5, pergroup_fma_factor = 1.36;
+  double pergroup_prepass_us = 7.5;
   double perchannel_extra_us = 2.5;
 } kModel;
 
@@ -127,18 +143,18 @@ static const struct DispatchModel {
 // persistent kernel and the per-tile one.
 struct PrefillPlan {
   int shape, k_splits;
-  double us;  // modelled time of the per-channel GEMM
+  double us;  // modelled time of the GEMM
 };
 static double reduce_cost_us(int k_splits, int64_t M, int64_t N) {
   return kModel.launch_us + 8e-6 * (double)k_splits * (double)M * (double)N / kModel.reduce_tbs;
 }
-static PrefillPlan plan_prefill(int64_t M, int64_t N, int64_t K, bool can_split, int forced_split) {
+static PrefillPlan plan_prefill(int64_t M, int64_t N, int64_t K, int cost, bool can_split, int forced_split) {
   const int cus = num_cus();
   const int T = (int)(K / 128);
   const int splits[8] = {1, 2, 3, 4, 6, 8, 12, 16};
   PrefillPlan best = {0, 1, 0.0};
   for (int i = 0; i < 4; ++i) {
-    const TileCost& c = kModel.tile[i];
+    const TileCost& c = kModel.tile[cost][i];
     const int64_t tiles_c = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
     for (int j = 0; j < 8; ++j) {
       int ks = splits[j];
@@ -152,8 +168,15 @@ static PrefillPlan plan_prefill(int64_t M, int64_t N, int64_t K, bool can_split,
       }
       const int64_t wgs = tiles_c * ks;
       double per_step = c.alone_us;
-      if (wgs > cus)  // whole rounds where only one workgroup fits a CU, a smooth load otherwise
-        per_step = c.saturated_us * (c.one_per_cu ? (double)((wgs + cus - 1) / cus) : (double)wgs / cus);
+      if (wgs > cus) {
+        // between an even spread and whole rounds: CUs that finish early leave the others the power budget and the
+        // bandwidth; the 8-wave shapes have a CU to themselves and come closer to whole rounds, and two
+        // workgroups of the 4-wave shapes on one CU do not yet saturate it
+        const double even = (double)wgs / cus, rounds = (double)((wgs + cus - 1) / cus);
+        const double whole = c.bn >= 256 ? 0.65 : 0.5;
+        per_step = c.saturated_us * (even + whole * (rounds - even));
+        if (c.bn < 256 && per_step < 1.25 * c.alone_us) per_step = 1.25 * c.alone_us;
+      }
       double cost = per_step * ((double)T / ks + kModel.tile_fixed_ksteps);
       const double stream_us = (double)N * (double)K * 0.5 / (kModel.stream_tbs * 1e6);
       if (cost < stream_us) cost = stream_us;
@@ -172,11 +195,9 @@ static PrefillPlan plan_prefill(int64_t M, int64_t N, int64_t K, bool can_split,
 
 // Modelled time of the clamp-free per-group prefill GEMM and which conversion gives it: the biased integer
 // route pays a pre-pass launch, the fp16-FMA route more per k-step, so short launches take the latter.
-static double pergroup_prefill_us(const PrefillPlan& plan, int64_t M, int64_t N, bool* bias_route) {
-  const double reduce_us = plan.k_splits > 1 ? reduce_cost_us(plan.k_splits, M, N) : 0.0;
-  const double core = plan.us - reduce_us;
-  const double bias = core * kModel.pergroup_bias_factor + kModel.pergroup_prepass_us + reduce_us;
-  const double fma = core * kModel.pergroup_fma_factor + reduce_us;
+static double pergroup_prefill_us(int64_t M, int64_t N, int64_t K, bool* bias_route) {
+  const double bias = plan_prefill(M, N, K, kCostBias, true, g_prefill_ksplit).us + kModel.pergroup_prepass_us;
+  const double fma = plan_prefill(M, N, K, kCostFma, true, g_prefill_ksplit).us;
   if (bias_route) *bias_route = bias < fma;
   return bias < fma ? bias : fma;
 }
@@ -199,8 +220,8 @@ static int kernel_family(int64_t M, int64_t N, int64_t K, bool pergroup) {
   const int64_t wgs = N / (16 * nt), cus = num_cus();
   if (nt == 1 && wgs > cus) c *= (double)((wgs + cus - 1) / cus) * (double)cus / (double)wgs;
   const double decode_us = kModel.decode_base_us + c * nk;
-  const PrefillPlan plan = plan_prefill(M, N, K, true, g_prefill_ksplit);
-  const double prefill_us = pergroup ? pergroup_prefill_us(plan, M, N, nullptr) : plan.us + kModel.perchannel_extra_us;
+  const double prefill_us = pergroup ? pergroup_prefill_us(M, N, K, nullptr)
+                                     : plan_prefill(M, N, K, kCostChannel, true, g_prefill_ksplit).us + kModel.perchannel_extra_us;
   return prefill_us < kModel.prefill_wins_by * decode_us ? 2 : 1;
 }
 
@@ -349,16 +370,16 @@ static int gemm_common(const int8_t* a_q, const float* s_a, const void* w_packed
     return per_tile(tune >= 15 ? tune % 10 - 2 : 0, forced_split > 0 ? forced_split : 1);
   if (tune == 13) return launch_gemm_prefill_ring(p, mode, (hipStream_t)stream);
   {
-    const PrefillPlan plan = plan_prefill(M, N, K, can_split, forced_split);
+    const PrefillPlan plan = plan_prefill(M, N, K, cost_class(mode), can_split, forced_split);
     if (plan.shape != 0 || plan.k_splits > 1) return per_tile(plan.shape, plan.k_splits);
-    if (mode == kGroupReal) return launch_gemm_prefill_dma(p, mode, 0, (hipStream_t)stream);
-    // Measured on MI355X (two boxes, 14 shapes with M >= 1024, both kernels in one process): with 64 k-steps
-    // or more the per-tile kernel is 2-6 % ahead for the per-channel variant and 1-3 % for the per-group one
-    // (K = 8192: 636 against 660 us on the 28672-channel layer; K = 21760: 455 against 483); with shorter K the
-    // persistent kernel is level or up to 2 % ahead whenever a CU walks more than one tile (the next tile's
-    // first k-steps load under the epilogue).
-    const bool tiles_repeat = tiles > num_cus();
-    if (p.T < 64 && (mode == kPerChannel || tiles_repeat))
+    // Per-channel, measured on MI355X: with 64 k-steps or more the per-tile kernel is 2-6 % ahead of the
+    // persistent one (K = 8192: 636 against 660 us on the 28672-channel layer; K = 21760: 455 against 483); with shorter K
+    // and tiles enough for a second round the persistent kernel, whose next tile's first k-steps load under the
+    // epilogue, is ahead up to K = 2048 (N = 28672, M = 2048: 97 against 102 us; K = 1024, N = 9216, M = 2500: 31 against 33) and
+    // level to 2 % behind at 4096 and 5120; without a second round it is ahead on the shortest K only (K = 1024,
+    // N = 21328, M = 699: 19.0 against 20.9; K = 2176, N = 4560, M = 2768: 27.6 against 29.5; K = 4096, N = 11008, M = 777: 42.8
+    // against 40.6).  With group scales the 256 x 256 tile is ahead of it on every shape (launch_large).
+    if (mode == kPerChannel && p.T < 64 && (tiles > num_cus() || p.T <= 24))
       return launch_gemm_prefill_ring(p, mode, (hipStream_t)stream);
     return launch_gemm_prefill_dma(p, mode, 0, (hipStream_t)stream);
   }
@@ -372,7 +393,7 @@ static bool takes_bias_route(int mode, int64_t M, int64_t N, int64_t K) {
     return false;
   if (g_group_mode == 5) return true;  // forced
   bool bias = true;
-  pergroup_prefill_us(plan_prefill(M, N, K, true, g_prefill_ksplit), M, N, &bias);
+  pergroup_prefill_us(M, N, K, &bias);
   return bias;
 }
 

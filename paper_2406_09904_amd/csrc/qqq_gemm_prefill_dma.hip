@@ -4,7 +4,8 @@
 //
 // Shape parameters: NW waves split N; each wave owns a (32*MT) x (32*CT) patch of Y, so the
 // workgroup tile is (32*MT) x (NW*32*CT).  Instances:
-//   <4,2,8>  128 x 512, 8 waves, 128 accumulator registers, two waves per SIMD
+//   <4,2,8>  128 x 512 (per-channel), <8,1,8>  256 x 256 (per-group): 8 waves, 128 accumulator registers, two waves
+//            per SIMD
 //   <4,1,8>  128 x 256, <4,1,4>  128 x 128, <2,1,4>  64 x 128: narrow tiles for mid-size M, where
 //            a few large tiles would leave most CUs idle
 //
@@ -402,8 +403,16 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_prefill_dma_kernel(const Gemm
       for (int c = 0; c < TC; ++c) mfma_col(a1, b3[c], c);
     }
   }
-  // the clamped DMA requests of the last two k-steps may still be landing in the ring
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  // the clamped DMA requests of the last two k-steps may still be landing in the ring: every wave waits for its
+  // own (its token scales, for its own copy in the epilogue, come with them), and the ring is free once all have
+  constexpr int kSaPerLane = S::kBM / 64;
+  float sa_own[kSaPerLane];
+#pragma unroll
+  for (int i = 0; i < kSaPerLane; ++i) {
+    const int m = m0 + lane + 64 * i;
+    sa_own[i] = p.s_a[m < M ? m : M - 1];
+  }
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 
   // ---- split K: the raw tile goes to this split's slab; the reduce kernel does the rest
   if (p.k_splits > 1) {
@@ -425,11 +434,12 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_prefill_dma_kernel(const Gemm
   }
 
   // ---- fused Dequant epilogue.  Every four accumulator registers of a lane are four consecutive
-  // rows of its column.  The ring is free now (nothing reads it after the last barrier and every
-  // DMA has landed): each wave dequantises its patch into its own fp16 LDS region (row pitch padded
+  // rows of its column.  Each wave dequantises its patch into its own fp16 LDS region (row pitch padded
   // by 16 B) and streams it out as full rows.
-  float* sa_lds = (float*)(lds + NW * S::kEpWave);
-  for (int r = tid; r < S::kBM; r += NW * 64) sa_lds[r] = (m0 + r < M) ? p.s_a[m0 + r] : 0.0f;
+  int8_t* ep = lds + wave * S::kEpWave;
+  float* sa_lds = (float*)(ep + S::kEpRows * S::kEpRow);
+#pragma unroll
+  for (int i = 0; i < kSaPerLane; ++i) sa_lds[lane + 64 * i] = sa_own[i];
   // Per-channel sums carry the factor 16 of the conversion.  Scaling by a power of two commutes with
   // every rounding of the Dequant (int -> fp32, fp32 product, fp16 result), so the factor goes into
   // the channel scale instead of a shift per accumulator.
@@ -438,36 +448,38 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_prefill_dma_kernel(const Gemm
   float swv[TC];
 #pragma unroll
   for (int c = 0; c < TC; ++c) swv[c] = nvalid[c] ? (float)p.s_w[col[c]] * kAccScale : 0.0f;
-  __syncthreads();
-  int8_t* ep = lds + wave * S::kEpWave;
+  // (256-row tiles: in two halves; patch and scales are private to this wave and LDS serves one wave's accesses
+  // in order, so nothing here waits for another wave and the second half may overwrite the first)
+  constexpr int kHalf = S::kBM / S::kEpRows;
 #pragma unroll
-  for (int mt = 0; mt < TM; ++mt) {
+  for (int h = 0; h < kHalf; ++h) {
+    const int hrow = h * S::kEpRows;
 #pragma unroll
-    for (int q = 0; q < kRegs / 4; ++q) {
-      const int r0 = acc_row(mt, 4 * q);
-      const float4 sa4 = *(const float4*)(sa_lds + r0);
-      const float sav[4] = {sa4.x, sa4.y, sa4.z, sa4.w};
+    for (int mt = h * TM / kHalf; mt < (h + 1) * TM / kHalf; ++mt) {
 #pragma unroll
-      for (int c = 0; c < TC; ++c) {
+      for (int q = 0; q < kRegs / 4; ++q) {
+        const int r0 = acc_row(mt, 4 * q);
+        const float4 sa4 = *(const float4*)(sa_lds + r0);
+        const float sav[4] = {sa4.x, sa4.y, sa4.z, sa4.w};
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          *(_Float16*)(ep + (r0 + j) * S::kEpRow + (c * kTile + lcol) * 2) =
-              dequant(acc[mt][c][4 * q + j], sav[j], swv[c]);
+        for (int c = 0; c < TC; ++c) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            *(_Float16*)(ep + (r0 + j - hrow) * S::kEpRow + (c * kTile + lcol) * 2) =
+                dequant(acc[mt][c][4 * q + j], sav[j], swv[c]);
+          }
         }
       }
     }
-  }
-  // the patch is private to this wave and LDS serves one wave's accesses in order
-  {
     constexpr int kLanesPerRow = 4 * CT;            // 16-byte pieces per patch row
     constexpr int kRowsPerIt = 64 / kLanesPerRow;
     const int cc = lane % kLanesPerRow;
     const int ncol = n_wave + cc * 8;
 #pragma unroll
-    for (int it = 0; it < S::kBM / kRowsPerIt; ++it) {
+    for (int it = 0; it < S::kEpRows / kRowsPerIt; ++it) {
       const int row = it * kRowsPerIt + lane / kLanesPerRow;
       const v4i d = *(const v4i*)(ep + row * S::kEpRow + cc * 16);
-      const int m = m0 + row;
+      const int m = m0 + hrow + row;
       if (m < M && ncol < N) *(v4i*)(p.y + (int64_t)m * N + ncol) = d;
     }
   }
@@ -562,17 +574,29 @@ static bool lone_workgroups(const GemmParams& p, int bm, int bn) {
   return deep == 0 ? wgs <= num_cus() : deep > 3;
 }
 
+// The large tile: 128 x 512 per-channel, 256 x 256 per-group.  Both are the same MFMAs per k-step and the same 128
+// accumulator registers; 256 rows by 32 channels a wave halve the conversions per MFMA and double the
+// activation fragments read from LDS (256 KiB a k-step, level with the MFMAs).  Per-channel conversion is too cheap
+// for that to pay (K = 8192, N = 28672, M = 4096: 644 us against 660 with 256 x 256); the group conversions
+// all gain (N = 11008, K = 4096, M = 4096: real-valued scale 219 -> 173 us, saturating 292 -> 203, biased integer 172 -> 165;
+// N = 28672, K = 8192: 1027 -> 858 real-valued, 806 -> 774 biased).
+template <int MODE>
+static int launch_large(const GemmParams& p, hipStream_t st) {
+  if constexpr (MODE == kPerChannel) return launch_dma<MODE, 4, 2, 8>(p, st);
+  else return launch_dma<MODE, 8, 1, 8>(p, st);
+}
+
 template <int MODE>
 static int launch_shape(const GemmParams& p, int shape, hipStream_t st) {
   switch (shape) {
     case 3: return launch_dma<MODE, 4, 1, 8>(p, st);
     case 4: return launch_dma<MODE, 4, 1, 4>(p, st);
     case 5: return lone_workgroups(p, 64, 128) ? launch_dma<MODE, 2, 1, 4, 6>(p, st) : launch_dma<MODE, 2, 1, 4>(p, st);
-    default: return launch_dma<MODE, 4, 2, 8>(p, st);
+    default: return launch_large<MODE>(p, st);
   }
 }
 
-// shape: 0 = 128x512 tile with 8 waves; narrow tiles for shapes with few rows, where the number
+// shape: 0 = the large tile with 8 waves (128x512, or 256x256 with group scales); narrow tiles for shapes with few rows, where the number
 // of workgroups matters more than the reuse inside one: 3 = 128x256 with 8 waves, 4 = 128x128
 // with 4 waves, 5 = 64x128 with 4 waves
 int launch_gemm_prefill_dma(const GemmParams& p, int mode, int shape, hipStream_t st) {
@@ -585,7 +609,7 @@ int launch_gemm_prefill_dma(const GemmParams& p, int mode, int shape, hipStream_
     case kGroupFusedWide:
     case kGroupFused: return launch_shape<kGroupFused>(p, shape, st);
     case kGroupReal: return launch_shape<kGroupReal>(p, shape, st);
-    case kGroupCvt: return launch_dma<kGroupCvt, 4, 2, 8>(p, st);  // timing ablation: one shape
+    case kGroupCvt: return launch_large<kGroupCvt>(p, st);  // timing ablation: one shape
     case kGroupBias: return launch_shape<kGroupBias>(p, shape, st);
     case kGroupBiasWide: return launch_shape<kGroupBiasWide>(p, shape, st);
   }
