@@ -193,6 +193,8 @@ static PrefillPlan plan_prefill(int64_t M, int64_t N, int64_t K, int cost, bool 
   return best;
 }
 
+int prefill_shape(int64_t M, int64_t N, int64_t K) { return plan_prefill(M, N, K, kCostChannel, false, 0).shape; }
+
 // Modelled time of the clamp-free per-group prefill GEMM and which conversion gives it: the biased integer
 // route pays a pre-pass launch, the fp16-FMA route more per k-step, so short launches take the latter.
 static double pergroup_prefill_us(int64_t M, int64_t N, int64_t K, bool* bias_route) {
@@ -323,6 +325,9 @@ static int gemm_common(const int8_t* a_q, const float* s_a, const void* w_packed
   p.ws_cnt = nullptr;
   p.ws_acc = nullptr;
   p.r_lo = p.r_hi = p.bias_w = nullptr;
+  p.y_ref = nullptr;
+  p.loss = nullptr;
+  p.point_bytes = 0;
   p.k_splits = 1;
   p.part = nullptr;
   p.a_fp16 = (const uint4*)a_fp16;

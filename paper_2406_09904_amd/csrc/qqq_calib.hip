@@ -39,28 +39,39 @@ static int fill_u32(void* p, size_t n, uint32_t v, hipStream_t st) {
 // ------------------------------------------------------------------ Sec. 3.1: channel maxima
 
 // absmax[t] = max_m |X[m,t]| on the fp16 bit patterns (magnitude order = integer order with the
-// sign cleared); each thread owns 8 consecutive channels (one 128-bit load per row), blocks split
-// the rows and meet through atomicMax on the (non-negative) bit patterns.  absmax holds fp16 bit
-// patterns as uint32 until absmax_finish_kernel widens them to fp32 and takes the overall maximum.
+// sign cleared); a workgroup is 32 column vectors (8 channels, one 128-bit load per row) by 8 row groups of
+// rows_per_block / 8 rows, which meet in LDS, and the workgroups through atomicMax on the (non-negative) bit
+// patterns.  absmax holds fp16 bit patterns as uint32 until absmax_finish_kernel widens them to fp32 and takes
+// the overall maximum.
 __global__ __launch_bounds__(256) void channel_absmax_kernel(const uint4* x, int64_t M, int64_t kvec,
                                                              int64_t rows_per_block, uint32_t* absmax_bits) {
-  const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (v >= kvec) return;
-  const int64_t m0 = (int64_t)blockIdx.y * rows_per_block;
-  int64_t m1 = m0 + rows_per_block;
+  __shared__ uint32_t part[8][32][9];
+  const int c = threadIdx.x & 31, g = threadIdx.x >> 5;
+  const int64_t v = (int64_t)blockIdx.x * 32 + c;
+  int64_t m1 = ((int64_t)blockIdx.y + 1) * rows_per_block;
   if (m1 > M) m1 = M;
   uint32_t mx[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int64_t m = m0; m < m1; ++m) {
-    const uint4 q = x[m * kvec + v];
-    const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+  if (v < kvec) {
+#pragma unroll 4
+    for (int64_t m = (int64_t)blockIdx.y * rows_per_block + g; m < m1; m += 8) {
+      const uint4 q = x[m * kvec + v];
+      const uint32_t w[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      mx[2 * i] = max(mx[2 * i], w[i] & 0x7FFFu);
-      mx[2 * i + 1] = max(mx[2 * i + 1], (w[i] >> 16) & 0x7FFFu);
+      for (int i = 0; i < 4; ++i) {
+        mx[2 * i] = max(mx[2 * i], w[i] & 0x7FFFu);
+        mx[2 * i + 1] = max(mx[2 * i + 1], (w[i] >> 16) & 0x7FFFu);
+      }
     }
   }
 #pragma unroll
-  for (int i = 0; i < 8; ++i) atomicMax(&absmax_bits[v * 8 + i], mx[i]);
+  for (int i = 0; i < 8; ++i) part[g][c][i] = mx[i];
+  __syncthreads();
+  const int cc = threadIdx.x >> 3, i = threadIdx.x & 7;  // one channel of the 256 per thread
+  uint32_t r = 0;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) r = max(r, part[k][cc][i]);
+  const int64_t t = ((int64_t)blockIdx.x * 32 + cc) * 8 + i;
+  if (t < kvec * 8) atomicMax(&absmax_bits[t], r);
 }
 
 // in place: fp16 bit patterns -> fp32 values; top[0] = the largest (one workgroup)
@@ -85,95 +96,261 @@ __global__ void sigma_grid_kernel(const float* top, int G, float* sigmas) {
   if (g < G) sigmas[g] = (float)((double)top[0] * (double)(g + 1) / (double)G);
 }
 
-// s_t = absmax_t / sigma (one fp32 division) where absmax_t > sigma, else 1
+// s_t = absmax_t / sigma (one fp32 division) where absmax_t > sigma, else 1; grid.y: several sigmas, their vectors
+// stride_bytes apart
 __global__ __launch_bounds__(256) void smoothing_vector_kernel(const float* absmax, const float* sigmas,
-                                                               const int32_t* index, int64_t K, float* s) {
+                                                               const int32_t* index, int64_t K, float* s,
+                                                               int64_t stride_bytes) {
   const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (t >= K) return;
-  const float sigma = sigmas[index ? index[0] : 0];
+  const float sigma = sigmas[(index ? index[0] : 0) + blockIdx.y];
   const float a = absmax[t];
-  s[t] = a > sigma ? a / sigma : 1.0f;
+  ((float*)((char*)s + stride_bytes * blockIdx.y))[t] = a > sigma ? a / sigma : 1.0f;
 }
 
-// out = fp16_rne(fp32(in) / s) (DIVIDE) or fp16_rne(fp32(in) * s): one fp32 operation, one rounding
+// eight channels of X' = fp16_rne(fp32(X) / s) (DIVIDE) or W' = fp16_rne(fp32(W) * s): one fp32 operation, one rounding
+template <bool DIVIDE>
+__device__ __forceinline__ uint4 smooth8(uint4 q, const float* s) {
+  const float4 s0 = *reinterpret_cast<const float4*>(s);
+  const float4 s1 = *reinterpret_cast<const float4*>(s + 4);
+  const float sv[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
+  const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+  uint32_t o[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const float a = half_bits_to_float(w[j] & 0xFFFFu), b = half_bits_to_float(w[j] >> 16);
+    float ra = DIVIDE ? a / sv[2 * j] : a * sv[2 * j];
+    float rb = DIVIDE ? b / sv[2 * j + 1] : b * sv[2 * j + 1];
+    // the fp32 result is rounded before the conversion sees it: left alone, the compiler turns
+    // multiply + convert into one mixed-precision instruction that rounds the exact product once
+    asm volatile("" : "+v"(ra), "+v"(rb));
+    o[j] = (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)ra) |
+           ((uint32_t)__builtin_bit_cast(uint16_t, (_Float16)rb) << 16);
+  }
+  return make_uint4(o[0], o[1], o[2], o[3]);
+}
+
 template <bool DIVIDE>
 __global__ __launch_bounds__(256) void smooth_apply_kernel(const uint4* in, const float* s, int64_t rows,
                                                            int64_t kvec, uint4* out) {
   const int64_t total = rows * kvec;
   const int64_t stride = (int64_t)gridDim.x * 256;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += stride) {
-    const int64_t v = i % kvec;
-    const uint4 q = in[i];
-    const float4 s0 = *reinterpret_cast<const float4*>(s + v * 8);
-    const float4 s1 = *reinterpret_cast<const float4*>(s + v * 8 + 4);
-    const float sv[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
-    const uint32_t w[4] = {q.x, q.y, q.z, q.w};
-    uint32_t o[4];
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += stride)
+    out[i] = smooth8<DIVIDE>(in[i], s + (i % kvec) * 8);
+}
+
+// ------------------------------------------------------------------ a grid point's operands
+
+// The smoothed, quantised operands of several grid points (grid.y), each point's buffers point_bytes apart, straight
+// from X and W: no smoothed tensor is written.  Arithmetic as in smooth_apply_kernel followed by the hot path's
+// quantisers, operation for operation.
+
+// One token per workgroup (qqq_quant_act on X ./ s).  KEEP: the smoothed row stays in registers (K <= 8192); else it
+// is computed twice.
+template <bool KEEP>
+__global__ __launch_bounds__(256) void point_activations_kernel(const uint4* x, const float* s, int kvec, int64_t point_bytes,
+                                                                int8_t* a_q, float* s_a) {
+  __shared__ uint32_t part[4];
+  const int64_t off = point_bytes * blockIdx.y, m = blockIdx.x;
+  const uint4* row = x + m * kvec;
+  const float* sv = (const float*)((const char*)s + off);
+  uint2* out = (uint2*)(a_q + off) + m * kvec;
+  constexpr int kVecs = KEEP ? 4 : 1;
+  uint4 v[kVecs];
+  uint32_t bits = 0;
+  if constexpr (KEEP) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const float a = half_bits_to_float(w[j] & 0xFFFFu), b = half_bits_to_float(w[j] >> 16);
-      float ra = DIVIDE ? a / sv[2 * j] : a * sv[2 * j];
-      float rb = DIVIDE ? b / sv[2 * j + 1] : b * sv[2 * j + 1];
-      // the fp32 result is rounded before the conversion sees it: left alone, the compiler turns
-      // multiply + convert into one mixed-precision instruction that rounds the exact product once
-      asm volatile("" : "+v"(ra), "+v"(rb));
-      o[j] = (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)ra) |
-             ((uint32_t)__builtin_bit_cast(uint16_t, (_Float16)rb) << 16);
+    for (int j = 0; j < kVecs; ++j) {
+      const int i = threadIdx.x + 256 * j;
+      if (i < kvec) bits = absmax_bits(v[j] = smooth8<true>(row[i], sv + 8 * i), bits);
     }
-    out[i] = make_uint4(o[0], o[1], o[2], o[3]);
+  } else {
+    for (int i = threadIdx.x; i < kvec; i += 256) bits = absmax_bits(smooth8<true>(row[i], sv + 8 * i), bits);
+  }
+  bits = wave_max_u32(bits);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = bits;
+  __syncthreads();
+  const float amax = half_bits_to_float(max(max(part[0], part[1]), max(part[2], part[3])));
+  const float sc = amax / 127.0f;
+  if (threadIdx.x == 0) ((float*)((char*)s_a + off))[m] = amax == 0.0f ? 0.0f : sc;
+  auto codes = [&](uint4 q) {
+    return amax == 0.0f ? make_uint2(0, 0) : make_uint2(quant4(q.x, q.y, sc), quant4(q.z, q.w, sc));
+  };
+  if constexpr (KEEP) {
+#pragma unroll
+    for (int j = 0; j < kVecs; ++j) {
+      const int i = threadIdx.x + 256 * j;
+      if (i < kvec) out[i] = codes(v[j]);
+    }
+  } else {
+    for (int i = threadIdx.x; i < kvec; i += 256) out[i] = codes(smooth8<true>(row[i], sv + 8 * i));
+  }
+}
+
+// 16 output channels per workgroup (qqq_quantize_w4_perchannel on W .* s, then qqq_pack_w4): a wave takes four
+// channels one after the other, its lanes hold the row (K <= 4096: in registers; else the row is smoothed
+// twice, 4096 channels at a time), and the codes meet in LDS in the packed layout's order, so whole 1 KiB chunks are
+// written.  Bound by vector instructions, about 14 per weight and grid point.
+template <bool ONE>
+__global__ __launch_bounds__(256) void point_weights_kernel(const uint4* w, const float* s, int64_t N, int kvec,
+                                                            int64_t point_bytes, uint8_t* packed, uint16_t* s_w) {
+  __shared__ uint32_t stage[32 * 256];  // 32 k-steps of 1 KiB
+  // the points of one group of channels run one after the other on the same XCD (workgroup ids go round the
+  // eight of them), so its rows come from that XCD's L2 after the first
+  const int64_t groups = N / 16;
+  const int points = gridDim.y;
+  const int64_t lin = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+  int64_t nt;
+  int pt;
+  if (groups % 8 == 0) {
+    const int64_t blk = lin / (8 * points), in = lin % (8 * points);
+    nt = blk * 8 + in % 8;
+    pt = (int)(in / 8);
+  } else {
+    nt = lin % groups;
+    pt = (int)(lin / groups);
+  }
+  const int64_t off = point_bytes * pt;
+  const float* sv = (const float*)((const char*)s + off);
+  uint32_t* out = (uint32_t*)(packed + off);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  float sc[4];
+  uint4 v[8];
+  auto smooth_row = [&](const uint4* row, int i0) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int i = i0 + lane + 64 * j;
+      v[j] = i < kvec ? smooth8<false>(row[i], sv + 8 * i) : make_uint4(0, 0, 0, 0);
+    }
+  };
+  auto scale_of_row = [&](int64_t n, const uint4* row) {
+    uint32_t bits = 0;
+    for (int i0 = 0; i0 < kvec; i0 += 512) {
+      smooth_row(row, i0);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) bits = absmax_bits(v[j], bits);
+      if constexpr (ONE) break;
+    }
+    const uint16_t sb = scale_bits(half_bits_to_float(wave_max_u32(bits)), 7.0f);
+    if (lane == 0) ((uint16_t*)((char*)s_w + off))[n] = sb;
+    return half_bits_to_float(sb);
+  };
+  // natural word i of channel nl = 16 nt + c: word (k-step i / 16, lane c + 16 kc, dword d) of the packed layout
+  auto put = [&](int c, float scale, int i0) {
+    const float rs = __builtin_amdgcn_rcpf(scale);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int i = lane + 64 * j;
+      if (i0 + i >= kvec) continue;
+      const uint32_t h[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
+      uint32_t word = 0;
+      if (scale != 0.0f) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          word |= (uint32_t)(rtn_code(h[e] & 0xFFFFu, scale, rs) & 0xF) << (8 * e) |
+                  (uint32_t)(rtn_code(h[e] >> 16, scale, rs) & 0xF) << (8 * e + 4);
+      }
+      const int o = i & 15, kc = (o & 7) >> 1, d = 2 * (o >> 3) + (o & 1);
+      stage[(i >> 4) * 256 + (c + 16 * kc) * 4 + d] = shuffle_nibbles_fwd(word);
+    }
+  };
+  auto flush = [&](int i0) {  // whole chunks of up to 32 k-steps
+    __syncthreads();
+    const int steps = min(32, (kvec - i0) >> 4);
+    for (int e = threadIdx.x; e < steps * 64; e += 256)
+      *reinterpret_cast<uint4*>(out + (((int64_t)(i0 >> 4) + (e >> 6)) * groups + nt) * 256 + (e & 63) * 4) =
+          *reinterpret_cast<const uint4*>(&stage[e * 4]);
+    __syncthreads();
+  };
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int c = 4 * wave + q;
+    const int64_t n = nt * 16 + c;
+    sc[q] = scale_of_row(n, w + n * kvec);
+    if constexpr (ONE) put(c, sc[q], 0);
+  }
+  if constexpr (ONE) {
+    flush(0);
+  } else {
+    for (int i0 = 0; i0 < kvec; i0 += 512) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int c = 4 * wave + q;
+        smooth_row(w + (nt * 16 + c) * kvec, i0);
+        put(c, sc[q], i0);
+      }
+      flush(i0);
+    }
   }
 }
 
 // ------------------------------------------------------------------ X W^T in fp32 (reference product of Eq. 2)
 
-// One wave per 32 x 32 output tile, v_mfma_f32_32x32x16_f16: lane l holds row (A) / column (B)
-// l % 32 and the 8 consecutive k of half l / 32, straight from global memory (each lane walks its
-// own row 16 bytes at a time, so every fetched cache line is used in full over four k-steps).
-// Register v of the result is row 8*(v/4) + 4*(l/32) + v%4, column l % 32.  A calibration-time
-// kernel: correctness and simplicity over speed.
-__global__ __launch_bounds__(64) void fp16_gemm_nt_kernel(const _Float16* x, const _Float16* w, int M, int N,
-                                                          int K, float* y) {
-  const int lane = threadIdx.x, r32 = lane & 31, h = lane >> 5;
-  const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 32;
-  const int mr = min(m0 + r32, M - 1), nr = min(n0 + r32, N - 1);
-  const v8h* xa = reinterpret_cast<const v8h*>(x + (int64_t)mr * K + 8 * h);
-  const v8h* wb = reinterpret_cast<const v8h*>(w + (int64_t)nr * K + 8 * h);
-  v16f acc;
+// 64 x 128 output tile per workgroup, a wave per 32 x 64 part of it (v_mfma_f32_32x32x16_f16, fp32 accumulation), 64 of
+// K at a time through two LDS stages with the next four times 64 already requested (a workgroup is alone on its CU,
+// so nothing else covers the latency: 62 us with the next 64 only).  Lane l holds row (A) / column (B) l % 32 and
+// the 8 consecutive k of half l / 32; register v of the result is row 8*(v/4) + 4*(l/32) + v%4, column l % 32.  The
+// 16-byte slots of a stage's row r are XOR-swizzled by (r/2)%8, which spreads both the writes and the 16 rows that a
+// fragment read takes at a time over the banks.  Bound by the LDS reads (three fragments for two MFMAs); the tile is
+// small so that a calibration batch fills the chip: M = 512, K = N = 4096 39 us (123 with one wave per 32 x 32 tile
+// reading its fragments straight from memory).
+__global__ __launch_bounds__(256) void fp16_gemm_nt_kernel(const uint4* x, const uint4* w, int M, int N, int kvec,
+                                                           float* y) {
+  __shared__ uint4 stage[2][192 * 8];  // 64 rows of X, then 128 of W, 8 vectors of 8 k each
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r32 = lane & 31, h = lane >> 5;
+  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 128;
+  const int wm = (wave & 1) * 32, wn = 64 + (wave >> 1) * 64;  // the wave's first row of X and of W in a stage
+  const uint4* src[6];
+  int slot[6], col[6];
 #pragma unroll
-  for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
-  for (int k = 0; k < K; k += 16) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa[k >> 3], wb[k >> 3], acc, 0, 0, 0);
-  const int n = n0 + r32;
-  if (n >= N) return;
+  for (int j = 0; j < 6; ++j) {  // (rows past M and N repeat the last one; their products are not stored)
+    const int e = tid + 256 * j, r = e >> 3;
+    col[j] = e & 7;
+    slot[j] = r * 8 + (col[j] ^ ((r >> 1) & 7));
+    src[j] = r < 64 ? x + (int64_t)min(m0 + r, M - 1) * kvec : w + (int64_t)min(n0 + r - 64, N - 1) * kvec;
+  }
+  uint4 next[4][6];  // (requested unconditionally, vectors past K clamped and zeroed on their way to LDS)
+  auto fetch = [&](uint4 (&q)[6], int v0) {
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int m = m0 + 8 * (v >> 2) + 4 * h + (v & 3);
-    if (m < M) y[(int64_t)m * N + n] = acc[v];
+    for (int j = 0; j < 6; ++j) q[j] = src[j][min(v0 + col[j], kvec - 1)];
+  };
+  v16f acc[2];
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[0][v] = acc[1][v] = 0.0f;
+  auto frag = [&](const uint4* st, int row, int s) {
+    return __builtin_bit_cast(v8h, st[row * 8 + ((2 * s + h) ^ ((row >> 1) & 7))]);
+  };
+#pragma unroll
+  for (int u = 0; u < 4; ++u) fetch(next[u], 8 * u);
+  for (int v0 = 0; v0 < kvec; v0 += 32) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {  // (stages past K hold zeros)
+      uint4* st = stage[u & 1];
+#pragma unroll
+      for (int j = 0; j < 6; ++j) st[slot[j]] = v0 + 8 * u + col[j] < kvec ? next[u][j] : make_uint4(0, 0, 0, 0);
+      fetch(next[u], v0 + 8 * u + 32);
+      lds_barrier();  // (the other stage is not written before everyone is past its reads)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const v8h a = frag(st, wm + r32, s), b0 = frag(st, wn + r32, s), b1 = frag(st, wn + 32 + r32, s);
+        acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b0, acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b1, acc[1], 0, 0, 0);
+      }
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    const int n = n0 + wn - 64 + 32 * c + r32;
+    if (n >= N) continue;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int m = m0 + wm + 8 * (v >> 2) + 4 * h + (v & 3);
+      if (m < M) y[(int64_t)m * N + n] = acc[c][v];
+    }
   }
 }
 
-// ------------------------------------------------------------------ loss of Eq. 2 and the grid's minimum
-
-// loss += sum ( fp64(acc) * fp64(s_a[m]) * fp64(s_w[n]) - fp64(y_ref) )^2, fp64 throughout
-__global__ __launch_bounds__(256) void smooth_loss_kernel(const int32_t* acc, const float* s_a,
-                                                          const uint16_t* s_w, const float* y_ref, int64_t M,
-                                                          int64_t N, double* loss) {
-  __shared__ double part[256];
-  const int64_t total = M * N;
-  const int64_t stride = (int64_t)gridDim.x * 256;
-  double sum = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += stride) {
-    const int64_t m = i / N, n = i - m * N;
-    const double d = (double)acc[i] * (double)s_a[m] * (double)half_bits_to_float(s_w[n]) - (double)y_ref[i];
-    sum += d * d;
-  }
-  part[threadIdx.x] = sum;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) atomicAdd(loss, part[0]);
-}
+// ------------------------------------------------------------------ the grid's minimum
 
 __global__ void argmin_kernel(const double* losses, int G, int32_t* best) {
   if (blockIdx.x != 0 || threadIdx.x != 0) return;
@@ -285,40 +462,24 @@ static bool calib_shape_ok(int64_t M, int64_t N, int64_t K) {
          K <= 131072;
 }
 
-// workspace layout of qqq_adaptive_smoothing
-struct SmoothWs {
-  size_t absmax, top, y_ref, xs, ws, s, a_q, s_a, w_nat, s_w, packed, acc, y, gemm, total;
-};
-static SmoothWs smooth_layout(int64_t M, int64_t N, int64_t K) {
-  SmoothWs L;
-  size_t at = 0;
-  auto take = [&](size_t bytes) { const size_t o = at; at += align256c(bytes); return o; };
-  L.absmax = take((size_t)K * 4);
-  L.top = take(256);
-  L.y_ref = take((size_t)M * N * 4);
-  L.xs = take((size_t)M * K * 2);
-  L.ws = take((size_t)N * K * 2);
-  L.s = take((size_t)K * 4);
-  L.a_q = take((size_t)M * K);
-  L.s_a = take((size_t)M * 4);
-  L.w_nat = take((size_t)N * K / 2);
-  L.s_w = take((size_t)N * 2);
-  L.packed = take((size_t)N * K / 2);
-  L.acc = take((size_t)M * N * 4);
-  L.y = take((size_t)M * N * 2);
-  L.gemm = take(qqq_gemm_workspace_bytes(M, N, K));
-  L.total = at;
-  return L;
+// Workspace of qqq_adaptive_smoothing: the channel maxima, X W^T, and room for the smoothing vectors and quantised
+// operands of some grid points (M K + N K / 2 bytes and a little each; the terms below hold at least two)
+static size_t smooth_workspace_bytes(int64_t M, int64_t N, int64_t K) {
+  const size_t mk = (size_t)M * K, nk = (size_t)N * K, mn = (size_t)M * N;
+  size_t total = 2 * align256c((size_t)K * 4) + 256 + align256c((size_t)M * 4) + align256c((size_t)N * 2);
+  for (size_t bytes : {mn * 4, mk * 2, nk * 2, mk, nk / 2, nk / 2, mn * 4, mn * 2, qqq_gemm_workspace_bytes(M, N, K)})
+    total += align256c(bytes);
+  return total;
 }
 
 static int launch_absmax(const void* x, int64_t M, int64_t K, float* absmax, float* top, hipStream_t st) {
   int rc = fill_u32(absmax, (size_t)K, 0u, st);
   if (rc != QQQ_OK) return rc;
   const int64_t kvec = K / 8;
-  int64_t row_blocks = (M + 63) / 64;
+  int64_t row_blocks = (M + 31) / 32;
   if (row_blocks > 1024) row_blocks = 1024;
   const int64_t rows_per_block = (M + row_blocks - 1) / row_blocks;
-  hipLaunchKernelGGL(channel_absmax_kernel, dim3((unsigned)((kvec + 255) / 256), (unsigned)row_blocks), dim3(256), 0,
+  hipLaunchKernelGGL(channel_absmax_kernel, dim3((unsigned)((kvec + 31) / 32), (unsigned)row_blocks), dim3(256), 0,
                      st, (const uint4*)x, M, kvec, rows_per_block, (uint32_t*)absmax);
   rc = check_launch("channel_absmax");
   if (rc != QQQ_OK) return rc;
@@ -329,7 +490,7 @@ static int launch_absmax(const void* x, int64_t M, int64_t K, float* absmax, flo
 static int launch_smooth(const void* x, const void* w, const float* absmax, const float* sigmas, const int32_t* index,
                          int64_t M, int64_t N, int64_t K, void* xs, void* ws, float* s, hipStream_t st) {
   hipLaunchKernelGGL(smoothing_vector_kernel, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, absmax, sigmas, index,
-                     K, s);
+                     K, s, (int64_t)0);
   int rc = check_launch("smoothing_vector");
   if (rc != QQQ_OK) return rc;
   const int64_t kvec = K / 8;
@@ -344,8 +505,8 @@ static int launch_smooth(const void* x, const void* w, const float* absmax, cons
 }
 
 static int launch_fp16_gemm(const void* x, const void* w, int64_t M, int64_t N, int64_t K, float* y, hipStream_t st) {
-  hipLaunchKernelGGL(fp16_gemm_nt_kernel, dim3((unsigned)((N + 31) / 32), (unsigned)((M + 31) / 32)), dim3(64), 0, st,
-                     (const _Float16*)x, (const _Float16*)w, (int)M, (int)N, (int)K, y);
+  hipLaunchKernelGGL(fp16_gemm_nt_kernel, dim3((unsigned)((N + 127) / 128), (unsigned)((M + 63) / 64)), dim3(256), 0, st,
+                     (const uint4*)x, (const uint4*)w, (int)M, (int)N, (int)(K / 8), y);
   return check_launch("fp16_gemm_nt");
 }
 
@@ -390,7 +551,7 @@ int qqq_fp16_gemm_nt(const void* x_fp16, const void* w_fp16, int64_t M, int64_t 
 
 size_t qqq_smoothing_workspace_bytes(int64_t M, int64_t N, int64_t K) {
   if (!calib_shape_ok(M, N, K)) return 0;
-  return smooth_layout(M, N, K).total;
+  return smooth_workspace_bytes(M, N, K);
 }
 
 int qqq_adaptive_smoothing(const void* x_fp16, const void* w_fp16, int64_t M, int64_t N, int64_t K, int grid_points,
@@ -408,23 +569,26 @@ int qqq_adaptive_smoothing(const void* x_fp16, const void* w_fp16, int64_t M, in
       (reinterpret_cast<uintptr_t>(best) & 3u))
     return set_error(QQQ_ERR_SHAPE, "adaptive_smoothing: matrices, s and workspace must be 16-byte aligned, sigmas and "
                      "best 4-byte, losses 8-byte");
-  const SmoothWs L = smooth_layout(M, N, K);
-  if (workspace_bytes < L.total)
-    return set_error(QQQ_ERR_WORKSPACE, "adaptive_smoothing: workspace %zu bytes < %zu needed", workspace_bytes, L.total);
-  char* base = (char*)workspace;
+  const size_t total = qqq_smoothing_workspace_bytes(M, N, K);
+  if (workspace_bytes < total)
+    return set_error(QQQ_ERR_WORKSPACE, "adaptive_smoothing: workspace %zu bytes < %zu needed", workspace_bytes, total);
   hipStream_t st = (hipStream_t)stream;
-  float* absmax = (float*)(base + L.absmax);
-  float* top = (float*)(base + L.top);
-  float* y_ref = (float*)(base + L.y_ref);
-  int8_t* a_q = (int8_t*)(base + L.a_q);
-  float* s_a = (float*)(base + L.s_a);
-  uint32_t* w_nat = (uint32_t*)(base + L.w_nat);
-  void* s_w = base + L.s_w;
-  void* packed = base + L.packed;
-  int32_t* acc = (int32_t*)(base + L.acc);
-  void* y = base + L.y;
-  void* gemm_ws = base + L.gemm;
-  const size_t gemm_ws_bytes = qqq_gemm_workspace_bytes(M, N, K);
+  char* base = (char*)workspace;
+  size_t at = 0;
+  auto take = [&](size_t bytes) { char* p = base + at; at += align256c(bytes); return p; };
+  float* absmax = (float*)take((size_t)K * 4);
+  float* top = (float*)take(256);
+  float* y_ref = (float*)take((size_t)M * N * 4);
+  // a grid point's smoothing vector and quantised operands; as many points at a time as the workspace holds
+  const size_t first = at;
+  float* s_point = (float*)take((size_t)K * 4);
+  int8_t* a_q = (int8_t*)take((size_t)M * K);
+  float* s_a = (float*)take((size_t)M * 4);
+  uint8_t* packed = (uint8_t*)take((size_t)N * K / 2);
+  uint16_t* s_w = (uint16_t*)take((size_t)N * 2);
+  const int64_t point_bytes = (int64_t)(at - first);
+  const int64_t room = (int64_t)(total - first) / point_bytes;  // at least two: see smooth_workspace_bytes
+  const int at_once = room < grid_points ? (int)room : grid_points;
 
   int rc = launch_absmax(x_fp16, M, K, absmax, top, st);
   if (rc != QQQ_OK) return rc;
@@ -432,21 +596,33 @@ int qqq_adaptive_smoothing(const void* x_fp16, const void* w_fp16, int64_t M, in
   if ((rc = check_launch("sigma_grid")) != QQQ_OK) return rc;
   if ((rc = launch_fp16_gemm(x_fp16, w_fp16, M, N, K, y_ref, st)) != QQQ_OK) return rc;
   if ((rc = fill_u32(losses, (size_t)grid_points * 2, 0u, st)) != QQQ_OK) return rc;
-  if (gemm_ws_bytes && (rc = fill_u32(gemm_ws, (gemm_ws_bytes + 3) / 4, 0u, st)) != QQQ_OK) return rc;
-  for (int g = 0; g < grid_points; ++g) {
-    // the candidate's smoothed layer, quantised as the hot path quantises it, and its loss
-    if ((rc = launch_smooth(x_fp16, w_fp16, absmax, sigmas + g, nullptr, M, N, K, base + L.xs, base + L.ws,
-                            (float*)(base + L.s), st)) != QQQ_OK) return rc;
-    if ((rc = qqq_quant_act(base + L.xs, M, K, K, a_q, s_a, stream)) != QQQ_OK) return rc;
-    if ((rc = qqq_quantize_w4_perchannel(base + L.ws, N, K, K, w_nat, s_w, stream)) != QQQ_OK) return rc;
-    if ((rc = qqq_pack_w4(w_nat, N, K, packed, stream)) != QQQ_OK) return rc;
-    if ((rc = qqq_gemm_w4a8_perchannel(a_q, s_a, packed, s_w, y, acc, M, N, K, gemm_ws, gemm_ws_bytes, stream)) != QQQ_OK)
-      return rc;
-    const int64_t total = M * N;
-    const unsigned blocks = (unsigned)((total + 255) / 256 < 2048 ? (total + 255) / 256 : 2048);
-    hipLaunchKernelGGL(smooth_loss_kernel, dim3(blocks), dim3(256), 0, st, acc, s_a, (const uint16_t*)s_w, y_ref, M, N,
-                       losses + g);
-    if ((rc = check_launch("smooth_loss")) != QQQ_OK) return rc;
+  GemmParams p = {};
+  p.a_q = a_q;
+  p.s_a = s_a;
+  p.w = (const uint4*)packed;
+  p.s_w = (const _Float16*)s_w;
+  p.M = (int)M;
+  p.N = (int)N;
+  p.K = (int)K;
+  p.T = (int)(K / 128);
+  p.k_splits = 1;
+  p.y_ref = y_ref;
+  p.point_bytes = point_bytes;
+  const int kvec = (int)(K / 8);
+  for (int g = 0; g < grid_points; g += at_once) {
+    // the candidates' smoothed layers, quantised as the hot path quantises them, and their losses
+    const unsigned points = (unsigned)(grid_points - g < at_once ? grid_points - g : at_once);
+    hipLaunchKernelGGL(smoothing_vector_kernel, dim3((unsigned)((K + 255) / 256), points), dim3(256), 0, st, absmax,
+                       sigmas + g, (const int32_t*)nullptr, K, s_point, point_bytes);
+    auto activations = K <= 8192 ? point_activations_kernel<true> : point_activations_kernel<false>;
+    hipLaunchKernelGGL(activations, dim3((unsigned)M, points), dim3(256), 0, st, (const uint4*)x_fp16, s_point, kvec,
+                       point_bytes, a_q, s_a);
+    auto weights = K <= 4096 ? point_weights_kernel<true> : point_weights_kernel<false>;
+    hipLaunchKernelGGL(weights, dim3((unsigned)(N / 16), points), dim3(256), 0, st, (const uint4*)w_fp16, s_point, N, kvec,
+                       point_bytes, packed, s_w);
+    if ((rc = check_launch("smoothing grid point")) != QQQ_OK) return rc;
+    p.loss = losses + g;
+    if ((rc = launch_gemm_loss(p, (int)points, st)) != QQQ_OK) return rc;
   }
   hipLaunchKernelGGL(argmin_kernel, dim3(1), dim3(64), 0, st, losses, grid_points, best);
   if ((rc = check_launch("argmin")) != QQQ_OK) return rc;

@@ -35,10 +35,23 @@
 
 namespace qqq {
 
-template <int MODE, int MT, int CT, int NW, int ST>
-__global__ __launch_bounds__(NW * 64, 1) void gemm_prefill_dma_kernel(const GemmParams p,
+// LOSS: the smoothing search's form (see GemmParams::loss).
+template <int MODE, int MT, int CT, int NW, int ST, bool LOSS = false>
+__global__ __launch_bounds__(NW * 64, 1) void gemm_prefill_dma_kernel(const GemmParams args,
                                                                      const int tiles_m,
                                                                      const int tiles_n) {
+  auto of_point = [&]() {
+    GemmParams q = args;
+    if constexpr (LOSS) {
+      const int64_t off = q.point_bytes * blockIdx.y;
+      q.a_q += off;
+      q.s_a = (const float*)((const char*)q.s_a + off);
+      q.w = (const uint4*)((const char*)q.w + off);
+      q.s_w = (const _Float16*)((const char*)q.s_w + off);
+    }
+    return q;
+  };
+  const GemmParams p = of_point();
   using S = DmaShape<MT, CT, NW, ST>;
   __shared__ __attribute__((aligned(1024))) int8_t lds[S::kLds];
 
@@ -48,7 +61,7 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_prefill_dma_kernel(const Gemm
   const int64_t K = p.K;
   const int ntiles = N >> 4;
   // split K: workgroup y of gridDim.y takes k-steps [t_first, t_first + T) of the tile
-  const int split = blockIdx.y;
+  const int split = LOSS ? 0 : blockIdx.y;
   const int t_first = (int)((int64_t)p.T * split / p.k_splits);
   const int T = (int)((int64_t)p.T * (split + 1) / p.k_splits) - t_first;
 
@@ -414,6 +427,36 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_prefill_dma_kernel(const Gemm
   }
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 
+  if constexpr (LOSS) {
+    static_assert(MODE == kPerChannel, "the search quantises per channel");
+    // fp64(acc) * fp64(s_a) * fp64(s_w) - fp64(y_ref), squared and summed in fp64 (acc carries the exact factor 16)
+    double sum = 0.0;
+#pragma unroll
+    for (int c = 0; c < TC; ++c) {
+      const double sw = nvalid[c] ? (double)(float)p.s_w[col[c]] : 0.0;
+#pragma unroll
+      for (int mt = 0; mt < TM; ++mt)
+#pragma unroll
+        for (int v = 0; v < kRegs; ++v) {
+          const int m = m0 + acc_row(mt, v);
+          if (m < M && nvalid[c]) {
+            const double d = (double)(acc[mt][c][v] >> 4) * (double)p.s_a[m] * sw - (double)p.y_ref[(int64_t)m * N + col[c]];
+            sum += d * d;
+          }
+        }
+    }
+    double* part = (double*)lds;
+    part[tid] = sum;
+    __syncthreads();
+#pragma unroll
+    for (int w = NW * 32; w > 0; w >>= 1) {
+      if (tid < w) part[tid] += part[tid + w];
+      __syncthreads();
+    }
+    if (tid == 0) atomicAdd(p.loss + blockIdx.y, part[0]);
+    return;
+  }
+
   // ---- split K: the raw tile goes to this split's slab; the reduce kernel does the rest
   if (p.k_splits > 1) {
     int32_t* part = p.part + (int64_t)split * M * N;
@@ -520,6 +563,27 @@ static int launch_dma(const GemmParams& p, hipStream_t st) {
   route_note("prefill per-tile tile=%dx%d waves=%d ring=%d ksplit=%d mode=%d grid=%lld", S::kBM, S::kBN, NW, ST,
              p.k_splits, MODE, (long long)grid);
   return QQQ_OK;
+}
+
+// One launch for several grid points of the smoothing search: gridDim.y of them, each a GEMM of the same shape
+template <int MT, int CT, int NW>
+static int launch_loss(const GemmParams& p, int points, hipStream_t st) {
+  using S = DmaShape<MT, CT, NW, 3>;
+  const int tiles_m = (p.M + S::kBM - 1) / S::kBM, tiles_n = (p.N + S::kBN - 1) / S::kBN;
+  if ((int64_t)tiles_m * tiles_n > 0x7FFFFFFF) return set_error(QQQ_ERR_SHAPE, "smoothing: grid too large");
+  hipLaunchKernelGGL((gemm_prefill_dma_kernel<kPerChannel, MT, CT, NW, 3, true>),
+                     dim3((unsigned)(tiles_m * tiles_n), (unsigned)points), dim3(NW * 64), 0, st, p, tiles_m, tiles_n);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return set_error(QQQ_ERR_HIP, "smoothing gemm launch: %s", hipGetErrorString(e));
+  return QQQ_OK;
+}
+int launch_gemm_loss(const GemmParams& p, int points, hipStream_t st) {
+  switch (prefill_shape((int64_t)p.M * points, p.N, p.K)) {
+    case 0: return launch_loss<4, 2, 8>(p, points, st);
+    case 3: return launch_loss<4, 1, 8>(p, points, st);
+    case 4: return launch_loss<4, 1, 4>(p, points, st);
+  }
+  return launch_loss<2, 1, 4>(p, points, st);
 }
 
 // Second kernel of a K-split launch: sums the splits' raw tiles and applies the Dequant epilogue

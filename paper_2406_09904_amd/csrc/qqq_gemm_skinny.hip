@@ -69,12 +69,6 @@ __device__ __forceinline__ void spread_group_scales(int sgv, int nl, int (&sg)[N
 // (their products land in k-steps that consume_batch skips and in output rows that are never
 // stored).  With no branch around a load the compiler can count the loads issued after a batch
 // and waits only for that batch when it is consumed, leaving the next one in flight.
-// Workgroup barrier that orders LDS traffic only.  __syncthreads() would also wait for every
-// global load in flight, and here the first weight batches are deliberately still on their way.
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 template <int MODE, int NT, int MT, int U>
 __device__ __forceinline__ void load_batch_w(Batch<NT, MT, U>& b, const GemmParams& p, int tb,
                                              int tstride, int t1, int ng, uint32_t lane) {

@@ -54,6 +54,11 @@ struct GemmParams {
   // storing its raw int32 tile into part[split][M][N]; a second kernel sums and dequantises
   int k_splits;
   int32_t* part;
+  // smoothing search only (gridDim.y grid points, each with its own a_q, s_a, w and s_w, point_bytes apart): the
+  // tile's squared distance from y_ref goes into loss[point] instead of an output
+  const float* y_ref;    // [M,N]
+  double* loss;
+  int64_t point_bytes;   // from one grid point's operands to the next one's
   // fused activation quantisation (decode kernel only): fp16 rows instead of a_q/s_a
   const uint4* a_fp16;  // [M, lda] fp16 as 128-bit vectors, or nullptr
   int64_t lda_vec;      // row stride of a_fp16 in 128-bit vectors
@@ -85,6 +90,8 @@ int get_prefill_tuning();
 int get_prefill_ring_depth();
 int launch_gemm_prefill_dma(const GemmParams& p, int mode, int shape, hipStream_t st);
 int launch_gemm_prefill_ring(const GemmParams& p, int mode, hipStream_t st);
+int launch_gemm_loss(const GemmParams& p, int points, hipStream_t st);
+int prefill_shape(int64_t M, int64_t N, int64_t K);  // tile the cost model picks for an unsplit per-channel GEMM
 int launch_splitk_reduce(const GemmParams& p, int mode, hipStream_t st);
 void set_prefill_ksplit(int s);
 int get_prefill_ksplit();
@@ -175,6 +182,12 @@ __device__ __forceinline__ void unpack_group_fused(uint32_t x, const GroupFusedC
   hi = (int)__builtin_amdgcn_perm(as_u32(f3), as_u32(f1), 0x06020400u);
 }
 
+// Workgroup barrier that orders LDS traffic only.  __syncthreads() would also wait for every global load in flight,
+// which some kernels deliberately leave on their way.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 // ---- per-token activation quantisation arithmetic (Sec. 4.1), shared by the stand-alone pass
 // ---- and the decode kernel's fused prologue so both produce the same bits
 __device__ __forceinline__ float half_bits_to_float(uint32_t h16) {
@@ -227,6 +240,37 @@ __device__ __forceinline__ uint32_t quant4(uint32_t w0, uint32_t w1, float s) {
   const int q2 = quant1(half_bits_to_float(w1 & 0xFFFFu), s, rs), q3 = quant1(half_bits_to_float(w1 >> 16), s, rs);
   return (uint32_t)(q0 & 0xFF) | ((uint32_t)(q1 & 0xFF) << 8) | ((uint32_t)(q2 & 0xFF) << 16) |
          ((uint32_t)(q3 & 0xFF) << 24);
+}
+
+// ---- weight quantisation arithmetic (symmetric round to nearest, codes in [-7,7]), shared by the front-end and the
+// ---- smoothing search
+// fp16 bits of amax / q (fp32 IEEE division, one rounding to fp16)
+__device__ __forceinline__ uint16_t scale_bits(float amax, float q) {
+  return __builtin_bit_cast(uint16_t, (_Float16)(amax / q));
+}
+
+// clamp(rne(w / s), -7, 7), the quotient being the correctly rounded fp32 one, computed without
+// dividing in the common case: q~ = w * rcp(s) is within 2^-22 relative of w/s, and so is the
+// rounded quotient (2^-24); for |q~| < 8 both are then within 2^-19 absolute of w/s, so unless q~
+// lies within 2^-16 of a half-integer the two round to the same integer.  Beyond 8 in magnitude
+// either rounding clamps to +-7.  Only near a tie the IEEE division decides.
+__device__ __forceinline__ int rtn_code(uint32_t h16, float s, float rs) {
+  const float w = half_bits_to_float(h16);
+  const float q = w * rs;
+  float r = __builtin_rintf(q);
+  if (__builtin_fabsf(q - r) > 0.5f - 0x1p-16f) r = __builtin_rintf(w / s);
+  return (int)__builtin_amdgcn_fmed3f(r, -7.0f, 7.0f);
+}
+
+// packed nibble q takes natural nibble 4*(q%2) + q/2  (order 0,4,1,5,2,6,3,7)
+__device__ __forceinline__ uint32_t shuffle_nibbles_fwd(uint32_t w) {
+  uint32_t out = 0;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const int src = 4 * (q & 1) + (q >> 1);
+    out |= ((w >> (4 * src)) & 0xFu) << (4 * q);
+  }
+  return out;
 }
 
 // Sec. 3.3.2, integer scale s <= 16, biased route: u = code + 8 per nibble, four u per dword scaled

@@ -4,16 +4,7 @@
 
 namespace qqq {
 
-// packed nibble q takes natural nibble 4*(q%2) + q/2  (order 0,4,1,5,2,6,3,7)
-__device__ __forceinline__ uint32_t shuffle_nibbles_fwd(uint32_t w) {
-  uint32_t out = 0;
-#pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const int src = 4 * (q & 1) + (q >> 1);
-    out |= ((w >> (4 * src)) & 0xFu) << (4 * q);
-  }
-  return out;
-}
+// inverse of shuffle_nibbles_fwd
 __device__ __forceinline__ uint32_t shuffle_nibbles_inv(uint32_t w) {
   uint32_t out = 0;
 #pragma unroll

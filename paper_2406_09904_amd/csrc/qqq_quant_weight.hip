@@ -24,24 +24,6 @@ __device__ __forceinline__ uint32_t row16_max_u32(uint32_t v) {  // max over a 1
   return v;
 }
 
-// fp16 bits of amax / q (fp32 IEEE division, one rounding to fp16)
-__device__ __forceinline__ uint16_t scale_bits(float amax, float q) {
-  return __builtin_bit_cast(uint16_t, (_Float16)(amax / q));
-}
-
-// clamp(rne(w / s), -7, 7), the quotient being the correctly rounded fp32 one, computed without
-// dividing in the common case: q~ = w * rcp(s) is within 2^-22 relative of w/s, and so is the
-// rounded quotient (2^-24); for |q~| < 8 both are then within 2^-19 absolute of w/s, so unless q~
-// lies within 2^-16 of a half-integer the two round to the same integer.  Beyond 8 in magnitude
-// either rounding clamps to +-7.  Only near a tie the IEEE division decides.
-__device__ __forceinline__ int rtn_code(uint32_t h16, float s, float rs) {
-  const float w = half_bits_to_float(h16);
-  const float q = w * rs;
-  float r = __builtin_rintf(q);
-  if (__builtin_fabsf(q - r) > 0.5f - 0x1p-16f) r = __builtin_rintf(w / s);
-  return (int)__builtin_amdgcn_fmed3f(r, -7.0f, 7.0f);
-}
-
 // eight fp16 weights -> eight nibbles; *cmax = max |code|
 template <bool CMAX>
 __device__ __forceinline__ uint32_t quant8(uint4 v, float s, float rs, int* cmax) {

@@ -1,0 +1,51 @@
+"""The smoothing search's fused grid points where its kernels change path: K at and past the rows kept in registers
+(4096 weights, 8192 activations), channel groups not divisible by the eight XCDs, more grid points than the workspace
+holds at a time, ragged token counts and every GEMM tile; against the steps it stands for, one by one.
+
+The smoothed tensors, thresholds and vectors are compared bit for bit.  A loss is an fp64 sum built on exact integers and
+the fp32 reference product: from the steps' own integers, scales and reference product in another order it differs by
+rounding of fp64 only, 1e-12 (and the search's own reference product is the one qqq_fp16_gemm_nt returns).
+"""
+import pytest
+import torch
+
+from paper_2406_09904_amd import binding as qqq
+from paper_2406_09904_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,K,N,G", [(1, 128, 16, 3), (70, 4096, 144, 9), (33, 4224, 272, 4), (200, 8192, 128, 3),
+                                     (19, 8320, 48, 2), (300, 512, 4096, 21), (700, 256, 2064, 40)])
+def test_grid_points_equal_their_steps(M, K, N, G):
+    x = torch.from_numpy(synth.activations_fp16(M, K, 700 + M, "normal", 4 / K, 40.0)).cuda()
+    w = torch.from_numpy(synth.weights_fp16(N, K, 701 + M)).cuda()
+    w[N // 2].zero_()                                    # a channel of zeros
+    got = qqq.qqq_adaptive_smoothing(x, w, G)
+    amax = qqq.qqq_channel_absmax(x)
+    assert torch.equal(amax, x.float().abs().amax(dim=0))
+    ref = qqq.qqq_fp16_gemm_nt(x, w).double()
+    losses = []
+    for g in range(G):
+        xs, ws, _ = qqq.qqq_smooth_apply(x, w, amax, got["sigmas"][g:g + 1].clone())
+        a_q, s_a = qqq.qqq_quant_act(xs)
+        w_nat, s_w = qqq.qqq_quantize_w4_perchannel(ws)
+        acc = torch.empty((M, N), dtype=torch.int32, device="cuda")
+        qqq.qqq_gemm_w4a8_perchannel(a_q, s_a, qqq.qqq_pack_w4(w_nat, K), s_w, qqq.new_workspace(M, N, K), acc_out=acc)
+        losses.append((acc.double() * s_a.double()[:, None] * s_w.double()[None, :] - ref).square().sum())
+    losses = torch.stack(losses)
+    assert torch.allclose(got["losses"], losses, rtol=1e-12, atol=0.0)
+    best = int(got["best"].item())
+    assert best == int(torch.argmin(got["losses"]).item())
+    xs, ws, s = qqq.qqq_smooth_apply(x, w, amax, got["sigmas"][best:best + 1].clone())
+    assert torch.equal(got["xs"], xs) and torch.equal(got["ws"], ws) and torch.equal(got["s"], s)
+
+
+@pytest.mark.parametrize("M,K,N", [(1, 16, 1), (65, 48, 129), (64, 64, 128), (130, 80, 255), (33, 1040, 300)])
+def test_reference_product_tiles(M, K, N):
+    """Ragged 64 x 128 tiles and K not divisible by a stage of 64: |error| <= K 2^-24 sum |x w| (fp32 sums in any order)."""
+    x = torch.from_numpy(synth.activations_fp16(M, K, 800 + K, "normal", 0.02, 10.0)).cuda()
+    w = torch.from_numpy(synth.weights_fp16(N, K, 801 + K)).cuda()
+    y = qqq.qqq_fp16_gemm_nt(x, w).double()
+    bound = (x.double().abs() @ w.double().abs().t()) * K * 2.0 ** -24
+    assert bool(((y - x.double() @ w.double().t()).abs() <= bound).all())
