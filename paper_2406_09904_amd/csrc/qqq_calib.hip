@@ -190,7 +190,8 @@ __global__ __launch_bounds__(256) void point_activations_kernel(const uint4* x, 
 // 16 output channels per workgroup (qqq_quantize_w4_perchannel on W .* s, then qqq_pack_w4): a wave takes four
 // channels one after the other, its lanes hold the row (K <= 4096: in registers; else the row is smoothed
 // twice, 4096 channels at a time), and the codes meet in LDS in the packed layout's order, so whole 1 KiB chunks are
-// written.  Bound by vector instructions, about 14 per weight and grid point.
+// written.  Bound by vector instructions, about 12 per weight and grid point (9.5 us a grid point at K = N = 4096, 10.6
+// with the codes rounded, tested and packed one by one).
 template <bool ONE>
 __global__ __launch_bounds__(256) void point_weights_kernel(const uint4* w, const float* s, int64_t N, int kvec,
                                                             int64_t point_bytes, uint8_t* packed, uint16_t* s_w) {
@@ -242,14 +243,7 @@ __global__ __launch_bounds__(256) void point_weights_kernel(const uint4* w, cons
     for (int j = 0; j < 8; ++j) {
       const int i = lane + 64 * j;
       if (i0 + i >= kvec) continue;
-      const uint32_t h[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
-      uint32_t word = 0;
-      if (scale != 0.0f) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          word |= (uint32_t)(rtn_code(h[e] & 0xFFFFu, scale, rs) & 0xF) << (8 * e) |
-                  (uint32_t)(rtn_code(h[e] >> 16, scale, rs) & 0xF) << (8 * e + 4);
-      }
+      const uint32_t word = scale != 0.0f ? quant8<false>(v[j], scale, rs, nullptr) : 0u;
       const int o = i & 15, kc = (o & 7) >> 1, d = 2 * (o >> 3) + (o & 1);
       stage[(i >> 4) * 256 + (c + 16 * kc) * 4 + d] = shuffle_nibbles_fwd(word);
     }

@@ -195,15 +195,14 @@ __device__ __forceinline__ float half_bits_to_float(uint32_t h16) {
 }
 
 // |max| over the 8 fp16 values of a 128-bit vector, on the bit patterns (for finite values the
-// magnitude order of fp16 equals the integer order of the bits with the sign cleared)
+// magnitude order of fp16 equals the integer order of the bits with the sign cleared), two at a time
 __device__ __forceinline__ uint32_t absmax_bits(uint4 v, uint32_t cur) {
+  typedef unsigned short us2 __attribute__((ext_vector_type(2)));
   const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+  us2 m = __builtin_bit_cast(us2, w[0] & 0x7FFF7FFFu);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const uint32_t lo = w[i] & 0x7FFFu, hi = (w[i] >> 16) & 0x7FFFu;
-    cur = max(cur, max(lo, hi));
-  }
-  return cur;
+  for (int i = 1; i < 4; ++i) m = __builtin_elementwise_max(m, __builtin_bit_cast(us2, w[i] & 0x7FFF7FFFu));
+  return max(cur, max((uint32_t)m[0], (uint32_t)m[1]));
 }
 
 // Maximum over the 64 lanes of a wave, in every lane (wave-uniform result).  Data-parallel
@@ -249,17 +248,44 @@ __device__ __forceinline__ uint16_t scale_bits(float amax, float q) {
   return __builtin_bit_cast(uint16_t, (_Float16)(amax / q));
 }
 
-// clamp(rne(w / s), -7, 7), the quotient being the correctly rounded fp32 one, computed without
+// Eight fp16 weights -> eight nibbles of a natural word; CMAX: *cmax = max(*cmax, max |code|).
+// code = clamp(rne(w / s), -7, 7), the quotient being the correctly rounded fp32 one, computed without
 // dividing in the common case: q~ = w * rcp(s) is within 2^-22 relative of w/s, and so is the
 // rounded quotient (2^-24); for |q~| < 8 both are then within 2^-19 absolute of w/s, so unless q~
 // lies within 2^-16 of a half-integer the two round to the same integer.  Beyond 8 in magnitude
-// either rounding clamps to +-7.  Only near a tie the IEEE division decides.
-__device__ __forceinline__ int rtn_code(uint32_t h16, float s, float rs) {
-  const float w = half_bits_to_float(h16);
-  const float q = w * rs;
-  float r = __builtin_rintf(q);
-  if (__builtin_fabsf(q - r) > 0.5f - 0x1p-16f) r = __builtin_rintf(w / s);
-  return (int)__builtin_amdgcn_fmed3f(r, -7.0f, 7.0f);
+// either rounding clamps to +-7.  Only near a tie the IEEE division decides: one test for the eight of them.
+// The nibbles are put together in fp32, where sum (code_i + 8) 16^i over four of them is exact, and flipped from
+// offset binary to two's complement at the end: 12 instructions for eight codes instead of 24.
+template <bool CMAX>
+__device__ __forceinline__ uint32_t quant8(uint4 v, float s, float rs, float* cmax) {
+  const uint32_t h[4] = {v.x, v.y, v.z, v.w};
+  float w[8], r[8], far = 0.0f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    w[i] = half_bits_to_float(i & 1 ? h[i >> 1] >> 16 : h[i >> 1] & 0xFFFFu);
+    const float q = w[i] * rs;
+    r[i] = __builtin_rintf(q);
+    far = __builtin_fmaxf(far, __builtin_fabsf(q - r[i]));
+  }
+  if (far > 0.5f - 0x1p-16f) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) r[i] = __builtin_rintf(w[i] / s);
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) r[i] = __builtin_amdgcn_fmed3f(r[i], -7.0f, 7.0f);
+  if constexpr (CMAX) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) *cmax = __builtin_fmaxf(*cmax, __builtin_fabsf(r[i]));
+  }
+  uint32_t half[2];
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    float t = r[4 * g] + 34952.0f;  // 0x8888
+    t = __builtin_fmaf(r[4 * g + 1], 16.0f, t);
+    t = __builtin_fmaf(r[4 * g + 2], 256.0f, t);
+    half[g] = (uint32_t)__builtin_fmaf(r[4 * g + 3], 4096.0f, t);
+  }
+  return (half[0] | (half[1] << 16)) ^ 0x88888888u;
 }
 
 // packed nibble q takes natural nibble 4*(q%2) + q/2  (order 0,4,1,5,2,6,3,7)

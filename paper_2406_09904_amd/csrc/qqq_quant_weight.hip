@@ -24,20 +24,6 @@ __device__ __forceinline__ uint32_t row16_max_u32(uint32_t v) {  // max over a 1
   return v;
 }
 
-// eight fp16 weights -> eight nibbles; *cmax = max |code|
-template <bool CMAX>
-__device__ __forceinline__ uint32_t quant8(uint4 v, float s, float rs, int* cmax) {
-  const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-  uint32_t out = 0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int c0 = rtn_code(w[i] & 0xFFFFu, s, rs), c1 = rtn_code(w[i] >> 16, s, rs);
-    if constexpr (CMAX) *cmax = max(*cmax, max(abs(c0), abs(c1)));
-    out |= (uint32_t)(c0 & 0xF) << (8 * i) | (uint32_t)(c1 & 0xF) << (8 * i + 4);
-  }
-  return out;
-}
-
 struct GroupOut {
   uint16_t* s_wg;    // [G][N] or nullptr
   uint16_t* s_star;  // [G][N]
@@ -153,11 +139,11 @@ __global__ __launch_bounds__(64 * kWaves) void quant_weight_group_kernel(const u
         const uint32_t gmax = row16_max_u32(absmax_bits(v[j], 0));
         const uint16_t sgb = scale_bits(half_bits_to_float(gmax), 7.0f);
         const float sg = half_bits_to_float(sgb);
-        int cmax = 0;
+        float cmax = 0.0f;
         uint32_t codes = 0;
         if (sg != 0.0f) codes = quant8<true>(v[j], sg, __builtin_amdgcn_rcpf(sg), &cmax);
         if (idx < nvec) out[idx] = codes;
-        dmax_bits = max(dmax_bits, __builtin_bit_cast(uint32_t, (float)cmax * sg));
+        dmax_bits = max(dmax_bits, __builtin_bit_cast(uint32_t, cmax * sg));
         if constexpr (STAGED)
           if ((lane & 15) == 0 && idx < nvec) stage[((idx >> 4) << go.rows_log2) + r] = sgb;
       }
