@@ -28,6 +28,7 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 
 constexpr int kFB = 64;    // channels per factorisation block
 constexpr int kSB = 128;   // channels per sweep block (= a group of the per-group quantiser)
+constexpr int kFO = 256, kSO = 512;  // channels after which the rest of the matrix is updated
 static_assert(kSB == QQQ_GROUP, "a sweep block is one group");
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -105,15 +106,16 @@ __global__ __launch_bounds__(256) void prepare_kernel(const double* H, const _Fl
 // of the operands, register v of the result is row 4 v + l / 16, column l % 16.  Row strides of the LDS tiles
 // (34 and 80 doubles) put the 32 lanes of half a wave on all 64 banks.  The matrix pipe is the limit: each
 // fragment read feeds two MFMAs.
-// UPPER: only the tiles that reach the diagonal or lie above it (a symmetric C kept as its upper triangle).
+// UPPER: C is columns col0 .. col0 + N of a symmetric matrix kept as its upper triangle; only the tiles that reach the
+// diagonal or lie above it.
 template <bool UPPER, bool SUB>
 __global__ __launch_bounds__(256) void f64_update_kernel(const double* A, int64_t lda, const double* B, int64_t ldb,
-                                                         double* C, int64_t ldc, int M, int N, int kd) {
+                                                         double* C, int64_t ldc, int M, int N, int kd, int col0) {
   constexpr int kAs = 34, kBs = 80;
   __shared__ __attribute__((aligned(16))) double sa[64 * kAs];
   __shared__ __attribute__((aligned(16))) double sb[32 * kBs];
   const int tn = blockIdx.x, tm = blockIdx.y;
-  if (UPPER && tn < tm) return;
+  if (UPPER && col0 + tn * 64 + 63 < tm * 64) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int m0 = tm * 64, n0 = tn * 64;
   const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
@@ -445,12 +447,21 @@ int begin(const char* who, const void* w_fp16, const double* H, int64_t N, int64
   hipLaunchKernelGGL(prepare_kernel, dim3((unsigned)(K + N < 4096 ? K + N : 4096)), dim3(256), 0, st, H,
                      (const _Float16*)w_fp16, keep, damp, N, K, A, W64);
   if ((rc = check_launch("gptq prepare")) != QQQ_OK) return rc;
-  for (int64_t c0 = (K - 1) / kFB * kFB; c0 >= 0; c0 -= kFB) {
-    const unsigned tiles = (unsigned)(c0 / kFB);
-    hipLaunchKernelGGL(factor_panel_kernel, dim3(tiles ? tiles : 1), dim3(256), 0, st, A, K, (int)c0);
-    if (tiles)
-      hipLaunchKernelGGL((f64_update_kernel<true, true>), dim3(tiles, tiles), dim3(256), 0, st, A + c0, K, A + c0 * K,
-                         K, A, K, (int)c0, (int)c0, (int)(K - c0 < kFB ? K - c0 : kFB));
+  // Blocks of 64 from the last; each at once reduces the columns of its own kFO, and all columns before those are
+  // reduced by the whole kFO together (see sweep)
+  auto reduce = [&](int64_t c0, int64_t kd, int64_t col0, int64_t cols, int64_t rows) {
+    if (cols <= 0 || rows <= 0) return;
+    hipLaunchKernelGGL((f64_update_kernel<true, true>), dim3((unsigned)((cols + 63) / 64), (unsigned)((rows + 63) / 64)),
+                       dim3(256), 0, st, A + c0, K, A + c0 * K + col0, K, A + col0, K, (int)rows, (int)cols, (int)kd, (int)col0);
+  };
+  for (int64_t o0 = (K - 1) / kFO * kFO; o0 >= 0; o0 -= kFO) {
+    const int64_t o1 = o0 + kFO < K ? o0 + kFO : K;
+    for (int64_t c0 = (o1 - 1) / kFB * kFB; c0 >= o0; c0 -= kFB) {
+      const unsigned tiles = (unsigned)(c0 / kFB);
+      hipLaunchKernelGGL(factor_panel_kernel, dim3(tiles ? tiles : 1), dim3(256), 0, st, A, K, (int)c0);
+      reduce(c0, K - c0 < kFB ? K - c0 : kFB, o0, c0 - o0, c0);
+    }
+    reduce(o0, o1 - o0, 0, o0, o0);
   }
   if ((rc = check_launch("gptq factorisation")) != QQQ_OK) return rc;
   out->A = A;
@@ -462,14 +473,22 @@ int begin(const char* who, const void* w_fp16, const double* H, int64_t N, int64
 // Eq. 4 over all channels; scales: [N], or [K/128, N] (written) with group scales
 template <bool GROUP>
 int sweep(const Work& wk, const void* w_fp16, int64_t N, int64_t K, uint16_t* scales, uint32_t* w_nat, hipStream_t st) {
-  for (int64_t c0 = 0; c0 < K; c0 += kSB) {
-    hipLaunchKernelGGL((sweep_kernel<GROUP>), dim3((unsigned)((N + 31) / 32)), dim3(128), 0, st, (const _Float16*)w_fp16,
-                       wk.A, wk.keep, N, K, (int)c0, GROUP ? scales + c0 / kSB * N : scales, wk.W64, w_nat);
-    const int64_t rest = K - c0 - kSB;
-    if (rest > 0)
-      hipLaunchKernelGGL((f64_update_kernel<false, false>), dim3((unsigned)((rest + 63) / 64), (unsigned)((N + 63) / 64)),
-                         dim3(256), 0, st, wk.W64 + c0, K, wk.A + c0 * K + c0 + kSB, K, wk.W64 + c0 + kSB, K, (int)N,
-                         (int)rest, kSB);
+  // Blocks of 128 from the first; each at once moves the channels of its own kSO, and all channels after those are
+  // moved by the whole kSO together: a quarter of the passes over the running weights, and products deep enough for the
+  // matrix cores
+  auto move = [&](int64_t k0, int64_t kd, int64_t c0, int64_t cols) {
+    if (cols <= 0) return;
+    hipLaunchKernelGGL((f64_update_kernel<false, false>), dim3((unsigned)((cols + 63) / 64), (unsigned)((N + 63) / 64)),
+                       dim3(256), 0, st, wk.W64 + k0, K, wk.A + k0 * K + c0, K, wk.W64 + c0, K, (int)N, (int)cols, (int)kd, 0);
+  };
+  for (int64_t o0 = 0; o0 < K; o0 += kSO) {
+    const int64_t o1 = o0 + kSO < K ? o0 + kSO : K;
+    for (int64_t c0 = o0; c0 < o1; c0 += kSB) {
+      hipLaunchKernelGGL((sweep_kernel<GROUP>), dim3((unsigned)((N + 31) / 32)), dim3(128), 0, st, (const _Float16*)w_fp16,
+                         wk.A, wk.keep, N, K, (int)c0, GROUP ? scales + c0 / kSB * N : scales, wk.W64, w_nat);
+      move(c0, kSB, c0 + kSB, o1 - c0 - kSB);
+    }
+    move(o0, kSO, o1, K - o1);
   }
   return check_launch("gptq sweep");
 }

@@ -29,7 +29,7 @@ def dev16(bits):
     return to_dev(np.ascontiguousarray(bits).view(np.uint16), torch)
 
 
-@pytest.mark.parametrize("K,N", [(8, 1), (64, 31), (72, 33), (128, 32), (200, 65), (328, 130), (576, 70)])
+@pytest.mark.parametrize("K,N", [(8, 1), (64, 31), (72, 33), (128, 32), (200, 65), (328, 130), (576, 70), (1160, 40)])
 def test_per_channel_sweep_at_block_edges(K, N):
     x, w = layer(2 * K + 10, K, N, 400 + K + N)
     H = cal.hessian(x)
@@ -52,7 +52,7 @@ def test_hessian_tiles(M, K, shift):
     assert np.array_equal(H, cal.hessian(x.view(np.uint16)))
 
 
-@pytest.mark.parametrize("K,N", [(128, 1), (256, 33), (640, 97)])
+@pytest.mark.parametrize("K,N", [(128, 1), (256, 33), (640, 97), (1152, 20)])
 def test_per_group_sweep_at_block_edges(K, N):
     x, w = layer(2 * K + 10, K, N, 500 + K + N)
     H = cal.hessian(x)
