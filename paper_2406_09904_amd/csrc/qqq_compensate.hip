@@ -15,8 +15,8 @@
 //   sweep          per 128 channels, from the first: sweep_kernel, then the update of the channels after
 // What is left serial is one dependent step per channel, in registers.
 // Bound: K = N = 4096 holds 2.3e10 + 6.9e10 fp64 operations, 1.3 ms at the 70 TFLOP/s a large fp64 product
-// reaches here.  Measured, K = N = 4096: 8.9 ms (an inverse by K rank-1 sweeps and a rank-1 update of both matrices
-// per channel: 360 ms); K = 2048, N = 5632 with group scales: 4.1 ms (81 ms).
+// reaches here.  Measured, K = N = 4096: 8.2 ms (an inverse by K rank-1 sweeps and a rank-1 update of both matrices
+// per channel: 360 ms); K = 2048, N = 5632 with group scales: 3.9 ms (81 ms).
 #include "qqq_calib.h"
 #include "qqq_internal.h"
 
@@ -100,7 +100,7 @@ __global__ __launch_bounds__(256) void prepare_kernel(const double* H, const _Fl
   }
 }
 
-// C += (or -=) A B in fp64: C [M,N], A [M,kd], B [kd,N], all row-major and 16-byte aligned, N and kd even.
+// C += (or -=) A B in fp64: C [M,N], A [M,kd], B [kd,N], all row-major and 16-byte aligned, N, kd and the strides even.
 // 64 x 64 tile per workgroup, a wave per 32 x 32 quarter, 32 of kd at a time through LDS with the next
 // 32 already requested.  v_mfma_f64_16x16x4_f64 (64 clocks): lane l holds row (column) l % 16 and k = l / 16
 // of the operands, register v of the result is row 4 v + l / 16, column l % 16.  Row strides of the LDS tiles
@@ -121,16 +121,24 @@ __global__ __launch_bounds__(256) void f64_update_kernel(const double* A, int64_
   const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
   const int l16 = lane & 15, q = lane >> 4;
 
+  // Every load is in range and unconditional: rows past M and columns past N repeat the last ones (they only reach results
+  // that are not stored), k past kd is replaced by zeros on the way to LDS, a k-step later.  (A conditional load of the
+  // struct becomes a choice between its address and one in scratch memory, which makes every load a flat one.)
+  const double2* pa[4];
+  const double2* pb[4];
   double2 ra[4], rb[4];
-  const double2 zero = make_double2(0.0, 0.0);
-  auto fetch = [&](int k0) {  // out-of-range elements feed zeros
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int e = tid + 256 * j;
+    pa[j] = reinterpret_cast<const double2*>(A + (int64_t)min(m0 + (e >> 4), M - 1) * lda);
+    pb[j] = reinterpret_cast<const double2*>(B + min(n0 + 2 * (e & 31), N - 2));
+  }
+  auto fetch = [&](int k0) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int e = tid + 256 * j;
-      const int row = e >> 4, ka = k0 + 2 * (e & 15);
-      ra[j] = (m0 + row < M && ka < kd) ? *reinterpret_cast<const double2*>(A + (int64_t)(m0 + row) * lda + ka) : zero;
-      const int k = k0 + (e >> 5), col = n0 + 2 * (e & 31);
-      rb[j] = (k < kd && col < N) ? *reinterpret_cast<const double2*>(B + (int64_t)k * ldb + col) : zero;
+      ra[j] = pa[j][min(k0 + 2 * (e & 15), kd - 2) >> 1];
+      rb[j] = pb[j][min(k0 + (e >> 5), kd - 1) * (ldb >> 1)];
     }
   };
   fetch(0);
@@ -142,15 +150,18 @@ __global__ __launch_bounds__(256) void f64_update_kernel(const double* A, int64_
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int row = m0 + wr + 16 * i + 4 * v + q, col = n0 + wc + 16 * j + l16;
-        acc[i][j][v] = (row < M && col < N) ? C[(int64_t)row * ldc + col] : 0.0;
+        acc[i][j][v] = C[(int64_t)min(row, M - 1) * ldc + min(col, N - 1)];
       }
   for (int k0 = 0; k0 < kd; k0 += 32) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int e = tid + 256 * j;
-      const double2 a = SUB ? make_double2(-ra[j].x, -ra[j].y) : ra[j];
+      double2 a = SUB ? make_double2(-ra[j].x, -ra[j].y) : ra[j];
+      double2 b = rb[j];
+      if (k0 + 2 * (e & 15) >= kd) a.x = a.y = 0.0;
+      if (k0 + (e >> 5) >= kd) b.x = b.y = 0.0;
       *reinterpret_cast<double2*>(&sa[(e >> 4) * kAs + 2 * (e & 15)]) = a;
-      *reinterpret_cast<double2*>(&sb[(e >> 5) * kBs + 2 * (e & 31)]) = rb[j];
+      *reinterpret_cast<double2*>(&sb[(e >> 5) * kBs + 2 * (e & 31)]) = b;
     }
     __syncthreads();
     if (k0 + 32 < kd) fetch(k0 + 32);
