@@ -15,8 +15,8 @@
 //   sweep          per 128 channels, from the first: sweep_kernel, then the update of the channels after
 // What is left serial is one dependent step per channel, in registers.
 // Bound: K = N = 4096 holds 2.3e10 + 6.9e10 fp64 operations, 1.3 ms at the 70 TFLOP/s a large fp64 product
-// reaches here.  Measured, K = N = 4096: 8.2 ms (an inverse by K rank-1 sweeps and a rank-1 update of both matrices
-// per channel: 360 ms); K = 2048, N = 5632 with group scales: 3.9 ms (81 ms).
+// reaches here.  Measured, K = N = 4096: 6.9 ms (an inverse by K rank-1 sweeps and a rank-1 update of both matrices
+// per channel: 360 ms); K = 2048, N = 5632 with group scales: 3.2 ms (81 ms).
 #include "qqq_calib.h"
 #include "qqq_internal.h"
 
@@ -47,6 +47,22 @@ __device__ __forceinline__ double quad_broadcast(double x) {
   const uint64_t u = __builtin_bit_cast(uint64_t, x);
   const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, sel, 0xF, 0xF, true);
   const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), sel, 0xF, 0xF, true);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+// one 64-bit value of lane SRC of every sixteen lanes, in all sixteen
+template <int SRC>
+__device__ __forceinline__ double row_broadcast(double x) {
+  constexpr int sel = 0x150 + SRC;  // row_newbcast
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, sel, 0xF, 0xF, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), sel, 0xF, 0xF, true);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+// one 64-bit value of one lane (the same index on every lane), in all lanes
+__device__ __forceinline__ double lane_value(double x, int src) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, src);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), src);
   return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 template <int XOR>  // value of lane ^ XOR within four lanes
@@ -193,84 +209,123 @@ __global__ __launch_bounds__(256) void f64_update_kernel(const double* A, int64_
 
 // One block [c0, c0 + 64) of H = R D R^T, the channels after it already eliminated from A.
 // Every workgroup factors the 64 x 64 diagonal block for itself (64 dependent steps: column j's pivot
-// d_j, R[i,j] = A[i,j] / d_j for i < j, A[i,k] -= R[i,j] A[k,j] for k < j) and then solves for its own 64 of
+// d_j, R[i,j] = A[i,j] / d_j for i < j, A[i,k] -= R[i,j] A[k,j] for k < j) and then solves for its own 32 of
 // the c0 rows above: y_j = a_j - sum_{k > j} y_k R[j,k], x_j = y_j / d_j, i.e. R = x and R D = y there.
 // Written: x in place (A[row, c0 + j]) and y transposed into the unused lower triangle (A[c0 + j, row]),
 // which is the row-major operand the update of the rows above wants; the diagonal block's R goes
 // transposed below the diagonal (its upper half is still being read by other workgroups).
-// Lane = row of the block, wave w = its columns w mod 4, so a step needs one barrier: the column's owner
-// publishes it, everyone divides and updates.
+// Bound by the chain of 64 pivots and, where code runs once, by its fetch: both halves walk 16 columns at a time
+// in a loop, so that one body of a few KiB serves the whole block (written out straight, 42 KiB of instructions
+// took 44.7 us a block whatever the row count; the loops take 24.7).
+// Diagonal block: the 16 columns first receive what the columns after them owe (fp64 MFMA, a wave per 16 rows), then
+// one wave with lane = row takes their 16 steps in registers; pivots and column elements reach all lanes
+// through v_readlane.  Rows above: 16 lanes per row, the solved element spread over them by a DPP move.
 __global__ __launch_bounds__(256) void factor_panel_kernel(double* A, int64_t K, int c0) {
-  __shared__ double colbuf[2][64];
-  __shared__ double rt[64][66];  // rt[j][i] = R[c0 + i, c0 + j] for i < j, else 0
-  __shared__ double rcp[64];     // 1 / d_j
+  constexpr int kS = 66;
+  __shared__ __attribute__((aligned(16))) double ys[64 * kS];  // [i][j]: the block, then R D for i < j, 0 from the diagonal on
+  __shared__ __attribute__((aligned(16))) double xs[64 * kS];  // [i][j]: R for i < j, else 0
+  __shared__ double rcp[64];                                   // 1 / d_j
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l16 = lane & 15, q = lane >> 4;
   const int nb = min(64, (int)K - c0);
-  // ---- the rows this workgroup solves: four lanes per row, lane's columns 4 r + (tid & 3)
-  const int64_t row = (int64_t)blockIdx.x * 64 + (tid >> 2);
-  const int ql = tid & 3;
-  const bool live = row < c0;
-  double y[16];
+  // ---- the rows this workgroup solves: 8 wave + 4 v + q, this lane's columns 16 r + l16
+  const int64_t row0 = (int64_t)blockIdx.x * 32 + 8 * wave + q;
+  double y[2][4];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) y[r] = (live && 4 * r + ql < nb) ? A[row * K + c0 + 4 * r + ql] : 0.0;
+  for (int v = 0; v < 2; ++v)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      y[v][r] = (row0 + 4 * v < c0 && 16 * r + l16 < nb) ? A[(row0 + 4 * v) * K + c0 + 16 * r + l16] : 0.0;
 
-  {  // ---- the diagonal block; channels past K are identity
-    double a[16];  // element (lane, 4 r + wave), valid for lane <= column
+  // ---- the diagonal block, upper triangle; channels past K are identity
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int j = 4 * r + wave;
-      a[r] = (lane < nb && j < nb && lane <= j) ? A[(int64_t)(c0 + lane) * K + c0 + j] : (lane == j ? 1.0 : 0.0);
-    }
+  for (int e = 0; e < 16; ++e) {
+    const int i = 4 * e + wave, j = lane;
+    ys[i * kS + j] = (i <= j && j < nb) ? A[(int64_t)(c0 + i) * K + c0 + j] : (i == j ? 1.0 : 0.0);
+  }
+  __syncthreads();
+#pragma nounroll
+  for (int p = 3; p >= 0; --p) {
+    if (p < 3) {
+      if (wave <= p) {
+        v4d acc;
 #pragma unroll
-    for (int j = 63; j >= 0; --j) {
-      double* col = colbuf[j & 1];
-      if (wave == (j & 3)) col[lane] = a[j >> 2];
-      __syncthreads();
-      const double rd = 1.0 / col[j];
-      const double x = lane < j ? col[lane] * rd : 0.0;
-      if (wave == (j & 3)) {
-        rt[j][lane] = x;
-        if (lane == 0) rcp[j] = rd;
+        for (int v = 0; v < 4; ++v) acc[v] = ys[(16 * wave + 4 * v + q) * kS + 16 * p + l16];
+        for (int k = 16 * (p + 1); k < 64; k += 4)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-xs[(16 * wave + l16) * kS + k + q], ys[(16 * p + l16) * kS + k + q],
+                                                     acc, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) ys[(16 * wave + 4 * v + q) * kS + 16 * p + l16] = acc[v];
       }
+      __syncthreads();
+    }
+    if (wave == 0) {
+      double a[16];  // element (lane, 16 p + k); below the diagonal whatever the steps leave, never used
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (4 * r < j) {  // (columns at or past j, and rows at or past j, are finished or zero: x is 0 there)
-          const int k = 4 * r + wave;
-          const double m = k < j ? col[k] : 0.0;
-          a[r] = __builtin_fma(-x, m, a[r]);
-        }
+      for (int k = 0; k < 16; ++k) a[k] = ys[lane * kS + 16 * p + k];
+#pragma unroll
+      for (int j = 15; j >= 0; --j) {
+        const double d = lane_value(a[j], 16 * p + j);
+        double rd = __builtin_amdgcn_rcp(d);  // two Newton steps: within an ulp or so of 1 / d
+        rd = __builtin_fma(__builtin_fma(-d, rd, 1.0), rd, rd);
+        rd = __builtin_fma(__builtin_fma(-d, rd, 1.0), rd, rd);
+        const bool above = lane < 16 * p + j;
+        const double x = above ? a[j] * rd : 0.0;
+#pragma unroll
+        for (int k = 0; k < j; ++k) a[k] = __builtin_fma(-x, lane_value(a[j], 16 * p + k), a[k]);
+        xs[lane * kS + 16 * p + j] = x;
+        ys[lane * kS + 16 * p + j] = above ? a[j] : 0.0;
+        if (lane == 0) rcp[16 * p + j] = rd;
+      }
+    }
+    __syncthreads();
+  }
+  if (blockIdx.x == 0) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int j = 4 * e + wave, i = lane;
+      if (i < j && j < nb) A[(int64_t)(c0 + j) * K + c0 + i] = xs[i * kS + j];
+    }
+  }
+  if (c0 == 0) return;
+  // ---- the solve, column by column from the last; xs is zero at and past the diagonal.  The 16 columns in turn are always
+  // y[.][3]: the others move up behind them (what moves into finished places is not used)
+#pragma nounroll
+  for (int p = 3; p >= 0; --p) {
+    // R[16 (p - 3 + r) + l16][16 p + j]; where that row is before the block, row l16 feeds places no longer used
+    const double* rr[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) rr[r] = xs + (16 * max(p - 3 + r, 0) + l16) * kS + 16 * p;
+#define QQQ_SOLVE(J)                                                                             \
+  {                                                                                              \
+    const double m0 = rr[0][J], m1 = rr[1][J], m2 = rr[2][J], m3 = rr[3][J];                     \
+    _Pragma("unroll") for (int v = 0; v < 2; ++v) {                                              \
+      const double yj = row_broadcast<J>(y[v][3]);                                               \
+      y[v][3] = __builtin_fma(-yj, m3, y[v][3]);                                                 \
+      y[v][2] = __builtin_fma(-yj, m2, y[v][2]);                                                 \
+      y[v][1] = __builtin_fma(-yj, m1, y[v][1]);                                                 \
+      y[v][0] = __builtin_fma(-yj, m0, y[v][0]);                                                 \
+    }                                                                                            \
+  }
+    QQQ_SOLVE(15) QQQ_SOLVE(14) QQQ_SOLVE(13) QQQ_SOLVE(12) QQQ_SOLVE(11) QQQ_SOLVE(10) QQQ_SOLVE(9) QQQ_SOLVE(8)
+    QQQ_SOLVE(7) QQQ_SOLVE(6) QQQ_SOLVE(5) QQQ_SOLVE(4) QQQ_SOLVE(3) QQQ_SOLVE(2) QQQ_SOLVE(1) QQQ_SOLVE(0)
+#undef QQQ_SOLVE
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+      const int col = 16 * p + l16;
+      if (row0 + 4 * v < c0 && col < nb) A[(row0 + 4 * v) * K + c0 + col] = y[v][3] * rcp[col];
+      ys[col * kS + 8 * wave + 4 * v + q] = y[v][3];  // (nothing reads the block's R D any more)
+      y[v][3] = y[v][2];
+      y[v][2] = y[v][1];
+      y[v][1] = y[v][0];
     }
   }
   __syncthreads();
-  if (blockIdx.x == 0) {
-    for (int e = tid; e < 64 * 64; e += 256) {
-      const int j = e >> 6, i = e & 63;
-      if (i < j && j < nb) A[(int64_t)(c0 + j) * K + c0 + i] = rt[j][i];
-    }
-  }
-  // ---- the solve, column by column from the last; rt is zero at and past the diagonal
-#define QQQ_SOLVE(J, O)                                                                      \
-  {                                                                                          \
-    const double yj = quad_broadcast<O>(y[(J) >> 2]);                                        \
-    _Pragma("unroll") for (int r = 0; r <= ((J) >> 2); ++r)                                  \
-        y[r] = __builtin_fma(-yj, rt[J][4 * r + ql], y[r]);                                  \
-  }
 #pragma unroll
-  for (int r4 = 15; r4 >= 0; --r4) {
-    QQQ_SOLVE(4 * r4 + 3, 3)
-    QQQ_SOLVE(4 * r4 + 2, 2)
-    QQQ_SOLVE(4 * r4 + 1, 1)
-    QQQ_SOLVE(4 * r4 + 0, 0)
-  }
-#undef QQQ_SOLVE
-  if (!live) return;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int j = 4 * r + ql;
-    if (j < nb) {
-      A[row * K + c0 + j] = y[r] * rcp[j];
-      A[(int64_t)(c0 + j) * K + row] = y[r];
-    }
+  for (int e = 0; e < 8; ++e) {
+    const int j = 8 * e + (tid >> 5), i = tid & 31;
+    const int64_t row = (int64_t)blockIdx.x * 32 + i;
+    if (j < nb && row < c0) A[(int64_t)(c0 + j) * K + row] = ys[j * kS + i];
   }
 }
 
@@ -468,7 +523,7 @@ int begin(const char* who, const void* w_fp16, const double* H, int64_t N, int64
   for (int64_t o0 = (K - 1) / kFO * kFO; o0 >= 0; o0 -= kFO) {
     const int64_t o1 = o0 + kFO < K ? o0 + kFO : K;
     for (int64_t c0 = (o1 - 1) / kFB * kFB; c0 >= o0; c0 -= kFB) {
-      const unsigned tiles = (unsigned)(c0 / kFB);
+      const unsigned tiles = (unsigned)(c0 / 32);
       hipLaunchKernelGGL(factor_panel_kernel, dim3(tiles ? tiles : 1), dim3(256), 0, st, A, K, (int)c0);
       reduce(c0, K - c0 < kFB ? K - c0 : kFB, o0, c0 - o0, c0);
     }
