@@ -12,13 +12,15 @@
 //
 // Both parts are blocked so that almost all of their arithmetic is fp64 MFMA (f64_update_kernel):
 //   factorisation  per 64 channels, from the last: factor_panel_kernel, then the update of the channels before
-//   sweep          per 128 channels, from the first: sweep_kernel, then the update of the channels after
+//   sweep          per 512 channels, from the first: sweep_kernel, then the update of the channels after
 // What is left serial is one dependent step per channel, in registers.
 // Bound: K = N = 4096 holds 2.3e10 + 6.9e10 fp64 operations, 1.3 ms at the 70 TFLOP/s a large fp64 product
-// reaches here.  Measured, K = N = 4096: 6.9 ms (an inverse by K rank-1 sweeps and a rank-1 update of both matrices
-// per channel: 360 ms); K = 2048, N = 5632 with group scales: 3.2 ms (81 ms).
+// reaches here.  Measured, K = N = 4096: 5.6 ms (an inverse by K rank-1 sweeps and a rank-1 update of both matrices
+// per channel: 360 ms); K = 2048, N = 5632 with group scales: 2.4 ms (81 ms).
 #include "qqq_calib.h"
 #include "qqq_internal.h"
+
+#include <type_traits>
 
 namespace qqq {
 
@@ -31,6 +33,9 @@ constexpr int kSB = 128;   // channels per sweep block (= a group of the per-gro
 constexpr int kFO = 256, kSO = 512;  // channels after which the rest of the matrix is updated
 static_assert(kSB == QQQ_GROUP, "a sweep block is one group");
 
+template <int V>
+using Width = std::integral_constant<int, V>;
+
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
@@ -40,15 +45,6 @@ int check_launch(const char* what) {
   return QQQ_OK;
 }
 
-// one 64-bit value of lane SRC of every four lanes, in all four (no LDS, no scalar registers)
-template <int SRC>
-__device__ __forceinline__ double quad_broadcast(double x) {
-  constexpr int sel = SRC * 0x55;  // quad_perm [SRC, SRC, SRC, SRC]
-  const uint64_t u = __builtin_bit_cast(uint64_t, x);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, sel, 0xF, 0xF, true);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), sel, 0xF, 0xF, true);
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
 // one 64-bit value of lane SRC of every sixteen lanes, in all sixteen
 template <int SRC>
 __device__ __forceinline__ double row_broadcast(double x) {
@@ -69,6 +65,18 @@ template <int XOR>  // value of lane ^ XOR within four lanes
 __device__ __forceinline__ uint32_t quad_swap(uint32_t x) {
   constexpr int sel = XOR == 1 ? 0xB1 : 0x4E;
   return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, sel, 0xF, 0xF, true);
+}
+__device__ __forceinline__ uint32_t half_row_mirror(uint32_t x) {  // value of lane 7 - i of every eight lanes
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xF, 0xF, true);
+}
+__device__ __forceinline__ float row_max(float x) {  // largest of every sixteen lanes, in all sixteen
+  auto rotated = [&](auto ctrl) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xF, 0xF, true));
+  };
+  x = fmaxf(x, rotated(Width<0x128>{}));  // row_ror by 8, 4, 2, 1
+  x = fmaxf(x, rotated(Width<0x124>{}));
+  x = fmaxf(x, rotated(Width<0x122>{}));
+  return fmaxf(x, rotated(Width<0x121>{}));
 }
 
 // keep[i] = 0 for a channel that never fired (H_ii == 0: its weight counts as 0), else 1;
@@ -329,127 +337,204 @@ __global__ __launch_bounds__(256) void factor_panel_kernel(double* A, int64_t K,
   }
 }
 
-// Channels [c0, c0 + 128) of every output channel, one after the other: code of the running weight, then the
-// move of the later channels of the block,
+// Channels [o0, o1) of every output channel, one after the other: code of the running weight, then the
+// move of the later channels,
 //   q = clamp(rne(fp32(w / s)), -7, 7), s == 0 gives 0;  w_j += (W_i - q s) R[i,j] for j > i.
-// Four lanes per output channel, lane's channels 4 r + (lane % 4) in registers; a step is the quotient, its
-// rounding and one multiply-add per later channel the lane holds, the broadcast of W_i - q s inside the
-// four lanes being a data-parallel move.  R's block sits in LDS as rows of what a step still needs (row i from
-// channel 4 (i / 4) on, zeros up to the diagonal).  Bound by the chain of dependent fp64 operations
-// (about 12 per channel), so workgroups are kept at 32 output channels to spread them over the chip.
+// An output channel never needs another one, so a workgroup takes 16 of them through all these channels, 128 at a time:
+// what the 128 owe to those before (from o0 on) as one fp64 MFMA product, then the chain.  Bound by that chain of
+// dependent fp64 operations (about 12 a channel): sixteen lanes per output channel, lane's channels 16 r + (lane % 16) in
+// registers, so that 4096 output channels put a wave on every SIMD; a step is the quotient, its rounding and one
+// multiply-add per 16 later channels, the broadcast of W_i - q s inside the sixteen lanes being a data-parallel move.
+// The steps are a loop over 16 channels whose registers move down one place each time: one body for 128 channels
+// (written out straight, 40 to 73 KiB of instructions, each fetched for one use, took 65 to 81 us per 128 channels and the
+// separate products 20 more; this form takes 33 for all of it, 4096 output channels).
+// R's block sits in LDS as rows of what a step still needs: row i from channel 16 (i / 16) on, zeros up to the diagonal, one
+// double apart from a multiple of the banks.
 // The quotient: w * (1/s) corrected by its exact remainder, which is the correctly rounded w / s.
 // GROUP: the scale is taken here, s = fp16(fp32(max |w|) / 7) over the block as Eq. 4 leaves its weights when the
 // sweep enters it.  What has been added up so far for channel j, P_j = sum over i < c0 of (W_i - Q_i) R[i,j], is
 // its move once the block's earlier channels have had theirs; with none of them quantised yet, the move z of
 // all channels solves z R = P over the block's triangle (z = P for its first channel).
-// W64's block is overwritten with W_i - q s, the left operand of the update of the channels after.
+// W64 is overwritten with W_i - q s, the left operand of the update of the channels after.
 template <bool GROUP>
-__global__ __launch_bounds__(128) void sweep_kernel(const _Float16* w, const double* A, const double* keep, int64_t N,
-                                                    int64_t K, int c0, uint16_t* scales, double* W64, uint32_t* w_nat) {
-  constexpr int kRows = 16 * (32 * 33 / 2);  // doubles: the sum over i of 128 - 4 (i / 4)
-  __shared__ __attribute__((aligned(16))) double rl[kRows];
-  const int tid = threadIdx.x, ql = tid & 3;
-  const int nb = min(kSB, (int)K - c0);
-  const int64_t row = (int64_t)blockIdx.x * 32 + (tid >> 2);
+__global__ __launch_bounds__(256, 2) void sweep_kernel(const _Float16* w, const double* A, const double* keep, int64_t N,
+                                                    int64_t K, int o0, int o1, uint16_t* scales, double* W64,
+                                                    uint32_t* w_nat) {
+  constexpr int kRows = 16 * (16 * 36 + 8);  // doubles: 16 rows of 129 - 16 r for r = 0 .. 7
+  constexpr int kXs = 130;                   // the product's 16 rows, in the same place before R is
+  __shared__ __attribute__((aligned(16))) double rl[kRows + 64];  // (a step reads up to three vectors of 16 past its row)
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l16 = lane & 15, q = lane >> 4;
+  const int64_t n0 = (int64_t)blockIdx.x * 16;
+  const int64_t row = n0 + 4 * wave + q;
   const int64_t n = row < N ? row : N - 1;  // (rows past N repeat the last one and store nothing)
-  const int64_t at = n * K + c0 + ql;
-
-  double acc[32];
-  float wo[32];
+  const int64_t nl = n0 + l16 < N ? n0 + l16 : N - 1;
+  auto r_base = [](int r) { return 16 * (129 * r - 8 * r * (r - 1)); };
+  // row 16 r + o of R from channel 16 r on, this lane's channels.  A step's row is read during the step before.  The scheduling
+  // barriers between steps keep the compiler from reading all sixteen at once, the empty asm statements from putting the
+  // multiply-adds of later channels off until after the loop (either way 16 rows of R in registers, and spills)
+  auto fetch_row = [&](int r, int o, auto& to) {
+    const double* from = rl + r_base(r) + o * (129 - 16 * r) + l16;
 #pragma unroll
-  for (int r = 0; r < 32; ++r) {
-    const bool in = 4 * r + ql < nb;
-    acc[r] = in ? W64[at + 4 * r] : 0.0;
-    wo[r] = (in && keep[c0 + 4 * r + ql] != 0.0) ? (float)w[at + 4 * r] : 0.0f;
-  }
-  // R: strictly upper part; where i and j share a factorisation block it lies transposed below the diagonal
-  for (int e = tid; e < 32 * 4 * 128; e += 128) {
-    const int i = e >> 7, j = e & 127;
-    const int r4 = i >> 2;
-    if (j < 4 * r4) continue;
-    double v = 0.0;
-    if (j > i && j < nb)
-      v = (i / kFB == j / kFB) ? A[(int64_t)(c0 + j) * K + c0 + i] : A[(int64_t)(c0 + i) * K + c0 + j];
-    const int base = 16 * (32 * r4 - r4 * (r4 - 1) / 2) + (i & 3) * (128 - 4 * r4);
-    rl[base + j - 4 * r4] = v;
-  }
-  __syncthreads();
-  // row i = 4 r + O of R from channel 4 r on, this lane's channels
-  auto r_row = [&](int r, int o) { return rl + 16 * (32 * r - r * (r - 1) / 2) + o * (128 - 4 * r) + ql; };
+    for (int k = 0; k < (int)(sizeof(to) / sizeof(double)); ++k) to[k] = from[16 * k];
+  };
 
-  double s;
-  if constexpr (GROUP) {
-    double z[32];
+#pragma nounroll
+  for (int c0 = o0; c0 < o1; c0 += kSB) {
+    const int nb = min(kSB, (int)K - c0);
+    const int64_t at = n * K + c0 + l16;
+    double acc[8];
+    float wo[8];
 #pragma unroll
-    for (int r = 0; r < 32; ++r) z[r] = acc[r] - (double)wo[r];
+    for (int r = 0; r < 8; ++r) {
+      const bool in = 16 * r + l16 < nb;
+      acc[r] = in ? W64[at + 16 * r] : 0.0;
+      wo[r] = (in && keep[c0 + 16 * r + l16] != 0.0) ? (float)w[at + 16 * r] : 0.0f;
+    }
+    if (c0 > o0) {  // this workgroup's W_i - q s of the channels since o0, by R; a wave takes channels 32 wave .. + 32
+      v4d m[2] = {};
+      const double* left = W64 + nl * K + 4 * q;                                         // row l16, k = 4 q + s
+      const double* right[2];                                                            // k = 4 q + s, column l16
+#pragma unroll
+      for (int t = 0; t < 2; ++t) right[t] = A + (int64_t)(4 * q) * K + min((int64_t)c0 + 32 * wave + 16 * t + l16, K - 1);
+      for (int k = o0; k < c0; k += 16) {
+        const double2 a01 = *reinterpret_cast<const double2*>(left + k);
+        const double2 a23 = *reinterpret_cast<const double2*>(left + k + 2);
+        const double a[4] = {a01.x, a01.y, a23.x, a23.y};
+        double b[2][4];
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int s = 0; s < 4; ++s) b[t][s] = right[t][(int64_t)(k + s) * K];
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+          for (int t = 0; t < 2; ++t) m[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[t][s], m[t], 0, 0, 0);
+      }
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) rl[(4 * v + q) * kXs + 32 * wave + 16 * t + l16] = m[t][v];
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < 8; ++r) acc[r] += rl[(4 * wave + q) * kXs + 16 * r + l16];
+      __syncthreads();
+    }
+    // R: strictly upper part; where i and j share a factorisation block it lies transposed below the diagonal.  16 x 16
+    // tiles on and above the diagonal, four to a wave at a time
+    for (int u = wave; u < 36; u += 4) {
+      int r = 0, t = u;
+      while (t >= 8 - r) t -= 8 - r++;
+      t += r;  // rows 16 r, columns 16 t >= 16 r
+      double* to = rl + r_base(r) + 16 * (t - r);
+      const bool transposed = (16 * r) / kFB == (16 * t) / kFB;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int x = 4 * v + q;
+        const int i = 16 * r + (transposed ? l16 : x), j = 16 * t + (transposed ? x : l16);
+        double e = 0.0;
+        if (j > i && j < nb) e = transposed ? A[(int64_t)(c0 + j) * K + c0 + i] : A[(int64_t)(c0 + i) * K + c0 + j];
+        to[(i & 15) * (129 - 16 * r) + (j & 15)] = e;
+      }
+    }
+    __syncthreads();
+
+    double s;
+    if constexpr (GROUP) {
+      double z[8];
+#pragma unroll
+      for (int r = 0; r < 8; ++r) z[r] = acc[r] - (double)wo[r];
+      float m = 0.0f;  // rounding is monotonic: the maximum may be rounded before it is complete
+      float wz[8];
+#pragma unroll
+      for (int r = 0; r < 8; ++r) wz[r] = wo[r];
 #define QQQ_SOLVE(O)                                                                                       \
   {                                                                                                        \
-    const double d = quad_broadcast<O>(z[r]);                                                              \
-    const double* ri = r_row(r, O);                                                                        \
-    _Pragma("unroll") for (int k = r; k < 32; ++k) z[k] = __builtin_fma(-d, ri[4 * (k - r)], z[k]);        \
+    double next[W];                                                                                        \
+    if (O < 15) fetch_row(r, O + 1, next);                                                                 \
+    const double d = row_broadcast<O>(z[0]);                                                               \
+    _Pragma("unroll") for (int k = 0; k < W; ++k) z[k] = __builtin_fma(-d, ri[k], z[k]);                   \
+    _Pragma("unroll") for (int k = 1; k < W; ++k) asm volatile("" : "+v"(z[k]));                           \
+    if (O < 15) {                                                                                          \
+      _Pragma("unroll") for (int k = 0; k < W; ++k) ri[k] = next[k];                                       \
+    }                                                                                                      \
+    __builtin_amdgcn_sched_barrier(0);                                                                     \
   }
+      auto solve = [&](int r, auto width) {
+        constexpr int W = decltype(width)::value;
+        double ri[W];
+        fetch_row(r, 0, ri);
+        QQQ_SOLVE(0) QQQ_SOLVE(1) QQQ_SOLVE(2) QQQ_SOLVE(3) QQQ_SOLVE(4) QQQ_SOLVE(5) QQQ_SOLVE(6) QQQ_SOLVE(7)
+        QQQ_SOLVE(8) QQQ_SOLVE(9) QQQ_SOLVE(10) QQQ_SOLVE(11) QQQ_SOLVE(12) QQQ_SOLVE(13) QQQ_SOLVE(14) QQQ_SOLVE(15)
+        m = fmaxf(m, (float)fabs((double)wz[0] + z[0]));
 #pragma unroll
-    for (int r = 0; r < 32; ++r) {
-      QQQ_SOLVE(0)
-      QQQ_SOLVE(1)
-      QQQ_SOLVE(2)
-      QQQ_SOLVE(3)
-    }
+        for (int k = 0; k < W - 1; ++k) {
+          z[k] = z[k + 1];
+          wz[k] = wz[k + 1];
+        }
+      };
 #undef QQQ_SOLVE
-    double amax = 0.0;
-#pragma unroll
-    for (int r = 0; r < 32; ++r) amax = fmax(amax, fabs((double)wo[r] + z[r]));
-    float m = (float)amax;  // rounding is monotonic: the maximum may be rounded before it is complete
-    m = fmaxf(m, __builtin_bit_cast(float, quad_swap<1>(__builtin_bit_cast(uint32_t, m))));
-    m = fmaxf(m, __builtin_bit_cast(float, quad_swap<2>(__builtin_bit_cast(uint32_t, m))));
-    const uint16_t sb = __builtin_bit_cast(uint16_t, (_Float16)(m / 7.0f));
-    if (ql == 0 && row < N) scales[n] = sb;
-    s = (double)half_bits_to_float(sb);
-  } else {
-    s = (double)half_bits_to_float(scales[n]);
-  }
-  const double rs = s == 0.0 ? 0.0 : 1.0 / s;  // 0 makes every quotient, and so every code, 0
+#pragma nounroll
+      for (int r = 0; r < 4; ++r) solve(r, Width<8>{});
+#pragma nounroll
+      for (int r = 4; r < 8; ++r) solve(r, Width<4>{});
+      m = row_max(m);
+      const uint16_t sb = __builtin_bit_cast(uint16_t, (_Float16)(m / 7.0f));
+      if (l16 == 0 && row < N) scales[(int64_t)(c0 / kSB) * N + n] = sb;
+      s = (double)half_bits_to_float(sb);
+    } else {
+      s = (double)half_bits_to_float(scales[n]);
+    }
+    const double rs = s == 0.0 ? 0.0 : 1.0 / s;  // 0 makes every quotient, and so every code, 0
 
-  uint32_t words[16];
-#pragma unroll
-  for (int r = 0; r < 16; ++r) words[r] = 0;
 #define QQQ_STEP(O)                                                                                        \
   {                                                                                                        \
-    const double v = acc[r];                                                                               \
+    double next[W];                                                                                        \
+    if (O < 15) fetch_row(r, O + 1, next);                                                                 \
+    const double v = acc[0];                                                                               \
     const double q0 = v * rs;                                                                              \
     const double quo = __builtin_fma(__builtin_fma(-q0, s, v), rs, q0);                                    \
     const float code = __builtin_amdgcn_fmed3f(__builtin_rintf((float)quo), -7.0f, 7.0f);                  \
-    const double diff = __builtin_fma(-(double)code, s, (double)wo[r]);                                    \
-    const double d = quad_broadcast<O>(diff);                                                              \
-    if (ql == O) {                                                                                         \
-      own_code = (int)code;                                                                                \
-      acc[r] = diff;                                                                                       \
+    const double diff = __builtin_fma(-(double)code, s, w0);                                               \
+    const double d = row_broadcast<O>(diff);                                                               \
+    own_code = l16 == O ? code : own_code;                                                                 \
+    own_diff = l16 == O ? diff : own_diff;                                                                 \
+    _Pragma("unroll") for (int k = 0; k < W; ++k) acc[k] = __builtin_fma(d, ri[k], acc[k]);                \
+    _Pragma("unroll") for (int k = 1; k < W; ++k) asm volatile("" : "+v"(acc[k]));                         \
+    if (O < 15) {                                                                                          \
+      _Pragma("unroll") for (int k = 0; k < W; ++k) ri[k] = next[k];                                       \
     }                                                                                                      \
-    const double* ri = r_row(r, O);                                                                        \
-    _Pragma("unroll") for (int k = r; k < 32; ++k) acc[k] = __builtin_fma(d, ri[4 * (k - r)], acc[k]);     \
+    __builtin_amdgcn_sched_barrier(0);                                                                     \
   }
+    auto steps = [&](int r, auto width) {
+      constexpr int W = decltype(width)::value;
+      const double w0 = (double)wo[0];
+      float own_code = 0.0f;
+      double own_diff = 0.0;
+      double ri[W];
+      fetch_row(r, 0, ri);
+      QQQ_STEP(0) QQQ_STEP(1) QQQ_STEP(2) QQQ_STEP(3) QQQ_STEP(4) QQQ_STEP(5) QQQ_STEP(6) QQQ_STEP(7)
+      QQQ_STEP(8) QQQ_STEP(9) QQQ_STEP(10) QQQ_STEP(11) QQQ_STEP(12) QQQ_STEP(13) QQQ_STEP(14) QQQ_STEP(15)
+      uint32_t word = ((uint32_t)(int)own_code & 0xFu) << (4 * (l16 & 7));  // eight lanes make a word
+      word |= quad_swap<1>(word);
+      word |= quad_swap<2>(word);
+      word |= half_row_mirror(word);
+      if (row < N && 16 * r + l16 < nb) {
+        if ((l16 & 7) == 0) w_nat[n * (K / 8) + c0 / 8 + 2 * r + (l16 >> 3)] = word;
+        if (c0 + kSB < K) W64[at + 16 * r] = own_diff;
+      }
 #pragma unroll
-  for (int r = 0; r < 32; ++r) {
-    int own_code = 0;
-    QQQ_STEP(0)
-    QQQ_STEP(1)
-    QQQ_STEP(2)
-    QQQ_STEP(3)
-    words[r >> 1] |= ((uint32_t)own_code & 0xFu) << (4 * ql + 16 * (r & 1));
-  }
+      for (int k = 0; k < W - 1; ++k) {
+        acc[k] = acc[k + 1];
+        wo[k] = wo[k + 1];
+      }
+    };
 #undef QQQ_STEP
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {  // every lane's nibbles of every word
-    words[r] |= quad_swap<1>(words[r]);
-    words[r] |= quad_swap<2>(words[r]);
-  }
-  if (row >= N) return;
-#pragma unroll
-  for (int r = 0; r < 16; ++r)
-    if ((r >> 2) == ql && 8 * r < nb) w_nat[n * (K / 8) + c0 / 8 + r] = words[r];
-  if (c0 + kSB < K) {
-#pragma unroll
-    for (int r = 0; r < 32; ++r) W64[at + 4 * r] = acc[r];
+#pragma nounroll
+    for (int r = 0; r < 4; ++r) steps(r, Width<8>{});
+#pragma nounroll
+    for (int r = 4; r < 8; ++r) steps(r, Width<4>{});
+    __syncthreads();  // R's place is free again, and W64 holds what the other waves wrote
   }
 }
 
@@ -539,22 +624,16 @@ int begin(const char* who, const void* w_fp16, const double* H, int64_t N, int64
 // Eq. 4 over all channels; scales: [N], or [K/128, N] (written) with group scales
 template <bool GROUP>
 int sweep(const Work& wk, const void* w_fp16, int64_t N, int64_t K, uint16_t* scales, uint32_t* w_nat, hipStream_t st) {
-  // Blocks of 128 from the first; each at once moves the channels of its own kSO, and all channels after those are
-  // moved by the whole kSO together: a quarter of the passes over the running weights, and products deep enough for the
-  // matrix cores
-  auto move = [&](int64_t k0, int64_t kd, int64_t c0, int64_t cols) {
-    if (cols <= 0) return;
-    hipLaunchKernelGGL((f64_update_kernel<false, false>), dim3((unsigned)((cols + 63) / 64), (unsigned)((N + 63) / 64)),
-                       dim3(256), 0, st, wk.W64 + k0, K, wk.A + k0 * K + c0, K, wk.W64 + c0, K, (int)N, (int)cols, (int)kd, 0);
-  };
+  // kSO channels at a time; all channels after those are moved by them together: passes over the running weights kept few,
+  // and products deep enough for the matrix cores
   for (int64_t o0 = 0; o0 < K; o0 += kSO) {
     const int64_t o1 = o0 + kSO < K ? o0 + kSO : K;
-    for (int64_t c0 = o0; c0 < o1; c0 += kSB) {
-      hipLaunchKernelGGL((sweep_kernel<GROUP>), dim3((unsigned)((N + 31) / 32)), dim3(128), 0, st, (const _Float16*)w_fp16,
-                         wk.A, wk.keep, N, K, (int)c0, GROUP ? scales + c0 / kSB * N : scales, wk.W64, w_nat);
-      move(c0, kSB, c0 + kSB, o1 - c0 - kSB);
-    }
-    move(o0, kSO, o1, K - o1);
+    hipLaunchKernelGGL((sweep_kernel<GROUP>), dim3((unsigned)((N + 15) / 16)), dim3(256), 0, st, (const _Float16*)w_fp16,
+                       wk.A, wk.keep, N, K, (int)o0, (int)o1, scales, wk.W64, w_nat);
+    if (o1 < K)
+      hipLaunchKernelGGL((f64_update_kernel<false, false>), dim3((unsigned)((K - o1 + 63) / 64), (unsigned)((N + 63) / 64)),
+                         dim3(256), 0, st, wk.W64 + o0, K, wk.A + o0 * K + o1, K, wk.W64 + o1, K, (int)N, (int)(K - o1),
+                         (int)kSO, 0);
   }
   return check_launch("gptq sweep");
 }

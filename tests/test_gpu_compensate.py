@@ -1,4 +1,4 @@
-"""The compensation sweep at the edges of its blocks (64 channels a factorisation block, 128 a sweep block, 32 output
+"""The compensation sweep at the edges of its blocks (64 channels a factorisation block, 128 a sweep block, 512 a sweep, 16 output
 channels a workgroup, 64 x 64 update tiles) against the CPU oracle, which forms and eliminates the inverse Hessian.
 
 Bar: scales bit for bit and codes identical; both sides decide a code by a quotient good to far better than 1e-9, so
