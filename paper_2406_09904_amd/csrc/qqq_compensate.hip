@@ -15,8 +15,8 @@
 //   sweep          per 512 channels, from the first: sweep_kernel, then the update of the channels after
 // What is left serial is one dependent step per channel, in registers.
 // Bound: K = N = 4096 holds 2.3e10 + 6.9e10 fp64 operations, 1.3 ms at the 70 TFLOP/s a large fp64 product
-// reaches here.  Measured, K = N = 4096: 5.6 ms (an inverse by K rank-1 sweeps and a rank-1 update of both matrices
-// per channel: 360 ms); K = 2048, N = 5632 with group scales: 2.4 ms (81 ms).
+// reaches here.  Measured, K = N = 4096: 4.95 ms (an inverse by K rank-1 sweeps and a rank-1 update of both matrices
+// per channel: 360 ms); K = 2048, N = 5632 with group scales: 2.1 ms (81 ms).
 #include "qqq_calib.h"
 #include "qqq_internal.h"
 
@@ -224,7 +224,7 @@ __global__ __launch_bounds__(256) void f64_update_kernel(const double* A, int64_
 // transposed below the diagonal (its upper half is still being read by other workgroups).
 // Bound by the chain of 64 pivots and, where code runs once, by its fetch: both halves walk 16 columns at a time
 // in a loop, so that one body of a few KiB serves the whole block (written out straight, 42 KiB of instructions
-// took 44.7 us a block whatever the row count; the loops take 24.7).
+// took 44.7 us a block whatever the row count; the loops take 20).
 // Diagonal block: the 16 columns first receive what the columns after them owe (fp64 MFMA, a wave per 16 rows), then
 // one wave with lane = row takes their 16 steps in registers; pivots and column elements reach all lanes
 // through v_readlane.  Rows above: 16 lanes per row, the solved element spread over them by a DPP move.
@@ -243,13 +243,14 @@ __global__ __launch_bounds__(256) void factor_panel_kernel(double* A, int64_t K,
   for (int v = 0; v < 2; ++v)
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-      y[v][r] = (row0 + 4 * v < c0 && 16 * r + l16 < nb) ? A[(row0 + 4 * v) * K + c0 + 16 * r + l16] : 0.0;
+      y[v][r] = A[min(row0 + 4 * v, (int64_t)c0) * K + c0 + min(16 * r + l16, nb - 1)];  // (what is not there is not stored)
 
   // ---- the diagonal block, upper triangle; channels past K are identity
 #pragma unroll
   for (int e = 0; e < 16; ++e) {
     const int i = 4 * e + wave, j = lane;
-    ys[i * kS + j] = (i <= j && j < nb) ? A[(int64_t)(c0 + i) * K + c0 + j] : (i == j ? 1.0 : 0.0);
+    const double a = A[(int64_t)(c0 + min(i, nb - 1)) * K + c0 + max(min(i, nb - 1), min(j, nb - 1))];
+    ys[i * kS + j] = (i <= j && j < nb) ? a : (i == j ? 1.0 : 0.0);
   }
   __syncthreads();
 #pragma nounroll
@@ -280,7 +281,10 @@ __global__ __launch_bounds__(256) void factor_panel_kernel(double* A, int64_t K,
         const bool above = lane < 16 * p + j;
         const double x = above ? a[j] * rd : 0.0;
 #pragma unroll
-        for (int k = 0; k < j; ++k) a[k] = __builtin_fma(-x, lane_value(a[j], 16 * p + k), a[k]);
+        for (int k = 0; k < j; ++k) {
+          a[k] = __builtin_fma(-x, lane_value(a[j], 16 * p + k), a[k]);
+          asm volatile("" : "+v"(a[k]));  // now, not when column k's turn comes (that keeps 240 broadcast values alive)
+        }
         xs[lane * kS + 16 * p + j] = x;
         ys[lane * kS + 16 * p + j] = above ? a[j] : 0.0;
         if (lane == 0) rcp[16 * p + j] = rd;
@@ -337,6 +341,16 @@ __global__ __launch_bounds__(256) void factor_panel_kernel(double* A, int64_t K,
   }
 }
 
+// the u-th 16 x 16 tile (rows 16 r, columns 16 t >= 16 r) of a sweep block's R, u < 36
+struct Tile { int r, t; bool transposed; };
+__device__ __forceinline__ Tile upper_tile(int u) {
+  int r = 0;
+#pragma unroll
+  for (int x = 1; x < 8; ++x) r += u >= 8 * x - x * (x - 1) / 2;
+  const int t = u - (8 * r - r * (r - 1) / 2) + r;
+  return {r, t, (16 * r) / kFB == (16 * t) / kFB};
+}
+
 // Channels [o0, o1) of every output channel, one after the other: code of the running weight, then the
 // move of the later channels,
 //   q = clamp(rne(fp32(w / s)), -7, 7), s == 0 gives 0;  w_j += (W_i - q s) R[i,j] for j > i.
@@ -347,7 +361,7 @@ __global__ __launch_bounds__(256) void factor_panel_kernel(double* A, int64_t K,
 // multiply-add per 16 later channels, the broadcast of W_i - q s inside the sixteen lanes being a data-parallel move.
 // The steps are a loop over 16 channels whose registers move down one place each time: one body for 128 channels
 // (written out straight, 40 to 73 KiB of instructions, each fetched for one use, took 65 to 81 us per 128 channels and the
-// separate products 20 more; this form takes 33 for all of it, 4096 output channels).
+// separate products 20 more; this form takes 22 for all of it, 4096 output channels).
 // R's block sits in LDS as rows of what a step still needs: row i from channel 16 (i / 16) on, zeros up to the diagonal, one
 // double apart from a multiple of the banks.
 // The quotient: w * (1/s) corrected by its exact remainder, which is the correctly rounded w / s.
@@ -363,7 +377,7 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const _Float16* w, const 
   constexpr int kRows = 16 * (16 * 36 + 8);  // doubles: 16 rows of 129 - 16 r for r = 0 .. 7
   constexpr int kXs = 130;                   // the product's 16 rows, in the same place before R is
   __shared__ __attribute__((aligned(16))) double rl[kRows + 64];  // (a step reads up to three vectors of 16 past its row)
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, q = lane >> 4;
   const int64_t n0 = (int64_t)blockIdx.x * 16;
   const int64_t row = n0 + 4 * wave + q;
@@ -393,23 +407,42 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const _Float16* w, const 
     }
     if (c0 > o0) {  // this workgroup's W_i - q s of the channels since o0, by R; a wave takes channels 32 wave .. + 32
       v4d m[2] = {};
-      const double* left = W64 + nl * K + 4 * q;                                         // row l16, k = 4 q + s
-      const double* right[2];                                                            // k = 4 q + s, column l16
+      const double* left = W64 + nl * K + 4 * q;  // row l16, k = 4 q + s
+      const double* right[2];                     // k = 4 q + s, column l16
 #pragma unroll
       for (int t = 0; t < 2; ++t) right[t] = A + (int64_t)(4 * q) * K + min((int64_t)c0 + 32 * wave + 16 * t + l16, K - 1);
-      for (int k = o0; k < c0; k += 16) {
-        const double2 a01 = *reinterpret_cast<const double2*>(left + k);
-        const double2 a23 = *reinterpret_cast<const double2*>(left + k + 2);
-        const double a[4] = {a01.x, a01.y, a23.x, a23.y};
-        double b[2][4];
+      // 64 channels of k at a time, each half requested while the other is multiplied (16 at a time and nothing ahead, the
+      // loads' latency was a third of the kernel)
+      double2 la[2][4];
+      double rb[2][2][8];
+      auto request = [&](int h, int k) {
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+        for (int u = 0; u < 2; ++u) {
+          la[h][2 * u] = *reinterpret_cast<const double2*>(left + k + 16 * u);
+          la[h][2 * u + 1] = *reinterpret_cast<const double2*>(left + k + 16 * u + 2);
 #pragma unroll
-          for (int s = 0; s < 4; ++s) b[t][s] = right[t][(int64_t)(k + s) * K];
+          for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
+            for (int s = 0; s < 4; ++s) rb[h][t][4 * u + s] = right[t][(int64_t)(k + 16 * u + s) * K];
+        }
+      };
+      auto multiply = [&](int h) {
 #pragma unroll
-          for (int t = 0; t < 2; ++t) m[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[t][s], m[t], 0, 0, 0);
+        for (int x = 0; x < 8; ++x) {
+          const double a = x & 1 ? la[h][x >> 1].y : la[h][x >> 1].x;
+#pragma unroll
+          for (int t = 0; t < 2; ++t) m[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, rb[h][t][x], m[t], 0, 0, 0);
+        }
+      };
+      request(0, o0);
+#pragma nounroll
+      for (int k = o0; k < c0; k += 64) {
+        request(1, k + 32);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(0);
+        request(0, min(k + 64, c0 - 32));  // (past the end: the last ones once more, unused)
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(1);
       }
 #pragma unroll
       for (int t = 0; t < 2; ++t)
@@ -421,20 +454,29 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const _Float16* w, const 
       __syncthreads();
     }
     // R: strictly upper part; where i and j share a factorisation block it lies transposed below the diagonal.  16 x 16
-    // tiles on and above the diagonal, four to a wave at a time
-    for (int u = wave; u < 36; u += 4) {
-      int r = 0, t = u;
-      while (t >= 8 - r) t -= 8 - r++;
-      t += r;  // rows 16 r, columns 16 t >= 16 r
-      double* to = rl + r_base(r) + 16 * (t - r);
-      const bool transposed = (16 * r) / kFB == (16 * t) / kFB;
+    // tiles on and above the diagonal, nine to a wave; every load is requested before the first value is placed
+    {
+      const double* block = A + (int64_t)c0 * K + c0;
+      double e[9][4];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int x = 4 * v + q;
-        const int i = 16 * r + (transposed ? l16 : x), j = 16 * t + (transposed ? x : l16);
-        double e = 0.0;
-        if (j > i && j < nb) e = transposed ? A[(int64_t)(c0 + j) * K + c0 + i] : A[(int64_t)(c0 + i) * K + c0 + j];
-        to[(i & 15) * (129 - 16 * r) + (j & 15)] = e;
+      for (int x = 0; x < 9; ++x) {
+        const Tile g = upper_tile(wave + 4 * x);
+        const int hi = (g.transposed ? g.t : g.r) * 16, lo = (g.transposed ? g.r : g.t) * 16;
+        // nb is a multiple of 8, so four rows exist or not together; eight columns past the matrix's last row are still
+        // the workspace's
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          e[x][v] = (block + (hi + 4 * v < nb ? hi + 4 * v : 0) * (int)K + (lo < nb ? lo : 0))[q * (int)K + l16];
+      }
+#pragma unroll
+      for (int x = 0; x < 9; ++x) {
+        const Tile g = upper_tile(wave + 4 * x);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int i = g.transposed ? l16 : 4 * v + q, j = g.transposed ? 4 * v + q : l16;
+          const bool in = 16 * g.t + j > 16 * g.r + i && 16 * g.t + j < nb;
+          rl[r_base(g.r) + 16 * (g.t - g.r) + i * (129 - 16 * g.r) + j] = in ? e[x][v] : 0.0;
+        }
       }
     }
     __syncthreads();
@@ -540,29 +582,36 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const _Float16* w, const 
 
 // After a per-group sweep, what the front-end derives from codes and group scales (Sec. 3.3.2, Fig. 5 offline):
 // s_Wc[n] = fp16(max_k |code * s_Wg| / 127) with the product in fp32, s*_Wg = fp16(s_Wg / s_Wc) capped at
-// 18.203125 (0 where s_Wc is 0), integer form clamp(rne(s*_Wg), 1, 18).  One thread per output channel.
+// 18.203125 (0 where s_Wc is 0), integer form clamp(rne(s*_Wg), 1, 18).  Sixteen lanes per output channel, a group each
+// (one thread per output channel left most CUs idle: 48 us at K = 2048, N = 5632).
 __global__ __launch_bounds__(256) void group_finish_kernel(const uint32_t* w_nat, const uint16_t* s_wg, int64_t N,
-                                                           int64_t K, int group, uint16_t* s_wc, uint16_t* s_star,
-                                                           int8_t* s_int) {
-  const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (n >= N) return;
-  const int64_t G = K / group;
+                                                           int64_t K, uint16_t* s_wc, uint16_t* s_star, int8_t* s_int) {
+  const int l16 = threadIdx.x & 15;
+  const int64_t row = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
+  const int64_t n = row < N ? row : N - 1;  // (rows past N repeat the last one and store nothing)
+  const int G = (int)(K / QQQ_GROUP);
   float dmax = 0.0f;
-  for (int64_t g = 0; g < G; ++g) {
+  for (int g = l16; g < G; g += 16) {
+    const uint32_t* words = w_nat + n * (K / 8) + g * (QQQ_GROUP / 8);
+    uint32_t word[QQQ_GROUP / 8];
+#pragma unroll
+    for (int j = 0; j < QQQ_GROUP / 8; ++j) word[j] = words[j];
     int cmax = 0;
-    for (int j = 0; j < group / 8; ++j) {
-      const uint32_t word = w_nat[n * (K / 8) + g * (group / 8) + j];
-      for (int q = 0; q < 8; ++q) {
-        const int code = ((int)(word << (28 - 4 * q))) >> 28;  // sign-extended nibble
+#pragma unroll
+    for (int j = 0; j < QQQ_GROUP / 8; ++j)
+#pragma unroll
+      for (int b = 0; b < 8; ++b) {
+        const int code = ((int)(word[j] << (28 - 4 * b))) >> 28;  // sign-extended nibble
         cmax = max(cmax, code < 0 ? -code : code);
       }
-    }
     dmax = fmaxf(dmax, (float)cmax * half_bits_to_float(s_wg[g * N + n]));
   }
+  dmax = row_max(dmax);
+  if (row >= N) return;
   const uint16_t wcb = __builtin_bit_cast(uint16_t, (_Float16)(dmax / 127.0f));
-  s_wc[n] = wcb;
+  if (l16 == 0) s_wc[n] = wcb;
   const float wc = half_bits_to_float(wcb);
-  for (int64_t g = 0; g < G; ++g) {
+  for (int g = l16; g < G; g += 16) {
     uint16_t star = 0;
     if (wc != 0.0f) {
       const _Float16 h = (_Float16)(half_bits_to_float(s_wg[g * N + n]) / wc);
@@ -681,8 +730,8 @@ int qqq_gptq_quantize_w4_pergroup(const void* w_fp16, const double* H, int64_t N
   if (rc != QQQ_OK) return rc;
   uint16_t* s_wg = (uint16_t*)s_wg_fp16;
   if ((rc = sweep<true>(wk, w_fp16, N, K, s_wg, w_nat, st)) != QQQ_OK) return rc;
-  hipLaunchKernelGGL(group_finish_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st, w_nat, s_wg, N, K,
-                     QQQ_GROUP, (uint16_t*)s_wc_fp16, (uint16_t*)s_star_fp16, s_int);
+  hipLaunchKernelGGL(group_finish_kernel, dim3((unsigned)((N + 15) / 16)), dim3(256), 0, st, w_nat, s_wg, N, K,
+                     (uint16_t*)s_wc_fp16, (uint16_t*)s_star_fp16, s_int);
   return check_launch("gptq_pergroup finish");
 }
 
