@@ -15,7 +15,7 @@
 //   sweep          per 512 channels, from the first: sweep_kernel, then the update of the channels after
 // What is left serial is one dependent step per channel, in registers.
 // Bound: K = N = 4096 holds 2.3e10 + 6.9e10 fp64 operations, 1.3 ms at the 70 TFLOP/s a large fp64 product
-// reaches here.  Measured, K = N = 4096: 4.95 ms (an inverse by K rank-1 sweeps and a rank-1 update of both matrices
+// reaches here.  Measured, K = N = 4096: 4.75 ms (an inverse by K rank-1 sweeps and a rank-1 update of both matrices
 // per channel: 360 ms); K = 2048, N = 5632 with group scales: 2.1 ms (81 ms).
 #include "qqq_calib.h"
 #include "qqq_internal.h"
@@ -130,16 +130,10 @@ __global__ __launch_bounds__(256) void prepare_kernel(const double* H, const _Fl
 // of the operands, register v of the result is row 4 v + l / 16, column l % 16.  Row strides of the LDS tiles
 // (34 and 80 doubles) put the 32 lanes of half a wave on all 64 banks.  The matrix pipe is the limit: each
 // fragment read feeds two MFMAs.
-// UPPER: C is columns col0 .. col0 + N of a symmetric matrix kept as its upper triangle; only the tiles that reach the
-// diagonal or lie above it.
-template <bool UPPER, bool SUB>
-__global__ __launch_bounds__(256) void f64_update_kernel(const double* A, int64_t lda, const double* B, int64_t ldb,
-                                                         double* C, int64_t ldc, int M, int N, int kd, int col0) {
-  constexpr int kAs = 34, kBs = 80;
-  __shared__ __attribute__((aligned(16))) double sa[64 * kAs];
-  __shared__ __attribute__((aligned(16))) double sb[32 * kBs];
-  const int tn = blockIdx.x, tm = blockIdx.y;
-  if (UPPER && col0 + tn * 64 + 63 < tm * 64) return;
+constexpr int kAs = 34, kBs = 80;  // row strides of the LDS tiles: 64 rows of A, 32 of B
+template <bool SUB>
+__device__ __forceinline__ void update_tile(const double* A, int64_t lda, const double* B, int64_t ldb, double* C, int64_t ldc,
+                                            int M, int N, int kd, int tm, int tn, double* sa, double* sb) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int m0 = tm * 64, n0 = tn * 64;
   const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
@@ -215,6 +209,17 @@ __global__ __launch_bounds__(256) void f64_update_kernel(const double* A, int64_
       }
 }
 
+// UPPER: C is columns col0 .. col0 + N of a symmetric matrix kept as its upper triangle; only the tiles that reach the
+// diagonal or lie above it.
+template <bool UPPER, bool SUB>
+__global__ __launch_bounds__(256) void f64_update_kernel(const double* A, int64_t lda, const double* B, int64_t ldb,
+                                                         double* C, int64_t ldc, int M, int N, int kd, int col0) {
+  __shared__ __attribute__((aligned(16))) double sa[64 * kAs];
+  __shared__ __attribute__((aligned(16))) double sb[32 * kBs];
+  if (UPPER && col0 + (int)blockIdx.x * 64 + 63 < (int)blockIdx.y * 64) return;
+  update_tile<SUB>(A, lda, B, ldb, C, ldc, M, N, kd, blockIdx.y, blockIdx.x, sa, sb);
+}
+
 // One block [c0, c0 + 64) of H = R D R^T, the channels after it already eliminated from A.
 // Every workgroup factors the 64 x 64 diagonal block for itself (64 dependent steps: column j's pivot
 // d_j, R[i,j] = A[i,j] / d_j for i < j, A[i,k] -= R[i,j] A[k,j] for k < j) and then solves for its own 32 of
@@ -228,11 +233,25 @@ __global__ __launch_bounds__(256) void f64_update_kernel(const double* A, int64_
 // Diagonal block: the 16 columns first receive what the columns after them owe (fp64 MFMA, a wave per 16 rows), then
 // one wave with lane = row takes their 16 steps in registers; pivots and column elements reach all lanes
 // through v_readlane.  Rows above: 16 lanes per row, the solved element spread over them by a DPP move.
-__global__ __launch_bounds__(256) void factor_panel_kernel(double* A, int64_t K, int c0) {
+// The first `solvers` workgroups do that.  The others, on the CUs the chain leaves idle, take a part of what the kFO
+// channels [t0, t0 + td) before these owe to the columns this kFO does not contain (Trailing): A[0..td0) -= R (R D)^T there,
+// 64 x 64 tiles of the upper triangle numbered column by column from `tile0`.  They touch nothing a block of this kFO reads
+// or writes: rows and columns below t0 - kFO, from operands at t0 and past it.
+struct Trailing { int t0, td, n, tile0; };  // first channel, channels, rows (= columns) updated, first tile
+__global__ __launch_bounds__(256) void factor_panel_kernel(double* A, int64_t K, int c0, int solvers, Trailing tr) {
   constexpr int kS = 66;
+  static_assert(64 * kS >= 64 * kAs && 64 * kS >= 32 * kBs, "an update tile's stages fit");
   __shared__ __attribute__((aligned(16))) double ys[64 * kS];  // [i][j]: the block, then R D for i < j, 0 from the diagonal on
   __shared__ __attribute__((aligned(16))) double xs[64 * kS];  // [i][j]: R for i < j, else 0
   __shared__ double rcp[64];                                   // 1 / d_j
+  if ((int)blockIdx.x >= solvers) {
+    const int u = tr.tile0 + (int)blockIdx.x - solvers;
+    int tn = (int)((__builtin_sqrtf(8.0f * (float)u + 1.0f) - 1.0f) * 0.5f);  // tile column tn starts at tn (tn + 1) / 2
+    while (tn * (tn + 1) / 2 > u) --tn;
+    while ((tn + 1) * (tn + 2) / 2 <= u) ++tn;
+    update_tile<true>(A + tr.t0, K, A + (int64_t)tr.t0 * K, K, A, K, tr.n, tr.n, tr.td, u - tn * (tn + 1) / 2, tn, ys, xs);
+    return;
+  }
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l16 = lane & 15, q = lane >> 4;
   const int nb = min(64, (int)K - c0);
@@ -648,20 +667,37 @@ int begin(const char* who, const void* w_fp16, const double* H, int64_t N, int64
                      (const _Float16*)w_fp16, keep, damp, N, K, A, W64);
   if ((rc = check_launch("gptq prepare")) != QQQ_OK) return rc;
   // Blocks of 64 from the last; each at once reduces the columns of its own kFO, and all columns before those are
-  // reduced by the whole kFO together (see sweep)
+  // reduced by the whole kFO together (see sweep): the next kFO's columns at once, the rest inside the launches of the next
+  // kFO's blocks, whose chains leave most CUs idle.  Those carry up to four tiles per CU each, more would take longer than the
+  // chain; what is left then (the first columns) goes at once as well.  (K = 4096: a launch with 288 tiles takes 21.5 us, 20.5
+  // without; the updates as launches of their own up to 100 us per kFO.)
   auto reduce = [&](int64_t c0, int64_t kd, int64_t col0, int64_t cols, int64_t rows) {
     if (cols <= 0 || rows <= 0) return;
     hipLaunchKernelGGL((f64_update_kernel<true, true>), dim3((unsigned)((cols + 63) / 64), (unsigned)((rows + 63) / 64)),
                        dim3(256), 0, st, A + c0, K, A + c0 * K + col0, K, A + col0, K, (int)rows, (int)cols, (int)kd, (int)col0);
   };
+  Trailing tr = {};
+  int tiles_left = 0;  // of tr
   for (int64_t o0 = (K - 1) / kFO * kFO; o0 >= 0; o0 -= kFO) {
     const int64_t o1 = o0 + kFO < K ? o0 + kFO : K;
     for (int64_t c0 = (o1 - 1) / kFB * kFB; c0 >= o0; c0 -= kFB) {
-      const unsigned tiles = (unsigned)(c0 / 32);
-      hipLaunchKernelGGL(factor_panel_kernel, dim3(tiles ? tiles : 1), dim3(256), 0, st, A, K, (int)c0);
+      const int solvers = c0 ? (int)(c0 / 32) : 1;
+      const int blocks_left = (int)((c0 - o0) / kFB) + 1;
+      const int carried = (tiles_left + blocks_left - 1) / blocks_left;
+      hipLaunchKernelGGL(factor_panel_kernel, dim3((unsigned)(solvers + carried)), dim3(256), 0, st, A, K, (int)c0, solvers, tr);
+      tr.tile0 += carried;
+      tiles_left -= carried;
       reduce(c0, K - c0 < kFB ? K - c0 : kFB, o0, c0 - o0, c0);
     }
-    reduce(o0, o1 - o0, 0, o0, o0);
+    if (o0 == 0) break;
+    const int64_t p0 = o0 - kFO;
+    reduce(o0, o1 - o0, p0, kFO, o0);
+    const int nt = (int)(p0 / 64), most = 4 * (kFO / kFB) * num_cus();
+    int at_once = 0;  // tile columns
+    while (nt * (nt + 1) / 2 - at_once * (at_once + 1) / 2 > most) ++at_once;
+    reduce(o0, o1 - o0, 0, (int64_t)at_once * 64, (int64_t)at_once * 64);
+    tr = {(int)o0, (int)(o1 - o0), (int)p0, at_once * (at_once + 1) / 2};
+    tiles_left = nt * (nt + 1) / 2 - tr.tile0;
   }
   if ((rc = check_launch("gptq factorisation")) != QQQ_OK) return rc;
   out->A = A;

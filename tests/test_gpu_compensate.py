@@ -64,3 +64,25 @@ def test_per_group_sweep_at_block_edges(K, N):
     assert np.array_equal(orc.w8_perchannel(w_nat.cpu().numpy().view(np.uint32), K), codes)
     assert np.array_equal(f16_bits(g_wg), s_wg) and np.array_equal(f16_bits(g_star), star)
     assert np.array_equal(f16_bits(g_wc), s_wc) and np.array_equal(g_int.cpu().numpy(), s_int)
+
+
+def test_factorisation_larger_than_its_launches_carry():
+    """K = 6528: the first blocks of the factorisation owe the columns before them more update tiles than the launches of
+    the next blocks take along.  Against a 64-bit torch sweep by the explicit inverse; the bar as above."""
+    K, N = 6528, 24
+    g = torch.Generator(device="cuda").manual_seed(77)
+    x = torch.randn((1500, 48), generator=g, device="cuda") @ torch.randn((48, K), generator=g, device="cuda") * 0.2
+    x = (x + torch.randn(x.shape, generator=g, device="cuda")).to(torch.float16).to(torch.float64)
+    H = 2.0 * (x.t().contiguous() @ x)
+    w = (torch.randn((N, K), generator=g, device="cuda") * 0.03).to(torch.float16)
+    w_nat, s_w = qqq.qqq_gptq_quantize_w4_perchannel(w, H, 0.01)
+    damped = H + 0.01 * H.diagonal().mean() * torch.eye(K, dtype=torch.float64, device="cuda")
+    U = torch.linalg.cholesky(torch.cholesky_inverse(torch.linalg.cholesky(damped)), upper=True)
+    U = U / U.diagonal()[:, None]
+    run, s = w.to(torch.float64), s_w.to(torch.float64)
+    codes = torch.zeros_like(run)
+    for i in range(K):
+        codes[:, i] = torch.round((run[:, i] / s).to(torch.float32)).clamp_(-7, 7)
+        run[:, i + 1:] -= (run[:, i] - codes[:, i] * s)[:, None] * U[i, i + 1:]
+    got = orc.w8_perchannel(w_nat.cpu().numpy().view(np.uint32), K)
+    assert np.array_equal(got, codes.cpu().numpy().astype(got.dtype))
