@@ -430,20 +430,36 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_prefill_dma_kernel(const Gemm
   if constexpr (LOSS) {
     static_assert(MODE == kPerChannel, "the search quantises per channel");
     // fp64(acc) * fp64(s_a) * fp64(s_w) - fp64(y_ref), squared and summed in fp64 (acc carries the exact factor 16)
+    // Half a channel's reference values are requested before the first is used, rows past M repeating the last one and counting
+    // nothing (a load under the row's own condition waits for memory every time: M = 512, K = N = 4096, eight grid points
+    // 76 us a launch, 69 so).
+    static_assert(S::kLds >= NW * 512 + NW * S::kBM * 4, "the partial sums and every wave's copy of the token scales");
+    float* sa = (float*)(lds + NW * 512) + wave * S::kBM;
+#pragma unroll
+    for (int i = 0; i < kSaPerLane; ++i) sa[lane + 64 * i] = sa_own[i];
     double sum = 0.0;
 #pragma unroll
     for (int c = 0; c < TC; ++c) {
       const double sw = nvalid[c] ? (double)(float)p.s_w[col[c]] : 0.0;
+      const float* ref = p.y_ref + (nvalid[c] ? col[c] : 0);
 #pragma unroll
-      for (int mt = 0; mt < TM; ++mt)
+      for (int half = 0; half < TM; half += TM / 2) {
+        float y[TM / 2][kRegs];
 #pragma unroll
-        for (int v = 0; v < kRegs; ++v) {
-          const int m = m0 + acc_row(mt, v);
-          if (m < M && nvalid[c]) {
-            const double d = (double)(acc[mt][c][v] >> 4) * (double)p.s_a[m] * sw - (double)p.y_ref[(int64_t)m * N + col[c]];
-            sum += d * d;
+        for (int mt = 0; mt < TM / 2; ++mt)
+#pragma unroll
+          for (int v = 0; v < kRegs; ++v) y[mt][v] = ref[(int64_t)min(m0 + acc_row(half + mt, v), M - 1) * N];
+#pragma unroll
+        for (int mt = 0; mt < TM / 2; ++mt)
+#pragma unroll
+          for (int v = 0; v < kRegs; ++v) {
+            const int r = acc_row(half + mt, v);
+            const double d = (double)(acc[half + mt][c][v] >> 4) * (double)sa[r] * sw - (double)y[mt][v];
+            const double kept = m0 + r < M && nvalid[c] ? d : 0.0;
+            sum += kept * kept;
           }
-        }
+        __builtin_amdgcn_sched_barrier(0);  // one half's values in registers at a time
+      }
     }
     double* part = (double*)lds;
     part[tid] = sum;
