@@ -72,7 +72,7 @@ int qqq_hessian(const void* x_fp16, int64_t M, int64_t K, double* H, void* strea
  *   H [K,K] fp64 (read only); w_nat [N,K/8] natural nibble words (for qqq_pack_w4); s_w_fp16 [N].
  *   workspace: qqq_gptq_workspace_bytes(N,K) bytes, contents irrelevant on entry.
  * Only the upper triangle of H is read (H is symmetric).
- * Cost: K^3/3 + N K^2 fp64 operations, about 3 K / 64 launches.
+ * Cost: K^3/3 + N K^2 fp64 operations, about 2.2 K / 64 launches.
  */
 size_t qqq_gptq_workspace_bytes(int64_t N, int64_t K);
 int qqq_gptq_quantize_w4_perchannel(const void* w_fp16, const double* H, int64_t N, int64_t K,
