@@ -79,6 +79,11 @@ __device__ __forceinline__ float row_max(float x) {  // largest of every sixteen
   return fmaxf(x, rotated(Width<0x121>{}));
 }
 
+// x clamped to [-limit, limit], a NaN left as it is
+__device__ __forceinline__ float keep_nan_clamp(float x, float limit) {
+  return __builtin_elementwise_minimum(__builtin_elementwise_maximum(x, -limit), limit);
+}
+
 // keep[i] = 0 for a channel that never fired (H_ii == 0: its weight counts as 0), else 1;
 // damp[0] = percdamp * mean of the diagonal, a never-firing channel counting 1
 __global__ __launch_bounds__(1024) void diagonal_kernel(const double* H, int64_t K, double percdamp, double* keep,
@@ -100,7 +105,8 @@ __global__ __launch_bounds__(1024) void diagonal_kernel(const double* H, int64_t
 }
 
 // Working copies: the upper triangle of the damped Hessian (the factorisation reads nothing below the
-// diagonal) and the running weights in fp64.  K % 8 == 0.  grid.y: rows of H, then rows of W.
+// diagonal) and the running weights in fp64, 0 in the place of an infinity or NaN (the sweep puts those back: here only
+// the moves are added up).  K % 8 == 0.  grid.x: rows of H, then rows of W.
 __global__ __launch_bounds__(256) void prepare_kernel(const double* H, const _Float16* w, const double* keep,
                                                       const double* damp, int64_t N, int64_t K, double* A, double* W64) {
   for (int64_t r = blockIdx.x; r < K + N; r += gridDim.x) {
@@ -116,8 +122,10 @@ __global__ __launch_bounds__(256) void prepare_kernel(const double* H, const _Fl
       const int64_t at0 = (r - K) * K;
       for (int64_t k = 2 * threadIdx.x; k < K; k += 512) {
         const uint32_t two = *reinterpret_cast<const uint32_t*>(w + at0 + k);
-        const double w0 = keep[k] != 0.0 ? (double)half_bits_to_float(two & 0xFFFFu) : 0.0;
-        const double w1 = keep[k + 1] != 0.0 ? (double)half_bits_to_float(two >> 16) : 0.0;
+        const bool in0 = keep[k] != 0.0 && (two & 0x7C00u) != 0x7C00u;
+        const bool in1 = keep[k + 1] != 0.0 && (two & 0x7C000000u) != 0x7C000000u;
+        const double w0 = in0 ? (double)half_bits_to_float(two & 0xFFFFu) : 0.0;
+        const double w1 = in1 ? (double)half_bits_to_float(two >> 16) : 0.0;
         *reinterpret_cast<double2*>(W64 + at0 + k) = make_double2(w0, w1);
       }
     }
@@ -385,6 +393,9 @@ __device__ __forceinline__ Tile upper_tile(int u) {
 // R's block sits in LDS as rows of what a step still needs: row i from channel 16 (i / 16) on, zeros up to the diagonal, one
 // double apart from a multiple of the banks.
 // The quotient: w * (1/s) corrected by its exact remainder, which is the correctly rounded w / s.
+// Where that is no number (an infinite or NaN weight or scale, a Hessian that holds one), the code is 0 and what it leaves
+// behind is NaN, so that the output channel's later codes and group scales are 0 too: the clamp is the pair of minimum and maximum that
+// keep a NaN (v_med3_f32 would make it -7), one instruction more in the chain.
 // GROUP: the scale is taken here, s = fp16(fp32(max |w|) / 7) over the block as Eq. 4 leaves its weights when the
 // sweep enters it.  What has been added up so far for channel j, P_j = sum over i < c0 of (W_i - Q_i) R[i,j], is
 // its move once the block's earlier channels have had theirs; with none of them quantised yet, the move z of
@@ -504,12 +515,15 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const _Float16* w, const 
     double s;
     if constexpr (GROUP) {
       double z[8];
-#pragma unroll
-      for (int r = 0; r < 8; ++r) z[r] = acc[r] - (double)wo[r];
-      float m = 0.0f;  // rounding is monotonic: the maximum may be rounded before it is complete
+      float m = 0.0f;  // rounding is monotonic: the maximum may be rounded before it is complete (and passes over a NaN)
       float wz[8];
 #pragma unroll
-      for (int r = 0; r < 8; ++r) wz[r] = wo[r];
+      for (int r = 0; r < 8; ++r) {
+        const bool number = __builtin_isfinite(wo[r]);
+        wz[r] = wo[r];
+        z[r] = acc[r] - (number ? (double)wo[r] : 0.0);
+        acc[r] = number ? acc[r] : (double)wo[r];
+      }
 #define QQQ_SOLVE(O)                                                                                       \
   {                                                                                                        \
     double next[W];                                                                                        \
@@ -536,10 +550,15 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const _Float16* w, const 
         }
       };
 #undef QQQ_SOLVE
+      if (c0 == 0) {  // no moves yet, whatever R holds
+#pragma unroll
+        for (int r = 0; r < 8; ++r) m = fmaxf(m, fabsf(wo[r]));
+      } else {
 #pragma nounroll
-      for (int r = 0; r < 4; ++r) solve(r, Width<8>{});
+        for (int r = 0; r < 4; ++r) solve(r, Width<8>{});
 #pragma nounroll
-      for (int r = 4; r < 8; ++r) solve(r, Width<4>{});
+        for (int r = 4; r < 8; ++r) solve(r, Width<4>{});
+      }
       m = row_max(m);
       const uint16_t sb = __builtin_bit_cast(uint16_t, (_Float16)(m / 7.0f));
       if (l16 == 0 && row < N) scales[(int64_t)(c0 / kSB) * N + n] = sb;
@@ -556,7 +575,7 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const _Float16* w, const 
     const double v = acc[0];                                                                               \
     const double q0 = v * rs;                                                                              \
     const double quo = __builtin_fma(__builtin_fma(-q0, s, v), rs, q0);                                    \
-    const float code = __builtin_amdgcn_fmed3f(__builtin_rintf((float)quo), -7.0f, 7.0f);                  \
+    const float code = keep_nan_clamp(__builtin_rintf((float)quo), 7.0f);                                  \
     const double diff = __builtin_fma(-(double)code, s, w0);                                               \
     const double d = row_broadcast<O>(diff);                                                               \
     own_code = l16 == O ? code : own_code;                                                                 \
@@ -577,7 +596,8 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const _Float16* w, const 
       fetch_row(r, 0, ri);
       QQQ_STEP(0) QQQ_STEP(1) QQQ_STEP(2) QQQ_STEP(3) QQQ_STEP(4) QQQ_STEP(5) QQQ_STEP(6) QQQ_STEP(7)
       QQQ_STEP(8) QQQ_STEP(9) QQQ_STEP(10) QQQ_STEP(11) QQQ_STEP(12) QQQ_STEP(13) QQQ_STEP(14) QQQ_STEP(15)
-      uint32_t word = ((uint32_t)(int)own_code & 0xFu) << (4 * (l16 & 7));  // eight lanes make a word
+      const int nibble = own_code == own_code ? (int)own_code : 0;
+      uint32_t word = ((uint32_t)nibble & 0xFu) << (4 * (l16 & 7));  // eight lanes make a word
       word |= quad_swap<1>(word);
       word |= quad_swap<2>(word);
       word |= half_row_mirror(word);

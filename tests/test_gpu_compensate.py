@@ -86,3 +86,72 @@ def test_factorisation_larger_than_its_launches_carry():
         run[:, i + 1:] -= (run[:, i] - codes[:, i] * s)[:, None] * U[i, i + 1:]
     got = orc.w8_perchannel(w_nat.cpu().numpy().view(np.uint32), K)
     assert np.array_equal(got, codes.cpu().numpy().astype(got.dtype))
+
+
+# ---- weights and Hessians that hold infinities or NaN: the output channel's codes are 0 from the first quotient that is no
+# ---- number on, its later group scales 0, a NaN does not count for a group's maximum; other output channels are as without
+INF, NAN = 0x7C00, 0x7E00
+
+
+def codes_of(w_nat, K):
+    return orc.w8_perchannel(w_nat.cpu().numpy().view(np.uint32), K)
+
+
+@pytest.mark.parametrize("K,N,at", [(72, 20, 40), (200, 40, 70), (1160, 33, 700)])
+def test_per_channel_weights_that_are_no_numbers(K, N, at):
+    x, w = layer(2 * K + 10, K, N, 900 + K)
+    H = cal.hessian(x)
+    codes, s_bits, _ = cal.gptq_quantize(w, H, 0.01)
+    for row, k, bits in ((3, at, INF), (5, at + 1, NAN), (7, 0, INF | 0x8000), (9, K - 1, INF)):
+        w[row, k] = bits                 # an infinite or NaN scale: every quotient of the row is NaN
+        codes[row] = 0
+    w_nat, s_w = qqq.qqq_gptq_quantize_w4_perchannel(dev16(w), torch.from_numpy(H).cuda(), 0.01)
+    assert np.array_equal(codes_of(w_nat, K), codes)
+    good = [n for n in range(N) if n not in (3, 5, 7, 9)]
+    assert np.array_equal(f16_bits(s_w)[good], s_bits[good])
+    assert not np.isfinite(f16_bits(s_w)[[3, 5, 7, 9]].view(np.float16)).any()
+
+
+def test_per_group_weights_that_are_no_numbers():
+    K, N = 640, 20
+    x, w = layer(2 * K + 10, K, N, 950)
+    places = ((2, 200, INF), (4, 300, NAN), (6, 10, NAN), (8, 130, INF | 0x8000), (11, 639, NAN))
+    for row, k, _ in places:
+        w[row, k] = 0
+    H = cal.hessian(x)
+    codes, s_wg, _ = cal.gptq_quantize_pergroup(w, H, 128, 0.01)
+    for row, k, bits in places:
+        w[row, k] = bits
+        g = k // 128
+        s_wg[g + 1:, row] = 0
+        if bits == NAN:                  # the channels before it keep their codes
+            codes[row, k:] = 0
+        else:                            # the group's scale is infinite
+            codes[row, 128 * g:] = 0
+            s_wg[g, row] = INF
+    got = qqq.qqq_gptq_quantize_w4_pergroup(dev16(w), torch.from_numpy(H).cuda(), 0.01)
+    assert np.array_equal(codes_of(got[0], K), codes)
+    assert np.array_equal(f16_bits(got[1]), s_wg)
+
+
+@pytest.mark.parametrize("percdamp", [0.01, 0.0])
+@pytest.mark.parametrize("K,at,value", [(72, 0, np.inf), (384, 60, np.inf), (384, 383, np.nan), (640, 300, np.nan)])
+def test_hessian_of_activations_that_are_no_numbers(K, at, value, percdamp):
+    """Only the first channel, which nothing moves, has a code; the first group's scale is that of the weights."""
+    N = 20
+    x, w = layer(2 * K + 10, K, N, 970 + K)
+    x = x.copy()
+    x[5, at] = np.array([value], np.float16).view(np.uint16)[0]
+    with np.errstate(invalid="ignore"):
+        H = torch.from_numpy(cal.hessian(x)).cuda()
+    s_bits = cal.channel_scales(w)
+    codes = np.zeros((N, K), np.int8)
+    codes[:, 0] = cal.rtn_codes(w[:, 0].view(np.float16), s_bits.view(np.float16))
+    w_nat, s_w = qqq.qqq_gptq_quantize_w4_perchannel(dev16(w), H, percdamp)
+    assert np.array_equal(codes_of(w_nat, K), codes) and np.array_equal(f16_bits(s_w), s_bits)
+    if K % 128 == 0:
+        s_wg = np.zeros((K // 128, N), np.uint16)
+        s_wg[0] = cal.channel_scales(np.ascontiguousarray(w[:, :128]))
+        codes[:, 0] = cal.rtn_codes(w[:, 0].view(np.float16), s_wg[0].view(np.float16))
+        got = qqq.qqq_gptq_quantize_w4_pergroup(dev16(w), H, percdamp)
+        assert np.array_equal(codes_of(got[0], K), codes) and np.array_equal(f16_bits(got[1]), s_wg)
