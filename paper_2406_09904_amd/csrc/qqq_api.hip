@@ -1,4 +1,5 @@
 // C-ABI entry points of libqqq: argument validation and kernel-family dispatch (host code only).
+#include <math.h>
 #include <stdarg.h>
 #include <stdio.h>
 #include <string.h>
@@ -77,30 +78,31 @@ static size_t split_bytes(int64_t M, int64_t N) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Dispatch model: every fitted constant the automatic kernel choice uses, in one place.  All were
-// measured on one MI355X with the kernels of this library on the benchmark's layer shapes
-// (K x N = 4096 x 4096, 4096 x 11008, 5120 x 13824, 11008 x 4096, 8192 x 28672, 21760 x 8192),
-// timing GEMM launches back to back from a HIP graph with the weights rotated through > 1 GiB:
-//   tile[]        K swept at fixed M, N for each forced tile shape; the slope is the cost of one
-//                 k-step (128 k) of one workgroup in microseconds, measured once with at most one
-//                 workgroup per CU ("alone") and once with several times more tiles than CUs,
-//                 divided by the tiles per CU ("saturated"); the intercept (~4 k-steps) is the
-//                 ring fill plus the epilogue of a tile.
-//   stream_tbs    what the weight stream of a launch reaches at best (plain-read probe, 35-117 MiB).
-//   launch_us     one more kernel in the stream (empty-kernel spacing).
-//   reduce_tbs    the K-split reduce kernel's traffic rate (splits * M * N int32 written and read).
-//   margins       how much cheaper (modelled) an alternative must be before the large tile or the
-//                 unsplit launch is given up.  With all of this, on 126 shapes drawn over K = 1024 .. 11008,
-//                 N = 1024 .. 28672, M = 65 .. 4096 and three conversions, the pick is 1 % behind the best forced
-//                 choice on average and 17 % at most.
-//   decode_*      time of the decode kernel for 17..64 rows: decode_base_us + c(M) * N*K/1e6 with
-//                 c linear in M per channel-group width, the width being the launcher's own choice
-//                 (fit over M = 17..64 on the six layers plus 8192 x 8192, 5120 x 5120).
-//   pergroup_prepass_us  what the biased integer route pays on top of its tiles: the pre-pass launch and the
-//                 correction at the start of each tile.
+// Dispatch model: every fitted constant the automatic kernel choice uses, in one place.  Fitted to every forced
+// choice on 2145 shapes (K = 1024 .. 11008, N = 1024 .. 28672, M = 17 .. 4096, five layers of the benchmark among them) times four
+// conversions on one MI355X: GEMM launches back to back from HIP graphs replayed in turn, packed weights rotated through
+// 512 MiB and more.
+//   tile[]        one row per conversion (what an int4 weight costs to convert decides how much a tile gains from
+//                 having many rows), one entry per tile shape.  With x workgroups per CU, r the whole part of x and f the
+//                 rest, a launch of T k-steps (128 k) takes, in microseconds,
+//                   x <= 1:  fixed + per_round     + T (alone (1 - x) + full x)
+//                   x >  1:  fixed + per_round * x + T (rounds x + [f > 0] rest (1 - f))
+//                 alone: a k-step of one workgroup on an idle chip; full: with one on every CU (shared bandwidth, lower
+//                 clock); rounds: of a whole round when there are several; rest: what a partial last round costs beyond its
+//                 share.  2 to 3 % rms on all of them.  An even spread or whole rounds alone miss by 10 to 30 %: M = 2048,
+//                 K = 4096, N = 11008 took 89 us in 1.4 rounds of 128 x 512 and takes 80 in 2.7 rounds of 128 x 256.
+//   stream_tbs    what the weight stream of a prefill launch reaches at best; nothing is modelled to be faster.
+//   split_*       the K-split's slabs and its second kernel: a launch, a part per split (they are read one after the other), and a
+//                 part per million raw int32 of the slabs (6 TB/s written and read).
+//   margin_split, min_ksteps_per_split  a split must be 3 % cheaper (modelled), its parts five k-steps long.
+//   margin_persistent  per-channel, the persistent kernel and the same tile one by one are as close as the model's error up to
+//                 40 k-steps (K = 5120, M = 2048, N = 13824: 118.8 and 119.0 us): there the persistent one keeps what is within
+//                 3.5 %; from 64 on it is 5 % behind on average.
+//   decode[]      the decode kernel at 17..64 rows, per conversion (per-channel; scale on partial sums; real-valued; saturating)
+//                 and channel tiles of a workgroup (1, 2, 4 or more): with g = N K / 1e6 weights, x workgroups per CU, w the
+//                 whole rounds over x, R the row tiles,  base + per_wg x R + g (w (a + b R) + c M).  4 to 9 % rms.
+// On those shapes the pick is 0.5 % behind the best forced choice on average, 5 to 9 % in one of a hundred.
 // A test times the automatic pick against every forced pick on a small grid (15 % bar).
-// What an int4 weight costs to convert decides how much a tile gains from having many rows, so tile[] is
-// measured per conversion.
 enum CostClass : int { kCostChannel, kCostBias, kCostFma, kCostReal, kCostClamp, kCostClasses };
 static int cost_class(int mode) {
   switch (mode) {
@@ -113,92 +115,106 @@ static int cost_class(int mode) {
   }
   return kCostFma;
 }
-struct TileCost { int shape, bm, bn; double alone_us, saturated_us; };
+constexpr int kPersistent = 6;  // as a shape: the persistent kernel; the others are those of launch_gemm_prefill_dma
+struct TileCost { int shape, bm, bn; double alone, full, rounds, rest, fixed, per_round; };
+struct DecodeCost { double base, per_wg, a, b, c; };
 static const struct DispatchModel {
-  TileCost tile[kCostClasses][4] = {
-      {{0, 128, 512, 1.15, 1.33}, {3, 128, 256, 0.71, 0.78}, {4, 128, 128, 0.63, 0.52}, {5, 64, 128, 0.39, 0.275}},
-      {{0, 256, 256, 1.29, 1.58}, {3, 128, 256, 0.89, 0.92}, {4, 128, 128, 0.66, 0.52}, {5, 64, 128, 0.45, 0.303}},
-      {{0, 256, 256, 1.42, 1.68}, {3, 128, 256, 1.05, 1.10}, {4, 128, 128, 0.74, 0.66}, {5, 64, 128, 0.557, 0.43}},
-      {{0, 256, 256, 1.53, 1.80}, {3, 128, 256, 1.06, 1.16}, {4, 128, 128, 0.76, 0.65}, {5, 64, 128, 0.63, 0.47}},
-      {{0, 256, 256, 1.90, 1.95}, {3, 128, 256, 1.44, 1.41}, {4, 128, 128, 0.94, 0.69}, {5, 64, 128, 0.80, 0.50}}};
-  double tile_fixed_ksteps = 4.0;
-  double stream_tbs = 5.0;
-  double launch_us = 2.4;
-  double reduce_tbs = 3.0;
-  double margin_split = 0.88, margin_leave_large_tile = 0.95;
-  int min_ksteps_per_split = 4;
-  double decode_base_us = 5.0;
-  double decode_c64_lo[2] = {0.038, 0.0015}, decode_c64_hi[2] = {0.044, 0.0011};  // 64- and 128-channel groups: M <= 32, M > 32
-  double decode_c32_lo[2] = {0.06, 0.0008}, decode_c32_hi[2] = {0.093, 0.0007};   // 32-channel groups
-  double decode_c16_lo[2] = {0.04, 0.0031}, decode_c16_hi[2] = {0.12, 0.0023};    // 16-channel groups
-  double prefill_wins_by = 0.92;             // the prefill path must be this much cheaper at 17..64 rows
-  double pergroup_prepass_us = 7.5;
-  double perchannel_extra_us = 2.5;
+  TileCost tile[kCostClasses][6] = {
+      {  // per-channel
+          {0, 128, 512, 0.866, 1.409, 1.244, 1.272, -4.0, 12.5},
+          {3, 128, 256, 0.490, 0.787, 0.705, 0.710, -1.4, 7.2},
+          {4, 128, 128, 0.399, 0.544, 0.446, 0.307, 2.6, 2.9},
+          {5, 64, 128, 0.252, 0.337, 0.259, 0.177, 3.6, 1.0},
+          {kPersistent, 128, 512, 0.968, 1.492, 1.380, 1.229, 0.9, 6.9}},
+      {  // biased integer (with its pre-pass)
+          {0, 128, 512, 1.152, 1.693, 1.517, 1.677, -2.6, 15.9},
+          {1, 256, 256, 1.053, 1.604, 1.438, 1.622, -2.7, 16.1},
+          {3, 128, 256, 0.644, 0.999, 0.857, 0.940, 1.0, 8.9},
+          {4, 128, 128, 0.511, 0.711, 0.547, 0.358, 5.7, 3.3},
+          {5, 64, 128, 0.406, 0.551, 0.339, 0.276, 6.9, 1.1},
+          {kPersistent, 128, 512, 1.228, 1.717, 1.599, 1.635, 2.1, 11.3}},
+      {  // fp16 FMA
+          {0, 128, 512, 1.717, 2.148, 2.074, 2.122, -4.4, 13.7},
+          {1, 256, 256, 1.252, 1.677, 1.594, 1.715, -4.2, 13.0},
+          {3, 128, 256, 0.885, 1.146, 1.073, 1.080, -1.3, 7.6},
+          {4, 128, 128, 0.578, 0.728, 0.587, 0.423, 2.8, 2.5},
+          {5, 64, 128, 0.439, 0.540, 0.392, 0.366, 4.0, 0.7},
+          {kPersistent, 128, 512, 1.704, 2.111, 2.087, 1.942, 0.2, 7.6}},
+      {  // real-valued scale
+          {0, 128, 512, 1.879, 2.220, 2.110, 2.285, -3.7, 13.0},
+          {1, 256, 256, 1.318, 1.692, 1.613, 1.768, -3.4, 12.1},
+          {3, 128, 256, 0.923, 1.155, 1.065, 1.170, -0.8, 7.1},
+          {4, 128, 128, 0.626, 0.763, 0.626, 0.494, 3.2, 2.2},
+          {5, 64, 128, 0.544, 0.637, 0.440, 0.445, 4.2, 0.5}},
+      {  // saturating
+          {0, 128, 512, 2.642, 2.916, 2.728, 3.140, -3.9, 13.9},
+          {1, 256, 256, 1.734, 2.045, 1.902, 2.213, -3.3, 12.5},
+          {3, 128, 256, 1.355, 1.564, 1.426, 1.659, -0.9, 7.6},
+          {4, 128, 128, 0.854, 0.961, 0.744, 0.710, 3.4, 2.1},
+          {5, 64, 128, 0.698, 0.780, 0.599, 0.689, 4.3, 0.5},
+          {kPersistent, 128, 512, 2.720, 2.961, 2.840, 2.993, 0.9, 7.0}}};
+  double stream_tbs = 4.6;
+  double split_us = 2.05, split_part_us = 0.28, split_mint32_us = 1.33;
+  double margin_split = 0.97, margin_persistent = 0.965;
+  int margin_persistent_ksteps = 40;
+  int min_ksteps_per_split = 5;
+  DecodeCost decode[4][3] = {
+      {{3.32, 0.094, 0.0351, 0.0235, 0.0018}, {3.01, 0.161, 0.0208, 0.0238, 0.0008}, {2.65, 0.618, 0.0402, 0.0118, 0.0003}},
+      {{3.40, 0.044, 0.0259, 0.0307, 0.0020}, {3.14, 0.180, 0.0110, 0.0304, 0.0010}, {2.89, 0.711, 0.0354, 0.0176, 0.0002}},
+      {{3.67, 0.128, 0.0429, 0.0263, 0.0020}, {3.28, 0.266, 0.0418, 0.0287, 0.0007}, {3.20, 0.650, 0.0794, 0.0140, 0.0001}},
+      {{3.76, 0.130, 0.1047, 0.0168, 0.0019}, {3.64, 0.223, 0.0813, 0.0294, 0.0005}, {3.58, 0.623, 0.1204, 0.0143, 0.0001}}};
 } kModel;
 
-// Tile shape and K split of the per-tile prefill kernel from the model: few rows want many small
-// tiles, many rows the large tile with the most reuse; when even the small tiles leave CUs idle and
-// K is long, splitting K over several workgroups per tile pays for the second kernel that sums the
-// raw tiles.  Shape 0 with one split means "the large tile": the caller then picks between the
-// persistent kernel and the per-tile one.
+// Tile shape and K split of the prefill path.  A split launches splits x tiles workgroups of T / splits k-steps plus
+// the reduce kernel, which writes and reads splits * M * N int32: it pays for long K and few tiles only (at most 1024 /
+// splits rows).
 struct PrefillPlan {
   int shape, k_splits;
   double us;  // modelled time of the GEMM
 };
-static double reduce_cost_us(int k_splits, int64_t M, int64_t N) {
-  return kModel.launch_us + 8e-6 * (double)k_splits * (double)M * (double)N / kModel.reduce_tbs;
-}
-static PrefillPlan plan_prefill(int64_t M, int64_t N, int64_t K, int cost, bool can_split, int forced_split) {
+static PrefillPlan plan_prefill(int64_t M, int64_t N, int64_t K, int cost, bool can_split, int forced_split, bool persistent = true) {
   const int cus = num_cus();
   const int T = (int)(K / 128);
   const int splits[8] = {1, 2, 3, 4, 6, 8, 12, 16};
+  const double stream_us = (double)N * (double)K * 0.5 / (kModel.stream_tbs * 1e6);
   PrefillPlan best = {0, 1, 0.0};
-  for (int i = 0; i < 4; ++i) {
-    const TileCost& c = kModel.tile[cost][i];
+  double best_score = 0.0;
+  for (const TileCost& c : kModel.tile[cost]) {
+    if (c.bm == 0) continue;
+    // (the persistent kernel needs three k-steps a tile and does not split them)
+    if (c.shape == kPersistent && (!persistent || T < 3 || forced_split > 1)) continue;
     const int64_t tiles_c = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
     for (int j = 0; j < 8; ++j) {
       int ks = splits[j];
-      if (forced_split > 0) {  // the knob: capped like the forced-shape route caps it
+      if (forced_split > 0) {  // the tuning knob: one split count, as far as it is allowed
+        if (j > 0) break;
         ks = forced_split;
-        if (ks > kSplitRows / M) ks = (int)(kSplitRows / M);
-        if (ks > T) ks = T;
-        if (ks < 1 || !can_split) ks = 1;
-      } else if (ks > 1 && (!can_split || ks * M > kSplitRows || T / ks < kModel.min_ksteps_per_split)) {
-        continue;
+        if (M <= kSplitMaxM && ks > kSplitRows / M) ks = (int)(kSplitRows / M);
+        if (!can_split || ks < 1) ks = 1;
+      } else if (ks > 1 && (!can_split || c.shape == kPersistent || ks > kSplitRows / M || T / ks < kModel.min_ksteps_per_split)) {
+        break;
       }
-      const int64_t wgs = tiles_c * ks;
-      double per_step = c.alone_us;
-      if (wgs > cus) {
-        // between an even spread and whole rounds: CUs that finish early leave the others the power budget and the
-        // bandwidth; the 8-wave shapes have a CU to themselves and come closer to whole rounds, and two
-        // workgroups of the 4-wave shapes on one CU do not yet saturate it
-        const double even = (double)wgs / cus, rounds = (double)((wgs + cus - 1) / cus);
-        const double whole = c.bn >= 256 ? 0.65 : 0.5;
-        per_step = c.saturated_us * (even + whole * (rounds - even));
-        if (c.bn < 256 && per_step < 1.25 * c.alone_us) per_step = 1.25 * c.alone_us;
-      }
-      double cost = per_step * ((double)T / ks + kModel.tile_fixed_ksteps);
-      const double stream_us = (double)N * (double)K * 0.5 / (kModel.stream_tbs * 1e6);
-      if (cost < stream_us) cost = stream_us;
-      if (ks > 1) cost += reduce_cost_us(ks, M, N);
-      // leaving the large tile has to pay, and so has a split (its model is the coarser one)
-      const bool first = (i == 0 && j == 0);
-      const double margin = ks > 1 && best.k_splits == 1
-                                ? kModel.margin_split
-                                : (best.shape == 0 && best.k_splits == 1 ? kModel.margin_leave_large_tile : 1.0);
-      if (first || cost < best.us * margin) best = {c.shape, ks, cost};
-      if (forced_split > 0) break;
+      const double x = (double)(tiles_c * ks) / cus, f = x - floor(x), t = (double)T / ks;
+      double us = c.fixed;
+      if (x <= 1.0) us += c.per_round + t * (c.alone * (1.0 - x) + c.full * x);
+      else us += c.per_round * x + t * (c.rounds * x + (f > 0.0 ? c.rest * (1.0 - f) : 0.0));
+      if (us < stream_us) us = stream_us;
+      if (ks > 1) us += kModel.split_us + ks * (kModel.split_part_us + kModel.split_mint32_us * 1e-6 * (double)M * (double)N);
+      double score = us;
+      if (ks > 1) score /= kModel.margin_split;
+      if (c.shape == kPersistent && cost == kCostChannel && T <= kModel.margin_persistent_ksteps) score *= kModel.margin_persistent;
+      if (best_score == 0.0 || score < best_score) best = {c.shape, ks, us}, best_score = score;
     }
   }
   return best;
 }
 
-int prefill_shape(int64_t M, int64_t N, int64_t K) { return plan_prefill(M, N, K, kCostChannel, false, 0).shape; }
+int prefill_shape(int64_t M, int64_t N, int64_t K) { return plan_prefill(M, N, K, kCostChannel, false, 0, false).shape; }
 
 // Modelled time of the clamp-free per-group prefill GEMM and which conversion gives it: the biased integer
 // route pays a pre-pass launch, the fp16-FMA route more per k-step, so short launches take the latter.
 static double pergroup_prefill_us(int64_t M, int64_t N, int64_t K, bool* bias_route) {
-  const double bias = plan_prefill(M, N, K, kCostBias, true, g_prefill_ksplit).us + kModel.pergroup_prepass_us;
+  const double bias = plan_prefill(M, N, K, kCostBias, true, g_prefill_ksplit).us;
   const double fma = plan_prefill(M, N, K, kCostFma, true, g_prefill_ksplit).us;
   if (bias_route) *bias_route = bias < fma;
   return bias < fma ? bias : fma;
@@ -207,24 +223,21 @@ static double pergroup_prefill_us(int64_t M, int64_t N, int64_t K, bool* bias_ro
 // Kernel family of a call: 1 = decode (split-K) kernel, 2 = prefill kernels.  Up to 16 rows the
 // decode kernel streams the weights at memory speed; beyond 64 it does not apply.  In between it
 // re-reads the activations once per 32 or 64 channels and its time grows with M, while the prefill
-// path's 64-row tiles do not care about M: the models decide.
-static int kernel_family(int64_t M, int64_t N, int64_t K, bool pergroup) {
+// path's 64-row tiles do not care about M: the models decide, each with what the call's own conversion costs there.
+// `cost`: any clamp-free integer scale is kCostFma (in the decode kernel its scale goes onto partial sums, in the
+// prefill kernels it takes the better of two routes).
+static int kernel_family(int64_t M, int64_t N, int64_t K, int cost) {
   if (g_override != 0) return g_override;
   if (M <= kDecodeAlwaysMaxM) return 1;
   if (M > kSkinnyMaxM) return 2;
-  const double nk = (double)N * (double)K * 1e-6;
-  const int nt = decode_channel_tiles(N, (int)((M + 15) / 16), true);  // the launcher's own rule
-  const double* f = nt >= 4 ? (M <= 32 ? kModel.decode_c64_lo : kModel.decode_c64_hi)
-                  : nt == 2 ? (M <= 32 ? kModel.decode_c32_lo : kModel.decode_c32_hi)
-                            : (M <= 32 ? kModel.decode_c16_lo : kModel.decode_c16_hi);
-  double c = f[0] + f[1] * (double)M;
-  // 16-channel groups in more than one round of workgroups: the last round counts as a whole one
-  const int64_t wgs = N / (16 * nt), cus = num_cus();
-  if (nt == 1 && wgs > cus) c *= (double)((wgs + cus - 1) / cus) * (double)cus / (double)wgs;
-  const double decode_us = kModel.decode_base_us + c * nk;
-  const double prefill_us = pergroup ? pergroup_prefill_us(M, N, K, nullptr)
-                                     : plan_prefill(M, N, K, kCostChannel, true, g_prefill_ksplit).us + kModel.perchannel_extra_us;
-  return prefill_us < kModel.prefill_wins_by * decode_us ? 2 : 1;
+  const bool clamp_free = cost == kCostFma || cost == kCostBias;
+  const int row_tiles = (int)((M + 15) / 16);
+  const int nt = decode_channel_tiles(N, row_tiles, cost == kCostChannel || clamp_free);  // the launcher's own rule
+  const DecodeCost& d = kModel.decode[cost == kCostChannel ? 0 : clamp_free ? 1 : cost == kCostReal ? 2 : 3][nt >= 4 ? 2 : nt - 1];
+  const double g = (double)N * (double)K * 1e-6, x = (double)(N / (16 * nt)) / num_cus();
+  const double decode_us = d.base + d.per_wg * x * row_tiles + g * (ceil(x) / x * (d.a + d.b * row_tiles) + d.c * (double)M);
+  const double prefill_us = clamp_free ? pergroup_prefill_us(M, N, K, nullptr) : plan_prefill(M, N, K, cost, true, g_prefill_ksplit).us;
+  return prefill_us < decode_us ? 2 : 1;
 }
 
 // per-group conversion route from the caller's promises about the group scales (and the codes)
@@ -232,7 +245,7 @@ static int group_mode(int sg_arg, int64_t M, int64_t N, int64_t K) {
   const bool symmetric = (sg_arg & QQQ_SG_SYMMETRIC_CODES) != 0;  // no code is -8
   const int sg_max = sg_arg & ~QQQ_SG_SYMMETRIC_CODES;
   int mode = kGroupClamp;
-  const bool decode = kernel_family(M, N, K, true) == 1;
+  const bool decode = kernel_family(M, N, K, kCostFma) == 1;
   if (sg_max >= 1 && sg_max <= 16) mode = decode ? kGroupLinear : kGroupFused;
   else if (symmetric && sg_max >= 17 && sg_max <= 18) mode = decode ? kGroupLinear : kGroupFusedWide;
   // (knob 3 asks for the fp16-FMA conversion: with scales of 17 and 18 that is its wide form)
@@ -285,7 +298,7 @@ static int gemm_validate(const int8_t* a_q, const float* s_a, const void* w_pack
                      "s_a, s_w and s_g 4-byte aligned");
   if (((M + 63) / 64) * ((N + 127) / 128) > 0x7FFFFFFF)
     return set_error(QQQ_ERR_SHAPE, "gemm: too many output tiles for one launch");
-  const int family = kernel_family(M, N, K, mode != kPerChannel);
+  const int family = kernel_family(M, N, K, cost_class(mode));
   if (family == 1 && M > kSkinnyMaxM)
     return set_error(QQQ_ERR_SHAPE, "gemm: skinny kernel forced but M=%lld > %d", (long long)M,
                      kSkinnyMaxM);
@@ -309,7 +322,7 @@ static int gemm_common(const int8_t* a_q, const float* s_a, const void* w_packed
     const int rc = gemm_validate(a_q, s_a, w_packed, s_g, s_w, y, M, N, K, workspace, workspace_bytes, mode, fused);
     if (rc != QQQ_OK || M == 0) return rc;
   }
-  const int family = kernel_family(M, N, K, mode != kPerChannel);
+  const int family = kernel_family(M, N, K, cost_class(mode));
   GemmParams p;
   p.a_q = a_q;
   p.s_a = s_a;
@@ -337,7 +350,6 @@ static int gemm_common(const int8_t* a_q, const float* s_a, const void* w_packed
     p.ws_acc = (int32_t*)((char*)workspace + ws_counter_bytes(N));
     return launch_gemm_skinny(p, mode, (hipStream_t)stream);
   }
-  const int64_t tiles = ((M + 127) / 128) * ((N + 511) / 512);
   const int tune = get_prefill_tuning();
   if (mode == kGroupCvt) return launch_gemm_prefill_dma(p, mode, 0, (hipStream_t)stream);
   // Clamp-free per-group request with a workspace of the queried size: the biased integer
@@ -371,22 +383,15 @@ static int gemm_common(const int8_t* a_q, const float* s_a, const void* w_packed
     return rc != QQQ_OK ? rc : launch_splitk_reduce(p, mode, (hipStream_t)stream);
   };
   const int forced_split = get_prefill_ksplit();
-  if (tune == 10 || (tune >= 15 && tune <= 17) || tune == 27 || tune == 37)
-    return per_tile(tune >= 15 ? tune % 10 - 2 : 0, forced_split > 0 ? forced_split : 1);
+  if (tune == 10 || tune == 11 || (tune >= 15 && tune <= 17) || tune == 27 || tune == 37)
+    return per_tile(tune >= 15 ? tune % 10 - 2 : (tune == 10 && mode != kPerChannel ? 1 : 0), forced_split > 0 ? forced_split : 1);
   if (tune == 13) return launch_gemm_prefill_ring(p, mode, (hipStream_t)stream);
   {
     const PrefillPlan plan = plan_prefill(M, N, K, cost_class(mode), can_split, forced_split);
-    if (plan.shape != 0 || plan.k_splits > 1) return per_tile(plan.shape, plan.k_splits);
-    // Per-channel, measured on MI355X: with 64 k-steps or more the per-tile kernel is 2-6 % ahead of the
-    // persistent one (K = 8192: 636 against 660 us on the 28672-channel layer; K = 21760: 455 against 483); with shorter K
-    // and tiles enough for a second round the persistent kernel, whose next tile's first k-steps load under the
-    // epilogue, is ahead up to K = 2048 (N = 28672, M = 2048: 97 against 102 us; K = 1024, N = 9216, M = 2500: 31 against 33) and
-    // level to 2 % behind at 4096 and 5120; without a second round it is ahead on the shortest K only (K = 1024,
-    // N = 21328, M = 699: 19.0 against 20.9; K = 2176, N = 4560, M = 2768: 27.6 against 29.5; K = 4096, N = 11008, M = 777: 42.8
-    // against 40.6).  With group scales the 256 x 256 tile is ahead of it on every shape (launch_large).
-    if (mode == kPerChannel && p.T < 64 && (tiles > num_cus() || p.T <= 24))
-      return launch_gemm_prefill_ring(p, mode, (hipStream_t)stream);
-    return launch_gemm_prefill_dma(p, mode, 0, (hipStream_t)stream);
+    // The persistent kernel's next tile loads its first k-steps under the epilogue: ahead on short K with many tiles (per-channel K = 1024,
+    // N = 27664, M = 2650 81 us against 95; saturating K = 1024, N = 16448, M = 1874 60 against 68), behind elsewhere.
+    if (plan.shape == kPersistent) return launch_gemm_prefill_ring(p, mode, (hipStream_t)stream);
+    return per_tile(plan.shape, plan.k_splits);
   }
 }
 
@@ -394,7 +399,7 @@ static bool takes_bias_route(int mode, int64_t M, int64_t N, int64_t K) {
   // (the workspace holds the pre-pass buffers only above the rows that always take the decode kernel)
   if (!((mode == kGroupFused || mode == kGroupFusedWide) && M > kDecodeAlwaysMaxM &&
         (g_group_mode == 0 || g_group_mode == 5) &&
-        kernel_family(M, N, K, true) == 2))
+        kernel_family(M, N, K, kCostFma) == 2))
     return false;
   if (g_group_mode == 5) return true;  // forced
   bool bias = true;
@@ -664,7 +669,7 @@ int qqq_gemm_w4a8_pergroup_f16scale(const int8_t* a_q, const float* s_a, const v
   route_reset();
   if (group != QQQ_GROUP) return set_error(QQQ_ERR_SHAPE, "pergroup: group must be 128, got %d", group);
   // knob 4: the conventional-conversion ablation of Fig. 9 (prefill kernel only)
-  const int mode = (g_group_mode == 4 && kernel_family(M, N, K, true) == 2) ? kGroupCvt : kGroupReal;
+  const int mode = (g_group_mode == 4 && kernel_family(M, N, K, kCostReal) == 2) ? kGroupCvt : kGroupReal;
   return gemm_common(a_q, s_a, w_packed, (const int8_t*)s_g_fp16, s_w_fp16, y_fp16, acc_out, M, N, K,
                      workspace, workspace_bytes, stream, mode);
 }

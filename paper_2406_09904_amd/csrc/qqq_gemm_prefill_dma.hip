@@ -4,7 +4,7 @@
 //
 // Shape parameters: NW waves split N; each wave owns a (32*MT) x (32*CT) patch of Y, so the
 // workgroup tile is (32*MT) x (NW*32*CT).  Instances:
-//   <4,2,8>  128 x 512 (per-channel), <8,1,8>  256 x 256 (per-group): 8 waves, 128 accumulator registers, two waves
+//   <4,2,8>  128 x 512, <8,1,8>  256 x 256 (group scales only): 8 waves, 128 accumulator registers, two waves
 //            per SIMD
 //   <4,1,8>  128 x 256, <4,1,4>  128 x 128, <2,1,4>  64 x 128: narrow tiles for mid-size M, where
 //            a few large tiles would leave most CUs idle
@@ -654,30 +654,26 @@ static bool lone_workgroups(const GemmParams& p, int bm, int bn) {
   return deep == 0 ? wgs <= num_cus() : deep > 3;
 }
 
-// The large tile: 128 x 512 per-channel, 256 x 256 per-group.  Both are the same MFMAs per k-step and the same 128
-// accumulator registers; 256 rows by 32 channels a wave halve the conversions per MFMA and double the
-// activation fragments read from LDS (256 KiB a k-step, level with the MFMAs).  Per-channel conversion is too cheap
-// for that to pay (K = 8192, N = 28672, M = 4096: 644 us against 660 with 256 x 256); the group conversions
-// all gain (N = 11008, K = 4096, M = 4096: real-valued scale 219 -> 173 us, saturating 292 -> 203, biased integer 172 -> 165;
-// N = 28672, K = 8192: 1027 -> 858 real-valued, 806 -> 774 biased).
-template <int MODE>
-static int launch_large(const GemmParams& p, hipStream_t st) {
-  if constexpr (MODE == kPerChannel) return launch_dma<MODE, 4, 2, 8>(p, st);
-  else return launch_dma<MODE, 8, 1, 8>(p, st);
-}
-
 template <int MODE>
 static int launch_shape(const GemmParams& p, int shape, hipStream_t st) {
   switch (shape) {
     case 3: return launch_dma<MODE, 4, 1, 8>(p, st);
     case 4: return launch_dma<MODE, 4, 1, 4>(p, st);
     case 5: return lone_workgroups(p, 64, 128) ? launch_dma<MODE, 2, 1, 4, 6>(p, st) : launch_dma<MODE, 2, 1, 4>(p, st);
-    default: return launch_large<MODE>(p, st);
+    case 1:
+      if constexpr (MODE != kPerChannel) return launch_dma<MODE, 8, 1, 8>(p, st);
   }
+  return launch_dma<MODE, 4, 2, 8>(p, st);
 }
 
-// shape: 0 = the large tile with 8 waves (128x512, or 256x256 with group scales); narrow tiles for shapes with few rows, where the number
-// of workgroups matters more than the reuse inside one: 3 = 128x256 with 8 waves, 4 = 128x128
+// The two large tiles are the same MFMAs per k-step and the same 128 accumulator registers; 256 rows by 32 channels a
+// wave halve the conversions per MFMA and double the activation fragments read from LDS (256 KiB a k-step, level with
+// the MFMAs).  Per-channel conversion is too cheap for that to pay (K = 8192, N = 28672, M = 4096: 644 us against 660 with
+// 256 x 256); with group scales 256 x 256 is ahead (N = 11008, K = 4096, M = 4096: real-valued scale 173 us against 219, saturating 203 against
+// 292, biased integer 165 against 172) except where 128 x 512 covers the rows in a round less (N = 14288, K = 4352, M = 1140,
+// biased: 252 tiles in 71 us, 280 of 256 x 256 or 504 of 128 x 256 in 80).
+// shape: 0 = 128x512 with 8 waves, 1 = 256x256 with 8 waves (group scales only); narrow tiles for shapes with few rows, where
+// the number of workgroups matters more than the reuse inside one: 3 = 128x256 with 8 waves, 4 = 128x128
 // with 4 waves, 5 = 64x128 with 4 waves
 int launch_gemm_prefill_dma(const GemmParams& p, int mode, int shape, hipStream_t st) {
   switch (mode) {
@@ -689,7 +685,7 @@ int launch_gemm_prefill_dma(const GemmParams& p, int mode, int shape, hipStream_
     case kGroupFusedWide:
     case kGroupFused: return launch_shape<kGroupFused>(p, shape, st);
     case kGroupReal: return launch_shape<kGroupReal>(p, shape, st);
-    case kGroupCvt: return launch_large<kGroupCvt>(p, st);  // timing ablation: one shape
+    case kGroupCvt: return launch_dma<kGroupCvt, 8, 1, 8>(p, st);  // timing ablation: one shape
     case kGroupBias: return launch_shape<kGroupBias>(p, shape, st);
     case kGroupBiasWide: return launch_shape<kGroupBiasWide>(p, shape, st);
   }

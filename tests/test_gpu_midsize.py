@@ -148,13 +148,20 @@ def test_forced_persistent_kernel(variant, hi, sg_max):
         check(*run(variant, a_q, s_a, w, s_w, K, s_g=s_g, sg_max=sg_max), o_acc, o_y)
 
 
-def test_automatic_choice_of_the_persistent_kernel_with_the_biased_route():
-    """More 128x512 tiles than CUs (9 x 32 = 288) and a short K: per-group with s_g <= 16 and a
-    workspace takes the persistent kernel with the biased conversion; every element against the oracle."""
-    M, K, N = 1100, 512, 16384
+@pytest.mark.parametrize("variant,sg_max,M,K,N,route", [
+    ("pc", 0, 1100, 512, 16384, "prefill persistent tile=128x512 mode=0"),
+    ("pc", 0, 599, 1024, 22944, "prefill persistent tile=128x512 mode=0"),
+    ("pg", 16, 599, 1024, 22944, "prefill persistent tile=128x512 mode=3"),
+    ("pg", 0, 599, 1024, 22944, "prefill persistent tile=128x512 mode=2"),
+    ("pg", 16, 1380, 1152, 27088, "group-bias pre-pass + prefill persistent tile=128x512 mode=5"),
+    ("pg", 16, 1100, 512, 16384, "prefill per-tile tile=64x128")])
+def test_automatic_choice_of_the_persistent_kernel(variant, sg_max, M, K, N, route):
+    """Short K and several 128x512 tiles per CU: the persistent kernel per conversion route, and a shape on which narrow
+    tiles are ahead of it; every element against the oracle."""
     a_q, s_a, w, s_w = inputs(M, K, N, 21)
-    s_g, o_acc, o_y = reference("pg", a_q, s_a, w, s_w, K, N, 19, 16)
-    check(*run("pg", a_q, s_a, w, s_w, K, s_g=s_g, sg_max=16), o_acc, o_y)
+    s_g, o_acc, o_y = reference(variant, a_q, s_a, w, s_w, K, N, 19, sg_max or 100)
+    check(*run(variant, a_q, s_a, w, s_w, K, s_g=s_g, sg_max=sg_max), o_acc, o_y)
+    assert route in qqq.last_route(), qqq.last_route()
 
 
 @pytest.mark.parametrize("M,K,N", [(1100, 512, 16400), (1100, 384, 44048), (2065, 640, 13824)])
@@ -164,7 +171,7 @@ def test_persistent_kernel_with_more_tiles_than_cus(M, K, N, variant, hi, sg_max
     and its DMA cursor crosses tile borders (297, 783 = three per CU, and 459 tiles), ragged in M
     and N, K down to the kernel's minimum of three k-steps: automatic selection (whatever the cost
     model picks for the shape) and the persistent kernel forced; every element against the oracle.
-    The automatic choice of the persistent kernel itself is checked at the benchmark's full sizes."""
+    The automatic choice of the persistent kernel itself is checked above and at the benchmark's full sizes."""
     a_q, s_a, w, s_w = inputs(M, K, N, M + K + N + 5)
     s_g, o_acc, o_y = reference(variant, a_q, s_a, w, s_w, K, N, 23, hi or 16)
     check(*run(variant, a_q, s_a, w, s_w, K, s_g=s_g, sg_max=sg_max), o_acc, o_y)
