@@ -43,6 +43,16 @@ __device__ __forceinline__ uint32_t block_max(uint32_t v, uint32_t* smem) {
 
 }  // namespace
 
+// absmax_bits one pattern at a time.  The per-channel kernel has little to do between its loads and its reduction, and there
+// this form is ahead of two at a time (N = 11008, K = 4096: 19.9 us against 20.5; N = 4096: 9.9 against 10.2); the per-group kernel is
+// bound by its instructions and takes the other.
+__device__ __forceinline__ uint32_t absmax_bits_each(uint4 v, uint32_t cur) {
+  const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) cur = max(cur, max(w[i] & 0x7FFFu, (w[i] >> 16) & 0x7FFFu));
+  return cur;
+}
+
 // Per-channel: one workgroup per channel.
 // VPT > 0: the row fits in VPT 128-bit vectors per thread and stays in registers.
 // VPT == 0: any K; the row is read twice (the second read hits L2).
@@ -63,10 +73,10 @@ __global__ __launch_bounds__(256) void quant_weight_channel_kernel(const uint4* 
       const int idx = threadIdx.x + 256 * j;
       v[j] = make_uint4(0, 0, 0, 0);
       if (idx < nvec) v[j] = row[idx];
-      amax_bits = absmax_bits(v[j], amax_bits);
+      amax_bits = absmax_bits_each(v[j], amax_bits);
     }
   } else {
-    for (int idx = threadIdx.x; idx < nvec; idx += 256) amax_bits = absmax_bits(row[idx], amax_bits);
+    for (int idx = threadIdx.x; idx < nvec; idx += 256) amax_bits = absmax_bits_each(row[idx], amax_bits);
   }
   amax_bits = block_max(amax_bits, smem);
   const uint16_t sb = scale_bits(half_bits_to_float(amax_bits), 7.0f);
