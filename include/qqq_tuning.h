@@ -15,8 +15,8 @@ extern "C" {
 #endif
 
 /*
- * Which kernels the most recent GEMM or linear call of the calling thread enqueued, as a short
- * host string (never NULL), e.g. "decode nt=4 mt=1 waves=8 depth=1 kslices=1 fused=1 mode=0 grid=448" or
+ * Which kernels the most recent GEMM or linear call (or qqq_fp16_gemm_nt, qqq_adaptive_smoothing) of the calling thread
+ * enqueued, as a short host string (never NULL), e.g. "decode nt=4 mt=1 waves=8 depth=1 kslices=1 fused=1 mode=0 grid=448" or
  * "prefill persistent tile=128x512 mode=0 tiles=1792 grid=256" or "prefill per-tile tile=64x128 waves=4
  * ring=6 ksplit=4 mode=5 grid=64 + k-split reduce"; a preceding "quant_act + " or "group-bias pre-pass + "
  * names the other launches of the call.  For benchmarks and tests that must know which route they measured or compared.

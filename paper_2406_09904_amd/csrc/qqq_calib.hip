@@ -344,6 +344,28 @@ __global__ __launch_bounds__(256) void fp16_gemm_nt_kernel(const uint4* x, const
   }
 }
 
+// The same product for small problems: one wave per 32 x 32 tile, no LDS.  Lane l holds row (A) / column (B) l % 32 and the 8
+// consecutive k of half l / 32 straight from memory (each lane walks its own row 16 bytes at a time); register v of the result
+// as above.
+__global__ __launch_bounds__(64) void fp16_gemm_nt_wave_kernel(const uint4* x, const uint4* w, int M, int N, int kvec, float* y) {
+  const int lane = threadIdx.x, r32 = lane & 31, h = lane >> 5;
+  const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 32;
+  const uint4* xa = x + (int64_t)min(m0 + r32, M - 1) * kvec + h;
+  const uint4* wb = w + (int64_t)min(n0 + r32, N - 1) * kvec + h;
+  v16f acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+  for (int i = 0; i < kvec; i += 2)
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, xa[i]), __builtin_bit_cast(v8h, wb[i]), acc, 0, 0, 0);
+  const int n = n0 + r32;
+  if (n >= N) return;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int m = m0 + 8 * (v >> 2) + 4 * h + (v & 3);
+    if (m < M) y[(int64_t)m * N + n] = acc[v];
+  }
+}
+
 // ------------------------------------------------------------------ the grid's minimum
 
 __global__ void argmin_kernel(const double* losses, int G, int32_t* best) {
@@ -498,9 +520,30 @@ static int launch_smooth(const void* x, const void* w, const float* absmax, cons
   return check_launch("smooth_apply (weights)");
 }
 
+// Which of the two: the tiles pay a fill of four stages of 64 k and a barrier each, the waves a memory latency per 16 k.  The
+// waves are ahead where K is tiny (M = 2048, N = 11008, K = 16: 16.6 us, bound by the output, against 35); up to K = 1280 while
+// they are few (M = 1, N = 300, K = 128 3.4 us against 5.4; M = 512, N = 1024, K = 512 7.0 against 7.6), a few more where the
+// rows do not all start on the same memory channels and an L2 holds them (M = 512, N = 1024, K = 1040 11.3 against 12.9; N = 2048,
+// K = 1024 19 against 13; M = 1, N = 11008, K = 1040 23 against 13.6); and with few rows, which come from the same cache lines, longer: up to 16 rows K = 2048 (3 to 16 %), up to four rows
+// K = 16384 (N = 512 109 us against 116), one wave alone always (M = 1, N = 16, K = 65536 362 against 427).
+static bool waves_ahead(int64_t M, int64_t N, int64_t K) {
+  const int64_t waves = ((M + 31) / 32) * ((N + 31) / 32), work = waves * K;
+  if (K <= 48 || (waves == 1 && M <= 16)) return true;
+  if (K <= 256) return work <= 230000;
+  if (K <= 1280) return work <= 300000 ? (M + N) * K <= 9000000 : waves <= 1024 && M <= 512 && K % 128 != 0 && (M + N) * K <= 2700000;
+  if (M <= 4 && K >= 8192) return work <= 300000 && K <= 16384;
+  return work <= 131072 && K <= (M <= 4 ? 8192 : M <= 16 ? 2048 : 0);
+}
 static int launch_fp16_gemm(const void* x, const void* w, int64_t M, int64_t N, int64_t K, float* y, hipStream_t st) {
+  if (waves_ahead(M, N, K)) {
+    hipLaunchKernelGGL(fp16_gemm_nt_wave_kernel, dim3((unsigned)((N + 31) / 32), (unsigned)((M + 31) / 32)), dim3(64), 0, st,
+                       (const uint4*)x, (const uint4*)w, (int)M, (int)N, (int)(K / 8), y);
+    route_note("fp16 tile=32x32");
+    return check_launch("fp16_gemm_nt (waves)");
+  }
   hipLaunchKernelGGL(fp16_gemm_nt_kernel, dim3((unsigned)((N + 127) / 128), (unsigned)((M + 63) / 64)), dim3(256), 0, st,
                      (const uint4*)x, (const uint4*)w, (int)M, (int)N, (int)(K / 8), y);
+  route_note("fp16 tile=64x128");
   return check_launch("fp16_gemm_nt");
 }
 
@@ -533,6 +576,7 @@ int qqq_smooth_apply(const void* x_fp16, const void* w_fp16, const float* absmax
 }
 
 int qqq_fp16_gemm_nt(const void* x_fp16, const void* w_fp16, int64_t M, int64_t N, int64_t K, float* y, void* stream) {
+  route_reset();
   if (M < 1 || N < 1 || M > 0x7FFFFFF0 || N > 0x7FFFFFF0 || K < 16 || K % 16 != 0 || K > (1 << 24) ||
       (M + 31) / 32 > 65535)
     return set_error(QQQ_ERR_SHAPE, "fp16_gemm_nt: unsupported M=%lld N=%lld K=%lld (need K%%16==0, M <= 2097120)",
@@ -551,6 +595,7 @@ size_t qqq_smoothing_workspace_bytes(int64_t M, int64_t N, int64_t K) {
 int qqq_adaptive_smoothing(const void* x_fp16, const void* w_fp16, int64_t M, int64_t N, int64_t K, int grid_points,
                            void* xs_fp16, void* ws_fp16, float* s, float* sigmas, double* losses, int32_t* best,
                            void* workspace, size_t workspace_bytes, void* stream) {
+  route_reset();
   if (!calib_shape_ok(M, N, K) || (M + 31) / 32 > 65535)
     return set_error(QQQ_ERR_SHAPE, "adaptive_smoothing: unsupported M=%lld N=%lld K=%lld (need N%%16==0, K%%128==0, "
                      "128<=K<=131072, M <= 2097120)", (long long)M, (long long)N, (long long)K);

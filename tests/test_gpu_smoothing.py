@@ -41,11 +41,17 @@ def test_grid_points_equal_their_steps(M, K, N, G):
     assert torch.equal(got["xs"], xs) and torch.equal(got["ws"], ws) and torch.equal(got["s"], s)
 
 
-@pytest.mark.parametrize("M,K,N", [(1, 16, 1), (65, 48, 129), (64, 64, 128), (130, 80, 255), (33, 1040, 300)])
-def test_reference_product_tiles(M, K, N):
-    """Ragged 64 x 128 tiles and K not divisible by a stage of 64: |error| <= K 2^-24 sum |x w| (fp32 sums in any order)."""
+@pytest.mark.parametrize("M,K,N,tile", [
+    (1, 16, 1, "32x32"), (65, 48, 129, "32x32"), (64, 64, 128, "32x32"), (130, 80, 255, "32x32"), (33, 1040, 300, "32x32"),
+    (16, 2048, 33, "32x32"), (4, 16384, 256, "32x32"), (2, 20480, 16, "32x32"), (257, 16, 9000, "32x32"), (512, 1040, 1024, "32x32"),
+    (65, 1296, 129, "64x128"), (64, 1344, 128, "64x128"), (130, 1360, 255, "64x128"), (17, 2064, 1, "64x128"),
+    (5, 16400, 300, "64x128"), (257, 128, 9000, "64x128")])
+def test_reference_product_tiles(M, K, N, tile):
+    """Ragged 64 x 128 tiles with K not divisible by a stage of 64, and the one-wave tiles of small problems:
+    |error| <= K 2^-24 sum |x w| (fp32 sums in any order)."""
     x = torch.from_numpy(synth.activations_fp16(M, K, 800 + K, "normal", 0.02, 10.0)).cuda()
     w = torch.from_numpy(synth.weights_fp16(N, K, 801 + K)).cuda()
     y = qqq.qqq_fp16_gemm_nt(x, w).double()
-    bound = (x.double().abs() @ w.double().abs().t()) * K * 2.0 ** -24
-    assert bool(((y - x.double() @ w.double().t()).abs() <= bound).all())
+    assert qqq.last_route() == "fp16 tile=" + tile
+    bound = (x.double().abs() @ w.double().abs().t().contiguous()) * K * 2.0 ** -24
+    assert bool(((y - x.double() @ w.double().t().contiguous()).abs() <= bound).all())
