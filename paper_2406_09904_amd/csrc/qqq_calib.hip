@@ -520,19 +520,13 @@ static int launch_smooth(const void* x, const void* w, const float* absmax, cons
   return check_launch("smooth_apply (weights)");
 }
 
-// Which of the two: the tiles pay a fill of four stages of 64 k and a barrier each, the waves a memory latency per 16 k.  The
-// waves are ahead where K is tiny (M = 2048, N = 11008, K = 16: 16.6 us, bound by the output, against 35); up to K = 1280 while
-// they are few (M = 1, N = 300, K = 128 3.4 us against 5.4; M = 512, N = 1024, K = 512 7.0 against 7.6), a few more where the
-// rows do not all start on the same memory channels and an L2 holds them (M = 512, N = 1024, K = 1040 11.3 against 12.9; N = 2048,
-// K = 1024 19 against 13; M = 1, N = 11008, K = 1040 23 against 13.6); and with few rows, which come from the same cache lines, longer: up to 16 rows K = 2048 (3 to 16 %), up to four rows
-// K = 16384 (N = 512 109 us against 116), one wave alone always (M = 1, N = 16, K = 65536 362 against 427).
+// Which of the two: the tiles pay a fill of four stages of 64 k and a barrier each, the waves a memory latency per 16 k.  With
+// operands that come from memory, as a layer's do, the waves are ahead up to K = 256 while they are few (M = 1, N = 300: K = 128 3.4 us
+// against 5.4, K = 256 level to 9 % ahead) and where K is tiny at any size (M = 2048, N = 11008, K = 16: 16.6 us, bound by the output, against 35).
+// From K = 512 on they are behind, 10 % there and up to 2.4 times beyond, although on operands that an L2 holds already they
+// would still lead by up to 17 % at K = 512 .. 1040.
 static bool waves_ahead(int64_t M, int64_t N, int64_t K) {
-  const int64_t waves = ((M + 31) / 32) * ((N + 31) / 32), work = waves * K;
-  if (K <= 48 || (waves == 1 && M <= 16)) return true;
-  if (K <= 256) return work <= 230000;
-  if (K <= 1280) return work <= 300000 ? (M + N) * K <= 9000000 : waves <= 1024 && M <= 512 && K % 128 != 0 && (M + N) * K <= 2700000;
-  if (M <= 4 && K >= 8192) return work <= 300000 && K <= 16384;
-  return work <= 131072 && K <= (M <= 4 ? 8192 : M <= 16 ? 2048 : 0);
+  return K <= 48 || (K <= 256 && ((M + 31) / 32) * ((N + 31) / 32) * K <= 180000);
 }
 static int launch_fp16_gemm(const void* x, const void* w, int64_t M, int64_t N, int64_t K, float* y, hipStream_t st) {
   if (waves_ahead(M, N, K)) {

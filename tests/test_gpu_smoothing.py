@@ -42,10 +42,9 @@ def test_grid_points_equal_their_steps(M, K, N, G):
 
 
 @pytest.mark.parametrize("M,K,N,tile", [
-    (1, 16, 1, "32x32"), (65, 48, 129, "32x32"), (64, 64, 128, "32x32"), (130, 80, 255, "32x32"), (33, 1040, 300, "32x32"),
-    (16, 2048, 33, "32x32"), (4, 16384, 256, "32x32"), (2, 20480, 16, "32x32"), (257, 16, 9000, "32x32"), (512, 1040, 1024, "32x32"),
-    (65, 1296, 129, "64x128"), (64, 1344, 128, "64x128"), (130, 1360, 255, "64x128"), (17, 2064, 1, "64x128"),
-    (5, 16400, 300, "64x128"), (257, 128, 9000, "64x128")])
+    (1, 16, 1, "32x32"), (65, 48, 129, "32x32"), (64, 64, 128, "32x32"), (130, 80, 255, "32x32"), (257, 16, 9000, "32x32"),
+    (33, 256, 7000, "32x32"), (33, 1040, 300, "64x128"), (65, 1296, 129, "64x128"), (64, 320, 128, "64x128"), (130, 336, 255, "64x128"),
+    (17, 2064, 1, "64x128"), (1, 272, 1, "64x128"), (257, 80, 9000, "64x128")])
 def test_reference_product_tiles(M, K, N, tile):
     """Ragged 64 x 128 tiles with K not divisible by a stage of 64, and the one-wave tiles of small problems:
     |error| <= K 2^-24 sum |x w| (fp32 sums in any order)."""
