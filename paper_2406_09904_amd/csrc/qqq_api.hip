@@ -89,7 +89,8 @@ static size_t split_bytes(int64_t M, int64_t N) {
 //                   x >  1:  fixed + per_round * x + T (rounds x + [f > 0] rest (1 - f))
 //                 alone: a k-step of one workgroup on an idle chip; full: with one on every CU (shared bandwidth, lower
 //                 clock); rounds: of a whole round when there are several; rest: what a partial last round costs beyond its
-//                 share.  2 to 3 % rms on all of them.  An even spread or whole rounds alone miss by 10 to 30 %: M = 2048,
+//                 share.  2 to 3 % rms on all of them.  (The smoothing search's row is fitted to the differences between the four tiles
+//                 on 2082 searches, so only its differences mean anything; its pick is 0.2 % behind the best tile, 5 % at most.)  An even spread or whole rounds alone miss by 10 to 30 %: M = 2048,
 //                 K = 4096, N = 11008 took 89 us in 1.4 rounds of 128 x 512 and takes 80 in 2.7 rounds of 128 x 256.
 //   stream_tbs    what the weight stream of a prefill launch reaches at best; nothing is modelled to be faster.
 //   split_*       the K-split's slabs and its second kernel: a launch, a part per split (they are read one after the other), and a
@@ -103,7 +104,7 @@ static size_t split_bytes(int64_t M, int64_t N) {
 //                 whole rounds over x, R the row tiles,  base + per_wg x R + g (w (a + b R) + c M).  4 to 9 % rms.
 // On those shapes the pick is 0.5 % behind the best forced choice on average, 5 to 9 % in one of a hundred.
 // A test times the automatic pick against every forced pick on a small grid (15 % bar).
-enum CostClass : int { kCostChannel, kCostBias, kCostFma, kCostReal, kCostClamp, kCostClasses };
+enum CostClass : int { kCostChannel, kCostBias, kCostFma, kCostReal, kCostClamp, kCostLoss, kCostClasses };
 static int cost_class(int mode) {
   switch (mode) {
     case kPerChannel: return kCostChannel;
@@ -152,7 +153,12 @@ static const struct DispatchModel {
           {3, 128, 256, 1.355, 1.564, 1.426, 1.659, -0.9, 7.6},
           {4, 128, 128, 0.854, 0.961, 0.744, 0.710, 3.4, 2.1},
           {5, 64, 128, 0.698, 0.780, 0.599, 0.689, 4.3, 0.5},
-          {kPersistent, 128, 512, 2.720, 2.961, 2.840, 2.993, 0.9, 7.0}}};
+          {kPersistent, 128, 512, 2.720, 2.961, 2.840, 2.993, 0.9, 7.0}},
+      {  // per-channel with the smoothing search's loss for an epilogue
+          {0, 128, 512, 1.241, 1.263, 1.603, 2.400, -0.4, 12.4},
+          {3, 128, 256, 0.806, 0.341, 0.898, 0.494, 0.8, 0.7},
+          {4, 128, 128, 0.717, 0.446, 0.476, 0.185, 0.9, 0.4},
+          {5, 64, 128, 0.551, 0.382, 0.235, 0.241, -1.2, 0.8}}};
   double stream_tbs = 4.6;
   double split_us = 2.05, split_part_us = 0.28, split_mint32_us = 1.33;
   double margin_split = 0.97, margin_persistent = 0.965;
@@ -167,12 +173,12 @@ static const struct DispatchModel {
 
 // Tile shape and K split of the prefill path.  A split launches splits x tiles workgroups of T / splits k-steps plus
 // the reduce kernel, which writes and reads splits * M * N int32: it pays for long K and few tiles only (at most 1024 /
-// splits rows).
+// splits rows).  products: that many of the same size in one launch.
 struct PrefillPlan {
   int shape, k_splits;
   double us;  // modelled time of the GEMM
 };
-static PrefillPlan plan_prefill(int64_t M, int64_t N, int64_t K, int cost, bool can_split, int forced_split, bool persistent = true) {
+static PrefillPlan plan_prefill(int64_t M, int64_t N, int64_t K, int cost, bool can_split, int forced_split, int products = 1) {
   const int cus = num_cus();
   const int T = (int)(K / 128);
   const int splits[8] = {1, 2, 3, 4, 6, 8, 12, 16};
@@ -182,7 +188,7 @@ static PrefillPlan plan_prefill(int64_t M, int64_t N, int64_t K, int cost, bool 
   for (const TileCost& c : kModel.tile[cost]) {
     if (c.bm == 0) continue;
     // (the persistent kernel needs three k-steps a tile and does not split them)
-    if (c.shape == kPersistent && (!persistent || T < 3 || forced_split > 1)) continue;
+    if (c.shape == kPersistent && (T < 3 || forced_split > 1)) continue;
     const int64_t tiles_c = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
     for (int j = 0; j < 8; ++j) {
       int ks = splits[j];
@@ -194,7 +200,7 @@ static PrefillPlan plan_prefill(int64_t M, int64_t N, int64_t K, int cost, bool 
       } else if (ks > 1 && (!can_split || c.shape == kPersistent || ks > kSplitRows / M || T / ks < kModel.min_ksteps_per_split)) {
         break;
       }
-      const double x = (double)(tiles_c * ks) / cus, f = x - floor(x), t = (double)T / ks;
+      const double x = (double)(tiles_c * ks * products) / cus, f = x - floor(x), t = (double)T / ks;
       double us = c.fixed;
       if (x <= 1.0) us += c.per_round + t * (c.alone * (1.0 - x) + c.full * x);
       else us += c.per_round * x + t * (c.rounds * x + (f > 0.0 ? c.rest * (1.0 - f) : 0.0));
@@ -209,7 +215,7 @@ static PrefillPlan plan_prefill(int64_t M, int64_t N, int64_t K, int cost, bool 
   return best;
 }
 
-int prefill_shape(int64_t M, int64_t N, int64_t K) { return plan_prefill(M, N, K, kCostChannel, false, 0, false).shape; }
+int loss_shape(int64_t M, int64_t N, int64_t K, int points) { return plan_prefill(M, N, K, kCostLoss, false, 0, points).shape; }
 
 // Modelled time of the clamp-free per-group prefill GEMM and which conversion gives it: the biased integer
 // route pays a pre-pass launch, the fp16-FMA route more per k-step, so short launches take the latter.

@@ -591,10 +591,11 @@ static int launch_loss(const GemmParams& p, int points, hipStream_t st) {
                      dim3((unsigned)(tiles_m * tiles_n), (unsigned)points), dim3(NW * 64), 0, st, p, tiles_m, tiles_n);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return set_error(QQQ_ERR_HIP, "smoothing gemm launch: %s", hipGetErrorString(e));
+  route_note("loss tile=%dx%d points=%d", S::kBM, S::kBN, points);
   return QQQ_OK;
 }
 int launch_gemm_loss(const GemmParams& p, int points, hipStream_t st) {
-  switch (prefill_shape((int64_t)p.M * points, p.N, p.K)) {
+  switch (loss_shape(p.M, p.N, p.K, points)) {
     case 0: return launch_loss<4, 2, 8>(p, points, st);
     case 3: return launch_loss<4, 1, 8>(p, points, st);
     case 4: return launch_loss<4, 1, 4>(p, points, st);

@@ -91,7 +91,7 @@ int get_prefill_ring_depth();
 int launch_gemm_prefill_dma(const GemmParams& p, int mode, int shape, hipStream_t st);
 int launch_gemm_prefill_ring(const GemmParams& p, int mode, hipStream_t st);
 int launch_gemm_loss(const GemmParams& p, int points, hipStream_t st);
-int prefill_shape(int64_t M, int64_t N, int64_t K);  // tile the cost model picks for an unsplit per-channel GEMM
+int loss_shape(int64_t M, int64_t N, int64_t K, int points);  // tile the cost model picks for launch_gemm_loss
 int launch_splitk_reduce(const GemmParams& p, int mode, hipStream_t st);
 void set_prefill_ksplit(int s);
 int get_prefill_ksplit();

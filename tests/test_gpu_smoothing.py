@@ -1,6 +1,6 @@
-"""The smoothing search's fused grid points where its kernels change path: K at and past the rows kept in registers
-(4096 weights, 8192 activations), channel groups not divisible by the eight XCDs, more grid points than the workspace
-holds at a time, ragged token counts and every GEMM tile; against the steps it stands for, one by one.
+"""The smoothing search where its kernels change path: K at and past the rows kept in registers (4096 weights, 8192
+activations), channel groups not divisible by the eight XCDs, more grid points than the workspace holds at a time, ragged token
+counts, and each of the four tiles of the loss product; against the steps it stands for, one by one.
 
 The smoothed tensors, thresholds and vectors are compared bit for bit.  A loss is an fp64 sum built on exact integers and
 the fp32 reference product: from the steps' own integers, scales and reference product in another order it differs by
@@ -15,13 +15,20 @@ from paper_2406_09904_amd import synth
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("M,K,N,G", [(1, 128, 16, 3), (70, 4096, 144, 9), (33, 4224, 272, 4), (200, 8192, 128, 3),
-                                     (19, 8320, 48, 2), (300, 512, 4096, 21), (700, 256, 2064, 40)])
-def test_grid_points_equal_their_steps(M, K, N, G):
+@pytest.mark.parametrize("M,K,N,G,route", [
+    (1, 128, 16, 3, "loss tile=64x128 points=3"), (70, 4096, 144, 9, "loss tile=64x128 points=5 + loss tile=64x128 points=4"),
+    (33, 4224, 272, 4, "loss tile=64x128 points=4"), (200, 8192, 128, 3, "loss tile=64x128 points=3"),
+    (9, 8320, 1040, 9, "loss tile=64x128 points=5 + loss tile=64x128 points=4"), (87, 128, 2832, 23, "loss tile=128x128 points=23"),
+    (300, 512, 2064, 9, "loss tile=128x256 points=9"), (300, 512, 4096, 21, "loss tile=128x256 points=21"),
+    (700, 256, 2064, 40, "loss tile=128x128 points=25 + loss tile=128x128 points=15"),
+    (500, 2944, 4080, 8, "loss tile=128x512 points=8"),
+    (19, 8320, 48, 2, "loss tile=64x128 points=2")])
+def test_grid_points_equal_their_steps(M, K, N, G, route):
     x = torch.from_numpy(synth.activations_fp16(M, K, 700 + M, "normal", 4 / K, 40.0)).cuda()
     w = torch.from_numpy(synth.weights_fp16(N, K, 701 + M)).cuda()
     w[N // 2].zero_()                                    # a channel of zeros
     got = qqq.qqq_adaptive_smoothing(x, w, G)
+    assert qqq.last_route().endswith(route), qqq.last_route()
     amax = qqq.qqq_channel_absmax(x)
     assert torch.equal(amax, x.float().abs().amax(dim=0))
     ref = qqq.qqq_fp16_gemm_nt(x, w).double()
