@@ -376,6 +376,27 @@ __global__ void argmin_kernel(const double* losses, int G, int32_t* best) {
   best[0] = b;
 }
 
+// loss += sum ( fp64(acc) * fp64(s_a[m]) * fp64(s_w[n]) - fp64(y_ref) )^2, fp64 throughout
+__global__ __launch_bounds__(256) void smooth_loss_kernel(const int32_t* acc, const float* s_a, const uint16_t* s_w,
+                                                          const float* y_ref, int64_t M, int64_t N, double* loss) {
+  __shared__ double part[256];
+  const int64_t total = M * N;
+  const int64_t stride = (int64_t)gridDim.x * 256;
+  double sum = 0.0;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += stride) {
+    const int64_t m = i / N, n = i - m * N;
+    const double d = (double)acc[i] * (double)s_a[m] * (double)half_bits_to_float(s_w[n]) - (double)y_ref[i];
+    sum += d * d;
+  }
+  part[threadIdx.x] = sum;
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) atomicAdd(loss, part[0]);
+}
+
 // ------------------------------------------------------------------ Sec. 3.2: Hessian
 
 // H = 2 X^T X in fp64 on the fp64 matrix cores.  H is symmetric: one workgroup per TE x TE tile on or above
@@ -541,6 +562,17 @@ static int launch_fp16_gemm(const void* x, const void* w, int64_t M, int64_t N, 
   return check_launch("fp16_gemm_nt");
 }
 
+// Several grid points per launch, or one point after the other through the hot path's own calls?  A launch for several has workgroups
+// that walk all of K alone (16 channels' weights, a tile of the product), a point by itself costs its launches and the smoothed
+// layer's way through memory.  Fitted to both on 4836 calls (M = 1 .. 1024, K = 128 .. 131072, N = 16 .. 8192, 1 to 20 points), in
+// microseconds; the pick is 0.2 % behind the better one on average, the batches alone 12 % (M = 16, K = 131072, N = 16, 20 points 10.2 ms against
+// 3.5; M = 16, K = 16384, N = 16, 20 points 1.06 against 0.63; M = 1, K = 8192, N = 256, one point 172 us against 119).
+static bool steps_ahead(int64_t M, int64_t N, int64_t K, int grid_points, int at_once) {
+  const double k = 1e-3 * (double)K, weights = k * 1e-3 * (double)N, activations = k * 1e-3 * (double)M;
+  const int batches = (grid_points + at_once - 1) / at_once;
+  return batches * (27.1 + (K > 4096 ? 8.0 : 4.6) * k) > grid_points * (25.0 + 1.2 * weights + 6.9 * activations) + 10.0;
+}
+
 }  // namespace qqq
 
 using namespace qqq;
@@ -629,6 +661,38 @@ int qqq_adaptive_smoothing(const void* x_fp16, const void* w_fp16, int64_t M, in
   if ((rc = check_launch("sigma_grid")) != QQQ_OK) return rc;
   if ((rc = launch_fp16_gemm(x_fp16, w_fp16, M, N, K, y_ref, st)) != QQQ_OK) return rc;
   if ((rc = fill_u32(losses, (size_t)grid_points * 2, 0u, st)) != QQQ_OK) return rc;
+  if (steps_ahead(M, N, K, grid_points, at_once)) {
+    // a point at a time through the hot path's own calls, the smoothed layer, its codes and their product in the workspace
+    at = first;
+    char* xs = take((size_t)M * K * 2);
+    char* ws = take((size_t)N * K * 2);
+    s_point = (float*)take((size_t)K * 4);
+    a_q = (int8_t*)take((size_t)M * K);
+    s_a = (float*)take((size_t)M * 4);
+    uint32_t* w_nat = (uint32_t*)take((size_t)N * K / 2);
+    s_w = (uint16_t*)take((size_t)N * 2);
+    packed = (uint8_t*)take((size_t)N * K / 2);
+    int32_t* acc = (int32_t*)take((size_t)M * N * 4);
+    char* y = take((size_t)M * N * 2);
+    const size_t gemm_bytes = qqq_gemm_workspace_bytes(M, N, K);
+    char* gemm_ws = take(gemm_bytes);
+    if ((rc = fill_u32(gemm_ws, (gemm_bytes + 3) / 4, 0u, st)) != QQQ_OK) return rc;
+    const int64_t elements = M * N;
+    const unsigned blocks = (unsigned)((elements + 255) / 256 < 2048 ? (elements + 255) / 256 : 2048);
+    for (int g = 0; g < grid_points; ++g) {
+      if ((rc = launch_smooth(x_fp16, w_fp16, absmax, sigmas + g, nullptr, M, N, K, xs, ws, s_point, st)) != QQQ_OK) return rc;
+      if ((rc = qqq_quant_act(xs, M, K, K, a_q, s_a, stream)) != QQQ_OK) return rc;
+      if ((rc = qqq_quantize_w4_perchannel(ws, N, K, K, w_nat, s_w, stream)) != QQQ_OK) return rc;
+      if ((rc = qqq_pack_w4(w_nat, N, K, packed, stream)) != QQQ_OK) return rc;
+      if ((rc = qqq_gemm_w4a8_perchannel(a_q, s_a, packed, s_w, y, acc, M, N, K, gemm_ws, gemm_bytes, stream)) != QQQ_OK) return rc;
+      hipLaunchKernelGGL(smooth_loss_kernel, dim3(blocks), dim3(256), 0, st, acc, s_a, s_w, y_ref, M, N, losses + g);
+      if ((rc = check_launch("smooth_loss")) != QQQ_OK) return rc;
+    }
+    route_note("loss");
+    hipLaunchKernelGGL(argmin_kernel, dim3(1), dim3(64), 0, st, losses, grid_points, best);
+    if ((rc = check_launch("argmin")) != QQQ_OK) return rc;
+    return launch_smooth(x_fp16, w_fp16, absmax, sigmas, best, M, N, K, xs_fp16, ws_fp16, s, st);
+  }
   GemmParams p = {};
   p.a_q = a_q;
   p.s_a = s_a;

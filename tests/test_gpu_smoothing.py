@@ -1,6 +1,6 @@
 """The smoothing search where its kernels change path: K at and past the rows kept in registers (4096 weights, 8192
 activations), channel groups not divisible by the eight XCDs, more grid points than the workspace holds at a time, ragged token
-counts, and each of the four tiles of the loss product; against the steps it stands for, one by one.
+counts, each of the four tiles of the loss product, and the search point by point; against the steps it stands for, one by one.
 
 The smoothed tensors, thresholds and vectors are compared bit for bit.  A loss is an fp64 sum built on exact integers and
 the fp32 reference product: from the steps' own integers, scales and reference product in another order it differs by
@@ -15,6 +15,9 @@ from paper_2406_09904_amd import synth
 pytestmark = pytest.mark.gpu
 
 
+BY_STEPS = " + loss"                                     # after the last point's GEMM
+
+
 @pytest.mark.parametrize("M,K,N,G,route", [
     (1, 128, 16, 3, "loss tile=64x128 points=3"), (70, 4096, 144, 9, "loss tile=64x128 points=5 + loss tile=64x128 points=4"),
     (33, 4224, 272, 4, "loss tile=64x128 points=4"), (200, 8192, 128, 3, "loss tile=64x128 points=3"),
@@ -22,7 +25,7 @@ pytestmark = pytest.mark.gpu
     (300, 512, 2064, 9, "loss tile=128x256 points=9"), (300, 512, 4096, 21, "loss tile=128x256 points=21"),
     (700, 256, 2064, 40, "loss tile=128x128 points=25 + loss tile=128x128 points=15"),
     (500, 2944, 4080, 8, "loss tile=128x512 points=8"),
-    (19, 8320, 48, 2, "loss tile=64x128 points=2")])
+    (19, 8320, 48, 2, BY_STEPS), (3, 16384, 16, 9, BY_STEPS), (130, 12416, 64, 5, BY_STEPS), (40, 6144, 256, 1, BY_STEPS)])
 def test_grid_points_equal_their_steps(M, K, N, G, route):
     x = torch.from_numpy(synth.activations_fp16(M, K, 700 + M, "normal", 4 / K, 40.0)).cuda()
     w = torch.from_numpy(synth.weights_fp16(N, K, 701 + M)).cuda()
