@@ -120,10 +120,15 @@ def _ptr(t, dtype=None):
 
 
 # The calling thread's current stream on its current device as the plain handle.  torch.cuda.current_stream() builds a Stream
-# object around the same handle, at a tenth of what a whole one-row linear call takes on the host.
-# (A torch built without a GPU has neither; the checks before every call then raise first.)
+# object around the same handle, at a tenth of what a whole one-row linear call takes on the host.  Both names are torch's own
+# business: where one is missing, the public way.
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 _device = getattr(torch._C, "_cuda_getDevice", None)
+if _raw_stream is None or _device is None:
+    _device = torch.cuda.current_device
+
+    def _raw_stream(device):
+        return torch.cuda.current_stream(device).cuda_stream
 
 
 def _stream():
