@@ -190,8 +190,9 @@ __global__ __launch_bounds__(256) void point_activations_kernel(const uint4* x, 
 // 16 output channels per workgroup (qqq_quantize_w4_perchannel on W .* s, then qqq_pack_w4): a wave takes four
 // channels one after the other, its lanes hold the row (K <= 4096: in registers; else the row is smoothed
 // twice, 4096 channels at a time), and the codes meet in LDS in the packed layout's order, so whole 1 KiB chunks are
-// written.  Bound by vector instructions, about 12 per weight and grid point (9.5 us a grid point at K = N = 4096, 10.6
-// with the codes rounded, tested and packed one by one).
+// written.  Bound by instructions, about 12 per weight and grid point (9.5 us a grid point at K = N = 4096, 10.6
+// with the codes rounded, tested and packed one by one).  The four channels and their eight vectors are written out, each with
+// the divisions of its near-ties inline: 50 KB of code (58 KB for K > 4096), most of it fetched once per workgroup.
 template <bool ONE>
 __global__ __launch_bounds__(256) void point_weights_kernel(const uint4* w, const float* s, int64_t N, int kvec,
                                                             int64_t point_bytes, uint8_t* packed, uint16_t* s_w) {
@@ -407,7 +408,7 @@ __global__ __launch_bounds__(256) void smooth_loss_kernel(const int32_t* acc, co
 // Row strides of the stages (72 and 48 halves) keep the four token rows of a fragment on different banks.
 // A wave holds a (TE/2) x (TE/2) quarter.  TE = 64 reads each fragment for two MFMAs; TE = 32 is for narrow layers,
 // where 64 x 64 tiles leave CUs idle.
-// Bound: the fp64 matrix rate (70 TFLOP/s in a large product).  K = 4096, 2048 tokens: 0.73 ms, 47 TFLOP/s of the one
+// Bound: the fp64 matrix rate (78.6 TFLOP/s nominal).  K = 4096, 2048 tokens: 0.73 ms, 47 TFLOP/s of the one
 // triangle (3.66 ms with both triangles on vector multiply-adds); K = 2048, 1111 tokens: 0.144 ms (0.55).
 // VEC: rows of X are 16-byte aligned (K % 8 == 0 and an aligned base); else element by element.
 template <int TE, bool VEC>

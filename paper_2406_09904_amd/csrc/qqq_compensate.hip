@@ -7,16 +7,17 @@
 // is row i of R^-1, so the running weight of channel j obeys
 //     w_j = W_j + sum_{i < j} (W_i - Q_i) R[i,j]
 // when its turn comes, W the original weights and Q the dequantised codes: the moves of Eq. 4, summed.  One factorisation of
-// K^3/3 multiply-adds and a triangular product of N K^2 / 2 replace an explicit inverse and a rank-1
+// K^3/6 multiply-adds and a triangular product of N K^2 / 2 replace an explicit inverse and a rank-1
 // update of both matrices per channel, and W_i - Q_i is exact in fp64 (fp16 minus int4 x fp16).
 //
 // Both parts are blocked so that almost all of their arithmetic is fp64 MFMA (f64_update_kernel):
 //   factorisation  per 64 channels, from the last: factor_panel_kernel, then the update of the channels before
 //   sweep          per 512 channels, from the first: sweep_kernel, then the update of the channels after
 // What is left serial is one dependent step per channel, in registers.
-// Bound: K = N = 4096 holds 2.3e10 + 6.9e10 fp64 operations, 1.3 ms at the 70 TFLOP/s a large fp64 product
-// reaches here.  Measured, K = N = 4096: 4.75 ms (an inverse by K rank-1 sweeps and a rank-1 update of both matrices
-// per channel: 360 ms); K = 2048, N = 5632 with group scales: 2.1 ms (81 ms).
+// Bound, without the Hessian: K = N = 4096 holds 2.3e10 + 6.9e10 fp64 operations, 1.2 ms at the nominal 78.6 TFLOP/s of the
+// fp64 matrix cores (1.8 ms at the 50 that f64_update_kernel reaches).  Measured, K = N = 4096: 4.05 ms, and 4.75 ms with the
+// Hessian of 2048 tokens (an inverse by K rank-1 sweeps and a rank-1 update of both matrices per channel: 360 ms); K = 2048,
+// N = 5632 with group scales: 1.95 ms, 2.1 ms with the Hessian of 1111 tokens (81 ms).
 #include "qqq_calib.h"
 #include "qqq_internal.h"
 

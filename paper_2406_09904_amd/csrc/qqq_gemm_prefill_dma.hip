@@ -432,7 +432,9 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_prefill_dma_kernel(const Gemm
     // fp64(acc) * fp64(s_a) * fp64(s_w) - fp64(y_ref), squared and summed in fp64 (acc carries the exact factor 16)
     // Half a channel's reference values are requested before the first is used, rows past M repeating the last one and counting
     // nothing (a load under the row's own condition waits for memory every time: M = 512, K = N = 4096, eight grid points
-    // 76 us a launch, 69 so).
+    // 76 us a launch, 69 so).  The selection of the rows below M compiles to a branch per element with its own LDS read of the
+    // token scale, and the squares are added up only after the last of them: the 128x512 tile holds 128 fp64 differences then,
+    // 256 VGPRs with 90 spilled (188 bytes of scratch a lane); the narrower tiles spill nothing.
     static_assert(S::kLds >= NW * 512 + NW * S::kBM * 4, "the partial sums and every wave's copy of the token scales");
     float* sa = (float*)(lds + NW * 512) + wave * S::kBM;
 #pragma unroll
@@ -458,7 +460,7 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_prefill_dma_kernel(const Gemm
             const double kept = m0 + r < M && nvalid[c] ? d : 0.0;
             sum += kept * kept;
           }
-        __builtin_amdgcn_sched_barrier(0);  // one half's values in registers at a time
+        __builtin_amdgcn_sched_barrier(0);  // the next half's requests stay behind this one's uses
       }
     }
     double* part = (double*)lds;
