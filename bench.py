@@ -238,23 +238,25 @@ def load_profile_json(fname, name):
         return None
 
 
-def load_traffic(name):
-    """HBM bytes per GEMM launch from the rocprofv3 --pmc summaries under profiles/, if present."""
+def load_traffic(name, route):
+    """HBM bytes per launch of the dominant kernel from the rocprofv3 --pmc summaries under profiles/,
+    if one is present for this workload and was taken of the kernel timed here (its route)."""
     rec = load_profile_json("traffic.json", name)
     try:
-        return int(rec["fetch_bytes"]) + int(rec["write_bytes"]) if rec else None
+        return int(rec["fetch_bytes"]) + int(rec["write_bytes"]) if rec and rec["route"] == route else None
     except (KeyError, TypeError, ValueError):
         return None
 
 
-def load_mfma_counters(name, kernel_us):
+def load_mfma_counters(name, route, kernel_us):
     """int8 MFMA utilisation of the dominant kernel from the SQ counter summaries under profiles/
     (SQ_INSTS_VALU_MFMA_MOPS_I8 * 512 operations per launch, SQ_VALU_MFMA_BUSY_CYCLES), where a
-    run for this workload was recorded: counted operations / (this run's kernel time * nominal peak)."""
+    run for this workload on the kernel timed here (its route) was recorded: counted operations /
+    (this run's kernel time * nominal peak)."""
     rec = load_profile_json("mfma_counters.json", name)
-    if not rec:
-        return None
     try:
+        if not rec or rec["route"] != route:
+            return None
         out = {"counted_ops": int(rec["mops_i8"]) * 512,
                "util_vs_nominal": round(int(rec["mops_i8"]) * 512 / (kernel_us * 1e-6) / (MFMA_I8_PEAK_TOPS * 1e12), 4)}
         if "mfma_pipe_busy_frac" in rec:
@@ -278,7 +280,7 @@ def workload_line(case, torch, steps, warmup, use_graph):
     wl = case.wl
     step, gemm, quant, graphed = measure(case, torch, steps, warmup, use_graph)
     roof = roofline_for(case, step["median"], gemm["median"])
-    roof["traffic"] = load_traffic(wl.name)
+    roof["traffic"] = load_traffic(wl.name, roof["kernel"])
     line = {"workload": wl.name, "variant": wl.variant, "M": wl.M, "K": wl.K, "N": wl.N,
             "steps": steps, "replays": REPLAYS, "weight_copies_rotated": case.copies, "hip_graph": graphed,
             "ms_per_step": round(step["median"], 6),
@@ -291,7 +293,7 @@ def workload_line(case, torch, steps, warmup, use_graph):
             "tops": round(case.ops / (step["median"] * 1e-3) / 1e12, 3),
             "roofline": roof}
     if roof["bound"] == "mfma":
-        line["mfma_util"] = load_mfma_counters(wl.name, roof["kernel_us"])
+        line["mfma_util"] = load_mfma_counters(wl.name, roof["kernel"], roof["kernel_us"])
     return line
 
 
@@ -384,8 +386,8 @@ def real_scale_lines(wls, torch, qqq, args, use_graph):
 def conversion_ablation(torch, qqq, wls, use_graph):
     """Per-group prefill GEMM on the cfg4 shape with each way of turning int4 code x group scale into
     int8 (Sec. 3.3.2; the paper's Fig. 9 ablates FastFP16toINT8 against the conventional conversion
-    instruction).  Same kernel family and tile shape; only the conversion differs.  The per-channel
-    GEMM on the same shape is the no-conversion reference."""
+    instruction).  Same kernel family, one tile shape for the group routes; only the conversion differs.
+    The per-channel GEMM on the same shape is the no-conversion reference."""
     wl = wls["cfg4_pg_m4096_k11008_n4096"]
     c = Case(wl, torch, qqq, rotate_bytes=1 << 28)
     sg16 = torch.from_numpy(wl.s_g_f16()).cuda()
@@ -409,7 +411,7 @@ def conversion_ablation(torch, qqq, wls, use_graph):
     def pc(i):
         qqq.qqq_gemm_w4a8_perchannel(c.a_q, c.s_a, c.w[i % c.copies], c.s_w, c.ws, y=c.y)
 
-    qqq.set_prefill_tuning(10)                      # one kernel and tile shape for every line
+    qqq.set_prefill_tuning(10)                      # the large tile of every route
     rows.append({"route": "per-channel (FastINT4toINT8, no group scale)", "gemm_us": t(pc)})
     rows.append({"route": "integer scale <= 16: packed 16-bit multiply + bias removal (default)",
                  "gemm_us": t(pg)})
@@ -479,7 +481,7 @@ def front_end_lines(torch, qqq, synth, use_graph):
 def offline_stage_lines(torch, qqq, synth):
     """The offline stage on one synthetic layer (include/qqq_calib.h): adaptive smoothing with a 16-point
     grid (Sec. 3.1) and Hessian-based compensation (Sec. 3.2).  Calibration-time code: wall time per
-    call with events, eager launches (thousands of small kernels; no roofline is claimed for it)."""
+    call with events, eager launches (one to some fifty kernels; no roofline is claimed for it)."""
     import numpy as np
     rows = []
 
