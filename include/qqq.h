@@ -104,7 +104,7 @@ int qqq_unpack_w4(const void* w_packed, int64_t N, int64_t K, uint32_t* w_nat, v
  * transposed copy of the group scales) and, for M <= 512, slabs for K-split partial tiles
  * (4 * 1024 * N bytes).  The decode kernel requires the workspace; the prefill kernels take it as
  * optional (without it, or with a smaller one, the per-group variant uses its costlier per-weight
- * conversion and K is never split).  One workspace must not be shared by GEMM calls that may run
+ * conversion, K is never split, and 17 to 64 rows run a prefill kernel whatever the model says).  One workspace must not be shared by GEMM calls that may run
  * concurrently (different streams).
  */
 size_t qqq_gemm_workspace_zero_bytes(int64_t M, int64_t N, int64_t K);

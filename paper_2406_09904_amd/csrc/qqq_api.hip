@@ -246,12 +246,22 @@ static int kernel_family(int64_t M, int64_t N, int64_t K, int cost) {
   return prefill_us < decode_us ? 2 : 1;
 }
 
+// The family of one call.  The decode kernel cannot do without its workspace, the prefill kernels can: where both serve, the model
+// only ranks them, and a call without the workspace (or with a smaller one, for instance one sized for more than 512 rows, which
+// holds no slabs) is not refused for that rank.
+static int call_family(int64_t M, int64_t N, int64_t K, int cost, const void* workspace, size_t workspace_bytes) {
+  const int family = kernel_family(M, N, K, cost);
+  const bool ranked = g_override == 0 && M > kDecodeAlwaysMaxM && M <= kSkinnyMaxM;
+  if (family == 1 && ranked && (!workspace || workspace_bytes < qqq_gemm_workspace_bytes(M, N, K))) return 2;
+  return family;
+}
+
 // per-group conversion route from the caller's promises about the group scales (and the codes)
-static int group_mode(int sg_arg, int64_t M, int64_t N, int64_t K) {
+static int group_mode(int sg_arg, int64_t M, int64_t N, int64_t K, const void* workspace, size_t workspace_bytes) {
   const bool symmetric = (sg_arg & QQQ_SG_SYMMETRIC_CODES) != 0;  // no code is -8
   const int sg_max = sg_arg & ~QQQ_SG_SYMMETRIC_CODES;
   int mode = kGroupClamp;
-  const bool decode = kernel_family(M, N, K, kCostFma) == 1;
+  const bool decode = call_family(M, N, K, kCostFma, workspace, workspace_bytes) == 1;
   if (sg_max >= 1 && sg_max <= 16) mode = decode ? kGroupLinear : kGroupFused;
   else if (symmetric && sg_max >= 17 && sg_max <= 18) mode = decode ? kGroupLinear : kGroupFusedWide;
   // (knob 3 asks for the fp16-FMA conversion: with scales of 17 and 18 that is its wide form)
@@ -304,7 +314,7 @@ static int gemm_validate(const int8_t* a_q, const float* s_a, const void* w_pack
                      "s_a, s_w and s_g 4-byte aligned");
   if (((M + 63) / 64) * ((N + 127) / 128) > 0x7FFFFFFF)
     return set_error(QQQ_ERR_SHAPE, "gemm: too many output tiles for one launch");
-  const int family = kernel_family(M, N, K, cost_class(mode));
+  const int family = call_family(M, N, K, cost_class(mode), workspace, workspace_bytes);
   if (family == 1 && M > kSkinnyMaxM)
     return set_error(QQQ_ERR_SHAPE, "gemm: skinny kernel forced but M=%lld > %d", (long long)M,
                      kSkinnyMaxM);
@@ -328,7 +338,7 @@ static int gemm_common(const int8_t* a_q, const float* s_a, const void* w_packed
     const int rc = gemm_validate(a_q, s_a, w_packed, s_g, s_w, y, M, N, K, workspace, workspace_bytes, mode, fused);
     if (rc != QQQ_OK || M == 0) return rc;
   }
-  const int family = kernel_family(M, N, K, cost_class(mode));
+  const int family = call_family(M, N, K, cost_class(mode), workspace, workspace_bytes);
   GemmParams p;
   p.a_q = a_q;
   p.s_a = s_a;
@@ -665,7 +675,7 @@ int qqq_gemm_w4a8_pergroup(const int8_t* a_q, const float* s_a, const void* w_pa
     return set_error(QQQ_ERR_SHAPE, "pergroup: sg_max must be in 0..127 (optionally or-ed with "
                      "QQQ_SG_SYMMETRIC_CODES), got %d", sg_max);
   return gemm_common(a_q, s_a, w_packed, s_g, s_w_fp16, y_fp16, acc_out, M, N, K, workspace,
-                     workspace_bytes, stream, group_mode(sg_max, M, N, K));
+                     workspace_bytes, stream, group_mode(sg_max, M, N, K, workspace, workspace_bytes));
 }
 
 int qqq_gemm_w4a8_pergroup_f16scale(const int8_t* a_q, const float* s_a, const void* w_packed,
@@ -675,7 +685,7 @@ int qqq_gemm_w4a8_pergroup_f16scale(const int8_t* a_q, const float* s_a, const v
   route_reset();
   if (group != QQQ_GROUP) return set_error(QQQ_ERR_SHAPE, "pergroup: group must be 128, got %d", group);
   // knob 4: the conventional-conversion ablation of Fig. 9 (prefill kernel only)
-  const int mode = (g_group_mode == 4 && kernel_family(M, N, K, kCostReal) == 2) ? kGroupCvt : kGroupReal;
+  const int mode = (g_group_mode == 4 && call_family(M, N, K, kCostReal, workspace, workspace_bytes) == 2) ? kGroupCvt : kGroupReal;
   return gemm_common(a_q, s_a, w_packed, (const int8_t*)s_g_fp16, s_w_fp16, y_fp16, acc_out, M, N, K,
                      workspace, workspace_bytes, stream, mode);
 }
@@ -710,7 +720,7 @@ int qqq_linear_w4a8_pergroup(const void* a_fp16, int64_t lda, const void* w_pack
     return set_error(QQQ_ERR_SHAPE, "pergroup: sg_max must be in 0..127 (optionally or-ed with "
                      "QQQ_SG_SYMMETRIC_CODES), got %d", sg_max);
   return linear_common(a_fp16, lda, w_packed, s_g, s_w_fp16, y_fp16, acc_out, M, N, K, workspace,
-                       workspace_bytes, stream, group_mode(sg_max, M, N, K));
+                       workspace_bytes, stream, group_mode(sg_max, M, N, K, workspace, workspace_bytes));
 }
 
 int qqq_linear_w4a8_perchannel_static(const void* a_fp16, int64_t lda, const void* w_packed,
