@@ -89,9 +89,10 @@ static size_t split_bytes(int64_t M, int64_t N) {
 //                   x >  1:  fixed + per_round * x + T (rounds x + [f > 0] rest (1 - f))
 //                 alone: a k-step of one workgroup on an idle chip; full: with one on every CU (shared bandwidth, lower
 //                 clock); rounds: of a whole round when there are several; rest: what a partial last round costs beyond its
-//                 share.  2 to 3 % rms on all of them.  (The smoothing search's row is fitted to the differences between the four tiles
-//                 on 2082 searches, so only its differences mean anything; its pick is 0.2 % behind the best tile, 5 % at most.)  An even spread or whole rounds alone miss by 10 to 30 %: M = 2048,
-//                 K = 4096, N = 11008 took 89 us in 1.4 rounds of 128 x 512 and takes 80 in 2.7 rounds of 128 x 256.
+//                 share.  2 to 3 % rms on all of them.  An even spread or whole rounds alone miss by 10 to 30 %: M = 2048, K = 4096, N = 11008
+//                 took 89 us in 1.4 rounds of 128 x 512 and takes 80 in 2.7 rounds of 128 x 256.  (The smoothing search's row is
+//                 fitted to the differences between the four tiles on 2082 searches, so only its differences mean anything; its
+//                 pick is 0.2 % behind the best tile, 5 % at most.)
 //   stream_tbs    what the weight stream of a prefill launch reaches at best; nothing is modelled to be faster.
 //   split_*       the K-split's slabs and its second kernel: a launch, a part per split (they are read one after the other), and a
 //                 part per million raw int32 of the slabs (6 TB/s written and read).
@@ -102,8 +103,9 @@ static size_t split_bytes(int64_t M, int64_t N) {
 //   decode[]      the decode kernel at 17..64 rows, per conversion (per-channel; scale on partial sums; real-valued; saturating)
 //                 and channel tiles of a workgroup (1, 2, 4 or more): with g = N K / 1e6 weights, x workgroups per CU, w the
 //                 whole rounds over x, R the row tiles,  base + per_wg x R + g (w (a + b R) + c M).  4 to 9 % rms.
-// On those shapes the pick is 0.5 % behind the best forced choice on average, 5 to 9 % in one of a hundred.
-// A test times the automatic pick against every forced pick on a small grid (15 % bar).
+// On those shapes the pick is 0.5 % behind the best forced choice on average; on 2000 others (four conversions each) 0.7 %, 6 % in
+// one of a hundred, and up to 33 % on a few saturating calls of 17..32 rows, where it stays with the decode kernel for too long.
+// Tests time the automatic pick against every forced pick on small grids (10 and 15 % bars).
 enum CostClass : int { kCostChannel, kCostBias, kCostFma, kCostReal, kCostClamp, kCostLoss, kCostClasses };
 static int cost_class(int mode) {
   switch (mode) {
