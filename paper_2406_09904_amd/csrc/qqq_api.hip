@@ -79,8 +79,8 @@ static size_t split_bytes(int64_t M, int64_t N) {
 
 // ---------------------------------------------------------------------------------------------
 // Dispatch model: every fitted constant the automatic kernel choice uses, in one place.  Fitted to every forced
-// choice on 2145 shapes (K = 1024 .. 11008, N = 1024 .. 28672, M = 17 .. 4096, five layers of the benchmark among them) times four
-// conversions on one MI355X: GEMM launches back to back from HIP graphs replayed in turn, packed weights rotated through
+// choice on 2145 shapes (K = 1024 .. 11008, N = 1024 .. 28672, M = 17 .. 4096, five layers of the benchmark among them) and on 964 beyond
+// them (K = 128 .. 65536, N = 16 .. 65536) times four conversions on one MI355X: GEMM launches back to back from HIP graphs replayed in turn, packed weights rotated through
 // 512 MiB and more.
 //   tile[]        one row per conversion (what an int4 weight costs to convert decides how much a tile gains from
 //                 having many rows), one entry per tile shape.  With x workgroups per CU, r the whole part of x and f the
@@ -93,16 +93,25 @@ static size_t split_bytes(int64_t M, int64_t N) {
 //                 took 89 us in 1.4 rounds of 128 x 512 and takes 80 in 2.7 rounds of 128 x 256.  (The smoothing search's row is
 //                 fitted to the differences between the four tiles on 2082 searches, so only its differences mean anything; its
 //                 pick is 0.2 % behind the best tile, 5 % at most.)
-//   stream_tbs    what the weight stream of a prefill launch reaches at best; nothing is modelled to be faster.
+//   short_tile[]  the same below short_ksteps k-steps, where the filling of the ring and the epilogue make up most of a tile, with a
+//                 last round that costs its own time whatever T:  x <= 1: fixed + per_round x + T (alone (1 - x) + full x);
+//                 x > 1: fixed + per_round x + T rounds x + [f > 0] rest (1 - f).  5 % rms (7 to 9 % in the other form; with the
+//                 rows of longer K the pick was up to 30 % off there, M = 1264, K = 256, N = 50432 62.6 us for 48.9).
+//   stream_tbs    what the weight stream of a prefill launch reaches at best; where it is what bounds several tiles, the one with the
+//                 least to do beside it is ahead (behind_stream).
+//   prepass_*     the biased route beyond the K that its rows were fitted to: a part per 1000 of K (K = 37760, M = 66, N = 4496 48.8 us
+//                 where the FMA route takes 38.2).
 //   split_*       the K-split's slabs and its second kernel: a launch, a part per split (they are read one after the other), and a
 //                 part per million raw int32 of the slabs (6 TB/s written and read).
-//   margin_split, min_ksteps_per_split  a split must be 3 % cheaper (modelled), its parts five k-steps long.
+//   margin_split, min_ksteps_per_split  a split must be 3 % cheaper (modelled), its parts four k-steps long.
 //   margin_persistent  per-channel, the persistent kernel and the same tile one by one are as close as the model's error up to
 //                 40 k-steps (K = 5120, M = 2048, N = 13824: 118.8 and 119.0 us): there the persistent one keeps what is within
 //                 3.5 %; from 64 on it is 5 % behind on average.
 //   decode[]      the decode kernel at 17..64 rows, per conversion (per-channel; scale on partial sums; real-valued; saturating)
 //                 and channel tiles of a workgroup (1, 2, 4 or more): with g = N K / 1e6 weights, x workgroups per CU, w the
-//                 whole rounds over x, R the row tiles,  base + per_wg x R + g (w (a + b R) + c M).  4 to 9 % rms.
+//                 whole rounds over x, R the row tiles,  base + per_wg x R + g (w (a + b R) + c M).  5 to 9 % rms.
+//   sliced[]      the same where a narrow layer's K is cut into S slices:  base + rows R + K / (1000 S) (step + step_rows R) +
+//                 slice S + c g M.  7 to 11 % rms.  (M = 30, K = 58240, N = 16: 5.6 us sliced, 30 in the prefill kernels.)
 // On those shapes the pick is 0.5 % behind the best forced choice on average; on 2000 others (four conversions each) 0.7 %, 6 % in
 // one of a hundred, and up to 33 % on a few saturating calls of 17..32 rows, where it stays with the decode kernel for too long.
 // Tests time the automatic pick against every forced pick on small grids (10 and 15 % bars).
@@ -121,6 +130,7 @@ static int cost_class(int mode) {
 constexpr int kPersistent = 6;  // as a shape: the persistent kernel; the others are those of launch_gemm_prefill_dma
 struct TileCost { int shape, bm, bn; double alone, full, rounds, rest, fixed, per_round; };
 struct DecodeCost { double base, per_wg, a, b, c; };
+struct SlicedCost { double base, rows, step, step_rows, slice, c; };
 static const struct DispatchModel {
   TileCost tile[kCostClasses][6] = {
       {  // per-channel
@@ -161,16 +171,56 @@ static const struct DispatchModel {
           {3, 128, 256, 0.806, 0.341, 0.898, 0.494, 0.8, 0.7},
           {4, 128, 128, 0.717, 0.446, 0.476, 0.185, 0.9, 0.4},
           {5, 64, 128, 0.551, 0.382, 0.235, 0.241, -1.2, 0.8}}};
-  double stream_tbs = 4.6;
+  TileCost short_tile[kCostLoss][6] = {
+      {  // per-channel
+          {0, 128, 512, 1.043, 0.802, 1.454, 4.510, 6.3, 6.7},
+          {3, 128, 256, 0.595, 0.458, 0.869, 3.563, 4.4, 3.8},
+          {4, 128, 128, 0.478, 0.482, 0.457, 0.192, 4.4, 2.0},
+          {5, 64, 128, 0.289, 0.400, 0.251, 0.473, 3.7, 1.0},
+          {kPersistent, 128, 512, 1.058, 0.414, 0.879, 4.655, 6.2, 7.2}},
+      {  // biased integer (with its pre-pass)
+          {0, 128, 512, 1.392, 0.916, 1.736, 6.391, 10.6, 8.7},
+          {1, 256, 256, 1.312, 0.544, 1.711, 5.160, 11.2, 8.3},
+          {3, 128, 256, 0.775, 0.495, 0.938, 4.567, 8.3, 5.4},
+          {4, 128, 128, 0.605, 0.532, 0.492, 0.531, 7.9, 2.7},
+          {5, 64, 128, 0.422, 0.691, 0.290, 0.971, 7.0, 1.3},
+          {kPersistent, 128, 512, 1.541, 0.624, 1.226, 6.961, 10.5, 9.1}},
+      {  // fp16 FMA
+          {0, 128, 512, 1.958, 1.462, 2.294, 7.365, 7.0, 6.9},
+          {1, 256, 256, 1.455, 0.983, 1.841, 5.057, 6.8, 6.2},
+          {3, 128, 256, 1.011, 0.743, 1.201, 4.662, 4.8, 4.1},
+          {4, 128, 128, 0.660, 0.644, 0.571, 0.706, 4.3, 2.0},
+          {5, 64, 128, 0.477, 0.594, 0.363, 1.235, 3.8, 0.9},
+          {kPersistent, 128, 512, 1.625, 0.686, 1.302, 7.576, 7.2, 7.7}},
+      {  // real-valued scale
+          {0, 128, 512, 2.105, 1.642, 2.494, 7.697, 7.0, 6.9},
+          {1, 256, 256, 1.513, 1.067, 1.944, 5.290, 6.7, 6.1},
+          {3, 128, 256, 1.053, 0.769, 1.257, 4.754, 4.8, 4.1},
+          {4, 128, 128, 0.704, 0.683, 0.619, 0.881, 4.3, 2.0},
+          {5, 64, 128, 0.581, 0.700, 0.409, 1.418, 3.8, 0.9}},
+      {  // saturating
+          {0, 128, 512, 2.889, 2.406, 3.416, 9.570, 7.5, 6.9},
+          {1, 256, 256, 1.945, 1.441, 2.398, 6.286, 7.0, 6.2},
+          {3, 128, 256, 1.505, 1.184, 1.733, 5.759, 5.0, 4.2},
+          {4, 128, 128, 0.929, 0.910, 0.749, 1.608, 4.3, 2.0},
+          {5, 64, 128, 0.727, 0.884, 0.582, 2.031, 3.8, 0.8},
+          {kPersistent, 128, 512, 2.503, 1.467, 2.313, 9.922, 7.8, 7.8}}};
+  double stream_tbs = 4.6, behind_stream = 0.1;
   double split_us = 2.05, split_part_us = 0.28, split_mint32_us = 1.33;
   double margin_split = 0.97, margin_persistent = 0.965;
   int margin_persistent_ksteps = 40;
-  int min_ksteps_per_split = 5;
+  int min_ksteps_per_split = 4, short_ksteps = 8;
+  int prepass_k = 11800;
+  double prepass_us = 0.227;
   DecodeCost decode[4][3] = {
-      {{3.32, 0.094, 0.0351, 0.0235, 0.0018}, {3.01, 0.161, 0.0208, 0.0238, 0.0008}, {2.65, 0.618, 0.0402, 0.0118, 0.0003}},
-      {{3.40, 0.044, 0.0259, 0.0307, 0.0020}, {3.14, 0.180, 0.0110, 0.0304, 0.0010}, {2.89, 0.711, 0.0354, 0.0176, 0.0002}},
-      {{3.67, 0.128, 0.0429, 0.0263, 0.0020}, {3.28, 0.266, 0.0418, 0.0287, 0.0007}, {3.20, 0.650, 0.0794, 0.0140, 0.0001}},
-      {{3.76, 0.130, 0.1047, 0.0168, 0.0019}, {3.64, 0.223, 0.0813, 0.0294, 0.0005}, {3.58, 0.623, 0.1204, 0.0143, 0.0001}}};
+      {{2.97, 0.131, 0.0384, 0.0299, 0.0012}, {2.92, 0.202, 0.0226, 0.0233, 0.0007}, {2.58, 0.498, 0.0401, 0.0138, 0.0002}},
+      {{3.02, 0.110, 0.0341, 0.0338, 0.0014}, {3.07, 0.206, 0.0161, 0.0287, 0.0009}, {2.88, 0.467, 0.0333, 0.0214, 0.0002}},
+      {{3.19, 0.180, 0.0443, 0.0395, 0.0009}, {3.20, 0.265, 0.0484, 0.0269, 0.0006}, {3.12, 0.528, 0.0793, 0.0170, 0.0}},
+      {{3.21, 0.192, 0.1050, 0.0374, 0.0001}, {3.40, 0.269, 0.0908, 0.0275, 0.0003}, {3.28, 0.565, 0.1223, 0.0167, 0.0}}};
+  SlicedCost sliced[4] = {{2.75, 0.521, 0.718, -0.135, 0.0228, 0.0048},
+                          {3.07, 0.439, 0.526, -0.096, 0.0306, 0.0061},
+                          {2.98, 0.582, 0.784, -0.184, 0.0270, 0.0064},
+                          {1.57, 1.012, 1.906, -0.480, 0.0255, 0.0071}};
 } kModel;
 
 // Tile shape and K split of the prefill path.  A split launches splits x tiles workgroups of T / splits k-steps plus
@@ -187,7 +237,9 @@ static PrefillPlan plan_prefill(int64_t M, int64_t N, int64_t K, int cost, bool 
   const double stream_us = (double)N * (double)K * 0.5 / (kModel.stream_tbs * 1e6);
   PrefillPlan best = {0, 1, 0.0};
   double best_score = 0.0;
-  for (const TileCost& c : kModel.tile[cost]) {
+  const bool short_k = T < kModel.short_ksteps && cost < kCostLoss;
+  const double prepass_us = cost == kCostBias && K > kModel.prepass_k ? kModel.prepass_us * 1e-3 * (double)(K - kModel.prepass_k) : 0.0;
+  for (const TileCost& c : short_k ? kModel.short_tile[cost] : kModel.tile[cost]) {
     if (c.bm == 0) continue;
     // (the persistent kernel needs three k-steps a tile and does not split them)
     if (c.shape == kPersistent && (T < 3 || forced_split > 1)) continue;
@@ -203,10 +255,11 @@ static PrefillPlan plan_prefill(int64_t M, int64_t N, int64_t K, int cost, bool 
         break;
       }
       const double x = (double)(tiles_c * ks * products) / cus, f = x - floor(x), t = (double)T / ks;
-      double us = c.fixed;
-      if (x <= 1.0) us += c.per_round + t * (c.alone * (1.0 - x) + c.full * x);
-      else us += c.per_round * x + t * (c.rounds * x + (f > 0.0 ? c.rest * (1.0 - f) : 0.0));
-      if (us < stream_us) us = stream_us;
+      double us = c.fixed + prepass_us;
+      us += short_k || x > 1.0 ? c.per_round * x : c.per_round;
+      if (x <= 1.0) us += t * (c.alone * (1.0 - x) + c.full * x);
+      else us += t * c.rounds * x + (f > 0.0 ? (short_k ? 1.0 : t) * c.rest * (1.0 - f) : 0.0);
+      if (us < stream_us) us = stream_us - kModel.behind_stream * (stream_us - us);
       if (ks > 1) us += kModel.split_us + ks * (kModel.split_part_us + kModel.split_mint32_us * 1e-6 * (double)M * (double)N);
       double score = us;
       if (ks > 1) score /= kModel.margin_split;
@@ -241,9 +294,17 @@ static int kernel_family(int64_t M, int64_t N, int64_t K, int cost) {
   const bool clamp_free = cost == kCostFma || cost == kCostBias;
   const int row_tiles = (int)((M + 15) / 16);
   const int nt = decode_channel_tiles(N, row_tiles, cost == kCostChannel || clamp_free);  // the launcher's own rule
-  const DecodeCost& d = kModel.decode[cost == kCostChannel ? 0 : clamp_free ? 1 : cost == kCostReal ? 2 : 3][nt >= 4 ? 2 : nt - 1];
+  const int row = cost == kCostChannel ? 0 : clamp_free ? 1 : cost == kCostReal ? 2 : 3;
+  const int slices = decode_k_slices(N, K, nt);
   const double g = (double)N * (double)K * 1e-6, x = (double)(N / (16 * nt)) / num_cus();
-  const double decode_us = d.base + d.per_wg * x * row_tiles + g * (ceil(x) / x * (d.a + d.b * row_tiles) + d.c * (double)M);
+  double decode_us;
+  if (slices > 1) {
+    const SlicedCost& d = kModel.sliced[row];
+    decode_us = d.base + d.rows * row_tiles + 1e-3 * (double)K / slices * (d.step + d.step_rows * row_tiles) + d.slice * slices + d.c * g * (double)M;
+  } else {
+    const DecodeCost& d = kModel.decode[row][nt >= 4 ? 2 : nt - 1];
+    decode_us = d.base + d.per_wg * x * row_tiles + g * (ceil(x) / x * (d.a + d.b * row_tiles) + d.c * (double)M);
+  }
   const double prefill_us = clamp_free ? pergroup_prefill_us(M, N, K, nullptr) : plan_prefill(M, N, K, cost, true, g_prefill_ksplit).us;
   return prefill_us < decode_us ? 2 : 1;
 }

@@ -521,22 +521,26 @@ int decode_channel_tiles(int64_t N, int mt, bool light_conversion) {
   return nt;
 }
 
-static void choose_split(const GemmParams& p, int mt, bool light_conversion, int& nt, int& w, int& s) {
-  nt = decode_channel_tiles(p.N, mt, light_conversion);
-  const int cus = num_cus();
-  w = (p.T >= 16) ? 8 : 4;
+static int decode_waves(int64_t K, int nt) {
   // a workgroup with 32 KiB of weights or less (16 channels, K <= 4096) finishes sooner on 4 waves, each with
   // two batches of loads, than on 8 with one and twice the partial tiles to add (K = N = 4096, M=16: 4.85 -> 4.7 us
   // on average over a profiled run)
-  if ((int64_t)16 * nt * p.K / 2 <= 32768) w = 4;
-  s = 1;
-  // Very narrow outputs: too few channel groups to occupy the chip, so slice K as well
-  const int ng = p.N / (16 * nt);
-  if (ng * 2 < cus) {
-    s = (cus + ng - 1) / ng;
-    const int max_s = p.T / (2 * w) > 0 ? p.T / (2 * w) : 1;
-    if (s > max_s) s = max_s;
-  }
+  return K / 128 < 16 || (int64_t)16 * nt * K / 2 <= 32768 ? 4 : 8;
+}
+
+// K slices of a launch (also read by the dispatch model).  Very narrow outputs: too few channel groups to occupy the chip, so
+// slice K as well
+int decode_k_slices(int64_t N, int64_t K, int nt) {
+  const int cus = num_cus(), ng = (int)(N / (16 * nt));
+  if (ng * 2 >= cus) return 1;
+  const int s = (cus + ng - 1) / ng, max_s = (int)(K / 128) / (2 * decode_waves(K, nt));
+  return s < max_s ? s : max_s > 0 ? max_s : 1;
+}
+
+static void choose_split(const GemmParams& p, int mt, bool light_conversion, int& nt, int& w, int& s) {
+  nt = decode_channel_tiles(p.N, mt, light_conversion);
+  w = decode_waves(p.K, nt);
+  s = decode_k_slices(p.N, p.K, nt);
 }
 
 template <int MODE>
