@@ -112,8 +112,9 @@ static size_t split_bytes(int64_t M, int64_t N) {
 //                 whole rounds over x, R the row tiles,  base + per_wg x R + g (w (a + b R) + c M).  5 to 9 % rms.
 //   sliced[]      the same where a narrow layer's K is cut into S slices:  base + rows R + K / (1000 S) (step + step_rows R) +
 //                 slice S + c g M.  7 to 11 % rms.  (M = 30, K = 58240, N = 16: 5.6 us sliced, 30 in the prefill kernels.)
-// On those shapes the pick is 0.5 % behind the best forced choice on average; on 2000 others (four conversions each) 0.7 %, 6 % in
-// one of a hundred, and up to 33 % on a few saturating calls of 17..32 rows, where it stays with the decode kernel for too long.
+// On 995 other shapes of the first kind (four conversions each) the pick is 0.8 % behind the best forced choice on average, 8 % in
+// one of a hundred, 19 % at most (saturating calls of 17..32 rows that stay with the decode kernel for too long); on 464 of the
+// second kind 1.4, 13 and 47 % (K = 256, N = 34432, M = 24: 8.2 us for 5.6).
 // Tests time the automatic pick against every forced pick on small grids (10 and 15 % bars).
 enum CostClass : int { kCostChannel, kCostBias, kCostFma, kCostReal, kCostClamp, kCostLoss, kCostClasses };
 static int cost_class(int mode) {
