@@ -92,7 +92,8 @@ static size_t split_bytes(int64_t M, int64_t N) {
 //                 share.  2 to 3 % rms on all of them.  An even spread or whole rounds alone miss by 10 to 30 %: M = 2048, K = 4096, N = 11008
 //                 took 89 us in 1.4 rounds of 128 x 512 and takes 80 in 2.7 rounds of 128 x 256.  (The smoothing search's row is
 //                 fitted to the differences between the four tiles on 2082 searches, so only its differences mean anything; its
-//                 pick is 0.2 % behind the best tile, 5 % at most.)
+//                 pick is 0.2 % behind the best tile, 5 % at most.)  The rows of 192 x 256, 128 x 128 and 64 x 128 are fitted to
+//                 8300 and 1300 launches of 1507 shapes of their own (2 to 4 % rms; 3 to 5 % below 8 k-steps).
 //   short_tile[]  the same below short_ksteps k-steps, where the filling of the ring and the epilogue make up most of a tile, with a
 //                 last round that costs its own time whatever T:  x <= 1: fixed + per_round x + T (alone (1 - x) + full x);
 //                 x > 1: fixed + per_round x + T rounds x + [f > 0] rest (1 - f).  5 % rms (7 to 9 % in the other form; with the
@@ -133,78 +134,88 @@ struct TileCost { int shape, bm, bn; double alone, full, rounds, rest, fixed, pe
 struct DecodeCost { double base, per_wg, a, b, c; };
 struct SlicedCost { double base, rows, step, step_rows, slice, c; };
 static const struct DispatchModel {
-  TileCost tile[kCostClasses][6] = {
+  TileCost tile[kCostClasses][7] = {
       {  // per-channel
           {0, 128, 512, 0.866, 1.409, 1.244, 1.272, -4.0, 12.5},
+          {2, 192, 256, 0.672, 1.131, 0.991, 0.995, -2.0, 9.4},
           {3, 128, 256, 0.490, 0.787, 0.705, 0.710, -1.4, 7.2},
-          {4, 128, 128, 0.399, 0.544, 0.446, 0.307, 2.6, 2.9},
-          {5, 64, 128, 0.252, 0.337, 0.259, 0.177, 3.6, 1.0},
+          {4, 128, 128, 0.364, 0.484, 0.400, 0.339, 2.1, 3.3},
+          {5, 64, 128, 0.241, 0.314, 0.240, 0.166, 3.0, 1.6},
           {kPersistent, 128, 512, 0.968, 1.492, 1.380, 1.229, 0.9, 6.9}},
       {  // biased integer (with its pre-pass)
           {0, 128, 512, 1.152, 1.693, 1.517, 1.677, -2.6, 15.9},
           {1, 256, 256, 1.053, 1.604, 1.438, 1.622, -2.7, 16.1},
+          {2, 192, 256, 0.847, 1.327, 1.154, 1.225, -0.3, 12.3},
           {3, 128, 256, 0.644, 0.999, 0.857, 0.940, 1.0, 8.9},
-          {4, 128, 128, 0.511, 0.711, 0.547, 0.358, 5.7, 3.3},
-          {5, 64, 128, 0.406, 0.551, 0.339, 0.276, 6.9, 1.1},
+          {4, 128, 128, 0.446, 0.641, 0.485, 0.404, 5.0, 4.0},
+          {5, 64, 128, 0.350, 0.482, 0.304, 0.283, 6.5, 1.6},
           {kPersistent, 128, 512, 1.228, 1.717, 1.599, 1.635, 2.1, 11.3}},
       {  // fp16 FMA
           {0, 128, 512, 1.717, 2.148, 2.074, 2.122, -4.4, 13.7},
           {1, 256, 256, 1.252, 1.677, 1.594, 1.715, -4.2, 13.0},
+          {2, 192, 256, 1.052, 1.447, 1.381, 1.319, -1.6, 9.5},
           {3, 128, 256, 0.885, 1.146, 1.073, 1.080, -1.3, 7.6},
-          {4, 128, 128, 0.578, 0.728, 0.587, 0.423, 2.8, 2.5},
-          {5, 64, 128, 0.439, 0.540, 0.392, 0.366, 4.0, 0.7},
+          {4, 128, 128, 0.572, 0.695, 0.561, 0.477, 2.6, 3.0},
+          {5, 64, 128, 0.464, 0.548, 0.391, 0.405, 3.8, 1.0},
           {kPersistent, 128, 512, 1.704, 2.111, 2.087, 1.942, 0.2, 7.6}},
       {  // real-valued scale
           {0, 128, 512, 1.879, 2.220, 2.110, 2.285, -3.7, 13.0},
           {1, 256, 256, 1.318, 1.692, 1.613, 1.768, -3.4, 12.1},
+          {2, 192, 256, 1.094, 1.396, 1.321, 1.374, -1.7, 9.5},
           {3, 128, 256, 0.923, 1.155, 1.065, 1.170, -0.8, 7.1},
-          {4, 128, 128, 0.626, 0.763, 0.626, 0.494, 3.2, 2.2},
-          {5, 64, 128, 0.544, 0.637, 0.440, 0.445, 4.2, 0.5}},
+          {4, 128, 128, 0.602, 0.723, 0.575, 0.521, 2.9, 2.8},
+          {5, 64, 128, 0.526, 0.605, 0.422, 0.477, 4.2, 0.8}},
       {  // saturating
           {0, 128, 512, 2.642, 2.916, 2.728, 3.140, -3.9, 13.9},
           {1, 256, 256, 1.734, 2.045, 1.902, 2.213, -3.3, 12.5},
+          {2, 192, 256, 1.536, 1.775, 1.624, 1.857, -1.6, 9.8},
           {3, 128, 256, 1.355, 1.564, 1.426, 1.659, -0.9, 7.6},
-          {4, 128, 128, 0.854, 0.961, 0.744, 0.710, 3.4, 2.1},
-          {5, 64, 128, 0.698, 0.780, 0.599, 0.689, 4.3, 0.5},
+          {4, 128, 128, 0.783, 0.907, 0.697, 0.773, 3.4, 2.4},
+          {5, 64, 128, 0.702, 0.784, 0.602, 0.721, 4.5, 0.6},
           {kPersistent, 128, 512, 2.720, 2.961, 2.840, 2.993, 0.9, 7.0}},
       {  // per-channel with the smoothing search's loss for an epilogue
           {0, 128, 512, 1.241, 1.263, 1.603, 2.400, -0.4, 12.4},
           {3, 128, 256, 0.806, 0.341, 0.898, 0.494, 0.8, 0.7},
           {4, 128, 128, 0.717, 0.446, 0.476, 0.185, 0.9, 0.4},
           {5, 64, 128, 0.551, 0.382, 0.235, 0.241, -1.2, 0.8}}};
-  TileCost short_tile[kCostLoss][6] = {
+  TileCost short_tile[kCostLoss][7] = {
       {  // per-channel
           {0, 128, 512, 1.043, 0.802, 1.454, 4.510, 6.3, 6.7},
+          {2, 192, 256, 0.800, 0.859, 1.321, 3.741, 5.6, 4.6},
           {3, 128, 256, 0.595, 0.458, 0.869, 3.563, 4.4, 3.8},
-          {4, 128, 128, 0.478, 0.482, 0.457, 0.192, 4.4, 2.0},
-          {5, 64, 128, 0.289, 0.400, 0.251, 0.473, 3.7, 1.0},
+          {4, 128, 128, 0.360, 0.409, 0.497, 0.304, 4.7, 2.0},
+          {5, 64, 128, 0.261, 0.391, 0.273, 0.268, 3.9, 0.9},
           {kPersistent, 128, 512, 1.058, 0.414, 0.879, 4.655, 6.2, 7.2}},
       {  // biased integer (with its pre-pass)
           {0, 128, 512, 1.392, 0.916, 1.736, 6.391, 10.6, 8.7},
           {1, 256, 256, 1.312, 0.544, 1.711, 5.160, 11.2, 8.3},
+          {2, 192, 256, 0.982, 0.793, 1.590, 5.199, 10.0, 6.0},
           {3, 128, 256, 0.775, 0.495, 0.938, 4.567, 8.3, 5.4},
-          {4, 128, 128, 0.605, 0.532, 0.492, 0.531, 7.9, 2.7},
-          {5, 64, 128, 0.422, 0.691, 0.290, 0.971, 7.0, 1.3},
+          {4, 128, 128, 0.477, 0.444, 0.571, 0.387, 8.3, 2.7},
+          {5, 64, 128, 0.353, 0.705, 0.334, 0.719, 7.2, 1.2},
           {kPersistent, 128, 512, 1.541, 0.624, 1.226, 6.961, 10.5, 9.1}},
       {  // fp16 FMA
           {0, 128, 512, 1.958, 1.462, 2.294, 7.365, 7.0, 6.9},
           {1, 256, 256, 1.455, 0.983, 1.841, 5.057, 6.8, 6.2},
+          {2, 192, 256, 1.194, 1.149, 1.720, 4.806, 6.0, 4.7},
           {3, 128, 256, 1.011, 0.743, 1.201, 4.662, 4.8, 4.1},
-          {4, 128, 128, 0.660, 0.644, 0.571, 0.706, 4.3, 2.0},
-          {5, 64, 128, 0.477, 0.594, 0.363, 1.235, 3.8, 0.9},
+          {4, 128, 128, 0.619, 0.642, 0.661, 1.047, 4.7, 2.0},
+          {5, 64, 128, 0.486, 0.631, 0.429, 1.121, 4.1, 0.9},
           {kPersistent, 128, 512, 1.625, 0.686, 1.302, 7.576, 7.2, 7.7}},
       {  // real-valued scale
           {0, 128, 512, 2.105, 1.642, 2.494, 7.697, 7.0, 6.9},
           {1, 256, 256, 1.513, 1.067, 1.944, 5.290, 6.7, 6.1},
+          {2, 192, 256, 1.222, 1.071, 1.669, 4.766, 6.0, 4.8},
           {3, 128, 256, 1.053, 0.769, 1.257, 4.754, 4.8, 4.1},
-          {4, 128, 128, 0.704, 0.683, 0.619, 0.881, 4.3, 2.0},
-          {5, 64, 128, 0.581, 0.700, 0.409, 1.418, 3.8, 0.9}},
+          {4, 128, 128, 0.655, 0.655, 0.695, 1.117, 4.8, 2.0},
+          {5, 64, 128, 0.556, 0.688, 0.452, 1.345, 4.1, 0.9}},
       {  // saturating
           {0, 128, 512, 2.889, 2.406, 3.416, 9.570, 7.5, 6.9},
           {1, 256, 256, 1.945, 1.441, 2.398, 6.286, 7.0, 6.2},
+          {2, 192, 256, 1.682, 1.438, 2.017, 5.916, 6.2, 5.1},
           {3, 128, 256, 1.505, 1.184, 1.733, 5.759, 5.0, 4.2},
-          {4, 128, 128, 0.929, 0.910, 0.749, 1.608, 4.3, 2.0},
-          {5, 64, 128, 0.727, 0.884, 0.582, 2.031, 3.8, 0.8},
+          {4, 128, 128, 0.842, 0.843, 0.753, 2.243, 4.8, 2.0},
+          {5, 64, 128, 0.723, 0.881, 0.615, 2.235, 4.2, 0.9},
           {kPersistent, 128, 512, 2.503, 1.467, 2.313, 9.922, 7.8, 7.8}}};
   double stream_tbs = 4.6, behind_stream = 0.1;
   double split_us = 2.05, split_part_us = 0.28, split_mint32_us = 1.33;
@@ -463,8 +474,8 @@ static int gemm_common(const int8_t* a_q, const float* s_a, const void* w_packed
     return rc != QQQ_OK ? rc : launch_splitk_reduce(p, mode, (hipStream_t)stream);
   };
   const int forced_split = get_prefill_ksplit();
-  if (tune == 10 || tune == 11 || (tune >= 15 && tune <= 17) || tune == 27 || tune == 37)
-    return per_tile(tune >= 15 ? tune % 10 - 2 : (tune == 10 && mode != kPerChannel ? 1 : 0), forced_split > 0 ? forced_split : 1);
+  if ((tune >= 10 && tune <= 12) || (tune >= 15 && tune <= 17) || tune == 27 || tune == 37)
+    return per_tile(tune == 12 ? 2 : tune >= 15 ? tune % 10 - 2 : (tune == 10 && mode != kPerChannel ? 1 : 0), forced_split > 0 ? forced_split : 1);
   if (tune == 13) return launch_gemm_prefill_ring(p, mode, (hipStream_t)stream);
   {
     const PrefillPlan plan = plan_prefill(M, N, K, cost_class(mode), can_split, forced_split);

@@ -6,7 +6,7 @@
 // workgroup tile is (32*MT) x (NW*32*CT).  Instances:
 //   <4,2,8>  128 x 512, <8,1,8>  256 x 256 (group scales only): 8 waves, 128 accumulator registers, two waves
 //            per SIMD
-//   <4,1,8>  128 x 256, <4,1,4>  128 x 128, <2,1,4>  64 x 128: narrow tiles for mid-size M, where
+//   <6,1,8>  192 x 256, <4,1,8>  128 x 256, <4,1,4>  128 x 128, <2,1,4>  64 x 128: narrow tiles for mid-size M, where
 //            a few large tiles would leave most CUs idle
 //
 // Why a DMA ring on gfx950.  The int8 MFMA pipe retires 32x32x32 (or two 16x16x64) multiply-accumulates
@@ -349,11 +349,13 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_prefill_dma_kernel(const Gemm
       stage = nstage;
     }
   } else {
-    // ---- main loop, 32x32x32 form, software-pipelined by hand and branch-free.  The activation
-    // fragments of MFMA step s+1 are read from LDS while the MFMAs of step s run; the workgroup
-    // barrier sits before the LAST MFMA step of a k-step (whose int8 operands are already
-    // converted), so that the LDS reads of the next k-step (first activation fragments, the lane's
-    // packed codes, its group scales) are in flight behind TM*TC MFMAs instead of stalling the pipe.
+    // ---- main loop, 32x32x32 form: the four MFMA steps of a k-step, branch-free.  With one wave per SIMD nothing else
+    // covers a wait, so everything a step needs is requested two steps ahead: the fragments of steps 0 and 1 of k-step t+1
+    // are read behind the MFMAs of steps 2 and 3 of k-step t (the workgroup barrier that makes them readable stands before
+    // step 2), those of steps 2 and 3 right after the MFMAs that used their registers.  The DMA requests go out a few per
+    // step, behind MFMAs: all at once they hold a wave up at the address unit for as long as half a k-step's MFMAs.
+    // (128 x 128 tiles, K = 8192, N = 4096, M = 128, per-channel: 27.2 us a launch, 32.4 with every request at the start and
+    // fragments one step ahead; real-valued scales 45.6, 46.8; 64 x 128 20.8, 21.4.  Fragments spread evenly over the k-step: 27.8.)
     v4i wq[TC][2];  // this lane's packed codes of the current k-step: [tile][piece]
     int sg[TC];       // and its group scales
     auto read_w = [&](const int8_t* sb) {
@@ -368,52 +370,77 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_prefill_dma_kernel(const Gemm
           sg[c] = (int)sb[sg_off + c * 32];
       }
     };
-    auto read_a = [&](v4i (&a)[TM], const int8_t* sb, int s) {
+    v4i f[4][TM], b[4][TC];  // fragments and converted codes of the MFMA steps
+    auto read_a = [&](const int8_t* sb, int s) {
 #pragma unroll
-      for (int mt = 0; mt < TM; ++mt) a[mt] = *(const v4i*)(sb + a_off[s] + mt * 4096);
+      for (int mt = 0; mt < TM; ++mt) f[s][mt] = *(const v4i*)(sb + a_off[s] + mt * 4096);
     };
     // MFMA step s uses piece s%2, dword pair s/2 of the lane's packed codes
-    auto make_b = [&](int c, int s) {
-      const v4i pc = wq[c][s & 1];
-      const uint32_t d0 = (uint32_t)((s >> 1) ? pc[2] : pc[0]), d1 = (uint32_t)((s >> 1) ? pc[3] : pc[1]);
-      return convert_b<MODE>(d0, d1, sg[c]);
-    };
-    auto mfma_col = [&](const v4i (&a)[TM], const v4i b, int c) {
+    auto make_b = [&](int s) {
 #pragma unroll
-      for (int mt = 0; mt < TM; ++mt) mfma(a[mt], b, acc[mt][c]);
+      for (int c = 0; c < TC; ++c) {
+        const v4i pc = wq[c][s & 1];
+        const uint32_t d0 = (uint32_t)((s >> 1) ? pc[2] : pc[0]), d1 = (uint32_t)((s >> 1) ? pc[3] : pc[1]);
+        b[s][c] = convert_b<MODE>(d0, d1, sg[c]);
+      }
     };
-    auto mfma_step = [&](const v4i (&a)[TM], int s) {
+    auto mfma_half = [&](int s, int half) {  // half of the row tiles
 #pragma unroll
-      for (int c = 0; c < TC; ++c) mfma_col(a, make_b(c, s), c);
+      for (int mt = half * TM / 2; mt < (half + 1) * TM / 2; ++mt)
+#pragma unroll
+        for (int c = 0; c < TC; ++c) mfma(f[s][mt], b[s][c], acc[mt][c]);
     };
-    v4i a0[TM], a1[TM];
+    constexpr int kEarly = kDmaPerStep / 2;  // requests of a k-step that go out in the second half of the k-step before
+    auto dma_pieces = [&](int t, int stage, int from, int to) {
+#pragma unroll
+      for (int piece = from; piece < to; ++piece) issue_dma_piece(t < T ? t : T - 1, stage, piece);
+    };
     read_w(lds);
-    read_a(a0, lds, 0);
-    for (int t = 0; t < T; ++t) {
-      // k-step t+ST-1 goes into the stage that was read during k-step t-1 (everyone is past the
-      // barrier inside it)
-      issue_dma(t + ST - 1 < T ? t + ST - 1 : T - 1, stage == 0 ? ST - 1 : stage - 1);
-      const int8_t* sb = lds + stage * S::kStage;
-      read_a(a1, sb, 1);
-      mfma_step(a0, 0);
-      read_a(a0, sb, 2);
-      mfma_step(a1, 1);
-      read_a(a1, sb, 3);
-      mfma_step(a0, 2);
-      v4i b3[TC];
 #pragma unroll
-      for (int c = 0; c < TC; ++c) b3[c] = make_b(c, 3);
+    for (int s = 0; s < 4; ++s) read_a(lds, s);
+    make_b(0);
+    dma_pieces(ST - 1, ST - 1, 0, kEarly);
+    for (int t = 0; t < T; ++t) {
+      // k-step t+ST-1 goes into the stage of k-step t-1, the first requests of k-step t+ST into this one's: every wave has read it
+      // all by the barrier
+      const int dstage = stage == 0 ? ST - 1 : stage - 1;
+      constexpr int kMid = kEarly + (kDmaPerStep - kEarly + 1) / 2;
+      mfma_half(0, 0);
+      make_b(1);
+      dma_pieces(t + ST - 1, dstage, kEarly, kMid);
+      __builtin_amdgcn_sched_barrier(0);
+      mfma_half(0, 1);
+      make_b(2);
+      __builtin_amdgcn_sched_barrier(0);
+      mfma_half(1, 0);
+      make_b(3);
+      dma_pieces(t + ST - 1, dstage, kMid, kDmaPerStep);
+      __builtin_amdgcn_sched_barrier(0);
+      mfma_half(1, 1);
+      __builtin_amdgcn_sched_barrier(0);
       // my DMA of k-step t+1 has landed (only the loads of the k-steps after it may still be in
       // flight), my LDS reads of this stage are done; then everyone's
       wait_all_but_newest_step();
-      stage = (stage == ST - 1) ? 0 : stage + 1;
-      // first LDS reads of k-step t+1 (stale data after the last k-step: read, never used) ...
-      const int8_t* nb = lds + stage * S::kStage;
-      read_a(a0, nb, 0);
+      const int nstage = (stage == ST - 1) ? 0 : stage + 1;
+      const int8_t* nb = lds + nstage * S::kStage;  // (stale data after the last k-step: read, never used)
       read_w(nb);
-      // ... in flight behind the last MFMA step of k-step t
-#pragma unroll
-      for (int c = 0; c < TC; ++c) mfma_col(a1, b3[c], c);
+      read_a(nb, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      mfma_half(2, 0);
+      read_a(nb, 1);
+      dma_pieces(t + ST, stage, 0, kEarly / 2);
+      __builtin_amdgcn_sched_barrier(0);
+      mfma_half(2, 1);
+      read_a(nb, 2);
+      __builtin_amdgcn_sched_barrier(0);
+      mfma_half(3, 0);
+      dma_pieces(t + ST, stage, kEarly / 2, kEarly);
+      __builtin_amdgcn_sched_barrier(0);
+      mfma_half(3, 1);
+      make_b(0);
+      read_a(nb, 3);
+      __builtin_amdgcn_sched_barrier(0);
+      stage = nstage;
     }
   }
   // the clamped DMA requests of the last two k-steps may still be landing in the ring: every wave waits for its
@@ -660,6 +687,7 @@ static bool lone_workgroups(const GemmParams& p, int bm, int bn) {
 template <int MODE>
 static int launch_shape(const GemmParams& p, int shape, hipStream_t st) {
   switch (shape) {
+    case 2: return launch_dma<MODE, 6, 1, 8>(p, st);
     case 3: return launch_dma<MODE, 4, 1, 8>(p, st);
     case 4: return launch_dma<MODE, 4, 1, 4>(p, st);
     case 5: return lone_workgroups(p, 64, 128) ? launch_dma<MODE, 2, 1, 4, 6>(p, st) : launch_dma<MODE, 2, 1, 4>(p, st);
@@ -675,7 +703,10 @@ static int launch_shape(const GemmParams& p, int shape, hipStream_t st) {
 // 256 x 256); with group scales 256 x 256 is ahead (N = 11008, K = 4096, M = 4096: real-valued scale 173 us against 219, saturating 203 against
 // 292, biased integer 165 against 172) except where 128 x 512 covers the rows in a round less (N = 14288, K = 4352, M = 1140,
 // biased: 252 tiles in 71 us, 280 of 256 x 256 or 504 of 128 x 256 in 80).
-// shape: 0 = 128x512 with 8 waves, 1 = 256x256 with 8 waves (group scales only); narrow tiles for shapes with few rows, where
+// 192 x 256 stands between 256 x 256 and 128 x 256 for rows that neither covers well: K = 4096, N = 11008, M = 777 is 172 tiles of
+// 256 x 256 (of 256 CUs, a quarter of their rows past M) in 56.3 us with real-valued scales, 215 of 192 x 256 in 48.8; per-channel 38.8 us
+// against 44.5 on 128 x 512.
+// shape: 0 = 128x512 with 8 waves, 1 = 256x256 with 8 waves (group scales only), 2 = 192x256 with 8 waves; narrow tiles for shapes with few rows, where
 // the number of workgroups matters more than the reuse inside one: 3 = 128x256 with 8 waves, 4 = 128x128
 // with 4 waves, 5 = 64x128 with 4 waves
 int launch_gemm_prefill_dma(const GemmParams& p, int mode, int shape, hipStream_t st) {

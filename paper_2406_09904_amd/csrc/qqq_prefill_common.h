@@ -52,7 +52,7 @@ struct DmaShape {
   static constexpr int kAPieces = kBM / (8 * NW);     // 1 KiB DMA pieces (8 rows) per wave
   static constexpr int kWChunks = 2 * CT;             // 1 KiB DMA chunks (16 channels) per wave
   static constexpr int kEpRow = 64 * CT + 16;         // fp16 row of the epilogue patch + bank pad
-  static constexpr int kEpRows = kBM < 128 ? kBM : 128;  // rows of it that are staged at a time
+  static constexpr int kEpRows = kBM <= 128 ? kBM : kBM / 2;  // rows of it that are staged at a time
   static constexpr int kEpWave = kEpRows * kEpRow + kBM * 4;  // and the wave's copy of the token scales
   static constexpr int kLds = kStages * kStage;
   static_assert(kBM % (8 * NW) == 0, "activation rows must split evenly over the waves");

@@ -1,5 +1,5 @@
-"""The 256 x 256 per-group prefill tile (its dequantised patch leaves in two halves) on ragged shapes against the CPU
-oracle: integers bit for bit, fp16 outputs within 1 ulp."""
+"""The 256 x 256 per-group and the 192 x 256 prefill tiles (their dequantised patches leave in two halves) on ragged
+shapes against the CPU oracle: integers bit for bit, fp16 outputs within 1 ulp."""
 import pytest
 
 from paper_2406_09904_amd import binding as qqq
@@ -26,4 +26,18 @@ def test_256_row_tile(M, K, N, k_splits, variant, hi, sg_max, knob):
     qqq.set_group_mode_override(knob)
     acc, y = run(variant, a_q, s_a, w, s_w, K, s_g=s_g, sg_max=sg_max)
     assert "tile=256x256" in qqq.last_route(), qqq.last_route()
+    check(acc, y, o_acc, o_y)
+
+
+@pytest.mark.parametrize("M,K,N,k_splits", [(192, 384, 256, 1), (197, 640, 784, 1), (400, 1408, 272, 2), (97, 128, 16, 1)])
+@pytest.mark.parametrize("variant,hi,sg_max,knob", [("pc", 0, 0, 0), ("pg", 16, 16, 3), ("pgb", 16, 16, 5), ("pg", 127, 0, 0),
+                                                    ("real", 0, 0, 0)])
+def test_192_row_tile(M, K, N, k_splits, variant, hi, sg_max, knob):
+    a_q, s_a, w, s_w = inputs(M, K, N, M + K + N + 37)
+    s_g, o_acc, o_y = reference(variant, a_q, s_a, w, s_w, K, N, 43, hi or 16)
+    qqq.set_prefill_tuning(12)
+    qqq.set_prefill_ksplit(k_splits)
+    qqq.set_group_mode_override(knob)
+    acc, y = run(variant, a_q, s_a, w, s_w, K, s_g=s_g, sg_max=sg_max)
+    assert "tile=192x256" in qqq.last_route(), qqq.last_route()
     check(acc, y, o_acc, o_y)
