@@ -412,7 +412,7 @@ __global__ __launch_bounds__(256) void smooth_loss_kernel(const int32_t* acc, co
 // triangle (3.66 ms with both triangles on vector multiply-adds); K = 2048, 1111 tokens: 0.144 ms (0.55).
 // VEC: rows of X are 16-byte aligned (K % 8 == 0 and an aligned base); else element by element.
 template <int TE, bool VEC>
-__global__ __launch_bounds__(256) void hessian_kernel(const _Float16* x, int64_t M, int64_t K, double* H) {
+__global__ __launch_bounds__(256, 4) void hessian_kernel(const _Float16* x, int64_t M, int64_t K, double* H) {
   constexpr int kTok = 2048 / TE, kStride = TE == 64 ? 72 : 48, kW = TE / 32, kVecs = TE / 8;
   typedef double v4d __attribute__((ext_vector_type(4)));
   constexpr int kTr = TE / 2 + 1;  // row stride of a quarter on its way to the mirrored place

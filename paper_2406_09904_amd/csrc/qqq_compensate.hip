@@ -15,9 +15,9 @@
 //   sweep          per 512 channels, from the first: sweep_kernel, then the update of the channels after
 // What is left serial is one dependent step per channel, in registers.
 // Bound, without the Hessian: K = N = 4096 holds 2.3e10 + 6.9e10 fp64 operations, 1.2 ms at the nominal 78.6 TFLOP/s of the
-// fp64 matrix cores (1.8 ms at the 50 that f64_update_kernel reaches).  Measured, K = N = 4096: 4.05 ms, and 4.75 ms with the
+// fp64 matrix cores (1.7 ms at the 54 that f64_update_kernel reaches).  Measured, K = N = 4096: 3.7 ms, and 4.4 ms with the
 // Hessian of 2048 tokens (an inverse by K rank-1 sweeps and a rank-1 update of both matrices per channel: 360 ms); K = 2048,
-// N = 5632 with group scales: 1.95 ms, 2.1 ms with the Hessian of 1111 tokens (81 ms).
+// N = 5632 with group scales: 1.75 ms, 1.9 ms with the Hessian of 1111 tokens (81 ms).
 #include "qqq_calib.h"
 #include "qqq_internal.h"
 
@@ -32,7 +32,7 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 constexpr int kFB = 64;    // channels per factorisation block
 constexpr int kSB = 128;   // channels per sweep block (= a group of the per-group quantiser)
 constexpr int kFO = 256, kSO = 512;  // channels after which the rest of the matrix is updated
-static_assert(kSB == QQQ_GROUP, "a sweep block is one group");
+static_assert(kSB == QQQ_GROUP && kSB == 128, "a sweep block is one group");
 
 template <int V>
 using Width = std::integral_constant<int, V>;
@@ -46,21 +46,70 @@ int check_launch(const char* what) {
   return QQQ_OK;
 }
 
-// one 64-bit value of lane SRC of every sixteen lanes, in all sixteen
+// One 64-bit value of lane SRC of every sixteen lanes, in all sixteen.
 template <int SRC>
 __device__ __forceinline__ double row_broadcast(double x) {
-  constexpr int sel = 0x150 + SRC;  // row_newbcast
-  const uint64_t u = __builtin_bit_cast(uint64_t, x);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, sel, 0xF, 0xF, true);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), sel, 0xF, 0xF, true);
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+  const long u = __builtin_bit_cast(long, x);
+  const long v = __builtin_amdgcn_update_dpp(0L, u, 0x150 + SRC, 0xF, 0xF, true);  // row_newbcast
+  return __builtin_bit_cast(double, v);
 }
-// one 64-bit value of one lane (the same index on every lane), in all lanes
-__device__ __forceinline__ double lane_value(double x, int src) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, x);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, src);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), src);
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+// Multiply-adds whose first factor is such a broadcast, x of lane L of every sixteen lanes: the data-parallel move is part of
+// v_fmac_f64, which costs what a multiply-add costs (5 clocks); a move of its own takes 6 and 8 of latency, two 32-bit
+// ones 12.  The compiler does not form it.  It has to stand two instructions behind the one that wrote x, which the compiler
+// does not see to inside an asm statement: the s_nop does, once for up to eight of them.
+#define QQQ_FMAC_DPP(ACC, X, M, L) "v_fmac_f64_dpp %" #ACC ", " X ", %" #M " row_newbcast:%" #L " row_mask:0xf bank_mask:0xf\n\t"
+// acc[k] += x * m[k]  (SUB: -=, acc[0] last, so that x may be acc[0] itself, in the same registers), k < N
+template <int L, bool SUB, int N, int A, int B>
+__device__ __forceinline__ void fmac_row(double (&acc)[A], double x, const double (&m)[B]) {
+  static_assert(N == 4 || N == 8, "");
+  if constexpr (N == 4) {
+    if constexpr (SUB)
+      asm volatile("s_nop 1\n\t" QQQ_FMAC_DPP(1, "-%4", 6, 9) QQQ_FMAC_DPP(2, "-%4", 7, 9) QQQ_FMAC_DPP(3, "-%4", 8, 9) QQQ_FMAC_DPP(0, "-%4", 5, 9)
+                   : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]) : "v"(x), "v"(m[0]), "v"(m[1]), "v"(m[2]), "v"(m[3]), "n"(L));
+    else
+      asm volatile("s_nop 1\n\t" QQQ_FMAC_DPP(0, "%4", 5, 9) QQQ_FMAC_DPP(1, "%4", 6, 9) QQQ_FMAC_DPP(2, "%4", 7, 9) QQQ_FMAC_DPP(3, "%4", 8, 9)
+                   : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]) : "v"(x), "v"(m[0]), "v"(m[1]), "v"(m[2]), "v"(m[3]), "n"(L));
+  } else {
+    if constexpr (SUB)
+      asm volatile("s_nop 1\n\t" QQQ_FMAC_DPP(1, "-%8", 10, 17) QQQ_FMAC_DPP(2, "-%8", 11, 17) QQQ_FMAC_DPP(3, "-%8", 12, 17) QQQ_FMAC_DPP(4, "-%8", 13, 17)
+                   QQQ_FMAC_DPP(5, "-%8", 14, 17) QQQ_FMAC_DPP(6, "-%8", 15, 17) QQQ_FMAC_DPP(7, "-%8", 16, 17) QQQ_FMAC_DPP(0, "-%8", 9, 17)
+                   : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]), "+v"(acc[5]), "+v"(acc[6]), "+v"(acc[7])
+                   : "v"(x), "v"(m[0]), "v"(m[1]), "v"(m[2]), "v"(m[3]), "v"(m[4]), "v"(m[5]), "v"(m[6]), "v"(m[7]), "n"(L));
+    else
+      asm volatile("s_nop 1\n\t" QQQ_FMAC_DPP(0, "%8", 9, 17) QQQ_FMAC_DPP(1, "%8", 10, 17) QQQ_FMAC_DPP(2, "%8", 11, 17) QQQ_FMAC_DPP(3, "%8", 12, 17)
+                   QQQ_FMAC_DPP(4, "%8", 13, 17) QQQ_FMAC_DPP(5, "%8", 14, 17) QQQ_FMAC_DPP(6, "%8", 15, 17) QQQ_FMAC_DPP(7, "%8", 16, 17)
+                   : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]), "+v"(acc[5]), "+v"(acc[6]), "+v"(acc[7])
+                   : "v"(x), "v"(m[0]), "v"(m[1]), "v"(m[2]), "v"(m[3]), "v"(m[4]), "v"(m[5]), "v"(m[6]), "v"(m[7]), "n"(L));
+  }
+}
+// acc[k] -= (x of lane k) * m, k = FROM down to FROM - N + 1
+template <int FROM, int N, int A>
+__device__ __forceinline__ void fmac_lanes(double (&acc)[A], double x, double m) {
+  static_assert(N >= 0 && N <= 4 && FROM - N + 1 >= 0, "");
+  if constexpr (N == 1)
+    asm volatile("s_nop 1\n\t" QQQ_FMAC_DPP(0, "-%1", 2, 3) : "+v"(acc[FROM]) : "v"(x), "v"(m), "n"(FROM));
+  if constexpr (N == 2)
+    asm volatile("s_nop 1\n\t" QQQ_FMAC_DPP(0, "-%2", 3, 4) QQQ_FMAC_DPP(1, "-%2", 3, 5)
+                 : "+v"(acc[FROM]), "+v"(acc[FROM - 1]) : "v"(x), "v"(m), "n"(FROM), "n"(FROM - 1));
+  if constexpr (N == 3)
+    asm volatile("s_nop 1\n\t" QQQ_FMAC_DPP(0, "-%3", 4, 5) QQQ_FMAC_DPP(1, "-%3", 4, 6) QQQ_FMAC_DPP(2, "-%3", 4, 7)
+                 : "+v"(acc[FROM]), "+v"(acc[FROM - 1]), "+v"(acc[FROM - 2]) : "v"(x), "v"(m), "n"(FROM), "n"(FROM - 1), "n"(FROM - 2));
+  if constexpr (N == 4)
+    asm volatile("s_nop 1\n\t" QQQ_FMAC_DPP(0, "-%4", 5, 6) QQQ_FMAC_DPP(1, "-%4", 5, 7) QQQ_FMAC_DPP(2, "-%4", 5, 8) QQQ_FMAC_DPP(3, "-%4", 5, 9)
+                 : "+v"(acc[FROM]), "+v"(acc[FROM - 1]), "+v"(acc[FROM - 2]), "+v"(acc[FROM - 3])
+                 : "v"(x), "v"(m), "n"(FROM), "n"(FROM - 1), "n"(FROM - 2), "n"(FROM - 3));
+}
+// acc[k] -= (its own lane L) * m, k < 4
+template <int L>
+__device__ __forceinline__ void fmac_own(double (&acc)[4], double m) {
+  asm volatile("s_nop 1\n\t" QQQ_FMAC_DPP(0, "-%0", 4, 5) QQQ_FMAC_DPP(1, "-%1", 4, 5) QQQ_FMAC_DPP(2, "-%2", 4, 5) QQQ_FMAC_DPP(3, "-%3", 4, 5)
+               : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]) : "v"(m), "n"(L));
+}
+#undef QQQ_FMAC_DPP
+// what an asm statement above has written, fit for the compiler's own data-parallel moves (which would not wait for it)
+__device__ __forceinline__ double fmac_settled(double x) {
+  asm volatile("s_nop 1" : "+v"(x));
+  return x;
 }
 template <int XOR>  // value of lane ^ XOR within four lanes
 __device__ __forceinline__ uint32_t quad_swap(uint32_t x) {
@@ -138,8 +187,9 @@ __global__ __launch_bounds__(256) void prepare_kernel(const double* H, const _Fl
 // 32 already requested.  v_mfma_f64_16x16x4_f64 (64 clocks): lane l holds row (column) l % 16 and k = l / 16
 // of the operands, register v of the result is row 4 v + l / 16, column l % 16.  Row strides of the LDS tiles
 // (34 and 80 doubles) put the 32 lanes of half a wave on all 64 banks; each fragment read feeds two MFMAs.  M = 4096,
-// N = 3584, kd = 512: 303 us, 50 TFLOP/s, the matrix pipe busy 0.66 of the cycles; 128 x 64 tiles and fragments read four k
-// ahead measured the same.
+// N = 3584, kd = 512: 280 us, 54 TFLOP/s (MFMAs alone, operands in registers, reach 70 at the 2.15 GHz they then leave); 128 x 64
+// tiles and fragments read four k ahead measured the same.  The second launch bound keeps the accumulators in the vector
+// registers: left alone the compiler moves them to the accumulation registers and back every 32 of kd (303 us).
 constexpr int kAs = 34, kBs = 80;  // row strides of the LDS tiles: 64 rows of A, 32 of B
 template <bool SUB>
 __device__ __forceinline__ void update_tile(const double* A, int64_t lda, const double* B, int64_t ldb, double* C, int64_t ldc,
@@ -222,7 +272,7 @@ __device__ __forceinline__ void update_tile(const double* A, int64_t lda, const 
 // UPPER: C is columns col0 .. col0 + N of a symmetric matrix kept as its upper triangle; only the tiles that reach the
 // diagonal or lie above it.
 template <bool UPPER, bool SUB>
-__global__ __launch_bounds__(256) void f64_update_kernel(const double* A, int64_t lda, const double* B, int64_t ldb,
+__global__ __launch_bounds__(256, 3) void f64_update_kernel(const double* A, int64_t lda, const double* B, int64_t ldb,
                                                          double* C, int64_t ldc, int M, int N, int kd, int col0) {
   __shared__ __attribute__((aligned(16))) double sa[64 * kAs];
   __shared__ __attribute__((aligned(16))) double sb[32 * kBs];
@@ -232,23 +282,25 @@ __global__ __launch_bounds__(256) void f64_update_kernel(const double* A, int64_
 
 // One block [c0, c0 + 64) of H = R D R^T, the channels after it already eliminated from A.
 // Every workgroup factors the 64 x 64 diagonal block for itself (64 dependent steps: column j's pivot
-// d_j, R[i,j] = A[i,j] / d_j for i < j, A[i,k] -= R[i,j] A[k,j] for k < j) and then solves for its own 32 of
+// d_j, R[i,j] = A[i,j] / d_j for i < j, A[i,k] -= R[i,j] A[k,j] for k < j) and then solves for its own 16 of
 // the c0 rows above: y_j = a_j - sum_{k > j} y_k R[j,k], x_j = y_j / d_j, i.e. R = x and R D = y there.
 // Written: x in place (A[row, c0 + j]) and y transposed into the unused lower triangle (A[c0 + j, row]),
 // which is the row-major operand the update of the rows above wants; the diagonal block's R goes
 // transposed below the diagonal (its upper half is still being read by other workgroups).
 // Bound by the chain of 64 pivots and, where code runs once, by its fetch: both halves walk 16 columns at a time
 // in a loop, so that one body of a few KiB serves the whole block (written out straight, 42 KiB of instructions
-// took 44.7 us a block whatever the row count; the loops take 20).
-// Diagonal block: the 16 columns first receive what the columns after them owe (fp64 MFMA, a wave per 16 rows), then
-// one wave with lane = row takes their 16 steps in registers; pivots and column elements reach all lanes
-// through v_readlane.  Rows above: 16 lanes per row, the solved element spread over them by a DPP move.
+// took 44.7 us a block whatever the row count).
+// Diagonal block, 16 columns at a time from the last: they receive what the columns after them owe (fp64 MFMA, a wave per 16 rows);
+// one wave takes the 16 steps of the 16 x 16 tile on the diagonal, a lane a row, with what is broadcast as part of the
+// multiply-adds and the next pivot's reciprocal between them; the waves of the rows above solve theirs by it, 16 lanes per row.
+// In clocks, a block: loads 3900, 16 columns 4600 (a pivot 150, the rest the products, the rows above, barriers), rows 5000; 13.3 us a
+// launch.  With lane = row for all 64 rows in one wave, pivots and column elements through v_readlane 8200 and 7400 for 32 rows: 21 us.
 // The first `solvers` workgroups do that.  The others, on the CUs the chain leaves idle, take a part of what the kFO
 // channels [t0, t0 + td) before these owe to the columns this kFO does not contain (Trailing): A[0..td0) -= R (R D)^T there,
 // 64 x 64 tiles of the upper triangle numbered column by column from `tile0`.  They touch nothing a block of this kFO reads
 // or writes: rows and columns below t0 - kFO, from operands at t0 and past it.
 struct Trailing { int t0, td, n, tile0; };  // first channel, channels, rows (= columns) updated, first tile
-__global__ __launch_bounds__(256) void factor_panel_kernel(double* A, int64_t K, int c0, int solvers, Trailing tr) {
+__global__ __launch_bounds__(256, 2) void factor_panel_kernel(double* A, int64_t K, int c0, int solvers, Trailing tr) {
   constexpr int kS = 66;
   static_assert(64 * kS >= 64 * kAs && 64 * kS >= 32 * kBs, "an update tile's stages fit");
   __shared__ __attribute__((aligned(16))) double ys[64 * kS];  // [i][j]: the block, then R D for i < j, 0 from the diagonal on
@@ -262,17 +314,14 @@ __global__ __launch_bounds__(256) void factor_panel_kernel(double* A, int64_t K,
     update_tile<true>(A + tr.t0, K, A + (int64_t)tr.t0 * K, K, A, K, tr.n, tr.n, tr.td, u - tn * (tn + 1) / 2, tn, ys, xs);
     return;
   }
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, q = lane >> 4;
   const int nb = min(64, (int)K - c0);
-  // ---- the rows this workgroup solves: 8 wave + 4 v + q, this lane's columns 16 r + l16
-  const int64_t row0 = (int64_t)blockIdx.x * 32 + 8 * wave + q;
-  double y[2][4];
+  // ---- the row this thread's sixteen lanes solve, this lane's columns 16 r + l16 in y[3 - r]
+  const int64_t row = (int64_t)blockIdx.x * 16 + 4 * wave + q;
+  double y[4];
 #pragma unroll
-  for (int v = 0; v < 2; ++v)
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      y[v][r] = A[min(row0 + 4 * v, (int64_t)c0) * K + c0 + min(16 * r + l16, nb - 1)];  // (what is not there is not stored)
+  for (int r = 0; r < 4; ++r) y[3 - r] = A[min(row, (int64_t)c0) * K + c0 + min(16 * r + l16, nb - 1)];  // (what is not there is not stored)
 
   // ---- the diagonal block, upper triangle; channels past K are identity
 #pragma unroll
@@ -284,39 +333,87 @@ __global__ __launch_bounds__(256) void factor_panel_kernel(double* A, int64_t K,
   __syncthreads();
 #pragma nounroll
   for (int p = 3; p >= 0; --p) {
-    if (p < 3) {
-      if (wave <= p) {
-        v4d acc;
+    // a wave's 16 rows of these columns less what the columns after owe them: register v is row 16 wave + 4 v + q, column 16 p + l16
+    double u[4];
+    if (wave <= p) {
+      v4d acc;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) acc[v] = ys[(16 * wave + 4 * v + q) * kS + 16 * p + l16];
-        for (int k = 16 * (p + 1); k < 64; k += 4)
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-xs[(16 * wave + l16) * kS + k + q], ys[(16 * p + l16) * kS + k + q],
-                                                     acc, 0, 0, 0);
+      for (int v = 0; v < 4; ++v) acc[v] = ys[(16 * wave + 4 * v + q) * kS + 16 * p + l16];
+      for (int k = 16 * (p + 1); k < 64; k += 16) {
+        double x[4], yk[4];  // (all requested before the first is multiplied)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) ys[(16 * wave + 4 * v + q) * kS + 16 * p + l16] = acc[v];
-      }
-      __syncthreads();
-    }
-    if (wave == 0) {
-      double a[16];  // element (lane, 16 p + k); below the diagonal whatever the steps leave, never used
-#pragma unroll
-      for (int k = 0; k < 16; ++k) a[k] = ys[lane * kS + 16 * p + k];
-#pragma unroll
-      for (int j = 15; j >= 0; --j) {
-        const double d = lane_value(a[j], 16 * p + j);
-        double rd = __builtin_amdgcn_rcp(d);  // two Newton steps: within an ulp or so of 1 / d
-        rd = __builtin_fma(__builtin_fma(-d, rd, 1.0), rd, rd);
-        rd = __builtin_fma(__builtin_fma(-d, rd, 1.0), rd, rd);
-        const bool above = lane < 16 * p + j;
-        const double x = above ? a[j] * rd : 0.0;
-#pragma unroll
-        for (int k = 0; k < j; ++k) {
-          a[k] = __builtin_fma(-x, lane_value(a[j], 16 * p + k), a[k]);
-          asm volatile("" : "+v"(a[k]));  // now, not when column k's turn comes (that keeps 240 broadcast values alive)
+        for (int w = 0; w < 4; ++w) {
+          x[w] = -xs[(16 * wave + l16) * kS + k + 4 * w + q];
+          yk[w] = ys[(16 * p + l16) * kS + k + 4 * w + q];
         }
-        xs[lane * kS + 16 * p + j] = x;
-        ys[lane * kS + 16 * p + j] = above ? a[j] : 0.0;
-        if (lane == 0) rcp[16 * p + j] = rd;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x[w], yk[w], acc, 0, 0, 0);
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        u[v] = acc[v];
+        if (wave == p) ys[(16 * wave + 4 * v + q) * kS + 16 * p + l16] = acc[v];
+      }
+    }
+    __syncthreads();
+    if (wave == 0) {
+      // t[k]: element (16 p + l16, 16 p + k) of the diagonal tile, once in every sixteen lanes.  Below the diagonal whatever the
+      // steps leave, never used
+      double t[16], own_rd = 0.0;
+#pragma unroll
+      for (int k = 0; k < 16; ++k) t[k] = ys[(16 * p + l16) * kS + 16 * p + k];
+      double rd;  // 1 / d within an ulp or so: two Newton steps
+      {
+        const double d = row_broadcast<15>(t[15]);
+        rd = __builtin_amdgcn_rcp(d);
+        rd = __builtin_fma(__builtin_fma(-d, rd, 1.0), rd, rd);
+        rd = __builtin_fma(__builtin_fma(-d, rd, 1.0), rd, rd);
+      }
+      // The next pivot first, and the steps of its reciprocal between the other multiply-adds (each is pinned to its place:
+      // left to the compiler they stand in a row, waiting for one another)
+      auto step = [&](auto at) {
+        constexpr int j = decltype(at)::value;
+        const double x = t[j] * rd;
+        own_rd = l16 == j ? rd : own_rd;
+        if constexpr (j > 0) {
+          constexpr int n = j - 1;  // columns left after the next pivot's
+          fmac_lanes<j - 1, 1>(t, t[j], x);
+          const double d = row_broadcast<j - 1>(fmac_settled(t[j - 1]));
+          double r = __builtin_amdgcn_rcp(d);
+          asm volatile("" : "+v"(r));
+          if constexpr (n > 0) fmac_lanes<n - 1, (n < 4 ? n : 4)>(t, t[j], x);
+          double e = __builtin_fma(-d, r, 1.0);
+          asm volatile("" : "+v"(e));
+          if constexpr (n > 4) fmac_lanes<n - 5, (n < 8 ? n - 4 : 4)>(t, t[j], x);
+          r = __builtin_fma(e, r, r);
+          asm volatile("" : "+v"(r));
+          if constexpr (n > 8) fmac_lanes<n - 9, (n < 12 ? n - 8 : 4)>(t, t[j], x);
+          e = __builtin_fma(-d, r, 1.0);
+          asm volatile("" : "+v"(e));
+          if constexpr (n > 12) fmac_lanes<n - 13, n - 12>(t, t[j], x);
+          rd = __builtin_fma(e, r, r);
+        }
+        xs[(16 * p + l16) * kS + 16 * p + j] = l16 < j ? x : 0.0;  // (nothing reads R D in a diagonal tile)
+      };
+      step(Width<15>{}); step(Width<14>{}); step(Width<13>{}); step(Width<12>{}); step(Width<11>{}); step(Width<10>{});
+      step(Width<9>{}); step(Width<8>{}); step(Width<7>{}); step(Width<6>{}); step(Width<5>{}); step(Width<4>{});
+      step(Width<3>{}); step(Width<2>{}); step(Width<1>{}); step(Width<0>{});
+      if (lane < 16) rcp[16 * p + lane] = own_rd;
+    }
+    __syncthreads();
+    if (wave < p) {  // the rows above, column by column from the last
+      const double* rr = xs + (16 * p + l16) * kS + 16 * p;
+      double m[16];
+#pragma unroll
+      for (int j = 15; j > 0; --j) m[j] = rr[j];
+      fmac_own<15>(u, m[15]); fmac_own<14>(u, m[14]); fmac_own<13>(u, m[13]); fmac_own<12>(u, m[12]); fmac_own<11>(u, m[11]);
+      fmac_own<10>(u, m[10]); fmac_own<9>(u, m[9]); fmac_own<8>(u, m[8]); fmac_own<7>(u, m[7]); fmac_own<6>(u, m[6]);
+      fmac_own<5>(u, m[5]); fmac_own<4>(u, m[4]); fmac_own<3>(u, m[3]); fmac_own<2>(u, m[2]); fmac_own<1>(u, m[1]);
+      const double rd = rcp[16 * p + l16];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        ys[(16 * wave + 4 * v + q) * kS + 16 * p + l16] = u[v];
+        xs[(16 * wave + 4 * v + q) * kS + 16 * p + l16] = u[v] * rd;
       }
     }
     __syncthreads();
@@ -330,43 +427,39 @@ __global__ __launch_bounds__(256) void factor_panel_kernel(double* A, int64_t K,
   }
   if (c0 == 0) return;
   // ---- the solve, column by column from the last; xs is zero at and past the diagonal.  The 16 columns in turn are always
-  // y[.][3]: the others move up behind them (what moves into finished places is not used)
+  // y[0]: the others move up behind them (what moves into finished places is not used)
 #pragma nounroll
   for (int p = 3; p >= 0; --p) {
     // R[16 (p - 3 + r) + l16][16 p + j]; where that row is before the block, row l16 feeds places no longer used
     const double* rr[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) rr[r] = xs + (16 * max(p - 3 + r, 0) + l16) * kS + 16 * p;
-#define QQQ_SOLVE(J)                                                                             \
-  {                                                                                              \
-    const double m0 = rr[0][J], m1 = rr[1][J], m2 = rr[2][J], m3 = rr[3][J];                     \
-    _Pragma("unroll") for (int v = 0; v < 2; ++v) {                                              \
-      const double yj = row_broadcast<J>(y[v][3]);                                               \
-      y[v][3] = __builtin_fma(-yj, m3, y[v][3]);                                                 \
-      y[v][2] = __builtin_fma(-yj, m2, y[v][2]);                                                 \
-      y[v][1] = __builtin_fma(-yj, m1, y[v][1]);                                                 \
-      y[v][0] = __builtin_fma(-yj, m0, y[v][0]);                                                 \
-    }                                                                                            \
+    for (int r = 0; r < 4; ++r) rr[3 - r] = xs + (16 * max(p - 3 + r, 0) + l16) * kS + 16 * p;
+    double m[2][4];  // a column's, requested during the column before
+#pragma unroll
+    for (int r = 0; r < 4; ++r) m[1][r] = rr[r][15];
+#define QQQ_SOLVE(J)                                                                                          \
+  {                                                                                                           \
+    if (J > 0) {                                                                                              \
+      _Pragma("unroll") for (int r = 0; r < 4; ++r) m[(J + 1) & 1][r] = rr[r][J > 0 ? J - 1 : 0];             \
+      __builtin_amdgcn_sched_barrier(0);                                                                      \
+    }                                                                                                         \
+    fmac_row<J, true, 4>(y, y[0], m[J & 1]);                                                                  \
   }
     QQQ_SOLVE(15) QQQ_SOLVE(14) QQQ_SOLVE(13) QQQ_SOLVE(12) QQQ_SOLVE(11) QQQ_SOLVE(10) QQQ_SOLVE(9) QQQ_SOLVE(8)
     QQQ_SOLVE(7) QQQ_SOLVE(6) QQQ_SOLVE(5) QQQ_SOLVE(4) QQQ_SOLVE(3) QQQ_SOLVE(2) QQQ_SOLVE(1) QQQ_SOLVE(0)
 #undef QQQ_SOLVE
+    const int col = 16 * p + l16;
+    if (row < c0 && col < nb) A[row * K + c0 + col] = y[0] * rcp[col];
+    ys[col * kS + 4 * wave + q] = y[0];  // (nothing reads the block's R D any more)
 #pragma unroll
-    for (int v = 0; v < 2; ++v) {
-      const int col = 16 * p + l16;
-      if (row0 + 4 * v < c0 && col < nb) A[(row0 + 4 * v) * K + c0 + col] = y[v][3] * rcp[col];
-      ys[col * kS + 8 * wave + 4 * v + q] = y[v][3];  // (nothing reads the block's R D any more)
-      y[v][3] = y[v][2];
-      y[v][2] = y[v][1];
-      y[v][1] = y[v][0];
-    }
+    for (int r = 0; r < 3; ++r) y[r] = y[r + 1];
   }
   __syncthreads();
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int j = 8 * e + (tid >> 5), i = tid & 31;
-    const int64_t row = (int64_t)blockIdx.x * 32 + i;
-    if (j < nb && row < c0) A[(int64_t)(c0 + j) * K + row] = ys[j * kS + i];
+  for (int e = 0; e < 4; ++e) {
+    const int j = 16 * e + (tid >> 4), i = tid & 15;
+    const int64_t to = (int64_t)blockIdx.x * 16 + i;
+    if (j < nb && to < c0) A[(int64_t)(c0 + j) * K + to] = ys[j * kS + i];
   }
 }
 
@@ -387,10 +480,11 @@ __device__ __forceinline__ Tile upper_tile(int u) {
 // what the 128 owe to those before (from o0 on) as one fp64 MFMA product, then the chain.  Bound by that chain of
 // dependent fp64 operations (about 12 a channel): sixteen lanes per output channel, lane's channels 16 r + (lane % 16) in
 // registers, so that 4096 output channels put a wave on every SIMD; a step is the quotient, its rounding and one
-// multiply-add per 16 later channels, the broadcast of W_i - q s inside the sixteen lanes being a data-parallel move.
+// multiply-add per 16 later channels, the broadcast of W_i - q s inside the sixteen lanes being part of it.
 // The steps are a loop over 16 channels whose registers move down one place each time: one body for 128 channels
 // (written out straight, 40 to 73 KiB of instructions, each fetched for one use, took 65 to 81 us per 128 channels and the
-// separate products 20 more; this form takes 22 for all of it, 4096 output channels).
+// separate products 20 more).  In clocks, 128 channels of 4096 output channels at K = 4096: weights 2500 (8600 as conditional loads),
+// product 8500 per 128 channels before, R 5000, chain 19500 (153 a step); 512 channels 78 us.
 // R's block sits in LDS as rows of what a step still needs: row i from channel 16 (i / 16) on, zeros up to the diagonal, one
 // double apart from a multiple of the banks.
 // The quotient: w * (1/s) corrected by its exact remainder, which is the correctly rounded w / s.
@@ -407,18 +501,19 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const _Float16* w, const 
                                                     int64_t K, int o0, int o1, uint16_t* scales, double* W64,
                                                     uint32_t* w_nat) {
   constexpr int kRows = 16 * (16 * 36 + 8);  // doubles: 16 rows of 129 - 16 r for r = 0 .. 7
-  constexpr int kXs = 130;                   // the product's 16 rows, in the same place before R is
+  // in the same place before R is: the product's 16 rows of the left operand and of the result
+  constexpr int kLs = kSO - kSB + 2, kXs = kSB + 2;
+  static_assert(16 * (kLs + kXs) <= kRows, "the product's operand and result fit");
   __shared__ __attribute__((aligned(16))) double rl[kRows + 64];  // (a step reads up to three vectors of 16 past its row)
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, q = lane >> 4;
   const int64_t n0 = (int64_t)blockIdx.x * 16;
   const int64_t row = n0 + 4 * wave + q;
   const int64_t n = row < N ? row : N - 1;  // (rows past N repeat the last one and store nothing)
-  const int64_t nl = n0 + l16 < N ? n0 + l16 : N - 1;
   auto r_base = [](int r) { return 16 * (129 * r - 8 * r * (r - 1)); };
   // row 16 r + o of R from channel 16 r on, this lane's channels.  A step's row is read during the step before.  The scheduling
-  // barriers between steps keep the compiler from reading all sixteen at once, the empty asm statements from putting the
-  // multiply-adds of later channels off until after the loop (either way 16 rows of R in registers, and spills)
+  // barriers between steps keep the compiler from reading all sixteen at once, the multiply-adds as volatile asm statements from
+  // putting those of later channels off until after the loop (either way 16 rows of R in registers, and spills)
   auto fetch_row = [&](int r, int o, auto& to) {
     const double* from = rl + r_base(r) + o * (129 - 16 * r) + l16;
 #pragma unroll
@@ -429,67 +524,77 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const _Float16* w, const 
   for (int c0 = o0; c0 < o1; c0 += kSB) {
     const int nb = min(kSB, (int)K - c0);
     const int64_t at = n * K + c0 + l16;
-    double acc[8];
+    // every load in range and unconditional, all requested before the first is used (a load under its own condition waits for
+    // the one before: 8.6 thousand clocks for these 24); channels past K count nothing
+    double acc[8], kept[8];
     float wo[8];
+    const int last = nb - 1 - l16;  // (nb is a multiple of 8: what is clamped may be another lane's)
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const int at_r = min(16 * r, last);
+      acc[r] = W64[at + at_r];
+      kept[r] = keep[c0 + l16 + at_r];
+      wo[r] = (float)w[at + at_r];
+    }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
       const bool in = 16 * r + l16 < nb;
-      acc[r] = in ? W64[at + 16 * r] : 0.0;
-      wo[r] = (in && keep[c0 + 16 * r + l16] != 0.0) ? (float)w[at + 16 * r] : 0.0f;
+      acc[r] = in ? acc[r] : 0.0;
+      wo[r] = in && kept[r] != 0.0 ? wo[r] : 0.0f;
     }
-    if (c0 > o0) {  // this workgroup's W_i - q s of the channels since o0, by R; a wave takes channels 32 wave .. + 32
+    if (c0 > o0) {
+      // This workgroup's W_i - q s of the channels since o0, by R; a wave takes channels 32 wave .. + 32, column 2 l16 + t in
+      // tile t: both tiles' elements of a row of R are one 128-bit load.  The left operand, the same for every wave, goes
+      // through LDS.  (Each wave fetching it for itself, and R in 64-bit loads, 80 loads a wave and 128 channels took 8.3
+      // thousand clocks where the products take 4.1.)
+#pragma nounroll
+      for (int k = 2 * l16; k < c0 - o0; k += 32) {
+        const int r = 4 * wave + q;
+        *reinterpret_cast<double2*>(&rl[r * kLs + k]) = *reinterpret_cast<const double2*>(W64 + (n0 + r < N ? n0 + r : N - 1) * K + o0 + k);
+      }
+      __syncthreads();
       v4d m[2] = {};
-      const double* left = W64 + nl * K + 4 * q;  // row l16, k = 4 q + s
-      const double* right[2];                     // k = 4 q + s, column l16
-#pragma unroll
-      for (int t = 0; t < 2; ++t) right[t] = A + (int64_t)(4 * q) * K + min((int64_t)c0 + 32 * wave + 16 * t + l16, K - 1);
-      // 64 channels of k at a time, each half requested while the other is multiplied (16 at a time and nothing ahead, the
-      // loads' latency was a third of the kernel)
-      double2 la[2][4];
-      double rb[2][2][8];
+      const uint32_t right = (uint32_t)(4 * q * K + min((int64_t)c0 + 32 * wave + 2 * l16, K - 2));  // of row k + s: k = 4 q + s
+      // 16 channels of k at a time, requested kAhead sixteens (1.5 thousand clocks of products) before they are multiplied
+      constexpr int kAhead = 3;
+      double2 rb[8][4];
       auto request = [&](int h, int k) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          la[h][2 * u] = *reinterpret_cast<const double2*>(left + k + 16 * u);
-          la[h][2 * u + 1] = *reinterpret_cast<const double2*>(left + k + 16 * u + 2);
-#pragma unroll
-          for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int s = 0; s < 4; ++s) rb[h][t][4 * u + s] = right[t][(int64_t)(k + 16 * u + s) * K];
-        }
+        for (int s = 0; s < 4; ++s) rb[h][s] = *reinterpret_cast<const double2*>(A + (int64_t)(k + s) * K + right);
+        __builtin_amdgcn_sched_barrier(0);
       };
-      auto multiply = [&](int h) {
 #pragma unroll
-        for (int x = 0; x < 8; ++x) {
-          const double a = x & 1 ? la[h][x >> 1].y : la[h][x >> 1].x;
-#pragma unroll
-          for (int t = 0; t < 2; ++t) m[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, rb[h][t][x], m[t], 0, 0, 0);
-        }
-      };
-      request(0, o0);
+      for (int h = 0; h < kAhead; ++h) request(h, o0 + 16 * h);
 #pragma nounroll
-      for (int k = o0; k < c0; k += 64) {
-        request(1, k + 32);
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(0);
-        request(0, min(k + 64, c0 - 32));  // (past the end: the last ones once more, unused)
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(1);
+      for (int k = o0; k < c0; k += 128) {  // (c0 - o0 is a multiple of kSB)
+#pragma unroll
+        for (int h = 0; h < 8; ++h) {
+          request((h + kAhead) % 8, min(k + 16 * (h + kAhead), c0 - 16));  // (past the end: the last ones once more, unused)
+          const double2* left = reinterpret_cast<const double2*>(&rl[l16 * kLs + k - o0 + 16 * h + 4 * q]);
+          const double2 l0 = left[0], l1 = left[1];
+          const double la[4] = {l0.x, l0.y, l1.x, l1.y};
+#pragma unroll
+          for (int x = 0; x < 4; ++x) {
+            m[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(la[x], rb[h][x].x, m[0], 0, 0, 0);
+            m[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(la[x], rb[h][x].y, m[1], 0, 0, 0);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) rl[(4 * v + q) * kXs + 32 * wave + 16 * t + l16] = m[t][v];
+      for (int v = 0; v < 4; ++v)
+        *reinterpret_cast<double2*>(&rl[16 * kLs + (4 * v + q) * kXs + 32 * wave + 2 * l16]) = make_double2(m[0][v], m[1][v]);
       __syncthreads();
 #pragma unroll
-      for (int r = 0; r < 8; ++r) acc[r] += rl[(4 * wave + q) * kXs + 16 * r + l16];
+      for (int r = 0; r < 8; ++r) acc[r] += rl[16 * kLs + (4 * wave + q) * kXs + 16 * r + l16];
       __syncthreads();
     }
     // R: strictly upper part; where i and j share a factorisation block it lies transposed below the diagonal.  16 x 16
     // tiles on and above the diagonal, nine to a wave; every load is requested before the first value is placed
+    double e[9][4];
     {
       const double* block = A + (int64_t)c0 * K + c0;
-      double e[9][4];
 #pragma unroll
       for (int x = 0; x < 9; ++x) {
         const Tile g = upper_tile(wave + 4 * x);
@@ -500,15 +605,16 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const _Float16* w, const 
         for (int v = 0; v < 4; ++v)
           e[x][v] = (block + (hi + 4 * v < nb ? hi + 4 * v : 0) * (int)K + (lo < nb ? lo : 0))[q * (int)K + l16];
       }
+      __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll
-      for (int x = 0; x < 9; ++x) {
-        const Tile g = upper_tile(wave + 4 * x);
+    for (int x = 0; x < 9; ++x) {
+      const Tile g = upper_tile(wave + 4 * x);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int i = g.transposed ? l16 : 4 * v + q, j = g.transposed ? 4 * v + q : l16;
-          const bool in = 16 * g.t + j > 16 * g.r + i && 16 * g.t + j < nb;
-          rl[r_base(g.r) + 16 * (g.t - g.r) + i * (129 - 16 * g.r) + j] = in ? e[x][v] : 0.0;
-        }
+      for (int v = 0; v < 4; ++v) {
+        const int i = g.transposed ? l16 : 4 * v + q, j = g.transposed ? 4 * v + q : l16;
+        const bool in = 16 * g.t + j > 16 * g.r + i && 16 * g.t + j < nb;
+        rl[r_base(g.r) + 16 * (g.t - g.r) + i * (129 - 16 * g.r) + j] = in ? e[x][v] : 0.0;
       }
     }
     __syncthreads();
@@ -529,9 +635,7 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const _Float16* w, const 
   {                                                                                                        \
     double next[W];                                                                                        \
     if (O < 15) fetch_row(r, O + 1, next);                                                                 \
-    const double d = row_broadcast<O>(z[0]);                                                               \
-    _Pragma("unroll") for (int k = 0; k < W; ++k) z[k] = __builtin_fma(-d, ri[k], z[k]);                   \
-    _Pragma("unroll") for (int k = 1; k < W; ++k) asm volatile("" : "+v"(z[k]));                           \
+    fmac_row<O, true, W>(z, z[0], ri);                                                                     \
     if (O < 15) {                                                                                          \
       _Pragma("unroll") for (int k = 0; k < W; ++k) ri[k] = next[k];                                       \
     }                                                                                                      \
@@ -578,11 +682,9 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const _Float16* w, const 
     const double quo = __builtin_fma(__builtin_fma(-q0, s, v), rs, q0);                                    \
     const float code = keep_nan_clamp(__builtin_rintf((float)quo), 7.0f);                                  \
     const double diff = __builtin_fma(-(double)code, s, w0);                                               \
-    const double d = row_broadcast<O>(diff);                                                               \
+    fmac_row<O, false, W>(acc, diff, ri);                                                                  \
     own_code = l16 == O ? code : own_code;                                                                 \
     own_diff = l16 == O ? diff : own_diff;                                                                 \
-    _Pragma("unroll") for (int k = 0; k < W; ++k) acc[k] = __builtin_fma(d, ri[k], acc[k]);                \
-    _Pragma("unroll") for (int k = 1; k < W; ++k) asm volatile("" : "+v"(acc[k]));                         \
     if (O < 15) {                                                                                          \
       _Pragma("unroll") for (int k = 0; k < W; ++k) ri[k] = next[k];                                       \
     }                                                                                                      \
@@ -690,9 +792,9 @@ int begin(const char* who, const void* w_fp16, const double* H, int64_t N, int64
   if ((rc = check_launch("gptq prepare")) != QQQ_OK) return rc;
   // Blocks of 64 from the last; each at once reduces the columns of its own kFO, and all columns before those are
   // reduced by the whole kFO together (see sweep): the next kFO's columns at once, the rest inside the launches of the next
-  // kFO's blocks, whose chains leave most CUs idle.  Those carry up to four tiles per CU each, more would take longer than the
-  // chain; what is left then (the first columns) goes at once as well.  (K = 4096: a launch with 288 tiles takes 21.5 us, 20.5
-  // without; the updates as launches of their own up to 100 us per kFO.)
+  // kFO's blocks, whose chains leave CUs idle.  Two workgroups of that kernel fit a CU: up to seven for every four CUs a launch keeps
+  // its time (K = 4096: 14.4 us without tiles, 17.7 at 226 workgroups, 23.4 at 436, 27.7 at 498, 38.8 at 635); what is
+  // left then (the first columns) goes at once as well.
   auto reduce = [&](int64_t c0, int64_t kd, int64_t col0, int64_t cols, int64_t rows) {
     if (cols <= 0 || rows <= 0) return;
     hipLaunchKernelGGL((f64_update_kernel<true, true>), dim3((unsigned)((cols + 63) / 64), (unsigned)((rows + 63) / 64)),
@@ -703,7 +805,7 @@ int begin(const char* who, const void* w_fp16, const double* H, int64_t N, int64
   for (int64_t o0 = (K - 1) / kFO * kFO; o0 >= 0; o0 -= kFO) {
     const int64_t o1 = o0 + kFO < K ? o0 + kFO : K;
     for (int64_t c0 = (o1 - 1) / kFB * kFB; c0 >= o0; c0 -= kFB) {
-      const int solvers = c0 ? (int)(c0 / 32) : 1;
+      const int solvers = c0 ? (int)(c0 / 16) : 1;
       const int blocks_left = (int)((c0 - o0) / kFB) + 1;
       const int carried = (tiles_left + blocks_left - 1) / blocks_left;
       hipLaunchKernelGGL(factor_panel_kernel, dim3((unsigned)(solvers + carried)), dim3(256), 0, st, A, K, (int)c0, solvers, tr);
@@ -714,7 +816,7 @@ int begin(const char* who, const void* w_fp16, const double* H, int64_t N, int64
     if (o0 == 0) break;
     const int64_t p0 = o0 - kFO;
     reduce(o0, o1 - o0, p0, kFO, o0);
-    const int nt = (int)(p0 / 64), most = 4 * (kFO / kFB) * num_cus();
+    const int nt = (int)(p0 / 64), most = (kFO / kFB) * max(num_cus() * 7 / 4 - (int)(p0 / 16), 0);
     int at_once = 0;  // tile columns
     while (nt * (nt + 1) / 2 - at_once * (at_once + 1) / 2 > most) ++at_once;
     reduce(o0, o1 - o0, 0, (int64_t)at_once * 64, (int64_t)at_once * 64);
