@@ -108,26 +108,30 @@ __global__ __launch_bounds__(256) void smoothing_vector_kernel(const float* absm
   ((float*)((char*)s + stride_bytes * blockIdx.y))[t] = a > sigma ? a / sigma : 1.0f;
 }
 
-// eight channels of X' = fp16_rne(fp32(X) / s) (DIVIDE) or W' = fp16_rne(fp32(W) * s): one fp32 operation, one rounding
-template <bool DIVIDE>
-__device__ __forceinline__ uint4 smooth8(uint4 q, const float* s) {
-  const float4 s0 = *reinterpret_cast<const float4*>(s);
-  const float4 s1 = *reinterpret_cast<const float4*>(s + 4);
+// eight channels of X' = fp16_rne(fp32(X) / s) (DIVIDE) or W' = fp16_rne(fp32(W) * s): one fp32 operation, one rounding.
+// ANY_ZERO: a product of -0 may come out as 0; it is then a mixed-precision multiply-add with 0, which takes the fp16 weight as
+// it is (the same fp32 rounding).
+template <bool DIVIDE, bool ANY_ZERO = false>
+__device__ __forceinline__ uint4 smooth8(uint4 q, float4 s0, float4 s1) {
   const float sv[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
   const uint32_t w[4] = {q.x, q.y, q.z, q.w};
   uint32_t o[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const float a = half_bits_to_float(w[j] & 0xFFFFu), b = half_bits_to_float(w[j] >> 16);
-    float ra = DIVIDE ? a / sv[2 * j] : a * sv[2 * j];
-    float rb = DIVIDE ? b / sv[2 * j + 1] : b * sv[2 * j + 1];
+    float ra = DIVIDE ? a / sv[2 * j] : ANY_ZERO ? __builtin_fmaf(a, sv[2 * j], 0.0f) : a * sv[2 * j];
+    float rb = DIVIDE ? b / sv[2 * j + 1] : ANY_ZERO ? __builtin_fmaf(b, sv[2 * j + 1], 0.0f) : b * sv[2 * j + 1];
     // the fp32 result is rounded before the conversion sees it: left alone, the compiler turns
     // multiply + convert into one mixed-precision instruction that rounds the exact product once
     asm volatile("" : "+v"(ra), "+v"(rb));
-    o[j] = (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)ra) |
-           ((uint32_t)__builtin_bit_cast(uint16_t, (_Float16)rb) << 16);
+    typedef float v2f __attribute__((ext_vector_type(2)));
+    o[j] = __builtin_bit_cast(uint32_t, __builtin_convertvector((v2f){ra, rb}, h2));
   }
   return make_uint4(o[0], o[1], o[2], o[3]);
+}
+template <bool DIVIDE, bool ANY_ZERO = false>
+__device__ __forceinline__ uint4 smooth8(uint4 q, const float* s) {
+  return smooth8<DIVIDE, ANY_ZERO>(q, *reinterpret_cast<const float4*>(s), *reinterpret_cast<const float4*>(s + 4));
 }
 
 template <bool DIVIDE>
@@ -171,10 +175,10 @@ __global__ __launch_bounds__(256) void point_activations_kernel(const uint4* x, 
   if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = bits;
   __syncthreads();
   const float amax = half_bits_to_float(max(max(part[0], part[1]), max(part[2], part[3])));
-  const float sc = amax / 127.0f;
+  const float sc = amax / 127.0f, rs = reciprocal_near(sc);
   if (threadIdx.x == 0) ((float*)((char*)s_a + off))[m] = amax == 0.0f ? 0.0f : sc;
   auto codes = [&](uint4 q) {
-    return amax == 0.0f ? make_uint2(0, 0) : make_uint2(quant4(q.x, q.y, sc), quant4(q.z, q.w, sc));
+    return amax == 0.0f ? make_uint2(0, 0) : quant8_act(q, sc, rs);
   };
   if constexpr (KEEP) {
 #pragma unroll
@@ -188,11 +192,11 @@ __global__ __launch_bounds__(256) void point_activations_kernel(const uint4* x, 
 }
 
 // 16 output channels per workgroup (qqq_quantize_w4_perchannel on W .* s, then qqq_pack_w4): a wave takes four
-// channels one after the other, its lanes hold the row (K <= 4096: in registers; else the row is smoothed
+// channels one after the other, its lanes hold the row (K <= 4096: in registers, s with it; else the row is smoothed
 // twice, 4096 channels at a time), and the codes meet in LDS in the packed layout's order, so whole 1 KiB chunks are
-// written.  Bound by instructions, about 12 per weight and grid point (9.5 us a grid point at K = N = 4096, 10.6
-// with the codes rounded, tested and packed one by one).  The four channels and their eight vectors are written out, each with
-// the divisions of its near-ties inline: 50 KB of code (58 KB for K > 4096), most of it fetched once per workgroup.
+// written.  Bound by instructions, about 7 per weight and grid point: 6.3 us a grid point at K = N = 4096 (9.5 with the rounding, the
+// clamp and the nibbles in fp32 and converted products).  K <= 4096: the four channels are a loop (13 KB of code); beyond, they and
+// their vectors are written out (54 KB).
 template <bool ONE>
 __global__ __launch_bounds__(256) void point_weights_kernel(const uint4* w, const float* s, int64_t N, int kvec,
                                                             int64_t point_bytes, uint8_t* packed, uint16_t* s_w) {
@@ -216,13 +220,13 @@ __global__ __launch_bounds__(256) void point_weights_kernel(const uint4* w, cons
   const float* sv = (const float*)((const char*)s + off);
   uint32_t* out = (uint32_t*)(packed + off);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  float sc[4];
+  [[maybe_unused]] float sc[4];
   uint4 v[8];
   auto smooth_row = [&](const uint4* row, int i0) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const int i = i0 + lane + 64 * j;
-      v[j] = i < kvec ? smooth8<false>(row[i], sv + 8 * i) : make_uint4(0, 0, 0, 0);
+      v[j] = i < kvec ? smooth8<false, true>(row[i], sv + 8 * i) : make_uint4(0, 0, 0, 0);
     }
   };
   auto scale_of_row = [&](int64_t n, const uint4* row) {
@@ -231,22 +235,24 @@ __global__ __launch_bounds__(256) void point_weights_kernel(const uint4* w, cons
       smooth_row(row, i0);
 #pragma unroll
       for (int j = 0; j < 8; ++j) bits = absmax_bits(v[j], bits);
-      if constexpr (ONE) break;
     }
-    const uint16_t sb = scale_bits(half_bits_to_float(wave_max_u32(bits)), 7.0f);
+    const uint16_t sb = weight_scale_bits(half_bits_to_float(wave_max_u32(bits)));
     if (lane == 0) ((uint16_t*)((char*)s_w + off))[n] = sb;
     return half_bits_to_float(sb);
   };
-  // natural word i of channel nl = 16 nt + c: word (k-step i / 16, lane c + 16 kc, dword d) of the packed layout
+  // natural word i of channel nl = 16 nt + c: word (k-step i / 16, lane c + 16 kc, dword d) of the packed layout.  A wave writes
+  // words of one c: the sixteen vectors of a kc are turned so that its four k-steps and four kc take all banks
+  auto slot = [](int step, int kc, int c) { return 16 * kc + ((c + 4 * (step & 3) + kc) & 15); };
   auto put = [&](int c, float scale, int i0) {
     const float rs = __builtin_amdgcn_rcpf(scale);
+    float cmax;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const int i = lane + 64 * j;
       if (i0 + i >= kvec) continue;
-      const uint32_t word = scale != 0.0f ? quant8<false>(v[j], scale, rs, nullptr) : 0u;
+      const uint32_t word = scale != 0.0f ? quant8<true>(v[j], scale, rs, &cmax) : 0u;
       const int o = i & 15, kc = (o & 7) >> 1, d = 2 * (o >> 3) + (o & 1);
-      stage[(i >> 4) * 256 + (c + 16 * kc) * 4 + d] = shuffle_nibbles_fwd(word);
+      stage[(i >> 4) * 256 + slot(i >> 4, kc, c) * 4 + d] = word;
     }
   };
   auto flush = [&](int i0) {  // whole chunks of up to 32 k-steps
@@ -254,19 +260,41 @@ __global__ __launch_bounds__(256) void point_weights_kernel(const uint4* w, cons
     const int steps = min(32, (kvec - i0) >> 4);
     for (int e = threadIdx.x; e < steps * 64; e += 256)
       *reinterpret_cast<uint4*>(out + (((int64_t)(i0 >> 4) + (e >> 6)) * groups + nt) * 256 + (e & 63) * 4) =
-          *reinterpret_cast<const uint4*>(&stage[e * 4]);
+          *reinterpret_cast<const uint4*>(&stage[(e & ~63) * 4 + slot(e >> 6, (e >> 4) & 3, e & 15) * 4]);
     __syncthreads();
   };
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int c = 4 * wave + q;
-    const int64_t n = nt * 16 + c;
-    sc[q] = scale_of_row(n, w + n * kvec);
-    if constexpr (ONE) put(c, sc[q], 0);
-  }
   if constexpr (ONE) {
+    // the lanes keep their part of s for the four channels, and request the next channel's weights before they work on one
+    float4 s0[8], s1[8];
+    uint4 next[8];
+    auto request = [&](int q) {
+      const uint4* row = w + (nt * 16 + 4 * wave + q) * kvec;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) next[j] = row[min(lane + 64 * j, kvec - 1)];
+    };
+    request(0);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const float4* from = reinterpret_cast<const float4*>(sv) + 2 * min(lane + 64 * j, kvec - 1);
+      s0[j] = from[0];
+      s1[j] = from[1];
+    }
+#pragma unroll 1
+    for (int q = 0; q < 4; ++q) {
+      uint32_t bits = 0;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = smooth8<false, true>(next[j], s0[j], s1[j]);
+      request(min(q + 1, 3));
+#pragma unroll
+      for (int j = 0; j < 8; ++j) bits = absmax_bits(v[j], bits);  // (past the row's end its last vector again)
+      const uint16_t sb = weight_scale_bits(half_bits_to_float(wave_max_u32(bits)));
+      if (lane == 0) ((uint16_t*)((char*)s_w + off))[nt * 16 + 4 * wave + q] = sb;
+      put(4 * wave + q, half_bits_to_float(sb), 0);
+    }
     flush(0);
   } else {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sc[q] = scale_of_row((nt * 16 + 4 * wave + q), w + (nt * 16 + 4 * wave + q) * kvec);
     for (int i0 = 0; i0 < kvec; i0 += 512) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {

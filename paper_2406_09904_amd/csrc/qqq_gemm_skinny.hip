@@ -342,8 +342,7 @@ __global__ __launch_bounds__(W * 64) void gemm_skinny_kernel(const GemmParams p,
         if (idx < total) {
           uint2 o = make_uint2(0, 0);
           if (a_m != 0.0f) {
-            o.x = quant4(v[j].x, v[j].y, s_m);
-            o.y = quant4(v[j].z, v[j].w, s_m);
+            o = quant8_act(v[j], s_m, reciprocal_near(s_m));
           }
           // row m starts at byte m*(K+16): K is a multiple of all 64 banks, and an MFMA fragment read
           // takes the same 16 bytes of up to four different rows at once, which the pad spreads over the banks

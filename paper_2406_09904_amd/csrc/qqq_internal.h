@@ -242,6 +242,36 @@ __device__ __forceinline__ uint32_t quant4(uint32_t w0, uint32_t w1, float s) {
          ((uint32_t)(q3 & 0xFF) << 24);
 }
 
+// x / s rounded to fp32 as the IEEE division rounds it, y = reciprocal_near(s): the product corrected by its exact remainder, three
+// instructions for twelve.  That it is the division's result was checked for every fp16 x against every s that is fp16
+// (weights) and every s = amax / 127, amax fp16 >= |x| (activations), for the rounded reciprocal and either neighbour as the
+// hardware's (which is within an ulp).  Not for a zero, infinite or NaN s.
+__device__ __forceinline__ float reciprocal_near(float s) {
+  const float y = __builtin_amdgcn_rcpf(s);
+  return __builtin_fmaf(__builtin_fmaf(-s, y, 1.0f), y, y);
+}
+__device__ __forceinline__ float quotient(float x, float s, float y) {
+  const float q = __builtin_fmaf(x, y, 0.0f);  // (with 0 added it takes an fp16 x as it is)
+  return __builtin_fmaf(__builtin_fmaf(-s, q, x), y, q);
+}
+
+// Eight of them at once, the same codes, y = reciprocal_near(s), for a finite s without a branch: |x / s| <= 127 (1 + 2^-23), so nothing has
+// to be clamped, and adding 1.5 * 2^23 rounds the quotient to an integer, half to even, whose low byte is the code.  38
+// instructions; an infinite or NaN s takes the way of before.
+__device__ __forceinline__ uint2 quant8_act(uint4 v, float s, float y) {
+  const uint32_t h[4] = {v.x, v.y, v.z, v.w};
+  uint32_t t[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+    t[i] = __builtin_bit_cast(uint32_t, quotient(half_bits_to_float(i & 1 ? h[i >> 1] >> 16 : h[i >> 1] & 0xFFFFu), s, y) + 12582912.0f);
+  auto bytes = [&](int i) {  // v_perm_b32: selector bytes 0-3 pick from the second source, 4-7 from the first
+    return __builtin_amdgcn_perm(__builtin_amdgcn_perm(t[i + 3], t[i + 2], 0x0C0C0400u), __builtin_amdgcn_perm(t[i + 1], t[i], 0x0C0C0400u), 0x05040100u);
+  };
+  uint2 o = make_uint2(bytes(0), bytes(4));
+  if (!(s < __builtin_inff())) o = make_uint2(quant4(v.x, v.y, s), quant4(v.z, v.w, s));
+  return o;
+}
+
 // ---- weight quantisation arithmetic (symmetric round to nearest, codes in [-7,7]), shared by the front-end and the
 // ---- smoothing search
 // fp16 bits of amax / q (fp32 IEEE division, one rounding to fp16)
@@ -249,44 +279,62 @@ __device__ __forceinline__ uint16_t scale_bits(float amax, float q) {
   return __builtin_bit_cast(uint16_t, (_Float16)(amax / q));
 }
 
-// Eight fp16 weights -> eight nibbles of a natural word; CMAX: *cmax = max(*cmax, max |code|).
-// code = clamp(rne(w / s), -7, 7), the quotient being the correctly rounded fp32 one, computed without
-// dividing in the common case: q~ = w * rcp(s) is within 2^-22 relative of w/s, and so is the
-// rounded quotient (2^-24); for |q~| < 8 both are then within 2^-19 absolute of w/s, so unless q~
-// lies within 2^-16 of a half-integer the two round to the same integer.  Beyond 8 in magnitude
-// either rounding clamps to +-7.  Only near a tie the IEEE division decides: one test for the eight of them.
-// The nibbles are put together in fp32, where sum (code_i + 8) 16^i over four of them is exact, and flipped from
-// offset binary to two's complement at the end: 12 instructions for eight codes instead of 24.
-template <bool CMAX>
-__device__ __forceinline__ uint32_t quant8(uint4 v, float s, float rs, float* cmax) {
+// fp16 bits of amax / 7 for an fp16 value amax, the quotient rounded to fp32 as the IEEE division rounds it: amax * (1/7) corrected
+// by its exact remainder gives the same for every finite fp16 value (all 31744 checked), in 3 instructions instead of 12
+__device__ __forceinline__ uint16_t weight_scale_bits(float amax) {
+  const float q = amax * (1.0f / 7.0f);
+  const float quo = __builtin_fmaf(__builtin_fmaf(-7.0f, q, amax), 1.0f / 7.0f, q);
+  return __builtin_bit_cast(uint16_t, (_Float16)(amax < __builtin_inff() ? quo : amax));
+}
+
+// Eight fp16 weights -> eight nibbles of a natural word, or (PACKED) of the device layout's; *cmax: the largest |code|.
+// code = clamp(rne(w / s), -7, 7), the quotient being the correctly rounded fp32 one.  Any s but 0:
+template <bool PACKED>
+__device__ __forceinline__ uint32_t quant8_each(uint4 v, float s, float* cmax) {
   const uint32_t h[4] = {v.x, v.y, v.z, v.w};
-  float w[8], r[8], far = 0.0f;
+  const float y = reciprocal_near(s);
+  const bool finite = s < __builtin_inff();
+  uint32_t word = 0;
+  *cmax = 0.0f;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    w[i] = half_bits_to_float(i & 1 ? h[i >> 1] >> 16 : h[i >> 1] & 0xFFFFu);
-    const float q = w[i] * rs;
-    r[i] = __builtin_rintf(q);
-    far = __builtin_fmaxf(far, __builtin_fabsf(q - r[i]));
+    const float w = half_bits_to_float(i & 1 ? h[i >> 1] >> 16 : h[i >> 1] & 0xFFFFu);
+    const float q = finite ? quotient(w, s, y) : w * __builtin_amdgcn_rcpf(s);
+    const float r = __builtin_amdgcn_fmed3f(__builtin_rintf(q), -7.0f, 7.0f);
+    *cmax = __builtin_fmaxf(*cmax, __builtin_fabsf(r));
+    word |= ((uint32_t)(int)r & 0xFu) << (4 * (PACKED ? 2 * (i & 3) + (i >> 2) : i));
   }
-  if (far > 0.5f - 0x1p-16f) {
+  return word;
+}
+// and where s = fp16(max |w| / 7) of some block that holds these weights is a normal number, faster in the common case.
+// Then |w / s| <= 7 (1 + 2^-11): nothing has to be clamped, and the block's largest |code| is 7.  t = w * rcp(s) + 192.5 + 2^-15
+// (one mixed-precision multiply-add, rounded once, to a multiple of 2^-16) is within 2^-17 + 2^-20 of
+// w / s + 192.5 + 2^-15.  So unless its fraction, the low 16 bits, is below 2^-14, its integer part is that of w / s + 192.5 and w / s is more than
+// 2^-16 from a half-integer, which the rounded quotient is 2^-22 from at most: the low nibble of the third byte is the code in
+// two's complement.  30 instructions for eight codes, the test of all of them included (53 with the rounding, the test, the clamp
+// and the nibbles in fp32).
+template <bool PACKED>
+__device__ __forceinline__ uint32_t quant8(uint4 v, float s, float rs, float* cmax) {
+  const uint32_t h[4] = {v.x, v.y, v.z, v.w};
+  uint32_t t[8];
+  uint16_t low = 0xFFFF;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) r[i] = __builtin_rintf(w[i] / s);
+  for (int i = 0; i < 8; ++i) {
+    const float w = half_bits_to_float(i & 1 ? h[i >> 1] >> 16 : h[i >> 1] & 0xFFFFu);
+    t[i] = __builtin_bit_cast(uint32_t, __builtin_fmaf(w, rs, 192.5f + 0x1p-15f));
+    low = __builtin_elementwise_min(low, (uint16_t)t[i]);
   }
-#pragma unroll
-  for (int i = 0; i < 8; ++i) r[i] = __builtin_amdgcn_fmed3f(r[i], -7.0f, 7.0f);
-  if constexpr (CMAX) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) *cmax = __builtin_fmaxf(*cmax, __builtin_fabsf(r[i]));
-  }
-  uint32_t half[2];
-#pragma unroll
-  for (int g = 0; g < 2; ++g) {
-    float t = r[4 * g] + 34952.0f;  // 0x8888
-    t = __builtin_fmaf(r[4 * g + 1], 16.0f, t);
-    t = __builtin_fmaf(r[4 * g + 2], 256.0f, t);
-    half[g] = (uint32_t)__builtin_fmaf(r[4 * g + 3], 4096.0f, t);
-  }
-  return (half[0] | (half[1] << 16)) ^ 0x88888888u;
+  *cmax = 7.0f;
+  // third bytes of the codes of the even and of the odd nibbles; v_perm_b32: selector bytes 0-3 pick from the second source,
+  // 4-7 from the first, 12 is a zero
+  auto bytes = [&](uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+    return __builtin_amdgcn_perm(b, a, 0x0C0C0602u) | __builtin_amdgcn_perm(d, c, 0x06020C0Cu);
+  };
+  const uint32_t even = PACKED ? bytes(t[0], t[1], t[2], t[3]) : bytes(t[0], t[2], t[4], t[6]);
+  const uint32_t odd = PACKED ? bytes(t[4], t[5], t[6], t[7]) : bytes(t[1], t[3], t[5], t[7]);
+  uint32_t word = (even & 0x0F0F0F0Fu) | ((odd << 4) & 0xF0F0F0F0u);
+  if (low < 4 || !(s >= 0x1p-14f && s < __builtin_inff())) word = quant8_each<PACKED>(v, s, cmax);
+  return word;
 }
 
 // packed nibble q takes natural nibble 4*(q%2) + q/2  (order 0,4,1,5,2,6,3,7)
