@@ -1,5 +1,5 @@
-// Offline (calibration-time) stage of QQQ on one layer: adaptive smoothing (Sec. 3.1, Eq. 1-2) and the
-// Hessian of Sec. 3.2 (its compensation sweep is in qqq_compensate.hip).  Entry points of include/qqq_calib.h.
+// Offline (calibration-time) stage of QQQ on one layer: adaptive smoothing (Sec. 3.1, Eq. 1-2).  Entry points of
+// include/qqq_calib.h (the Hessian of Sec. 3.2 is in qqq_hessian.hip, its compensation sweep in qqq_compensate.hip).
 //
 // Everything that decides an integer code is done in a fixed precision and operation order (stated at
 // each kernel) so that the result can be checked bit for bit; floating-point contraction is off in
@@ -426,102 +426,6 @@ __global__ __launch_bounds__(256) void smooth_loss_kernel(const int32_t* acc, co
   if (threadIdx.x == 0) atomicAdd(loss, part[0]);
 }
 
-// ------------------------------------------------------------------ Sec. 3.2: Hessian
-
-// H = 2 X^T X in fp64 on the fp64 matrix cores.  H is symmetric: one workgroup per TE x TE tile on or above
-// the diagonal, written to both places.  Both operands are columns of X, kept in LDS as the fp16 they are
-// (2048 / TE tokens at a time, the next ones already requested) and widened when a fragment is read:
-// v_mfma_f64_16x16x4_f64 takes 64 clocks, so the widening and the LDS reads are free next to it.  Lane l holds
-// column l % 16 and token l / 16 of both operands; register v of the result is row 4 v + l / 16, column l % 16.
-// Row strides of the stages (72 and 48 halves) keep the four token rows of a fragment on different banks.
-// A wave holds a (TE/2) x (TE/2) quarter.  TE = 64 reads each fragment for two MFMAs; TE = 32 is for narrow layers,
-// where 64 x 64 tiles leave CUs idle.
-// Bound: the fp64 matrix rate (78.6 TFLOP/s nominal).  K = 4096, 2048 tokens: 0.73 ms, 47 TFLOP/s of the one
-// triangle (3.66 ms with both triangles on vector multiply-adds); K = 2048, 1111 tokens: 0.144 ms (0.55).
-// VEC: rows of X are 16-byte aligned (K % 8 == 0 and an aligned base); else element by element.
-template <int TE, bool VEC>
-__global__ __launch_bounds__(256, 4) void hessian_kernel(const _Float16* x, int64_t M, int64_t K, double* H) {
-  constexpr int kTok = 2048 / TE, kStride = TE == 64 ? 72 : 48, kW = TE / 32, kVecs = TE / 8;
-  typedef double v4d __attribute__((ext_vector_type(4)));
-  constexpr int kTr = TE / 2 + 1;  // row stride of a quarter on its way to the mirrored place
-  __shared__ __attribute__((aligned(16))) union {
-    uint16_t x[2][kTok * kStride];
-    double t[4][TE / 2 * kTr];
-  } sm;
-  // tile pair (ti <= tj) of the linear index
-  int tj = (int)((__builtin_sqrtf(8.0f * (float)blockIdx.x + 1.0f) - 1.0f) * 0.5f);
-  while ((int64_t)(tj + 1) * (tj + 2) / 2 <= (int64_t)blockIdx.x) ++tj;
-  while ((int64_t)tj * (tj + 1) / 2 > (int64_t)blockIdx.x) --tj;
-  const int ti = (int)((int64_t)blockIdx.x - (int64_t)tj * (tj + 1) / 2);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, q = lane >> 4;
-  const int wr = (wave >> 1) * (TE / 2), wc = (wave & 1) * (TE / 2);
-  const int64_t c0[2] = {(int64_t)ti * TE, (int64_t)tj * TE};
-  const int srow = tid / kVecs, scol = 8 * (tid % kVecs);  // this thread's 8 elements of a stage
-
-  uint4 next[2];
-  auto fetch = [&](int64_t m0) {  // tokens past M and channels past K feed zeros
-#pragma unroll
-    for (int o = 0; o < 2; ++o) {
-      const int64_t m = m0 + srow, c = c0[o] + scol;
-      if constexpr (VEC) {
-        next[o] = (m < M && c < K) ? *reinterpret_cast<const uint4*>(x + m * K + c) : make_uint4(0, 0, 0, 0);
-      } else {
-        uint32_t e[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-          e[i] = (m < M && c + i < K) ? (uint32_t)reinterpret_cast<const uint16_t*>(x)[m * K + c + i] : 0u;
-        next[o] = make_uint4(e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16);
-      }
-    }
-  };
-  v4d acc[kW][kW];
-#pragma unroll
-  for (int i = 0; i < kW; ++i)
-#pragma unroll
-    for (int j = 0; j < kW; ++j) acc[i][j] = (v4d){0.0, 0.0, 0.0, 0.0};
-  fetch(0);
-  for (int64_t m0 = 0; m0 < M; m0 += kTok) {
-#pragma unroll
-    for (int o = 0; o < 2; ++o) *reinterpret_cast<uint4*>(&sm.x[o][srow * kStride + scol]) = next[o];
-    __syncthreads();
-    if (m0 + kTok < M) fetch(m0 + kTok);
-#pragma unroll
-    for (int s = 0; s < kTok / 4; ++s) {
-      double a[kW], b[kW];
-#pragma unroll
-      for (int i = 0; i < kW; ++i) {
-        a[i] = (double)half_bits_to_float(sm.x[0][(4 * s + q) * kStride + wr + 16 * i + l16]);
-        b[i] = (double)half_bits_to_float(sm.x[1][(4 * s + q) * kStride + wc + 16 * i + l16]);
-      }
-#pragma unroll
-      for (int i = 0; i < kW; ++i)
-#pragma unroll
-        for (int j = 0; j < kW; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
-    __syncthreads();
-  }
-  double* const tr = sm.t[wave];
-#pragma unroll
-  for (int i = 0; i < kW; ++i)
-#pragma unroll
-    for (int j = 0; j < kW; ++j)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int r = 16 * i + 4 * v + q, c = 16 * j + l16;
-        const double h = 2.0 * acc[i][j][v];
-        const int64_t gi = c0[0] + wr + r, gj = c0[1] + wc + c;
-        if (gi < K && gj < K) H[gi * K + gj] = h;
-        tr[c * kTr + r] = h;
-      }
-  if (ti == tj) return;  // the whole diagonal tile was computed, both halves bit for bit alike
-  // mirrored: rows of the quarter's transpose, from the wave's own patch (one wave's LDS accesses stay in order)
-  constexpr int kE = TE / 2;
-  for (int e = lane; e < kE * kE; e += 64) {
-    const int c = e / kE, r = e % kE;
-    const int64_t gi = c0[1] + wc + c, gj = c0[0] + wr + r;
-    if (gi < K && gj < K) H[gi * K + gj] = tr[c * kTr + r];
-  }
-}
 
 static bool calib_shape_ok(int64_t M, int64_t N, int64_t K) {
   return M >= 1 && M <= 0x7FFFFFFF && N >= 16 && N % 16 == 0 && N <= 0x7FFFFFF0 && K >= 128 && K % 128 == 0 &&
@@ -753,25 +657,6 @@ int qqq_adaptive_smoothing(const void* x_fp16, const void* w_fp16, int64_t M, in
   hipLaunchKernelGGL(argmin_kernel, dim3(1), dim3(64), 0, st, losses, grid_points, best);
   if ((rc = check_launch("argmin")) != QQQ_OK) return rc;
   return launch_smooth(x_fp16, w_fp16, absmax, sigmas, best, M, N, K, xs_fp16, ws_fp16, s, st);
-}
-
-int qqq_hessian(const void* x_fp16, int64_t M, int64_t K, double* H, void* stream) {
-  if (M < 1 || M > 0x7FFFFFFF || K < 1 || K > 16384)
-    return set_error(QQQ_ERR_SHAPE, "hessian: unsupported M=%lld K=%lld (need 1 <= K <= 16384)", (long long)M, (long long)K);
-  if (!x_fp16 || !H) return set_error(QQQ_ERR_NULL, "hessian: null pointer argument");
-  if ((reinterpret_cast<uintptr_t>(x_fp16) & 1u) || (reinterpret_cast<uintptr_t>(H) & 7u))
-    return set_error(QQQ_ERR_SHAPE, "hessian: x must be 2-byte, H 8-byte aligned");
-  // 64 x 64 tiles where they give every CU at least two, else 32 x 32
-  auto tiles = [&](int64_t te) { const int64_t t = (K + te - 1) / te; return t * (t + 1) / 2; };
-  const bool wide = tiles(64) >= 2 * (int64_t)num_cus();
-  const bool vec = K % 8 == 0 && aligned16c(x_fp16);
-  const dim3 grid((unsigned)tiles(wide ? 64 : 32));
-#define QQQ_HESSIAN(TE, VEC) \
-  hipLaunchKernelGGL((hessian_kernel<TE, VEC>), grid, dim3(256), 0, (hipStream_t)stream, (const _Float16*)x_fp16, M, K, H)
-  if (wide) { if (vec) QQQ_HESSIAN(64, true); else QQQ_HESSIAN(64, false); }
-  else { if (vec) QQQ_HESSIAN(32, true); else QQQ_HESSIAN(32, false); }
-#undef QQQ_HESSIAN
-  return check_launch("hessian");
 }
 
 }  // extern "C"

@@ -155,3 +155,36 @@ def test_hessian_of_activations_that_are_no_numbers(K, at, value, percdamp):
         codes[:, 0] = cal.rtn_codes(w[:, 0].view(np.float16), s_wg[0].view(np.float16))
         got = qqq.qqq_gptq_quantize_w4_pergroup(dev16(w), H, percdamp)
         assert np.array_equal(codes_of(got[0], K), codes) and np.array_equal(f16_bits(got[1]), s_wg)
+
+
+@pytest.mark.parametrize("M,K,edge", [(128, 968, None), (193, 1032, 127.4375), (130, 1160, 127.5), (150, 1032, np.inf), (129, 968, np.nan)])
+def test_hessian_from_digits(M, K, edge):
+    """The int8 products: sums of whole numbers, so every element is the exact sum rounded once.  Values over fp16's whole range
+    below 127.5, subnormal ones among them; from 127.5 on (one value of one channel here) its tiles take the fp64 products."""
+    rng = np.random.default_rng(M + K)
+    x = (rng.standard_normal((M, K)) * np.exp2(rng.integers(-22, 5, K))).astype(np.float16)
+    x[rng.integers(0, M, 50), rng.integers(0, K, 50)] = np.float16(2.0 ** -24)
+    at = K - 3
+    if edge is not None:
+        x[M - 1 if M % 2 else 0, at] = edge   # seen by the last stage or by the first
+        x[0, 5] = -edge if np.isfinite(edge) and edge < 127.5 else x[0, 5]
+    H = qqq.qqq_hessian(torch.from_numpy(x).cuda()).cpu().numpy()
+    assert np.array_equal(H.view(np.int64), H.T.copy().view(np.int64))
+    x64 = x.astype(np.float64)
+    exact = np.ones((K, K), bool)
+    if edge is not None and not edge < 127.5:
+        lo = at // 64 * 64   # the 64 x 64 tiles with the channel in their rows or columns
+        exact[lo:lo + 64, :] = exact[:, lo:lo + 64] = False
+        with np.errstate(invalid="ignore"):
+            want = 2.0 * (x64.T @ x64)
+        got, ref = H[~exact], want[~exact]
+        assert np.array_equal(np.isfinite(got), np.isfinite(ref))
+        ok = np.isfinite(ref)
+        scale = np.sqrt(np.outer(np.diag(want), np.diag(want)))[~exact][ok]
+        assert (np.abs(got[ok] - ref[ok]) <= 2.0 ** -52 * M * scale).all()   # M fp64 roundings of partial sums below that product
+        x64[:, at] = 0.0
+    m = (x64 * 2.0 ** 24).astype(np.int64)
+    hi, lo = m >> 12, m & 0xFFF
+    s = (hi.T @ hi).astype(object) * 2 ** 24 + (hi.T @ lo + lo.T @ hi).astype(object) * 2 ** 12 + (lo.T @ lo).astype(object)
+    want = s.astype(np.float64) * 2.0 ** -47   # int -> float rounds once, half to even
+    assert np.array_equal(H[exact], want[exact])
