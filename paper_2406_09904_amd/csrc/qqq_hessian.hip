@@ -143,18 +143,6 @@ __global__ __launch_bounds__(256, 4) void hessian_kernel(const _Float16* x, int6
 // [2048, 1024]: 39 (74), [300, 1024]: 12.5 (15.4).
 constexpr int kMaxTokens = 16384;
 
-// The pair of this workgroup, of `blocks` blocks of channels: every XCD takes one stretch of the order (workgroups go to the 8 XCDs in
-// turn), and the order goes through bands of 8 q's, p by p, so that the 64 tiles an XCD works on at a time share 8 + 8 panels of x in
-// its L2.
-__device__ __forceinline__ Pair banded_pair(int blocks) {
-  const int n = gridDim.x, xcd = blockIdx.x & 7;
-  const int index = xcd * (n >> 3) + min(xcd, n & 7) + (int)(blockIdx.x >> 3);
-  const int q0 = triangle_pair(index).q & ~7, width = min(8, blocks - q0), rest = index - q0 * (q0 + 1) / 2;
-  if (rest < width * q0) return {rest / width, q0 + rest % width};
-  const Pair corner = triangle_pair(rest - width * q0);
-  return {q0 + corner.p, q0 + corner.q};
-}
-
 __global__ __launch_bounds__(256, 2) void hessian_digits_kernel(const _Float16* x, int M, int K, double* H) {
   constexpr int kPlane = 128 * 64 + 8 * 64, kStage = 4 * kPlane;  // channel c at 64 (c + c / 16)
   __shared__ __attribute__((aligned(16))) union {
@@ -162,7 +150,7 @@ __global__ __launch_bounds__(256, 2) void hessian_digits_kernel(const _Float16* 
     TileStage<64> tile;
   } sm;
   __shared__ int s_large[2];
-  const Pair t = banded_pair((K + 63) / 64);
+  const Pair t = triangle_pair(blockIdx.x);
   const int r0 = t.p * 64, c0 = t.q * 64;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, kb = lane >> 4, wr = wave >> 1, wc = wave & 1;
