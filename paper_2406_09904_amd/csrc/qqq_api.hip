@@ -92,8 +92,10 @@ static size_t split_bytes(int64_t M, int64_t N) {
 //                 share.  2 to 3 % rms on all of them.  An even spread or whole rounds alone miss by 10 to 30 %: M = 2048, K = 4096, N = 11008
 //                 took 89 us in 1.4 rounds of 128 x 512 and takes 80 in 2.7 rounds of 128 x 256.  (The smoothing search's row is
 //                 fitted to the differences between the four tiles on 2082 searches, so only its differences mean anything; its
-//                 pick is 0.2 % behind the best tile, 5 % at most.)  The rows of 192 x 256, 128 x 128 and 64 x 128 are fitted to
-//                 8300 and 1300 launches of 1507 shapes of their own (2 to 4 % rms; 3 to 5 % below 8 k-steps).
+//                 pick is 0.2 % behind the best tile, 5 % at most.)  The rows of 192 x 256, 128 x 128 and 64 x 128, and from 8 k-steps on
+//                 all of the per-channel (but 128 x 512) and biased ones, are fitted to 30000 launches of 3457 shapes of their own
+//                 (2 to 4 % rms; 3 to 5 % below 8 k-steps); 2 % stand on rounds and rest of the per-channel 128 x 128 and 64 x 128, whose
+//                 wrong choice costs more than the larger tiles' (up to 20 % on M = 309, K = 6656, N = 16432).
 //   short_tile[]  the same below short_ksteps k-steps, where the filling of the ring and the epilogue make up most of a tile, with a
 //                 last round that costs its own time whatever T:  x <= 1: fixed + per_round x + T (alone (1 - x) + full x);
 //                 x > 1: fixed + per_round x + T rounds x + [f > 0] rest (1 - f).  5 % rms (7 to 9 % in the other form; with the
@@ -113,9 +115,8 @@ static size_t split_bytes(int64_t M, int64_t N) {
 //                 whole rounds over x, R the row tiles,  base + per_wg x R + g (w (a + b R) + c M).  5 to 9 % rms.
 //   sliced[]      the same where a narrow layer's K is cut into S slices:  base + rows R + K / (1000 S) (step + step_rows R) +
 //                 slice S + c g M.  7 to 11 % rms.  (M = 30, K = 58240, N = 16: 5.6 us sliced, 30 in the prefill kernels.)
-// On 995 other shapes of the first kind (four conversions each) the pick is 0.8 % behind the best forced choice on average, 8 % in
-// one of a hundred, 19 % at most (saturating calls of 17..32 rows that stay with the decode kernel for too long); on 464 of the
-// second kind 1.4, 13 and 47 % (K = 256, N = 34432, M = 24: 8.2 us for 5.6).
+// On 724 other shapes of the first kind (four conversions each) the pick is 0.7 % behind the best forced choice on average, 6 % in
+// one of a hundred, 12 % at most; on 166 of the second kind 1.1, 11 and 19 %.
 // Tests time the automatic pick against every forced pick on small grids (10 and 15 % bars).
 enum CostClass : int { kCostChannel, kCostBias, kCostFma, kCostReal, kCostClamp, kCostLoss, kCostClasses };
 static int cost_class(int mode) {
@@ -137,18 +138,18 @@ static const struct DispatchModel {
   TileCost tile[kCostClasses][7] = {
       {  // per-channel
           {0, 128, 512, 0.866, 1.409, 1.244, 1.272, -4.0, 12.5},
-          {2, 192, 256, 0.672, 1.131, 0.991, 0.995, -2.0, 9.4},
-          {3, 128, 256, 0.490, 0.787, 0.705, 0.710, -1.4, 7.2},
-          {4, 128, 128, 0.364, 0.484, 0.400, 0.339, 2.1, 3.3},
-          {5, 64, 128, 0.241, 0.314, 0.240, 0.166, 3.0, 1.6},
+          {2, 192, 256, 0.672, 1.067, 0.976, 1.002, -1.5, 9.0},
+          {3, 128, 256, 0.484, 0.752, 0.691, 0.736, -0.8, 6.8},
+          {4, 128, 128, 0.351, 0.491, 0.421, 0.320, 2.6, 2.8},
+          {5, 64, 128, 0.240, 0.320, 0.253, 0.156, 3.4, 1.2},
           {kPersistent, 128, 512, 0.968, 1.492, 1.380, 1.229, 0.9, 6.9}},
       {  // biased integer (with its pre-pass)
-          {0, 128, 512, 1.152, 1.693, 1.517, 1.677, -2.6, 15.9},
-          {1, 256, 256, 1.053, 1.604, 1.438, 1.622, -2.7, 16.1},
-          {2, 192, 256, 0.847, 1.327, 1.154, 1.225, -0.3, 12.3},
-          {3, 128, 256, 0.644, 0.999, 0.857, 0.940, 1.0, 8.9},
-          {4, 128, 128, 0.446, 0.641, 0.485, 0.404, 5.0, 4.0},
-          {5, 64, 128, 0.350, 0.482, 0.304, 0.283, 6.5, 1.6},
+          {0, 128, 512, 1.140, 1.686, 1.498, 1.676, -1.9, 15.4},
+          {1, 256, 256, 1.043, 1.592, 1.422, 1.591, -1.6, 15.4},
+          {2, 192, 256, 0.842, 1.277, 1.151, 1.233, 0.9, 11.3},
+          {3, 128, 256, 0.633, 0.970, 0.842, 0.983, 1.8, 8.4},
+          {4, 128, 128, 0.439, 0.641, 0.506, 0.380, 5.8, 3.3},
+          {5, 64, 128, 0.344, 0.483, 0.320, 0.259, 7.0, 1.2},
           {kPersistent, 128, 512, 1.228, 1.717, 1.599, 1.635, 2.1, 11.3}},
       {  // fp16 FMA
           {0, 128, 512, 1.717, 2.148, 2.074, 2.122, -4.4, 13.7},
@@ -156,7 +157,7 @@ static const struct DispatchModel {
           {2, 192, 256, 1.052, 1.447, 1.381, 1.319, -1.6, 9.5},
           {3, 128, 256, 0.885, 1.146, 1.073, 1.080, -1.3, 7.6},
           {4, 128, 128, 0.572, 0.695, 0.561, 0.477, 2.6, 3.0},
-          {5, 64, 128, 0.464, 0.548, 0.391, 0.405, 3.8, 1.0},
+          {5, 64, 128, 0.439, 0.540, 0.392, 0.366, 4.0, 0.7},
           {kPersistent, 128, 512, 1.704, 2.111, 2.087, 1.942, 0.2, 7.6}},
       {  // real-valued scale
           {0, 128, 512, 1.879, 2.220, 2.110, 2.285, -3.7, 13.0},
@@ -171,7 +172,7 @@ static const struct DispatchModel {
           {2, 192, 256, 1.536, 1.775, 1.624, 1.857, -1.6, 9.8},
           {3, 128, 256, 1.355, 1.564, 1.426, 1.659, -0.9, 7.6},
           {4, 128, 128, 0.783, 0.907, 0.697, 0.773, 3.4, 2.4},
-          {5, 64, 128, 0.702, 0.784, 0.602, 0.721, 4.5, 0.6},
+          {5, 64, 128, 0.698, 0.780, 0.599, 0.689, 4.3, 0.5},
           {kPersistent, 128, 512, 2.720, 2.961, 2.840, 2.993, 0.9, 7.0}},
       {  // per-channel with the smoothing search's loss for an epilogue
           {0, 128, 512, 1.241, 1.263, 1.603, 2.400, -0.4, 12.4},
@@ -200,7 +201,7 @@ static const struct DispatchModel {
           {2, 192, 256, 1.194, 1.149, 1.720, 4.806, 6.0, 4.7},
           {3, 128, 256, 1.011, 0.743, 1.201, 4.662, 4.8, 4.1},
           {4, 128, 128, 0.619, 0.642, 0.661, 1.047, 4.7, 2.0},
-          {5, 64, 128, 0.486, 0.631, 0.429, 1.121, 4.1, 0.9},
+          {5, 64, 128, 0.477, 0.594, 0.363, 1.235, 3.8, 0.9},
           {kPersistent, 128, 512, 1.625, 0.686, 1.302, 7.576, 7.2, 7.7}},
       {  // real-valued scale
           {0, 128, 512, 2.105, 1.642, 2.494, 7.697, 7.0, 6.9},
@@ -215,7 +216,7 @@ static const struct DispatchModel {
           {2, 192, 256, 1.682, 1.438, 2.017, 5.916, 6.2, 5.1},
           {3, 128, 256, 1.505, 1.184, 1.733, 5.759, 5.0, 4.2},
           {4, 128, 128, 0.842, 0.843, 0.753, 2.243, 4.8, 2.0},
-          {5, 64, 128, 0.723, 0.881, 0.615, 2.235, 4.2, 0.9},
+          {5, 64, 128, 0.727, 0.884, 0.582, 2.031, 3.8, 0.8},
           {kPersistent, 128, 512, 2.503, 1.467, 2.313, 9.922, 7.8, 7.8}}};
   double stream_tbs = 4.6, behind_stream = 0.1;
   double split_us = 2.05, split_part_us = 0.28, split_mint32_us = 1.33;
@@ -499,7 +500,7 @@ static bool takes_bias_route(int mode, int64_t M, int64_t N, int64_t K) {
 }
 
 // One launch that quantises and multiplies.  Every workgroup quantises all M rows for itself, which a
-// second launch (3.3-3.7 us) costs more than: always up to 8192 activations, up to 32768 with two or three
+// second launch (2.7-3.3 us) costs more than: always up to 8192 activations, up to 32768 with two or three
 // rows, and with four rows on the large layers only (measured on five layers: M=2 0.8-2.5 us ahead everywhere,
 // M=3 0.1-1.7 us; M=4 0.8 us ahead on 8192 x 28672, 0.2 us behind on the layers of 70 M weights and less).
 static bool fused_ok(int64_t M, int64_t N, int64_t K) {

@@ -356,6 +356,10 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_prefill_dma_kernel(const Gemm
     // step, behind MFMAs: all at once they hold a wave up at the address unit for as long as half a k-step's MFMAs.
     // (128 x 128 tiles, K = 8192, N = 4096, M = 128, per-channel: 27.2 us a launch, 32.4 with every request at the start and
     // fragments one step ahead; real-valued scales 45.6, 46.8; 64 x 128 20.8, 21.4.  Fragments spread evenly over the k-step: 27.8.)
+    // 64 x 128 tiles with the saturating and the fp16-FMA conversion keep all requests at the start and fragments one step ahead: two
+    // MFMAs a step leave no room for their conversion's instructions between the scheduling barriers (2-4 % slower with them over 1300
+    // shapes), nor does the real-valued scale's where several workgroups share a CU (three stages: 1-2 %; six: 2-4 % faster from K = 4096 on).
+    constexpr bool kSpread = TM > 2 || !(MODE == kGroupClamp || MODE == kGroupFused || MODE == kGroupFusedWide || (MODE == kGroupReal && ST == 3));
     v4i wq[TC][2];  // this lane's packed codes of the current k-step: [tile][piece]
     int sg[TC];       // and its group scales
     auto read_w = [&](const int8_t* sb) {
@@ -370,77 +374,127 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_prefill_dma_kernel(const Gemm
           sg[c] = (int)sb[sg_off + c * 32];
       }
     };
-    v4i f[4][TM], b[4][TC];  // fragments and converted codes of the MFMA steps
-    auto read_a = [&](const int8_t* sb, int s) {
+    if constexpr (kSpread) {
+      v4i f[4][TM], b[4][TC];  // fragments and converted codes of the MFMA steps
+      auto read_a = [&](const int8_t* sb, int s) {
 #pragma unroll
-      for (int mt = 0; mt < TM; ++mt) f[s][mt] = *(const v4i*)(sb + a_off[s] + mt * 4096);
-    };
-    // MFMA step s uses piece s%2, dword pair s/2 of the lane's packed codes
-    auto make_b = [&](int s) {
+        for (int mt = 0; mt < TM; ++mt) f[s][mt] = *(const v4i*)(sb + a_off[s] + mt * 4096);
+      };
+      // MFMA step s uses piece s%2, dword pair s/2 of the lane's packed codes
+      auto make_b = [&](int s) {
 #pragma unroll
-      for (int c = 0; c < TC; ++c) {
+        for (int c = 0; c < TC; ++c) {
+          const v4i pc = wq[c][s & 1];
+          const uint32_t d0 = (uint32_t)((s >> 1) ? pc[2] : pc[0]), d1 = (uint32_t)((s >> 1) ? pc[3] : pc[1]);
+          b[s][c] = convert_b<MODE>(d0, d1, sg[c]);
+        }
+      };
+      auto mfma_half = [&](int s, int half) {  // half of the row tiles
+#pragma unroll
+        for (int mt = half * TM / 2; mt < (half + 1) * TM / 2; ++mt)
+#pragma unroll
+          for (int c = 0; c < TC; ++c) mfma(f[s][mt], b[s][c], acc[mt][c]);
+      };
+      constexpr int kEarly = kDmaPerStep / 2;  // requests of a k-step that go out in the second half of the k-step before
+      auto dma_pieces = [&](int t, int stage, int from, int to) {
+#pragma unroll
+        for (int piece = from; piece < to; ++piece) issue_dma_piece(t < T ? t : T - 1, stage, piece);
+      };
+      read_w(lds);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) read_a(lds, s);
+      make_b(0);
+      dma_pieces(ST - 1, ST - 1, 0, kEarly);
+      for (int t = 0; t < T; ++t) {
+        // k-step t+ST-1 goes into the stage of k-step t-1, the first requests of k-step t+ST into this one's: every wave has read it
+        // all by the barrier
+        const int dstage = stage == 0 ? ST - 1 : stage - 1;
+        constexpr int kMid = kEarly + (kDmaPerStep - kEarly + 1) / 2;
+        mfma_half(0, 0);
+        make_b(1);
+        dma_pieces(t + ST - 1, dstage, kEarly, kMid);
+        __builtin_amdgcn_sched_barrier(0);
+        mfma_half(0, 1);
+        make_b(2);
+        __builtin_amdgcn_sched_barrier(0);
+        mfma_half(1, 0);
+        make_b(3);
+        dma_pieces(t + ST - 1, dstage, kMid, kDmaPerStep);
+        __builtin_amdgcn_sched_barrier(0);
+        mfma_half(1, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        // my DMA of k-step t+1 has landed (only the loads of the k-steps after it may still be in
+        // flight), my LDS reads of this stage are done; then everyone's
+        wait_all_but_newest_step();
+        const int nstage = (stage == ST - 1) ? 0 : stage + 1;
+        const int8_t* nb = lds + nstage * S::kStage;  // (stale data after the last k-step: read, never used)
+        read_w(nb);
+        read_a(nb, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        mfma_half(2, 0);
+        read_a(nb, 1);
+        dma_pieces(t + ST, stage, 0, kEarly / 2);
+        __builtin_amdgcn_sched_barrier(0);
+        mfma_half(2, 1);
+        read_a(nb, 2);
+        __builtin_amdgcn_sched_barrier(0);
+        mfma_half(3, 0);
+        dma_pieces(t + ST, stage, kEarly / 2, kEarly);
+        __builtin_amdgcn_sched_barrier(0);
+        mfma_half(3, 1);
+        make_b(0);
+        read_a(nb, 3);
+        __builtin_amdgcn_sched_barrier(0);
+        stage = nstage;
+      }
+    } else {
+      auto read_a = [&](v4i (&a)[TM], const int8_t* sb, int s) {
+#pragma unroll
+        for (int mt = 0; mt < TM; ++mt) a[mt] = *(const v4i*)(sb + a_off[s] + mt * 4096);
+      };
+      // MFMA step s uses piece s%2, dword pair s/2 of the lane's packed codes
+      auto make_b = [&](int c, int s) {
         const v4i pc = wq[c][s & 1];
         const uint32_t d0 = (uint32_t)((s >> 1) ? pc[2] : pc[0]), d1 = (uint32_t)((s >> 1) ? pc[3] : pc[1]);
-        b[s][c] = convert_b<MODE>(d0, d1, sg[c]);
+        return convert_b<MODE>(d0, d1, sg[c]);
+      };
+      auto mfma_col = [&](const v4i (&a)[TM], const v4i b, int c) {
+#pragma unroll
+        for (int mt = 0; mt < TM; ++mt) mfma(a[mt], b, acc[mt][c]);
+      };
+      auto mfma_step = [&](const v4i (&a)[TM], int s) {
+#pragma unroll
+        for (int c = 0; c < TC; ++c) mfma_col(a, make_b(c, s), c);
+      };
+      v4i a0[TM], a1[TM];
+      read_w(lds);
+      read_a(a0, lds, 0);
+      for (int t = 0; t < T; ++t) {
+        // k-step t+ST-1 goes into the stage that was read during k-step t-1 (everyone is past the
+        // barrier inside it)
+        issue_dma(t + ST - 1 < T ? t + ST - 1 : T - 1, stage == 0 ? ST - 1 : stage - 1);
+        const int8_t* sb = lds + stage * S::kStage;
+        read_a(a1, sb, 1);
+        mfma_step(a0, 0);
+        read_a(a0, sb, 2);
+        mfma_step(a1, 1);
+        read_a(a1, sb, 3);
+        mfma_step(a0, 2);
+        v4i b3[TC];
+#pragma unroll
+        for (int c = 0; c < TC; ++c) b3[c] = make_b(c, 3);
+        // my DMA of k-step t+1 has landed (only the loads of the k-steps after it may still be in
+        // flight), my LDS reads of this stage are done; then everyone's
+        wait_all_but_newest_step();
+        stage = (stage == ST - 1) ? 0 : stage + 1;
+        // first LDS reads of k-step t+1 (stale data after the last k-step: read, never used) ...
+        const int8_t* nb = lds + stage * S::kStage;
+        read_a(a0, nb, 0);
+        read_w(nb);
+        // ... in flight behind the last MFMA step of k-step t
+#pragma unroll
+        for (int c = 0; c < TC; ++c) mfma_col(a1, b3[c], c);
       }
-    };
-    auto mfma_half = [&](int s, int half) {  // half of the row tiles
-#pragma unroll
-      for (int mt = half * TM / 2; mt < (half + 1) * TM / 2; ++mt)
-#pragma unroll
-        for (int c = 0; c < TC; ++c) mfma(f[s][mt], b[s][c], acc[mt][c]);
-    };
-    constexpr int kEarly = kDmaPerStep / 2;  // requests of a k-step that go out in the second half of the k-step before
-    auto dma_pieces = [&](int t, int stage, int from, int to) {
-#pragma unroll
-      for (int piece = from; piece < to; ++piece) issue_dma_piece(t < T ? t : T - 1, stage, piece);
-    };
-    read_w(lds);
-#pragma unroll
-    for (int s = 0; s < 4; ++s) read_a(lds, s);
-    make_b(0);
-    dma_pieces(ST - 1, ST - 1, 0, kEarly);
-    for (int t = 0; t < T; ++t) {
-      // k-step t+ST-1 goes into the stage of k-step t-1, the first requests of k-step t+ST into this one's: every wave has read it
-      // all by the barrier
-      const int dstage = stage == 0 ? ST - 1 : stage - 1;
-      constexpr int kMid = kEarly + (kDmaPerStep - kEarly + 1) / 2;
-      mfma_half(0, 0);
-      make_b(1);
-      dma_pieces(t + ST - 1, dstage, kEarly, kMid);
-      __builtin_amdgcn_sched_barrier(0);
-      mfma_half(0, 1);
-      make_b(2);
-      __builtin_amdgcn_sched_barrier(0);
-      mfma_half(1, 0);
-      make_b(3);
-      dma_pieces(t + ST - 1, dstage, kMid, kDmaPerStep);
-      __builtin_amdgcn_sched_barrier(0);
-      mfma_half(1, 1);
-      __builtin_amdgcn_sched_barrier(0);
-      // my DMA of k-step t+1 has landed (only the loads of the k-steps after it may still be in
-      // flight), my LDS reads of this stage are done; then everyone's
-      wait_all_but_newest_step();
-      const int nstage = (stage == ST - 1) ? 0 : stage + 1;
-      const int8_t* nb = lds + nstage * S::kStage;  // (stale data after the last k-step: read, never used)
-      read_w(nb);
-      read_a(nb, 0);
-      __builtin_amdgcn_sched_barrier(0);
-      mfma_half(2, 0);
-      read_a(nb, 1);
-      dma_pieces(t + ST, stage, 0, kEarly / 2);
-      __builtin_amdgcn_sched_barrier(0);
-      mfma_half(2, 1);
-      read_a(nb, 2);
-      __builtin_amdgcn_sched_barrier(0);
-      mfma_half(3, 0);
-      dma_pieces(t + ST, stage, kEarly / 2, kEarly);
-      __builtin_amdgcn_sched_barrier(0);
-      mfma_half(3, 1);
-      make_b(0);
-      read_a(nb, 3);
-      __builtin_amdgcn_sched_barrier(0);
-      stage = nstage;
     }
   }
   // the clamped DMA requests of the last two k-steps may still be landing in the ring: every wave waits for its
