@@ -2,6 +2,8 @@
 #include "qqq_calib.h"
 #include "qqq_internal.h"
 
+#include <type_traits>
+
 #pragma clang fp contract(off)
 
 namespace qqq {
@@ -125,11 +127,12 @@ __global__ __launch_bounds__(256, 4) void hessian_kernel(const _Float16* x, int6
 // The same sums on the int8 matrix cores, exactly.  An fp16 value is an integer multiple of 2^-24; below 127.5 in magnitude that
 // integer is four digits d_p of base 256, each in [-128, 127], so that
 //     sum x y = 2^-48 sum_L 256^L T_L,   T_L = sum over tokens and p + q = L of d_p(x) d_q(y),  L = 0 .. 6:
-// sixteen int8 products whose int32 sums are exact (|T_L| <= 2^16 M, M <= kMaxTokens), put together in 64-bit integers and rounded to
+// sixteen int8 products whose int32 sums are exact (|T_L| <= 5 * 2^14 M, M <= kMaxTokens), put together in 64-bit integers and rounded to
 // fp64 once.  (The fp64 products round whenever the running sum outgrows 53 bits.)  Sixteen of 5 POP/s nominal are four times
-// the fp64 matrix cores' 78.6 TFLOP/s.  A tile whose columns hold a larger magnitude, an infinity or a NaN is done by hessian_tile
-// instead, from the stage on that shows it: a channel that is large throughout costs its tiles one stage, one large value in the last
-// tokens of every channel would make the launch half as long again as the fp64 products alone.
+// the fp64 matrix cores' 78.6 TFLOP/s.
+// Larger values: from the stage on that shows one, a tile takes five digits (enough below 32640; twenty-five products, L = 0 .. 8), on top
+// of the sums that it has, so nothing is done twice, wherever in the tokens they stand.  Only a value from 32640 on, an infinity or a NaN has
+// its tiles done by hessian_tile, from the first token.
 // Tile: 64 x 64 of H by 4 waves, 32 x 32 each: seven levels of a 32 x 32 accumulator are 112 registers, so a CU takes two
 // workgroups, one splitting while the other multiplies.  A stage is 64 tokens: every thread takes 4 tokens of 4 channels twice, splits
 // them (an fp16 value times 2^24 is exact in fp32; adding 0x808080 makes the bytes of the integer the digits plus 128) and stores the
@@ -140,8 +143,11 @@ __global__ __launch_bounds__(256, 4) void hessian_kernel(const _Float16* x, int6
 // past M the compiler waited for all requests at once.
 // Bound: 32 MFMAs of 32 clocks and 242 vector instructions of 4 a wave and stage, two waves on a SIMD; without the split a launch takes
 // 174 us of the 270, so products and split overlap little.  [M, K] = [2048, 4096]: 271 us (hessian_kernel 680), [1111, 2048]: 58 (134),
-// [2048, 1024]: 39 (74), [300, 1024]: 12.5 (15.4).
+// [2048, 1024]: 41 (74), [300, 1024]: 13.4 (16.5).  With large values, [2048, 4096], hessian_kernel 680: in 0.2, 1 and 5 % of the channels 314, 366
+// and 410 us, everywhere 406, in the last token of every channel 299; [2048, 1024], hessian_kernel 75: 62 and in the last token 46.
+// (hessian_tile from the stage on that shows one, as for infinities: 442, 606, 706, 706, 932; 101 and 132.)
 constexpr int kMaxTokens = 16384;
+constexpr int kFour = 0x57F8, kFive = 0x77F8;  // fp16 bits of 127.5 and 32640: what four and five digits hold lies below
 
 __global__ __launch_bounds__(256, 2) void hessian_digits_kernel(const _Float16* x, int M, int K, double* H) {
   constexpr int kPlane = 128 * 64 + 8 * 64, kStage = 4 * kPlane;  // channel c at 64 (c + c / 16)
@@ -149,12 +155,12 @@ __global__ __launch_bounds__(256, 2) void hessian_digits_kernel(const _Float16* 
     int8_t d[2 * kStage];
     TileStage<64> tile;
   } sm;
-  __shared__ int s_large[2];
+  __shared__ int s_large[2], s_over[2];  // the stage in buffer 0 / 1 of sm.d holds a value from 127.5 on, from 32640 on
   const Pair t = triangle_pair(blockIdx.x);
   const int r0 = t.p * 64, c0 = t.q * 64;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, kb = lane >> 4, wr = wave >> 1, wc = wave & 1;
-  if (tid < 2) s_large[tid] = 0;
+  if (tid < 2) s_large[tid] = s_over[tid] = 0;
 
   // what this thread splits: for two of a stage's four 16-byte slots (16 tokens) 4 tokens, 4 kb .., of channels 4 l16 .. of the tile's
   // rows (waves 0, 1) or columns (2, 3)
@@ -174,14 +180,17 @@ __global__ __launch_bounds__(256, 2) void hessian_digits_kernel(const _Float16* 
   };
   typedef unsigned short us2 __attribute__((ext_vector_type(2)));
   us2 top = {0, 0};  // largest magnitude seen, as bits
-  auto split = [&](int i, int pair, int8_t* to) {  // channels 2 pair, 2 pair + 1 of the four
+  // Channels 2 pair, 2 pair + 1 of the four.  From 128 on, and for infinities and NaN, the conversion leaves the range of int (in five digits:
+  // infinities and NaN); this relies on v_cvt_i32_f32 giving some integer there.  Which does not matter: its products are taken off
+  // again or thrown away
+  auto split = [&](int i, int pair, int8_t* to) {
     uint32_t m[2][4];  // the integers + 0x808080
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const uint32_t two = pair ? raw[i][j][1] : raw[i][j][0];
       top = __builtin_elementwise_max(top, __builtin_bit_cast(us2, two & 0x7FFF7FFFu));
-      m[0][j] = (uint32_t)((int)__builtin_fmaf(half_bits_to_float(two & 0xFFFFu), 16777216.0f, 0.0f) + 0x808080);
-      m[1][j] = (uint32_t)((int)__builtin_fmaf(half_bits_to_float(two >> 16), 16777216.0f, 0.0f) + 0x808080);
+      m[0][j] = (uint32_t)(int)__builtin_fmaf(half_bits_to_float(two & 0xFFFFu), 16777216.0f, 0.0f) + 0x808080u;
+      m[1][j] = (uint32_t)(int)__builtin_fmaf(half_bits_to_float(two >> 16), 16777216.0f, 0.0f) + 0x808080u;
     }
     int8_t* at = to + store0 + (((slot0 + i) ^ turn) << 4);
 #pragma unroll
@@ -196,7 +205,47 @@ __global__ __launch_bounds__(256, 2) void hessian_digits_kernel(const _Float16* 
     }
   };
 
-  v16i acc[7];
+  // Five digits, in stages of 32 tokens (two stages of five planes fit where two of 64 tokens and four do): 4 tokens, 4 kb .., of slot wave % 2.
+  // Adding 1.5 * 2^23 rounds x to a whole number, which then stands in the sum's low bits: the upper two digits come from it (128 added) and the carry
+  // of the lower three, those from 2^24 times what is left of x (at most 2^23; kMagic's part taken out by one multiply-add), all exact.
+  // 32 bytes left free after 16 channels, slots XOR-swizzled by (channel / 8) % 2: all banks once, as above
+  constexpr int kPlane5 = kPlane / 2, kStage5 = 5 * kPlane5;
+  const int store5 = (row0 + row0 / 16) * 32 + 4 * kb + (((wave & 1) ^ ((l16 >> 1) & 1)) << 4);
+  auto request5 = [&](int i) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) raw[i][j] = __builtin_amdgcn_raw_buffer_load_b64(rows, at0 + j * row_bytes, 0, 0);
+    at0 += 32 * row_bytes;
+  };
+  auto split5 = [&](int i, int pair, int8_t* to) {
+    uint32_t lo[2][4], hi[2][4];  // the lower integer + 0x808080; the upper + 0x80 in the low half
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t two = pair ? raw[i][j][1] : raw[i][j][0];
+      top = __builtin_elementwise_max(top, __builtin_bit_cast(us2, two & 0x7FFF7FFFu));
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        constexpr float kMagic = 12582912.0f + 128.0f;
+        const float v = half_bits_to_float(e ? two >> 16 : two & 0xFFFFu), t = __builtin_fmaf(v, 1.0f, kMagic);
+        const float left = __builtin_fmaf(v, 16777216.0f, __builtin_fmaf(t, -16777216.0f, kMagic * 16777216.0f));
+        lo[e][j] = (uint32_t)(int)left + 0x808080u;
+        hi[e][j] = __builtin_bit_cast(uint32_t, t) + (lo[e][j] >> 24);
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      auto bytes = [](const uint32_t (&w)[4], uint32_t select) {  // two bytes of each of the four words, byte by byte
+        return make_uint2(__builtin_amdgcn_perm(w[1], w[0], select), __builtin_amdgcn_perm(w[3], w[2], select));
+      };
+      const uint2 l01 = bytes(lo[e], 0x05010400u), l2 = bytes(lo[e], 0x07030602u), h = bytes(hi[e], 0x05010400u);
+      const uint32_t digit[5] = {__builtin_amdgcn_perm(l01.y, l01.x, 0x05040100u) ^ 0x80808080u, __builtin_amdgcn_perm(l01.y, l01.x, 0x07060302u) ^ 0x80808080u,
+                                 __builtin_amdgcn_perm(l2.y, l2.x, 0x05040100u) ^ 0x80808080u, __builtin_amdgcn_perm(h.y, h.x, 0x05040100u) ^ 0x80808080u,
+                                 __builtin_amdgcn_perm(h.y, h.x, 0x07060302u)};
+#pragma unroll
+      for (int p = 0; p < 5; ++p) *reinterpret_cast<uint32_t*>(to + store5 + p * kPlane5 + 32 * (2 * pair + e)) = digit[p];
+    }
+  };
+
+  v16i acc[9];
 #pragma unroll
   for (int l = 0; l < 7; ++l)
 #pragma unroll
@@ -208,6 +257,7 @@ __global__ __launch_bounds__(256, 2) void hessian_digits_kernel(const _Float16* 
 
   request(0);
   request(1);
+  __syncthreads();  // (s_large and s_over are zero)
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     split(i, 0, sm.d);
@@ -216,12 +266,16 @@ __global__ __launch_bounds__(256, 2) void hessian_digits_kernel(const _Float16* 
     request(i);
     __builtin_amdgcn_sched_barrier(0);
   }
+  auto shown = [&](int limit) { return max((int)top[0], (int)top[1]) >= limit; };
+  if (shown(kFour)) s_large[0] = 1;
   __syncthreads();
-  int stage = 0;
-  for (int m0 = 0; m0 < M; m0 += 64) {
+  int stage = 0, m0 = 0;
+  const int at_once = __builtin_amdgcn_readfirstlane(s_large[0]);
+  int large = at_once;
+  for (; (m0 < M) & !large; m0 += 64) {
     const int8_t* s = sm.d + stage * kStage;
     int8_t* next = sm.d + (stage ^ 1) * kStage;  // (behind the last stage: zeros, not used)
-    const int large = s_large[stage ^ 1];  // (set before the last barrier, not in this stage: all waves read alike)
+    const int flag = s_large[stage];  // (set before the last barrier, and not again in this stage: all waves read alike)
     v4i a[2], b[2][4];
     auto read_a = [&](int g) { a[g & 1] = *reinterpret_cast<const v4i*>(s + (g & 3) * kPlane + fa + fk[g >> 2]); };
     auto read_b = [&](int k, int q) { b[k][q] = *reinterpret_cast<const v4i*>(s + q * kPlane + fb + fk[k]); };
@@ -245,23 +299,102 @@ __global__ __launch_bounds__(256, 2) void hessian_digits_kernel(const _Float16* 
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    if (max((int)top[0], (int)top[1]) >= 0x57F8) s_large[stage] = 1;  // 127.5
+    if (shown(kFour)) s_large[stage ^ 1] = 1;
+    large = __builtin_amdgcn_readfirstlane(flag);
     __syncthreads();
-    if (large) break;
     stage ^= 1;
   }
-  if (s_large[0] | s_large[1]) {  // (uniform)
-    hessian_tile<64, true>(x, M, K, H, t.p, t.q, sm.tile);
-    return;
+  const bool five = large;  // (uniform)
+  if (five) {
+    if (!at_once) m0 -= 64, stage ^= 1;
+#pragma unroll
+    for (int l = 7; l < 9; ++l)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[l][v] = 0;
+    // That stage's digits are none of its values', and it was multiplied before the flag had come (waiting for the flag took 1 to 5 % longer
+    // where nothing is large): its products off again, as -a b = ~a b + b
+    const int8_t* s = sm.d + stage * kStage;
+    if (!at_once)
+#pragma unroll
+    for (int g = 0; g < 8; ++g) {
+      const v4i a = ~*reinterpret_cast<const v4i*>(s + (g & 3) * kPlane + fa + fk[g >> 2]);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const v4i b = *reinterpret_cast<const v4i*>(s + q * kPlane + fb + fk[g >> 2]);
+        acc[(g & 3) + q] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, acc[(g & 3) + q], 0, 0, 0);
+        acc[(g & 3) + q] = __builtin_amdgcn_mfma_i32_32x32x32_i8((v4i)0x01010101, b, acc[(g & 3) + q], 0, 0, 0);
+      }
+    }
+    const int fk5 = (l32 + l32 / 16) * 32 + ((half ^ ((l32 >> 3) & 1)) << 4);
+    int over = 0;
+    auto multiply = [&](auto buffer) {  // the stage in it, while the next is split into the other
+      constexpr int kThis = decltype(buffer)::value, kNext = kThis ^ 1;
+      const int8_t* s = sm.d + kThis * kStage5 + fk5;
+      over |= s_over[kThis];  // (set before the last barrier, and not again in this stage)
+      v4i a[2], b[5];
+      auto read_a = [&](int p) { a[p & 1] = *reinterpret_cast<const v4i*>(s + p * kPlane5 + fa / 2); };
+      read_a(0);
+#pragma unroll
+      for (int q = 0; q < 5; ++q) b[q] = *reinterpret_cast<const v4i*>(s + q * kPlane5 + fb / 2);
+#pragma unroll
+      for (int p = 0; p < 5; ++p) {
+        if (p < 4) read_a(p + 1);
+        if (p == 0 || p == 2) split5(kNext, p / 2, sm.d + kNext * kStage5);
+#pragma unroll
+        for (int q = 0; q < 5; ++q) acc[p + q] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[p & 1], b[q], acc[p + q], 0, 0, 0);
+        if (p & 1) {
+#pragma unroll
+          for (int n = 0; n < 10; ++n) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, 12, 0);
+          }
+          if (p == 3) request5(kNext);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      if (shown(kFive)) s_over[kNext] = 1;
+      __syncthreads();
+    };
+    at0 = (uint32_t)(m0 + 16 * (wave & 1) + 4 * kb) * row_bytes + 2u * channel;
+    request5(0);
+    request5(1);
+    __syncthreads();  // (every wave has read the buffers)
+    split5(0, 0, sm.d);
+    split5(0, 1, sm.d);
+    request5(0);
+    if (shown(kFive)) s_over[0] = 1;
+    __syncthreads();
+#pragma nounroll
+    for (; m0 < M && !__builtin_amdgcn_readfirstlane(over); m0 += 64) {  // (a way out between the two makes the compiler hold the sums twice)
+      multiply(std::integral_constant<int, 0>{});
+      multiply(std::integral_constant<int, 1>{});
+    }
+    if (__builtin_amdgcn_readfirstlane(over)) {  // (behind a barrier)
+      hessian_tile<64, true>(x, M, K, H, t.p, t.q, sm.tile);
+      return;
+    }
   }
-  // register v of a 32 x 32 tile is row 8 (v / 4) + 4 (lane / 32) + v % 4, column lane % 32
+  // register v of a 32 x 32 tile is row 8 (v / 4) + 4 (lane / 32) + v % 4, column lane % 32; the factor 2 * 2^-48 is exact
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
     int64_t lo = (int64_t)acc[0][v] + ((int64_t)acc[1][v] << 8) + ((int64_t)acc[2][v] << 16);
-    const int64_t hi = (int64_t)acc[3][v] + ((int64_t)acc[4][v] << 8) + ((int64_t)acc[5][v] << 16) + ((int64_t)acc[6][v] << 24) + (lo >> 24);
-    lo &= 0xFFFFFF;
-    // |hi| < 2^53: both are exact, so this rounds the sum once; the factor 2 * 2^-48 is exact
-    const double h = __builtin_fma((double)hi, 16777216.0, (double)lo) * 0x1p-47;
+    double h;
+    if (!five) {
+      const int64_t hi = (int64_t)acc[3][v] + ((int64_t)acc[4][v] << 8) + ((int64_t)acc[5][v] << 16) + ((int64_t)acc[6][v] << 24) + (lo >> 24);
+      lo &= 0xFFFFFF;
+      h = __builtin_fma((double)hi, 16777216.0, (double)lo) * 0x1p-47;  // |hi| < 2^53: both are exact, so this rounds the sum once
+    } else {
+      lo += (int64_t)acc[3][v] << 24;
+      const int64_t hi = (int64_t)acc[4][v] + ((int64_t)acc[5][v] << 8) + ((int64_t)acc[6][v] << 16) + ((int64_t)acc[7][v] << 24) +
+                         ((int64_t)acc[8][v] << 32) + (lo >> 32);
+      const uint64_t low = (uint32_t)lo;
+      // The sum is hi 2^32 + low, |hi| < 2^61.  Its 62 leading bits as an integer, the lowest of them set if anything below is: the
+      // conversion rounds that as it would the whole
+      const int shift = min(32, __builtin_clzll((uint64_t)(hi < 0 ? ~hi : hi) | 1) - 1);
+      const uint64_t rest = low << shift;
+      const int64_t lead = (int64_t)(((uint64_t)hi << shift) + (rest >> 32)) | ((uint32_t)rest != 0);
+      h = __builtin_ldexp((double)lead, -15 - shift);
+    }
     const int64_t gi = r0 + 32 * wr + 8 * (v >> 2) + 4 * half + (v & 3), gj = c0 + 32 * wc + l32;
     if (gi < K && gj < K) {
       H[gi * K + gj] = h;
@@ -286,10 +419,17 @@ int qqq_hessian(const void* x_fp16, int64_t M, int64_t K, double* H, void* strea
     return set_error(QQQ_ERR_SHAPE, "hessian: x must be 2-byte, H 8-byte aligned");
   auto tiles = [&](int64_t te) { const int64_t t = (K + te - 1) / te; return t * (t + 1) / 2; };
   // 64 x 64 tiles where they give every CU at least two, else 32 x 32
-  const bool wide = tiles(64) >= 2 * (int64_t)num_cus();
+  const int64_t cus = num_cus();
+  const bool wide = tiles(64) >= 2 * cus;
   const bool vec = K % 8 == 0 && (reinterpret_cast<uintptr_t>(x_fp16) & 15u) == 0;
-  // the digits where a CU in two has a 64 x 64 tile and a tile more than two stages: its time is at least that of a tile's stages
-  if (vec && M <= kMaxTokens && M >= 128 && tiles(64) >= num_cus() / 2) {
+  // Digits where a CU in two has a 64 x 64 tile, from so many stages of 64 tokens on that they gain at least about what large values in every
+  // channel can make them lose: more stages the fewer rounds of 32 x 32 tiles the fp64 products take.  us, fp64 / digits / digits with
+  // large values everywhere: K = 968 M = 640 20.8 17.5 25.2, M = 1024 30.0 23.3 34.4; K = 1024 M = 192 11.0 10.3 13.6, M = 256 13.1 11.2 15.3; K = 1280
+  // M = 128 11.0 10.6 12.9, M = 192 13.8 11.7 14.5; K = 1536 M = 256 19.2 17.3 21.8, M = 320 22.6 18.8 24.4; K = 2048 M = 96 18.9 19.3 24.2, M = 128
+  // 22.6 19.5 24.4; K = 4096 M = 128 53.6 44.4 57.6.
+  const int64_t rounds = (tiles(32) + cus - 1) / cus;
+  const int64_t stages = wide ? 2 : tiles(64) > cus ? 5 : rounds >= 4 ? 3 : rounds == 3 ? 4 : 16;
+  if (vec && M <= kMaxTokens && M >= 128 && (M + 63) / 64 >= stages && tiles(64) >= cus / 2) {
     hipLaunchKernelGGL(hessian_digits_kernel, dim3((unsigned)tiles(64)), dim3(256), 0, (hipStream_t)stream, (const _Float16*)x_fp16,
                        (int)M, (int)K, H);
     const hipError_t e = hipGetLastError();

@@ -157,10 +157,12 @@ def test_hessian_of_activations_that_are_no_numbers(K, at, value, percdamp):
         assert np.array_equal(codes_of(got[0], K), codes) and np.array_equal(f16_bits(got[1]), s_wg)
 
 
-@pytest.mark.parametrize("M,K,edge", [(128, 968, None), (193, 1032, 127.4375), (130, 1160, 127.5), (150, 1032, np.inf), (129, 968, np.nan)])
+@pytest.mark.parametrize("M,K,edge", [(128, 968, None), (193, 1032, 127.4375), (130, 1160, 127.5), (150, 1032, np.inf), (129, 968, np.nan),
+                                      (257, 1160, None), (200, 1288, 32640.0), (194, 1032, -np.inf), (321, 1160, np.nan)])
 def test_hessian_from_digits(M, K, edge):
     """The int8 products: sums of whole numbers, so every element is the exact sum rounded once.  Values over fp16's whole range
-    below 127.5, subnormal ones among them; from 127.5 on (one value of one channel here) its tiles take the fp64 products."""
+    below 127.5, subnormal ones among them.  Where one value of one channel is larger, its tiles are compared with fp64 products: from 32640 on
+    they are made of those.  (Shapes of up to two stages of tokens, and few of K = 968, are computed in fp64 throughout.)"""
     rng = np.random.default_rng(M + K)
     x = (rng.standard_normal((M, K)) * np.exp2(rng.integers(-22, 5, K))).astype(np.float16)
     x[rng.integers(0, M, 50), rng.integers(0, K, 50)] = np.float16(2.0 ** -24)
@@ -188,3 +190,68 @@ def test_hessian_from_digits(M, K, edge):
     s = (hi.T @ hi).astype(object) * 2 ** 24 + (hi.T @ lo + lo.T @ hi).astype(object) * 2 ** 12 + (lo.T @ lo).astype(object)
     want = s.astype(np.float64) * 2.0 ** -47   # int -> float rounds once, half to even
     assert np.array_equal(H[exact], want[exact])
+
+
+def exact_hessian(x):
+    """2 X^T X of finite fp16 values in whole numbers (multiples of 2^-48), rounded to fp64 once."""
+    m = (x.astype(np.float64) * 2.0 ** 24).astype(np.int64)
+    hi, lo = m >> 20, m & 0xFFFFF
+    s = (hi.T @ hi).astype(object) * 2 ** 40 + (hi.T @ lo + lo.T @ hi).astype(object) * 2 ** 20 + (lo.T @ lo).astype(object)
+    return s.astype(np.float64) * 2.0 ** -47
+
+
+@pytest.mark.parametrize("M,K,kind", [(449, 1032, "everywhere"), (256, 1160, "channels"), (450, 1032, "last token"),
+                                      (193, 1288, "one value"), (129, 2056, "bits"), (257, 1032, "bits"), (383, 1032, "middle")])
+def test_hessian_from_five_digits(M, K, kind):
+    """Values from 127.5 up to the last one below 32640: the sums go on with a fifth digit from where they stand, and stay exact."""
+    rng = np.random.default_rng(M + K)
+    x = (rng.standard_normal((M, K)) * np.exp2(rng.integers(-22, 5, K))).astype(np.float16)
+    if kind == "everywhere":
+        x = np.clip(x.astype(np.float32) * 2000, -32624, 32624).astype(np.float16)
+    elif kind == "channels":
+        x[:, 7], x[:, K // 2], x[:, K - 1] = 32624, -32624, x[:, K - 1] * np.float16(64) + np.float16(200)
+    elif kind == "last token":
+        x[M - 1, :] = rng.choice([-127.5, 127.5, 128, 999, -32624], K)
+    elif kind == "one value":
+        x[70, 100] = -127.5
+    elif kind == "middle":
+        x[130:200, :64] = -500.25
+    else:   # every finite magnitude below 32640 alike, subnormal ones among them
+        bits = rng.integers(0, 0x77F8, (M, K)).astype(np.uint16) | (rng.integers(0, 2, (M, K)) << 15).astype(np.uint16)
+        x = bits.view(np.float16)
+    H = qqq.qqq_hessian(torch.from_numpy(x).cuda()).cpu().numpy()
+    assert np.array_equal(H, exact_hessian(x))
+
+
+@pytest.mark.parametrize("M", [16384, 16385])
+@pytest.mark.parametrize("values", [[127.4375, -127.4375, 127.0, -2.0 ** -24], [32624.0, -32624.0, 127.5, 2.0 ** -24, -32512.0]])
+def test_hessian_at_the_token_limit(M, values):
+    """Channels that are constant at the ends of four and five digits, at the last token count of the int8 products' 32-bit sums and one past
+    it (fp64 products).  Every partial sum has at most 22 + 15 bits, so both are exact."""
+    K = 1032
+    c = np.resize(np.array(values), K)
+    x = torch.from_numpy(c.astype(np.float16)).cuda().repeat(M, 1)
+    H = qqq.qqq_hessian(x).cpu().numpy()
+    assert np.array_equal(H, 2.0 * M * np.outer(c, c))
+
+
+@pytest.mark.parametrize("share", [0.01, 1.0])
+def test_hessian_of_heavy_channels_is_no_slower_than_fp64(share):
+    """Large values in one channel of a hundred, and in all: 16384 tokens on the int8 products against 16385 on the fp64 ones."""
+    K = 1032
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randn((16385, K), generator=g, device="cuda").half()
+    x[:, torch.randperm(K, generator=g, device="cuda")[:max(1, int(K * share))]] *= 200
+    times = []
+    for rows in (x[:16384], x):
+        best = float("inf")
+        for _ in range(6):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            for _ in range(3):
+                qqq.qqq_hessian(rows)
+            e1.record()
+            torch.cuda.synchronize()
+            best = min(best, e0.elapsed_time(e1))
+        times.append(best)
+    assert times[0] < 1.1 * times[1], times
