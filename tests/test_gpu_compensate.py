@@ -158,7 +158,7 @@ def test_hessian_of_activations_that_are_no_numbers(K, at, value, percdamp):
 
 
 @pytest.mark.parametrize("M,K,edge", [(128, 968, None), (193, 1032, 127.4375), (130, 1160, 127.5), (150, 1032, np.inf), (129, 968, np.nan),
-                                      (257, 1160, None), (200, 1288, 32640.0), (194, 1032, -np.inf), (321, 1160, np.nan)])
+                                      (257, 1160, None), (200, 1288, 32640.0), (194, 1032, np.inf), (321, 1160, np.nan)])
 def test_hessian_from_digits(M, K, edge):
     """The int8 products: sums of whole numbers, so every element is the exact sum rounded once.  Values over fp16's whole range
     below 127.5, subnormal ones among them.  Where one value of one channel is larger, its tiles are compared with fp64 products: from 32640 on
