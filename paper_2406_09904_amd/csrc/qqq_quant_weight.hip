@@ -9,12 +9,14 @@
 // 2 B in, 0.5 B out per weight.
 #include "qqq_internal.h"
 
+#include <type_traits>
+
 namespace qqq {
 
 namespace {
 
 constexpr float kStarCap = 18.203125f;  // largest fp16 s with rne(7 * s) <= 127
-constexpr int kWaves = 4;               // waves per workgroup, one channel per wave at a time
+constexpr int kWaves = 4;               // waves, and channels, per workgroup of the per-group kernel
 
 __device__ __forceinline__ uint32_t row16_max_u32(uint32_t v) {  // max over a 16-lane row, in every lane
   v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false));
@@ -29,7 +31,6 @@ struct GroupOut {
   uint16_t* s_star;  // [G][N]
   int8_t* s_int;     // [G][N] or nullptr
   int G;
-  int rows_log2;     // channels per workgroup = 1 << rows_log2, at least kWaves
 };
 
 __device__ __forceinline__ uint32_t block_max(uint32_t v, uint32_t* smem) {
@@ -105,25 +106,32 @@ __global__ __launch_bounds__(256) void quant_weight_channel_kernel(const uint4* 
   }
 }
 
-// Per-group: one wave per channel at a time, `rows` channels per workgroup.  A group of 128 is 16
+// Per-group: one wave per channel, four channels per workgroup.  A group of 128 is 16
 // consecutive vectors, i.e. one 16-lane row of a wave, so its scale needs no memory of the rest of
 // the channel: the wave streams the row once, four vectors per lane at a time, and leaves the group
 // scales in LDS; the channel's s_Wc follows from a wave reduction at the end of the row.
 // The scale tables are [G][N]: one channel owns one element of every table row.  The workgroup's
-// LDS stage is [G][rows], and after a barrier the tables are written in runs of `rows` elements,
+// LDS stage is [G][kWaves], and after a barrier the tables are written in runs of four elements,
 // the division s_Wg / s_Wc being done there.  STAGED == false (a table too tall for LDS): the
 // wave reads its row a second time (from L2) and writes its table elements one by one.
+// Bound by memory at the largest (K = 8192, N = 28672: 131 us, 4.6 TB/s), below that by how many rows are in flight and the two latencies
+// a row exposes (K = 4096, N = 11008: 25.6 us, 4.5 TB/s; N = 4096: 11.8).  The range checks are only where a row ends
+// (per 2048 weights): with checks everywhere and eight channels a workgroup from N = 18432 on 131 was 137, 25.6 27.0, 11.8 12.9, and K = 11008, N = 6656
+// 49.3 us 53.1.  Four channels throughout: eight are 1 to 9 % slower from K = 4096 on (K = 8192, N = 8704: 45.4 us against 42.8), up to 8 % faster only
+// for rows of at most 2048 and N >= 12288, and leave the chip idle on narrow layers (K = 8192, N = 1024: 14.7 against 9.6).
+template <int V>
+using Count = std::integral_constant<int, V>;
+
 template <bool STAGED>
 __global__ __launch_bounds__(64 * kWaves) void quant_weight_group_kernel(const uint4* __restrict__ w,
                                                                          int64_t ldw_vec, int nvec, int64_t N,
                                                                          uint32_t* __restrict__ w_nat,
                                                                          uint16_t* __restrict__ s_wc,
                                                                          const GroupOut go) {
-  extern __shared__ uint16_t stage[];  // [G][rows] s_Wg bits, then [rows] s_Wc bits
+  extern __shared__ uint16_t stage[];  // [G][kWaves] s_Wg bits, then [kWaves] s_Wc bits
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int rows = 1 << go.rows_log2;
-  const int64_t n0 = (int64_t)blockIdx.x << go.rows_log2;
+  const int64_t n0 = (int64_t)blockIdx.x * kWaves;
   auto emit = [&](int64_t at, uint16_t wg_bits, float wc) {
     const float sg = half_bits_to_float(wg_bits);
     uint16_t star = 0;
@@ -135,26 +143,26 @@ __global__ __launch_bounds__(64 * kWaves) void quant_weight_group_kernel(const u
     if (go.s_wg) go.s_wg[at] = wg_bits;
     if (go.s_int) go.s_int[at] = (int8_t)fminf(fmaxf(__builtin_rintf(half_bits_to_float(star)), 1.0f), 18.0f);
   };
-  for (int r = wave; r < rows; r += kWaves) {
-    const int64_t n = n0 + r;
-    if (n >= N) break;
+  const int64_t n = n0 + wave;
+  const int cells = go.G * kWaves;
+  if (n < N) {
     const uint4* row = w + n * ldw_vec;
     uint32_t* out = w_nat + n * (int64_t)nvec;
     uint32_t dmax_bits = 0;  // bits of max |code * s_Wg|, a non-negative float
-#pragma unroll 1
-    for (int i0 = 0; i0 < nvec; i0 += 256) {
-      uint4 v[4];
+    // `count` 64s of vectors, the last of them not all there if they are the row's `rest`; all are requested before the first is looked at
+    auto vectors = [&](int i0, auto count, auto rest) {
+      constexpr int kCount = decltype(count)::value;
+      constexpr bool kRest = decltype(rest)::value;
+      uint4 v[kCount];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
+      for (int j = 0; j < kCount; ++j) {
         const int idx = i0 + 64 * j + lane;
-        v[j] = row[min(idx, nvec - 1)];  // (in range and unconditional: a load under its own condition waits for the one before)
+        v[j] = row[kRest ? min(idx, nvec - 1) : idx];  // (in range and unconditional: a load under its own condition waits for the one before)
       }
       __builtin_amdgcn_sched_barrier(0);
+      if (kRest && i0 + 64 * (kCount - 1) + lane >= nvec) v[kCount - 1] = make_uint4(0, 0, 0, 0);
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (i0 + 64 * j + lane >= nvec) v[j] = make_uint4(0, 0, 0, 0);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
+      for (int j = 0; j < kCount; ++j) {
         const int idx = i0 + 64 * j + lane;
         const uint32_t gmax = row16_max_u32(absmax_bits(v[j], 0));
         const uint16_t sgb = weight_scale_bits(half_bits_to_float(gmax));
@@ -162,17 +170,27 @@ __global__ __launch_bounds__(64 * kWaves) void quant_weight_group_kernel(const u
         float cmax = 0.0f;
         uint32_t codes = 0;
         if (sg != 0.0f) codes = quant8<false>(v[j], sg, __builtin_amdgcn_rcpf(sg), &cmax);
-        if (idx < nvec) out[idx] = codes;
+        if (!kRest || idx < nvec) out[idx] = codes;
         dmax_bits = max(dmax_bits, __builtin_bit_cast(uint32_t, cmax * sg));
         if constexpr (STAGED)
-          if ((lane & 15) == 0 && idx < nvec) stage[((idx >> 4) << go.rows_log2) + r] = sgb;
+          if ((lane & 15) == 0 && (!kRest || idx < nvec)) stage[(idx >> 4) * kWaves + wave] = sgb;
       }
+    };
+    int i0 = 0;
+#pragma unroll 1
+    for (; i0 + 256 <= nvec; i0 += 256) vectors(i0, Count<4>{}, std::false_type{});
+    switch ((nvec - i0 + 63) >> 6) {
+      case 1: vectors(i0, Count<1>{}, std::true_type{}); break;
+      case 2: vectors(i0, Count<2>{}, std::true_type{}); break;
+      case 3: vectors(i0, Count<3>{}, std::true_type{}); break;
+      case 4: vectors(i0, Count<4>{}, std::true_type{}); break;
+      default: break;
     }
     dmax_bits = wave_max_u32(dmax_bits);
     const uint16_t wcb = scale_bits(__builtin_bit_cast(float, dmax_bits), 127.0f);
     if (lane == 0) s_wc[n] = wcb;
     if constexpr (STAGED) {
-      if (lane == 0) stage[(go.G << go.rows_log2) + r] = wcb;
+      if (lane == 0) stage[cells + wave] = wcb;
     } else {
       const float wc = half_bits_to_float(wcb);
       for (int i0 = 0; i0 < nvec; i0 += 64) {  // the group maxima again, from L2
@@ -186,11 +204,9 @@ __global__ __launch_bounds__(64 * kWaves) void quant_weight_group_kernel(const u
   }
   if constexpr (STAGED) {
     __syncthreads();
-    const int cells = go.G << go.rows_log2;
     for (int c = threadIdx.x; c < cells; c += 64 * kWaves) {
-      const int r = c & (rows - 1);
-      if (n0 + r < N)
-        emit((int64_t)(c >> go.rows_log2) * N + n0 + r, stage[c], half_bits_to_float(stage[cells + r]));
+      const int r = c & (kWaves - 1);
+      if (n0 + r < N) emit((int64_t)(c / kWaves) * N + n0 + r, stage[c], half_bits_to_float(stage[cells + r]));
     }
   }
 }
@@ -219,21 +235,12 @@ int launch_quant_weight(const void* w, int64_t N, int64_t K, int64_t ldw, bool g
     go.s_star = s_star;
     go.s_int = s_int;
     go.G = (int)(K / QQQ_GROUP);
-    // channels per workgroup: as many as keep about nine workgroups per compute unit (K = 4096, N = 11008: 26.2 us with four
-    // channels, 27.0 with eight, four workgroups), at least one per wave and at most 32 (one 64-byte run of fp16 per table row), with a stage of at most 48 KB
-    auto stage_bytes = [&](int lg) { return (((size_t)go.G << lg) + ((size_t)1 << lg)) * 2; };
-    int lg = 5;
-    while (lg > 2 && (N >> lg) < 9 * (int64_t)num_cus()) --lg;
-    while (lg > 2 && stage_bytes(lg) > 48u * 1024u) --lg;
-    go.rows_log2 = lg;
-    const bool staged = stage_bytes(lg) <= 48u * 1024u;
-    const dim3 grid((unsigned)((N + (1 << lg) - 1) >> lg)), block(64 * kWaves);
-    if (staged)
-      hipLaunchKernelGGL((quant_weight_group_kernel<true>), grid, block, stage_bytes(lg), st, wp, ldw_vec, nvec, N,
-                         w_nat, s_ch, go);
+    const size_t stage = (size_t)(go.G + 1) * kWaves * 2;
+    const dim3 grid((unsigned)((N + kWaves - 1) / kWaves)), block(64 * kWaves);
+    if (stage <= 48u * 1024u)
+      hipLaunchKernelGGL((quant_weight_group_kernel<true>), grid, block, stage, st, wp, ldw_vec, nvec, N, w_nat, s_ch, go);
     else
-      hipLaunchKernelGGL((quant_weight_group_kernel<false>), grid, block, 0, st, wp, ldw_vec, nvec, N, w_nat,
-                         s_ch, go);
+      hipLaunchKernelGGL((quant_weight_group_kernel<false>), grid, block, 0, st, wp, ldw_vec, nvec, N, w_nat, s_ch, go);
   }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return set_error(QQQ_ERR_HIP, "quant_weight launch: %s", hipGetErrorString(e));

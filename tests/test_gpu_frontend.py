@@ -60,6 +60,14 @@ def test_pergroup_matches_oracle(N, K):
     check_pergroup(synth.weights_fp16(N, K, 200 + N))
 
 
+@pytest.mark.parametrize("N,K", [(1, 512), (5, 1408), (6, 1536), (7, 2048), (3, 2176), (2, 3968), (9, 4096),
+                                 (1, 785920), (2, 786432)])
+def test_pergroup_row_ends(N, K):
+    """One to four 64s of vectors after whole passes of 256 (the last 64 whole or not), none; channels that leave waves of the last
+    workgroup idle; the tallest scale table that LDS takes and the next."""
+    check_pergroup(synth.weights_fp16(N, K, 300 + N))
+
+
 def test_wide_dynamic_range_zero_blocks_and_tiny_channels():
     """Magnitudes from fp16 subnormals to thousands; all-zero channels and groups; channels so small
     that s_Wc is subnormal in fp16 (the cap on the fused scale may bind)."""
