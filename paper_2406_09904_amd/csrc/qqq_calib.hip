@@ -194,13 +194,18 @@ __global__ __launch_bounds__(256) void point_activations_kernel(const uint4* x, 
 // 16 output channels per workgroup (qqq_quantize_w4_perchannel on W .* s, then qqq_pack_w4): a wave takes four
 // channels one after the other, its lanes hold the row (K <= 4096: in registers, s with it; else the row is smoothed
 // twice, 4096 channels at a time), and the codes meet in LDS in the packed layout's order, so whole 1 KiB chunks are
-// written.  Bound by instructions, about 7 per weight and grid point: 6.3 us a grid point at K = N = 4096 (9.5 with the rounding, the
-// clamp and the nibbles in fp32 and converted products).  K <= 4096: the four channels are a loop (13 KB of code); beyond, they and
-// their vectors are written out (54 KB).
-template <bool ONE>
-__global__ __launch_bounds__(256) void point_weights_kernel(const uint4* w, const float* s, int64_t N, int kvec,
+// written.  About 7 instructions per weight and grid point, 3.2 us of the 6.3 that a grid point takes at K = N = 4096 (9.5 with the rounding,
+// the clamp and the nibbles in fp32 and converted products); what else bounds it there, where 176 registers leave two waves a SIMD, is open.
+// V: 64s of vectors of the row, a body of its own for each up to 8, so that short rows neither work on vectors that are not there nor hold
+// registers for them (one body of 8 for all: a search of 17 points at M = 64, K = 128, N = 8192 157 us, 88 now; 12 points at M = 128, K = 2048,
+// N = 4096 158, 142 now).  V = 0: any row, 8 at a time, in loops and 108 registers, four workgroups a CU (the channels written out, 142 registers and three
+// workgroups: 5 points at M = 100, K = 8192, N = 3088 277 us, 244 now).
+template <int V>
+__global__ __launch_bounds__(256, V ? 1 : 4) void point_weights_kernel(const uint4* w, const float* s, int64_t N, int kvec,
                                                             int64_t point_bytes, uint8_t* packed, uint16_t* s_w) {
-  __shared__ uint32_t stage[32 * 256];  // 32 k-steps of 1 KiB
+  constexpr bool ONE = V > 0;
+  constexpr int kV = ONE ? V : 8;
+  __shared__ uint32_t stage[4 * kV * 256];  // 1 KiB a k-step
   // the points of one group of channels run one after the other on the same XCD (workgroup ids go round the
   // eight of them), so its rows come from that XCD's L2 after the first
   const int64_t groups = N / 16;
@@ -220,11 +225,11 @@ __global__ __launch_bounds__(256) void point_weights_kernel(const uint4* w, cons
   const float* sv = (const float*)((const char*)s + off);
   uint32_t* out = (uint32_t*)(packed + off);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  [[maybe_unused]] float sc[4];
-  uint4 v[8];
+  __shared__ float scales[ONE ? 1 : 16];
+  uint4 v[kV];
   auto smooth_row = [&](const uint4* row, int i0) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
+    for (int j = 0; j < kV; ++j) {
       const int i = i0 + lane + 64 * j;
       v[j] = i < kvec ? smooth8<false, true>(row[i], sv + 8 * i) : make_uint4(0, 0, 0, 0);
     }
@@ -234,7 +239,7 @@ __global__ __launch_bounds__(256) void point_weights_kernel(const uint4* w, cons
     for (int i0 = 0; i0 < kvec; i0 += 512) {
       smooth_row(row, i0);
 #pragma unroll
-      for (int j = 0; j < 8; ++j) bits = absmax_bits(v[j], bits);
+      for (int j = 0; j < kV; ++j) bits = absmax_bits(v[j], bits);
     }
     const uint16_t sb = weight_scale_bits(half_bits_to_float(wave_max_u32(bits)));
     if (lane == 0) ((uint16_t*)((char*)s_w + off))[n] = sb;
@@ -247,7 +252,7 @@ __global__ __launch_bounds__(256) void point_weights_kernel(const uint4* w, cons
     const float rs = __builtin_amdgcn_rcpf(scale);
     float cmax;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
+    for (int j = 0; j < kV; ++j) {
       const int i = lane + 64 * j;
       if (i0 + i >= kvec) continue;
       const uint32_t word = scale != 0.0f ? quant8<true>(v[j], scale, rs, &cmax) : 0u;
@@ -265,16 +270,16 @@ __global__ __launch_bounds__(256) void point_weights_kernel(const uint4* w, cons
   };
   if constexpr (ONE) {
     // the lanes keep their part of s for the four channels, and request the next channel's weights before they work on one
-    float4 s0[8], s1[8];
-    uint4 next[8];
+    float4 s0[kV], s1[kV];
+    uint4 next[kV];
     auto request = [&](int q) {
       const uint4* row = w + (nt * 16 + 4 * wave + q) * kvec;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) next[j] = row[min(lane + 64 * j, kvec - 1)];
+      for (int j = 0; j < kV; ++j) next[j] = row[min(lane + 64 * j, kvec - 1)];
     };
     request(0);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
+    for (int j = 0; j < kV; ++j) {
       const float4* from = reinterpret_cast<const float4*>(sv) + 2 * min(lane + 64 * j, kvec - 1);
       s0[j] = from[0];
       s1[j] = from[1];
@@ -283,24 +288,24 @@ __global__ __launch_bounds__(256) void point_weights_kernel(const uint4* w, cons
     for (int q = 0; q < 4; ++q) {
       uint32_t bits = 0;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) v[j] = smooth8<false, true>(next[j], s0[j], s1[j]);
+      for (int j = 0; j < kV; ++j) v[j] = smooth8<false, true>(next[j], s0[j], s1[j]);
       request(min(q + 1, 3));
 #pragma unroll
-      for (int j = 0; j < 8; ++j) bits = absmax_bits(v[j], bits);  // (past the row's end its last vector again)
+      for (int j = 0; j < kV; ++j) bits = absmax_bits(v[j], bits);  // (past the row's end its last vector again)
       const uint16_t sb = weight_scale_bits(half_bits_to_float(wave_max_u32(bits)));
       if (lane == 0) ((uint16_t*)((char*)s_w + off))[nt * 16 + 4 * wave + q] = sb;
       put(4 * wave + q, half_bits_to_float(sb), 0);
     }
     flush(0);
   } else {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) sc[q] = scale_of_row((nt * 16 + 4 * wave + q), w + (nt * 16 + 4 * wave + q) * kvec);
+#pragma unroll 1
+    for (int q = 0; q < 4; ++q) scales[4 * wave + q] = scale_of_row((nt * 16 + 4 * wave + q), w + (nt * 16 + 4 * wave + q) * kvec);
     for (int i0 = 0; i0 < kvec; i0 += 512) {
-#pragma unroll
+#pragma unroll 1
       for (int q = 0; q < 4; ++q) {
         const int c = 4 * wave + q;
         smooth_row(w + (nt * 16 + c) * kvec, i0);
-        put(c, sc[q], i0);
+        put(c, scales[c], i0);
       }
       flush(i0);
     }
@@ -647,7 +652,10 @@ int qqq_adaptive_smoothing(const void* x_fp16, const void* w_fp16, int64_t M, in
     auto activations = K <= 8192 ? point_activations_kernel<true> : point_activations_kernel<false>;
     hipLaunchKernelGGL(activations, dim3((unsigned)M, points), dim3(256), 0, st, (const uint4*)x_fp16, s_point, kvec,
                        point_bytes, a_q, s_a);
-    auto weights = K <= 4096 ? point_weights_kernel<true> : point_weights_kernel<false>;
+    static constexpr decltype(&point_weights_kernel<0>) kWeights[9] = {
+        point_weights_kernel<0>, point_weights_kernel<1>, point_weights_kernel<2>, point_weights_kernel<3>, point_weights_kernel<4>,
+        point_weights_kernel<5>, point_weights_kernel<6>, point_weights_kernel<7>, point_weights_kernel<8>};
+    const auto weights = kWeights[K <= 4096 ? (K + 511) / 512 : 0];
     hipLaunchKernelGGL(weights, dim3((unsigned)(N / 16), points), dim3(256), 0, st, (const uint4*)w_fp16, s_point, N, kvec,
                        point_bytes, packed, s_w);
     if ((rc = check_launch("smoothing grid point")) != QQQ_OK) return rc;

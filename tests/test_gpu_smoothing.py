@@ -25,6 +25,9 @@ BY_STEPS = " + loss"                                     # after the last point'
     (300, 512, 2064, 9, "loss tile=128x256 points=9"), (300, 512, 4096, 21, "loss tile=128x256 points=21"),
     (700, 256, 2064, 40, "loss tile=128x128 points=25 + loss tile=128x128 points=15"),
     (500, 2944, 4080, 8, "loss tile=128x512 points=8"),
+    (5, 512, 48, 3, "loss tile=64x128 points=3"), (5, 640, 48, 3, "loss tile=64x128 points=3"), (5, 1024, 48, 3, "loss tile=64x128 points=3"),
+    (5, 1152, 144, 3, "loss tile=64x128 points=3"), (5, 2048, 48, 3, "loss tile=64x128 points=3"), (5, 2176, 48, 3, "loss tile=64x128 points=3"),
+    (5, 2688, 48, 3, "loss tile=64x128 points=3"), (5, 3200, 48, 3, "loss tile=64x128 points=3"), (5, 3968, 48, 3, "loss tile=64x128 points=3"),
     (19, 8320, 48, 2, BY_STEPS), (3, 16384, 16, 9, BY_STEPS), (130, 12416, 64, 5, BY_STEPS), (40, 6144, 256, 1, BY_STEPS)])
 def test_grid_points_equal_their_steps(M, K, N, G, route):
     x = torch.from_numpy(synth.activations_fp16(M, K, 700 + M, "normal", 4 / K, 40.0)).cuda()
