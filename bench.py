@@ -723,6 +723,18 @@ def ceilings(torch, qqq, synth):
     return out
 
 
+def stdout_line(out):
+    """The benchmark line without what makes it long: routes, spreads and oracle times of the other configuration points (about 1 KB
+    each).  All of it is on stderr, as one JSON line as well."""
+    line = dict(out)
+    if "sweep" in out:
+        line["sweep"] = [{"workload": l["workload"], "ms_per_step": l["ms_per_step"], "gemm_us": l["gemm_us"], "tops": l["tops"],
+                          "bound": l["roofline"]["bound"], "frac": l["roofline"]["frac"]} for l in out["sweep"]]
+    if out.get("cpu_baseline"):
+        line["cpu_baseline"] = {k: v for k, v in out["cpu_baseline"].items() if k != "per_workload"}
+    return line
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -836,7 +848,8 @@ def main():
         if "sweep" in out:
             for l in out["sweep"]:
                 l["oracle"] = out["cpu_baseline"]["per_workload"].get(l["workload"])
-    print(json.dumps(out), flush=True)
+    print("details " + json.dumps(out), file=sys.stderr, flush=True)
+    print(json.dumps(stdout_line(out)), flush=True)
     return 0
 
 
