@@ -94,7 +94,7 @@ def test_linear_pergroup(M, K, N, hi, sg_max):
     assert np.array_equal(acc, acc2) and np.array_equal(y, y2)
 
 
-@pytest.mark.parametrize("M,K,N", [(70, 1024, 512), (200, 384, 528), (130, 2560, 1040)])
+@pytest.mark.parametrize("M,K,N", [(70, 1024, 512), (200, 384, 528), (130, 2560, 1040), (256, 8320, 144), (257, 8320, 144)])
 @pytest.mark.parametrize("wide", [False, True])
 def test_linear_pergroup_biased_route_on_short_launches(M, K, N, wide):
     """The biased integer conversion forced where the automatic choice would skip its pre-pass: the

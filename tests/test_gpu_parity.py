@@ -75,7 +75,8 @@ def test_pack_unpack_roundtrip(N, K):
 
 # ----------------------------------------------------------------------------- quant_act
 @pytest.mark.parametrize("M,K", [(1, 128), (3, 4096), (16, 8192), (37, 5120), (5, 11008),
-                                 (2, 8), (4, 20000), (300, 1024)])
+                                 (2, 8), (4, 20000), (300, 1024),
+                                 (256, 4096), (257, 4096), (257, 5120), (257, 11008), (3, 8200), (3, 16376), (2, 16384)])
 def test_quant_act_bit_exact(M, K):
     a = synth.activations_fp16(M, K, 1000 + M + K)
     if M >= 3:
