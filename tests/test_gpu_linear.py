@@ -132,6 +132,19 @@ def test_linear_fused_large_prologue(M, K, N, pergroup):
     assert np.array_equal(acc, acc2) and np.array_equal(y, y2)
 
 
+def test_linear_fused_with_infinities_and_nan():
+    """Rows that hold no numbers: the decode kernel's own quantisation gives the codes of the quantiser's launch."""
+    M, K, N = 3, 1024, 64
+    a = synth.activations_fp16(M, K, 78)
+    a[0, 5], a[2, 9] = -np.inf, np.nan
+    w = synth.random_w_nat(N, K, 79)
+    s_w = synth.weight_scales_fp16(N, 80, 0.001, 0.01)
+    acc1, _ = run_linear(a, w, s_w, K, fused=1)
+    assert "fused=1" in qqq.last_route(), qqq.last_route()
+    acc0, _ = run_linear(a, w, s_w, K, fused=0)
+    assert np.array_equal(acc1, acc0)
+
+
 @pytest.mark.parametrize("group_mode", [1, 2, 3])
 def test_linear_fused_every_group_route(group_mode):
     M, K, N = 3, 2560, 336            # fused: 7680 activations

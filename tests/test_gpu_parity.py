@@ -90,6 +90,21 @@ def test_quant_act_bit_exact(M, K):
     assert np.array_equal(d_q.cpu().numpy(), o_q)
 
 
+@pytest.mark.parametrize("K", [128, 1024, 5120, 20000])
+def test_quant_act_of_infinities_and_nan(K):
+    """An infinite maximum: finite values give 0 and infinities the clamp's lower end; a NaN anywhere in the row: the lower end throughout.
+    (No oracle: the codes that the kernel's division gave.)"""
+    a = synth.activations_fp16(5, K, 3000 + K)
+    a[0, 3], a[1, K - 1], a[2, 7], a[3, 0], a[3, 1] = np.inf, -np.inf, np.nan, np.nan, np.inf
+    a_q, s_a = (t.cpu().numpy() for t in qqq.qqq_quant_act(to_dev(a.view(np.uint16), torch)))
+    want = np.zeros((4, K), np.int8)
+    want[0, 3], want[1, K - 1], want[2:] = -127, -127, -127
+    assert np.array_equal(a_q[:4], want)
+    assert np.isinf(s_a[:2]).all() and np.isnan(s_a[2:4]).all()
+    o_q, o_s = orc.quant_act(a[4:].view(np.uint16))
+    assert np.array_equal(a_q[4:], o_q) and np.array_equal(s_a[4:], o_s)
+
+
 def test_quant_act_edge_rows_and_row_stride():
     K = 1024
     a = np.zeros((8, K), np.float16)
