@@ -181,7 +181,7 @@ def test_persistent_kernel_with_more_tiles_than_cus(M, K, N, variant, hi, sg_max
     assert "prefill persistent" in qqq.last_route(), qqq.last_route()
 
 
-@pytest.mark.parametrize("tune,k_splits", [(10, 1), (13, 1), (15, 1), (16, 1), (17, 1), (27, 1), (37, 1), (15, 2), (17, 3)])
+@pytest.mark.parametrize("tune,k_splits", [(10, 1), (12, 1), (13, 1), (15, 1), (16, 1), (17, 1), (27, 1), (37, 1), (12, 2), (15, 2), (17, 3)])
 def test_wide_biased_route_through_every_prefill_kernel(tune, k_splits):
     """Integer scales up to 18 with codes in [-7,7] (what the front-end emits): the byte-wise integer route forms
     (7 - code) * s_g and the kernels carry the negated sums; forced through every tile shape, the persistent kernel
