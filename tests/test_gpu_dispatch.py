@@ -36,7 +36,7 @@ def test_automatic_pick_is_close_to_the_best_forced_pick(M, K, N, variant):
 
     auto_us, auto_route = us()
     forced = {}
-    picks = [(2, 10, 1), (2, 15, 1), (2, 16, 1), (2, 17, 1), (2, 13, 0)]
+    picks = [(2, 10, 1), (2, 12, 1), (2, 15, 1), (2, 16, 1), (2, 17, 1), (2, 13, 0)]
     if M <= 512:
         picks += [(2, t, s) for t in (15, 16, 17) for s in (2, 4)]
     if M <= 64:
@@ -56,7 +56,7 @@ def test_automatic_pick_is_close_to_the_best_forced_pick(M, K, N, variant):
 # prices every group conversion alike, is 11 to 66 % off
 ROUNDS = [(49, 2432, 26304, "pc"), (56, 8192, 28672, "pc"), (61, 2432, 26912, "pg"), (61, 2432, 26912, "real"),
           (61, 2432, 26912, "any"), (1541, 6272, 12048, "pc"), (936, 1536, 16464, "pg"), (1140, 4352, 14288, "pg"),
-          (615, 9856, 9136, "pg"), (1516, 1408, 11968, "any")]
+          (615, 9856, 9136, "pg"), (1516, 1408, 11968, "any"), (777, 4096, 11008, "real"), (777, 4096, 11008, "pc")]
 
 
 def automatic_against_forced(M, K, N, variant):
@@ -74,7 +74,7 @@ def automatic_against_forced(M, K, N, variant):
             "any": lambda w: qqq.qqq_gemm_w4a8_pergroup(a_q, s_a, w, s_g, s_w, ws, sg_max=0, y=y),
             "real": lambda w: qqq.qqq_gemm_w4a8_pergroup_f16scale(a_q, s_a, w, s_real, s_w, ws, y=y)}[variant]
     picks = [(0, 0, 0)] + ([(1, 0, 0)] if M <= 64 else []) + [
-        (2, tune, split) for tune in (10, 11, 13, 15, 16, 17) for split in ((1, 2, 4) if M <= 64 else (1,))
+        (2, tune, split) for tune in (10, 11, 12, 13, 15, 16, 17) for split in ((1, 2, 4) if M <= 64 else (1,))
         if tune != 13 or K >= 384]
     graphs, routes = [], []
     for family, tune, split in picks:
@@ -106,6 +106,20 @@ def automatic_against_forced(M, K, N, variant):
 @pytest.mark.parametrize("M,K,N,variant", ROUNDS)
 def test_automatic_pick_between_whole_rounds(M, K, N, variant):
     automatic_against_forced(M, K, N, variant)
+
+
+@pytest.mark.parametrize("variant", ["pc", "real"])
+def test_automatic_pick_takes_the_192_row_tile(variant):
+    """215 tiles of 192 x 256 for 777 rows of 4096 x 11008 (172 of 256 x 256 with a quarter of their rows past M)."""
+    M, K, N = 777, 4096, 11008
+    a_q, s_a = qqq.qqq_quant_act(torch.ones((M, K), dtype=torch.float16, device="cuda"))
+    w = torch.zeros((N, K // 8), dtype=torch.int32, device="cuda")
+    s_w, ws = torch.ones((N,), dtype=torch.float16, device="cuda"), qqq.new_workspace(M, N, K)
+    if variant == "pc":
+        qqq.qqq_gemm_w4a8_perchannel(a_q, s_a, qqq.qqq_pack_w4(w, K), s_w, ws)
+    else:
+        qqq.qqq_gemm_w4a8_pergroup_f16scale(a_q, s_a, qqq.qqq_pack_w4(w, K), torch.ones((K // 128, N), dtype=torch.float16, device="cuda"), s_w, ws)
+    assert "tile=192x256" in qqq.last_route(), qqq.last_route()
 
 
 # the ends of the range of K and N: long K on a narrow layer, where the decode kernel slices K (a model that does not know of the
