@@ -15,9 +15,9 @@
 //   sweep          per 512 channels, from the first: sweep_kernel, then the update of the channels after
 // What is left serial is one dependent step per channel, in registers.
 // Bound, without the Hessian: K = N = 4096 holds 2.3e10 + 6.9e10 fp64 operations, 1.2 ms at the nominal 78.6 TFLOP/s of the
-// fp64 matrix cores (1.7 ms at the 54 that f64_update_kernel reaches).  Measured, K = N = 4096: 3.7 ms, and 4.4 ms with the
+// fp64 matrix cores (1.7 ms at the 54 that f64_update_kernel reaches).  Measured, K = N = 4096: 3.7 ms, and 4.0 ms with the
 // Hessian of 2048 tokens (an inverse by K rank-1 sweeps and a rank-1 update of both matrices per channel: 360 ms); K = 2048,
-// N = 5632 with group scales: 1.75 ms, 1.9 ms with the Hessian of 1111 tokens (81 ms).
+// N = 5632 with group scales: 1.75 ms, 1.8 ms with the Hessian of 1111 tokens (81 ms).
 #include "qqq_calib.h"
 #include "qqq_internal.h"
 
@@ -303,8 +303,11 @@ struct Trailing { int t0, td, n, tile0; };  // first channel, channels, rows (= 
 __global__ __launch_bounds__(256, 2) void factor_panel_kernel(double* A, int64_t K, int c0, int solvers, Trailing tr) {
   constexpr int kS = 66;
   static_assert(64 * kS >= 64 * kAs && 64 * kS >= 32 * kBs, "an update tile's stages fit");
-  __shared__ __attribute__((aligned(16))) double ys[64 * kS];  // [i][j]: the block, then R D for i < j, 0 from the diagonal on
-  __shared__ __attribute__((aligned(16))) double xs[64 * kS];  // [i][j]: R for i < j, else 0
+  // [i][j], in 16 x 16 tiles.  ys: the block's upper triangle; tiles above the diagonal become R D when their columns' turn comes, those on it
+  // keep the block as the columns after left it.  xs: R in the tiles above the diagonal and on it, there 0 from the diagonal on,
+  // each from its columns' turn on; the tiles below are never written, nor read
+  __shared__ __attribute__((aligned(16))) double ys[64 * kS];
+  __shared__ __attribute__((aligned(16))) double xs[64 * kS];
   __shared__ double rcp[64];                                   // 1 / d_j
   if ((int)blockIdx.x >= solvers) {
     const int u = tr.tile0 + (int)blockIdx.x - solvers;
@@ -426,7 +429,7 @@ __global__ __launch_bounds__(256, 2) void factor_panel_kernel(double* A, int64_t
     }
   }
   if (c0 == 0) return;
-  // ---- the solve, column by column from the last; xs is zero at and past the diagonal.  The 16 columns in turn are always
+  // ---- the solve, column by column from the last; xs is zero from the diagonal on in the tiles on it.  The 16 columns in turn are always
   // y[0]: the others move up behind them (what moves into finished places is not used)
 #pragma nounroll
   for (int p = 3; p >= 0; --p) {
@@ -792,9 +795,9 @@ int begin(const char* who, const void* w_fp16, const double* H, int64_t N, int64
   if ((rc = check_launch("gptq prepare")) != QQQ_OK) return rc;
   // Blocks of 64 from the last; each at once reduces the columns of its own kFO, and all columns before those are
   // reduced by the whole kFO together (see sweep): the next kFO's columns at once, the rest inside the launches of the next
-  // kFO's blocks, whose chains leave CUs idle.  Two workgroups of that kernel fit a CU: up to seven for every four CUs a launch keeps
-  // its time (K = 4096: 14.4 us without tiles, 17.7 at 226 workgroups, 23.4 at 436, 27.7 at 498, 38.8 at 635); what is
-  // left then (the first columns) goes at once as well.
+  // kFO's blocks, whose chains leave CUs idle.  Two workgroups of that kernel fit a CU, and up to seven for every four CUs what a
+  // launch carries costs less in it than by itself (K = 4096: a launch takes 14.4 us without tiles, 17.7 with 226 workgroups, 23.4 with 436,
+  // 27.7 with 498, 38.8 with 635); what is left then (the first columns) goes at once as well.
   auto reduce = [&](int64_t c0, int64_t kd, int64_t col0, int64_t cols, int64_t rows) {
     if (cols <= 0 || rows <= 0) return;
     hipLaunchKernelGGL((f64_update_kernel<true, true>), dim3((unsigned)((cols + 63) / 64), (unsigned)((rows + 63) / 64)),

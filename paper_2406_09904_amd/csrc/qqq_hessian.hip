@@ -41,8 +41,8 @@ struct TileStage {
 // Row strides of the stages (72 and 48 halves) keep the four token rows of a fragment on different banks.
 // A wave holds a (TE/2) x (TE/2) quarter.  TE = 64 reads each fragment for two MFMAs; TE = 32 is for narrow layers,
 // where 64 x 64 tiles leave CUs idle.
-// Bound: the fp64 matrix rate (78.6 TFLOP/s nominal).  K = 4096, 2048 tokens: 0.73 ms, 47 TFLOP/s of the one
-// triangle (3.66 ms with both triangles on vector multiply-adds); K = 2048, 1111 tokens: 0.144 ms (0.55).
+// Bound: the fp64 matrix rate (78.6 TFLOP/s nominal).  K = 4096, 2048 tokens: 0.68 ms, 51 TFLOP/s of the one
+// triangle (3.66 ms with both triangles on vector multiply-adds); K = 2048, 1111 tokens: 0.136 ms (0.55).
 // VEC: rows of X are 16-byte aligned (K % 8 == 0 and an aligned base); else element by element.
 template <int TE, bool VEC>
 __device__ __forceinline__ void hessian_tile(const _Float16* x, int64_t M, int64_t K, double* H, int ti, int tj, TileStage<TE>& sm) {
