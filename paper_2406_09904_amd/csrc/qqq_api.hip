@@ -91,8 +91,9 @@ static size_t split_bytes(int64_t M, int64_t N) {
 //                 clock); rounds: of a whole round when there are several; rest: what a partial last round costs beyond its
 //                 share.  2 to 3 % rms on all of them.  An even spread or whole rounds alone miss by 10 to 30 %: M = 2048, K = 4096, N = 11008
 //                 took 89 us in 1.4 rounds of 128 x 512 and takes 80 in 2.7 rounds of 128 x 256.  (The smoothing search's row is
-//                 fitted to the differences between the four tiles on 2082 searches, so only its differences mean anything; its
-//                 pick is 0.2 % behind the best tile, 5 % at most.)  The rows of 192 x 256, 128 x 128 and 64 x 128, and from 8 k-steps on
+//                 fitted to the differences between the four tiles on 2082 searches, so only its differences mean anything; on 4316 others,
+//                 with the loops and quantisers of now, its pick is 0.2 % behind the best tile, 4 % in one of a hundred, 9 % at most, and
+//                 a row fitted to those is no better.)  The rows of 192 x 256, 128 x 128 and 64 x 128, and from 8 k-steps on
 //                 all of the per-channel (but 128 x 512) and biased ones, are fitted to 30000 launches of 3457 shapes of their own
 //                 (2 to 4 % rms; 3 to 5 % below 8 k-steps); 2 % stand on rounds and rest of the per-channel 128 x 128 and 64 x 128, whose
 //                 wrong choice costs more than the larger tiles' (up to 20 % on M = 309, K = 6656, N = 16432).
@@ -115,8 +116,10 @@ static size_t split_bytes(int64_t M, int64_t N) {
 //                 whole rounds over x, R the row tiles,  base + per_wg x R + g (w (a + b R) + c M).  5 to 9 % rms.
 //   sliced[]      the same where a narrow layer's K is cut into S slices:  base + rows R + K / (1000 S) (step + step_rows R) +
 //                 slice S + c g M.  7 to 11 % rms.  (M = 30, K = 58240, N = 16: 5.6 us sliced, 30 in the prefill kernels.)
-// On 724 other shapes of the first kind (four conversions each) the pick is 0.7 % behind the best forced choice on average, 6 % in
-// one of a hundred, 12 % at most; on 166 of the second kind 1.1, 11 and 19 %.
+// On 1332 other shapes of the first kind (four conversions each) the pick is 0.3 % behind the best forced choice on average, 6 % in
+// one of a hundred, 14 % at most; on 861 of the second kind 0.4, 13 and 24 %.  Rows fitted anew, also with a term for the weight
+// stream beside the tiles, change these by less than 0.1 % (what is missed most: 64 x 128 tiles of two to seven row tiles, whose weights
+// come from memory for few rows, 10 to 25 % slower than modelled; and fewer than 8 k-steps).
 // Tests time the automatic pick against every forced pick on small grids (10 and 15 % bars).
 enum CostClass : int { kCostChannel, kCostBias, kCostFma, kCostReal, kCostClamp, kCostLoss, kCostClasses };
 static int cost_class(int mode) {

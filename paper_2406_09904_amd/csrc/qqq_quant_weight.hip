@@ -114,9 +114,9 @@ __global__ __launch_bounds__(256) void quant_weight_channel_kernel(const uint4* 
 // LDS stage is [G][kWaves], and after a barrier the tables are written in runs of four elements,
 // the division s_Wg / s_Wc being done there.  STAGED == false (a table too tall for LDS): the
 // wave reads its row a second time (from L2) and writes its table elements one by one.
-// Bound by memory at the largest (K = 8192, N = 28672: 131 us, 4.6 TB/s), below that by how many rows are in flight and the two latencies
-// a row exposes (K = 4096, N = 11008: 25.6 us, 4.5 TB/s; N = 4096: 11.8).  The range checks are only where a row ends
-// (per 2048 weights): with checks everywhere and eight channels a workgroup from N = 18432 on 131 was 137, 25.6 27.0, 11.8 12.9, and K = 11008, N = 6656
+// K = 8192, N = 28672: 131 us, 4.6 TB/s; K = 4096, N = 11008: 25.6 us, 4.5 TB/s; N = 4096: 11.8.  Neither memory alone (a copy reaches
+// 6.1 TB/s) nor instructions (about 8 a weight, 0.4 of these times): between a wave's requests and its codes nothing else of
+// that wave runs.  The range checks are only where a row ends (per 2048 weights): with checks everywhere and eight channels a workgroup from N = 18432 on 131 was 137, 25.6 27.0, 11.8 12.9, and K = 11008, N = 6656
 // 49.3 us 53.1.  Four channels throughout: eight are 1 to 9 % slower from K = 4096 on (K = 8192, N = 8704: 45.4 us against 42.8), up to 8 % faster only
 // for rows of at most 2048 and N >= 12288, and leave the chip idle on narrow layers (K = 8192, N = 1024: 14.7 against 9.6).
 template <int V>
