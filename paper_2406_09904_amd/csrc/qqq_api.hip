@@ -116,10 +116,11 @@ static size_t split_bytes(int64_t M, int64_t N) {
 //                 whole rounds over x, R the row tiles,  base + per_wg x R + g (w (a + b R) + c M).  5 to 9 % rms.
 //   sliced[]      the same where a narrow layer's K is cut into S slices:  base + rows R + K / (1000 S) (step + step_rows R) +
 //                 slice S + c g M.  7 to 11 % rms.  (M = 30, K = 58240, N = 16: 5.6 us sliced, 30 in the prefill kernels.)
-// On 1332 other shapes of the first kind (four conversions each) the pick is 0.3 % behind the best forced choice on average, 6 % in
-// one of a hundred, 14 % at most; on 861 of the second kind 0.4, 13 and 24 %.  Rows fitted anew, also with a term for the weight
-// stream beside the tiles, change these by less than 0.1 % (what is missed most: 64 x 128 tiles of two to seven row tiles, whose weights
-// come from memory for few rows, 10 to 25 % slower than modelled; and fewer than 8 k-steps).
+// On 2000 other shapes of the first kind (four conversions each) the pick is 0.8 % behind the best forced choice on average, 7 % in
+// one of a hundred, 27 % at most; on 988 of the second kind 1.1, 13 and 30 %.  Rows fitted anew, also with a term for the weight
+// stream beside the tiles, change that by less than 0.1 % (what is missed most: 64 x 128 tiles of two to seven row tiles, whose weights
+// come from memory for few rows, 10 to 25 % slower than modelled; fewer than 8 k-steps; saturating calls of 17 .. 32 rows that stay with
+// the decode kernel for too long).
 // Tests time the automatic pick against every forced pick on small grids (10 and 15 % bars).
 enum CostClass : int { kCostChannel, kCostBias, kCostFma, kCostReal, kCostClamp, kCostLoss, kCostClasses };
 static int cost_class(int mode) {
