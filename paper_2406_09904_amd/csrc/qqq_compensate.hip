@@ -10,14 +10,14 @@
 // K^3/6 multiply-adds and a triangular product of N K^2 / 2 replace an explicit inverse and a rank-1
 // update of both matrices per channel, and W_i - Q_i is exact in fp64 (fp16 minus int4 x fp16).
 //
-// Both parts are blocked so that almost all of their arithmetic is fp64 MFMA (f64_update_kernel):
-//   factorisation  per 64 channels, from the last: factor_panel_kernel, then the update of the channels before
+// Both parts are blocked so that almost all of their arithmetic is fp64 MFMA (f64_update_kernel, factor_update):
+//   factorisation  factor_kernel: 64 channels at a time, from the last
 //   sweep          per 512 channels, from the first: sweep_kernel, then the update of the channels after
 // What is left serial is one dependent step per channel, in registers.
 // Bound, without the Hessian: K = N = 4096 holds 2.3e10 + 6.9e10 fp64 operations, 1.2 ms at the nominal 78.6 TFLOP/s of the
-// fp64 matrix cores (1.7 ms at the 54 that f64_update_kernel reaches).  Measured, K = N = 4096: 3.7 ms, and 4.0 ms with the
+// fp64 matrix cores (1.7 ms at the 54 that f64_update_kernel reaches).  Measured, K = N = 4096: 3.0 ms, and 3.3 ms with the
 // Hessian of 2048 tokens (an inverse by K rank-1 sweeps and a rank-1 update of both matrices per channel: 360 ms); K = 2048,
-// N = 5632 with group scales: 1.75 ms, 1.8 ms with the Hessian of 1111 tokens (81 ms).
+// N = 5632 with group scales: 1.5 ms, 1.55 ms with the Hessian of 1111 tokens (81 ms).
 #include "qqq_calib.h"
 #include "qqq_internal.h"
 
@@ -31,7 +31,7 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 
 constexpr int kFB = 64;    // channels per factorisation block
 constexpr int kSB = 128;   // channels per sweep block (= a group of the per-group quantiser)
-constexpr int kFO = 256, kSO = 512;  // channels after which the rest of the matrix is updated
+constexpr int kSO = 512;  // channels after which the rest of the weights is updated
 static_assert(kSB == QQQ_GROUP && kSB == 128, "a sweep block is one group");
 
 template <int V>
@@ -158,15 +158,16 @@ __global__ __launch_bounds__(1024) void diagonal_kernel(const double* H, int64_t
 // diagonal) and the running weights in fp64, 0 in the place of an infinity or NaN (the sweep puts those back: here only
 // the moves are added up).  K % 8 == 0.  grid.x: rows of H, then rows of W.
 __global__ __launch_bounds__(256) void prepare_kernel(const double* H, const _Float16* w, const double* keep,
-                                                      const double* damp, int64_t N, int64_t K, double* A, double* W64) {
+                                                      const double* damp, int64_t N, int64_t K, double* A, int64_t ld, double* W64,
+                                                      uint32_t* flags, int n_flags) {
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < n_flags; i += gridDim.x * 256) flags[i] = 0;
   for (int64_t r = blockIdx.x; r < K + N; r += gridDim.x) {
     if (r < K) {
       for (int64_t j = (r & ~(int64_t)1) + 2 * threadIdx.x; j < K; j += 512) {
-        const int64_t at = r * K + j;
-        double h0 = H[at], h1 = H[at + 1];  // (H is 8-byte aligned)
+        double h0 = H[r * K + j], h1 = H[r * K + j + 1];  // (H is 8-byte aligned)
         if (j == r) h0 = (h0 == 0.0 ? 1.0 : h0) + damp[0];
         if (j + 1 == r) h1 = (h1 == 0.0 ? 1.0 : h1) + damp[0];
-        *reinterpret_cast<double2*>(A + at) = make_double2(h0, h1);
+        *reinterpret_cast<double2*>(A + r * ld + j) = make_double2(h0, h1);
       }
     } else {
       const int64_t at0 = (r - K) * K;
@@ -182,7 +183,7 @@ __global__ __launch_bounds__(256) void prepare_kernel(const double* H, const _Fl
   }
 }
 
-// C += (or -=) A B in fp64: C [M,N], A [M,kd], B [kd,N], all row-major and 16-byte aligned, N, kd and the strides even.
+// C += A B in fp64: C [M,N], A [M,kd], B [kd,N], all row-major and 16-byte aligned, N, kd and the strides even.
 // 64 x 64 tile per workgroup, a wave per 32 x 32 quarter, 32 of kd at a time through LDS with the next
 // 32 already requested.  v_mfma_f64_16x16x4_f64 (64 clocks): lane l holds row (column) l % 16 and k = l / 16
 // of the operands, register v of the result is row 4 v + l / 16, column l % 16.  Row strides of the LDS tiles
@@ -191,7 +192,6 @@ __global__ __launch_bounds__(256) void prepare_kernel(const double* H, const _Fl
 // tiles and fragments read four k ahead measured the same.  The second launch bound keeps the accumulators in the vector
 // registers: left alone the compiler moves them to the accumulation registers and back every 32 of kd (303 us).
 constexpr int kAs = 34, kBs = 80;  // row strides of the LDS tiles: 64 rows of A, 32 of B
-template <bool SUB>
 __device__ __forceinline__ void update_tile(const double* A, int64_t lda, const double* B, int64_t ldb, double* C, int64_t ldc,
                                             int M, int N, int kd, int tm, int tn, double* sa, double* sb) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -234,7 +234,7 @@ __device__ __forceinline__ void update_tile(const double* A, int64_t lda, const 
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int e = tid + 256 * j;
-      double2 a = SUB ? make_double2(-ra[j].x, -ra[j].y) : ra[j];
+      double2 a = ra[j];
       double2 b = rb[j];
       if (k0 + 2 * (e & 15) >= kd) a.x = a.y = 0.0;
       if (k0 + (e >> 5) >= kd) b.x = b.y = 0.0;
@@ -269,71 +269,192 @@ __device__ __forceinline__ void update_tile(const double* A, int64_t lda, const 
       }
 }
 
-// UPPER: C is columns col0 .. col0 + N of a symmetric matrix kept as its upper triangle; only the tiles that reach the
-// diagonal or lie above it.
-template <bool UPPER, bool SUB>
 __global__ __launch_bounds__(256, 3) void f64_update_kernel(const double* A, int64_t lda, const double* B, int64_t ldb,
-                                                         double* C, int64_t ldc, int M, int N, int kd, int col0) {
+                                                         double* C, int64_t ldc, int M, int N, int kd) {
   __shared__ __attribute__((aligned(16))) double sa[64 * kAs];
   __shared__ __attribute__((aligned(16))) double sb[32 * kBs];
-  if (UPPER && col0 + (int)blockIdx.x * 64 + 63 < (int)blockIdx.y * 64) return;
-  update_tile<SUB>(A, lda, B, ldb, C, ldc, M, N, kd, blockIdx.y, blockIdx.x, sa, sb);
+  update_tile(A, lda, B, ldb, C, ldc, M, N, kd, blockIdx.y, blockIdx.x, sa, sb);
 }
 
-// One block [c0, c0 + 64) of H = R D R^T, the channels after it already eliminated from A.
-// Every workgroup factors the 64 x 64 diagonal block for itself (64 dependent steps: column j's pivot
-// d_j, R[i,j] = A[i,j] / d_j for i < j, A[i,k] -= R[i,j] A[k,j] for k < j) and then solves for its own 16 of
-// the c0 rows above: y_j = a_j - sum_{k > j} y_k R[j,k], x_j = y_j / d_j, i.e. R = x and R D = y there.
-// Written: x in place (A[row, c0 + j]) and y transposed into the unused lower triangle (A[c0 + j, row]),
-// which is the row-major operand the update of the rows above wants; the diagonal block's R goes
-// transposed below the diagonal (its upper half is still being read by other workgroups).
-// Bound by the chain of 64 pivots and, where code runs once, by its fetch: both halves walk 16 columns at a time
-// in a loop, so that one body of a few KiB serves the whole block (written out straight, 42 KiB of instructions
-// took 44.7 us a block whatever the row count).
-// Diagonal block, 16 columns at a time from the last: they receive what the columns after them owe (fp64 MFMA, a wave per 16 rows);
+// ---- H = R D R^T, all of it in one launch.
+// Blocks of 64 channels from the last: block k's diagonal tile is factored (64 dependent pivots), the row tiles i < k above it are solved
+// (y_j = a_j - sum_{k' > j} y_k' R[j,k'], x_j = y_j / d_j: R = x and R D = y there), and every tile (i, j), i <= j < k, gets A -= R[i,k] (R D)[j,k]^T.
+// What bounds it is the chain of all pivots, so one workgroup does nothing else: block after block it factors the tile, solves the row tile
+// next to it and takes that off the next tile, without leaving its CU.  All other workgroups draw tickets for the rest (Tasks), in a fixed order in which a
+// task needs only earlier ones and the chain's earlier blocks, so that a drawn task's waits end however few workgroups run beside it.  There are two
+// queues, a workgroup in three on the one that the chain waits for (solves, updates by one panel), the others on the updates by four panels at once, whose
+// tasks are long; three workgroups keep chain and queues going.  What a task needs is told by flags: a block factored, a tile solved, the number of panels that a tile has received.
+// Tiles receive the panels of their own four blocks (kOuter) and of the next four one by one, and those of later blocks four at a time, during the steps of
+// the four blocks after them; the columns that turn to single panels next come first, in 64 x 64 tiles, the others in 128 x 128.
+// Between XCDs caches are coherent at kernel boundaries only, so what one workgroup writes for another goes through to memory (agent-scope
+// stores, a wait, then the flag).  R D is kept transposed below the diagonal, each line written once and read only after its flag, so updates read it
+// with plain loads, and take R from it too (x = y / d, the same bits); tiles that change are read at agent scope.
+// One workgroup a CU: with two, solves and updates on a CU held each other up and the chain with them (K = 4096, 64 x 64 tiles only: 2530 us, 1660 with one).
+// us, K = 1024 / 2048 / 4096: about 270 / 570 / 1470 (a launch per block, its workgroups all factoring the tile again, with the updates carried in or between:
+// 385 / 800 / 1960).  A block of the chain takes 16.5 us of waiting for nobody: the tile 7.7, the row tile 3.6, off the next tile 2.1, flags and loads 3.
+// At K = 4096 the first half of the blocks waits for updates: a 64 x 64 tile takes 5 us for one panel, 15 for four, a 128 x 128 tile 45 for four.
+constexpr int kOuter = 4;
+constexpr int kS = 66;  // row stride of a 64 x 64 block in LDS
+
+struct Factor {
+  double* A;        // [K][ld], ld a multiple of 16: a tile's rows are whole cache lines
+  double* rcp;      // [K] 1 / d_j
+  uint32_t* ticket;
+  uint32_t* factored;  // [nb]
+  uint32_t* applied;   // [nb][nb]: panels tile (i, j) has received
+  uint32_t* solved;    // [nb][nb]: tile i of panel k, at [k][i]
+  int K, ld, nb;
+};
+
+template <typename T>
+__device__ __forceinline__ T agent_load(const T* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <typename T>
+__device__ __forceinline__ void agent_store(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// Until flag[l] >= least[l] for every lane l of wave 0 that asks; all threads wait.
+__device__ __forceinline__ void await(const uint32_t* flag, uint32_t least, bool asks) {
+  if (threadIdx.x < 64)
+    while (!__all(!asks || agent_load(flag) >= least)) __builtin_amdgcn_s_sleep(1);
+  lds_barrier();
+}
+// What this workgroup has written stands in memory: then the flag.
+__device__ __forceinline__ void publish(uint32_t* flag, uint32_t v) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  lds_barrier();
+  if (threadIdx.x == 0) agent_store(flag, v);
+}
+
+// The tasks of one step (block k) in order: far updates of the four blocks before last by the last four (those columns get block k's panel
+// next), a quarter of the other far updates, the solves of panel k, its near updates.
+struct Tasks {
+  int k, g, nb, p0, np;  // g: block k's four; panels [p0, p0 + np) of the four after
+  int n_next, far0, n_far, n_solve, n_near;
+  __device__ __forceinline__ Tasks(int nb_, int k_) : k(k_), g(k_ / kOuter), nb(nb_) {
+    p0 = kOuter * (g + 1);
+    np = p0 < nb ? min(kOuter, nb - p0) : 0;
+    const int n = max(kOuter * (g - 1), 0), wide = triangle(n / 2), quarter = p0 - 1 - k;
+    n_next = np && k == p0 - 1 && g > 0 ? triangle(kOuter * g) - triangle(n) : 0;
+    far0 = np ? wide * quarter / kOuter : 0;
+    n_far = np ? wide * (quarter + 1) / kOuter - far0 : 0;
+    n_solve = max(k - 1, 0);
+    n_near = k > 0 ? triangle(k) - triangle(n) - 1 : 0;
+  }
+  static __device__ __forceinline__ int triangle(int n) { return n * (n + 1) / 2; }
+  __device__ __forceinline__ int count() const { return n_next + n_far + n_solve + n_near; }
+};
+struct Tile64 { int i, j; };
+// tile number u of a triangle counted from its last: columns from the last, rows from the diagonal up
+__device__ __forceinline__ Tile64 tile_from_last(int total, int u) {
+  const int v = total - 1 - u;
+  int j = (int)((__builtin_sqrtf(8.0f * (float)v + 1.0f) - 1.0f) * 0.5f);  // column j starts at j (j + 1) / 2
+  while (j * (j + 1) / 2 > v) --j;
+  while ((j + 1) * (j + 2) / 2 <= v) ++j;
+  return {v - j * (j + 1) / 2, j};
+}
+
+// What a tile of EDGE x EDGE at rows 64 i, columns 64 j receives from panels [p0, p0 + np): -= R[rows, panels] (R D)[columns, panels]^T, a wave per
+// quarter of it, 32 channels at a time through two LDS stages: the next one is placed, and the one after it requested, behind half of a
+// stage's products.  Both operands are k-major, R = R D / d is formed on the way.  MFMA layout and row strides as in update_tile.  `mine`: this wave's
+// quarter is wanted (of a 128 x 128 tile on the diagonal three are).
+template <int EDGE>
+__device__ __forceinline__ void factor_update(const Factor& f, int i, int j, int p0, int np, bool mine, double* stages) {
+  constexpr int kStride = EDGE + 16, kQ = EDGE / 32, kRows = 512 / EDGE, kLoads = 32 / kRows;  // 16 x 16 tiles a side of a quarter; rows of a load
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, q = lane >> 4;
+  const int wr = (wave >> 1) * (EDGE / 2), wc = (wave & 1) * (EDGE / 2);
+  const int k1 = min((p0 + np) * 64, f.K), row0 = tid / (EDGE / 2), col0 = 2 * (tid % (EDGE / 2));
+  const double* pa = f.A + 64 * i + col0;
+  const double* pb = f.A + 64 * j + col0;
+  double2 ra[kLoads], rb[kLoads];
+  double rk[kLoads];
+  auto fetch = [&](int k0) {  // (past the end: the last row again)
+#pragma unroll
+    for (int x = 0; x < kLoads; ++x) {
+      const int k = min(k0 + row0 + kRows * x, k1 - 1);
+      ra[x] = *reinterpret_cast<const double2*>(pa + (int64_t)k * f.ld);
+      rb[x] = *reinterpret_cast<const double2*>(pb + (int64_t)k * f.ld);
+      rk[x] = f.rcp[k];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto place = [&](int h, int k0) {
+    double* const sa = stages + h * 2 * 32 * kStride;
+    double* const sb = sa + 32 * kStride;
+#pragma unroll
+    for (int x = 0; x < kLoads; ++x) {
+      const int row = row0 + kRows * x;
+      const bool in = k0 + row < k1;
+      const double2 a = in ? make_double2(-(ra[x].x * rk[x]), -(ra[x].y * rk[x])) : make_double2(0.0, 0.0);
+      const double2 b = in ? rb[x] : make_double2(0.0, 0.0);
+      *reinterpret_cast<double2*>(&sa[row * kStride + col0]) = a;
+      *reinterpret_cast<double2*>(&sb[row * kStride + col0]) = b;
+    }
+  };
+  fetch(64 * p0);
+  double* const c = f.A + (int64_t)(64 * i + wr + q) * f.ld + 64 * j + wc + l16;
+  v4d acc[kQ][kQ];
+#pragma unroll
+  for (int x = 0; x < kQ; ++x)
+#pragma unroll
+    for (int y = 0; y < kQ; ++y) acc[x][y] = (v4d){0.0, 0.0, 0.0, 0.0};
+  if (mine)
+#pragma unroll
+    for (int x = 0; x < kQ; ++x)
+#pragma unroll
+      for (int y = 0; y < kQ; ++y)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[x][y][v] = agent_load(c + (int64_t)(16 * x + 4 * v) * f.ld + 16 * y);
+  place(0, 64 * p0);
+  fetch(64 * p0 + 32);
+  lds_barrier();
+  int h = 0;
+#pragma nounroll
+  for (int k0 = 64 * p0; k0 < k1; k0 += 32) {
+    const double* const sa = stages + h * 2 * 32 * kStride;
+    const double* const sb = sa + 32 * kStride;
+    double a[2][kQ], b[2][kQ];
+    auto read = [&](int s) {
+#pragma unroll
+      for (int x = 0; x < kQ; ++x) {
+        a[s & 1][x] = sa[(4 * s + q) * kStride + wr + 16 * x + l16];
+        b[s & 1][x] = sb[(4 * s + q) * kStride + wc + 16 * x + l16];
+      }
+    };
+    read(0);
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      if (s < 7) read(s + 1);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int x = 0; x < kQ; ++x)
+#pragma unroll
+        for (int y = 0; y < kQ; ++y) acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s & 1][x], b[s & 1][y], acc[x][y], 0, 0, 0);
+      if (s == 3) {
+        place(h ^ 1, k0 + 32);
+        fetch(k0 + 64);
+      }
+    }
+    h ^= 1;
+    lds_barrier();
+  }
+  if (mine)
+#pragma unroll
+    for (int x = 0; x < kQ; ++x)
+#pragma unroll
+      for (int y = 0; y < kQ; ++y)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) agent_store(c + (int64_t)(16 * x + 4 * v) * f.ld + 16 * y, (double)acc[x][y][v]);
+}
+
+// The diagonal block in ys, 16 columns at a time from the last: they receive what the columns after them owe (fp64 MFMA, a wave per 16 rows);
 // one wave takes the 16 steps of the 16 x 16 tile on the diagonal, a lane a row, with what is broadcast as part of the
 // multiply-adds and the next pivot's reciprocal between them; the waves of the rows above solve theirs by it, 16 lanes per row.
-// In clocks, a block: loads 3900, 16 columns 4600 (a pivot 150, the rest the products, the rows above, barriers), rows 5000; 13.3 us a
-// launch.  With lane = row for all 64 rows in one wave, pivots and column elements through v_readlane 8200 and 7400 for 32 rows: 21 us.
-// The first `solvers` workgroups do that.  The others, on the CUs the chain leaves idle, take a part of what the kFO
-// channels [t0, t0 + td) before these owe to the columns this kFO does not contain (Trailing): A[0..td0) -= R (R D)^T there,
-// 64 x 64 tiles of the upper triangle numbered column by column from `tile0`.  They touch nothing a block of this kFO reads
-// or writes: rows and columns below t0 - kFO, from operands at t0 and past it.
-struct Trailing { int t0, td, n, tile0; };  // first channel, channels, rows (= columns) updated, first tile
-__global__ __launch_bounds__(256, 2) void factor_panel_kernel(double* A, int64_t K, int c0, int solvers, Trailing tr) {
-  constexpr int kS = 66;
-  static_assert(64 * kS >= 64 * kAs && 64 * kS >= 32 * kBs, "an update tile's stages fit");
-  // [i][j], in 16 x 16 tiles.  ys: the block's upper triangle; tiles above the diagonal become R D when their columns' turn comes, those on it
-  // keep the block as the columns after left it.  xs: R in the tiles above the diagonal and on it, there 0 from the diagonal on,
-  // each from its columns' turn on; the tiles below are never written, nor read
-  __shared__ __attribute__((aligned(16))) double ys[64 * kS];
-  __shared__ __attribute__((aligned(16))) double xs[64 * kS];
-  __shared__ double rcp[64];                                   // 1 / d_j
-  if ((int)blockIdx.x >= solvers) {
-    const int u = tr.tile0 + (int)blockIdx.x - solvers;
-    int tn = (int)((__builtin_sqrtf(8.0f * (float)u + 1.0f) - 1.0f) * 0.5f);  // tile column tn starts at tn (tn + 1) / 2
-    while (tn * (tn + 1) / 2 > u) --tn;
-    while ((tn + 1) * (tn + 2) / 2 <= u) ++tn;
-    update_tile<true>(A + tr.t0, K, A + (int64_t)tr.t0 * K, K, A, K, tr.n, tr.n, tr.td, u - tn * (tn + 1) / 2, tn, ys, xs);
-    return;
-  }
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l16 = lane & 15, q = lane >> 4;
-  const int nb = min(64, (int)K - c0);
-  // ---- the row this thread's sixteen lanes solve, this lane's columns 16 r + l16 in y[3 - r]
-  const int64_t row = (int64_t)blockIdx.x * 16 + 4 * wave + q;
-  double y[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) y[3 - r] = A[min(row, (int64_t)c0) * K + c0 + min(16 * r + l16, nb - 1)];  // (what is not there is not stored)
-
-  // ---- the diagonal block, upper triangle; channels past K are identity
-#pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    const int i = 4 * e + wave, j = lane;
-    const double a = A[(int64_t)(c0 + min(i, nb - 1)) * K + c0 + max(min(i, nb - 1), min(j, nb - 1))];
-    ys[i * kS + j] = (i <= j && j < nb) ? a : (i == j ? 1.0 : 0.0);
-  }
-  __syncthreads();
+// [i][j], in 16 x 16 tiles.  ys: the block's upper triangle; tiles above the diagonal become R D when their columns' turn comes, those on it
+// keep the block as the columns after left it.  xs: R in the tiles above the diagonal and on it, there 0 from the diagonal on,
+// each from its columns' turn on; the tiles below are never written, nor read.
+// Both halves walk 16 columns at a time in a loop, so that one body of a few KiB serves the whole block (written out straight, 42 KiB of
+// instructions took 44.7 us a block whatever the row count).  In clocks: 16 columns 4600 (a pivot 150, the rest the products, the rows above, barriers).
+__device__ __forceinline__ void factor_diagonal(double* ys, double* xs, double* rcp) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, q = lane >> 4;
 #pragma nounroll
   for (int p = 3; p >= 0; --p) {
     // a wave's 16 rows of these columns less what the columns after owe them: register v is row 16 wave + 4 v + q, column 16 p + l16
@@ -421,48 +542,195 @@ __global__ __launch_bounds__(256, 2) void factor_panel_kernel(double* A, int64_t
     }
     __syncthreads();
   }
-  if (blockIdx.x == 0) {
+}
+
+// Tile i of panel k (block at c0 = 64 k, its R in xs and rcp), a wave per 16 rows: 16 columns at a time from the last receive what the columns
+// after them owe (fp64 MFMA), then the 16 one after the other, 16 lanes a row.  u[p][v]: row 16 wave + 4 v + q, column 16 p + l16.  R goes to
+// its place, R D to ys, [column][row].  (All columns after each column in vector multiply-adds: 4.8 us,
+// 2.7 so.)
+__device__ __forceinline__ void load_rows(const Factor& f, int i, int c0, double (&u)[4][4]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, q = lane >> 4, nb = min(64, f.K - c0);
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int j = 4 * e + wave, i = lane;
-      if (i < j && j < nb) A[(int64_t)(c0 + j) * K + c0 + i] = xs[i * kS + j];
+  for (int p = 3; p >= 0; --p)
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      u[p][v] = agent_load(f.A + (int64_t)(64 * i + 16 * wave + 4 * v + q) * f.ld + c0 + min(16 * p + l16, nb - 1));
+}
+__device__ __forceinline__ void solve_rows(const Factor& f, int i, int c0, double (&u)[4][4], double* ys, const double* xs, const double* rcp) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, q = lane >> 4, nb = min(64, f.K - c0);
+#pragma unroll
+  for (int p = 3; p >= 0; --p) {
+    v4d acc = {u[p][0], u[p][1], u[p][2], u[p][3]};
+#pragma unroll
+    for (int k = 16 * (p + 1); k < 64; k += 4)
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-ys[(k + q) * kS + 16 * wave + l16], xs[(16 * p + l16) * kS + k + q], acc, 0, 0, 0);
+    const double* rr = xs + (16 * p + l16) * kS + 16 * p;
+    double m[16];
+#pragma unroll
+    for (int j = 15; j > 0; --j) m[j] = rr[j];
+    double y[4] = {acc[0], acc[1], acc[2], acc[3]};
+    fmac_own<15>(y, m[15]); fmac_own<14>(y, m[14]); fmac_own<13>(y, m[13]); fmac_own<12>(y, m[12]); fmac_own<11>(y, m[11]);
+    fmac_own<10>(y, m[10]); fmac_own<9>(y, m[9]); fmac_own<8>(y, m[8]); fmac_own<7>(y, m[7]); fmac_own<6>(y, m[6]);
+    fmac_own<5>(y, m[5]); fmac_own<4>(y, m[4]); fmac_own<3>(y, m[3]); fmac_own<2>(y, m[2]); fmac_own<1>(y, m[1]);
+    const int col = 16 * p + l16;
+    const double rd = rcp[col];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int row = 16 * wave + 4 * v + q;
+      ys[col * kS + row] = col < nb ? y[v] : 0.0;
+      if (col < nb) f.A[(int64_t)(64 * i + row) * f.ld + c0 + col] = y[v] * rd;
     }
   }
-  if (c0 == 0) return;
-  // ---- the solve, column by column from the last; xs is zero from the diagonal on in the tiles on it.  The 16 columns in turn are always
-  // y[0]: the others move up behind them (what moves into finished places is not used)
-#pragma nounroll
-  for (int p = 3; p >= 0; --p) {
-    // R[16 (p - 3 + r) + l16][16 p + j]; where that row is before the block, row l16 feeds places no longer used
-    const double* rr[4];
+  lds_barrier();
 #pragma unroll
-    for (int r = 0; r < 4; ++r) rr[3 - r] = xs + (16 * max(p - 3 + r, 0) + l16) * kS + 16 * p;
-    double m[2][4];  // a column's, requested during the column before
-#pragma unroll
-    for (int r = 0; r < 4; ++r) m[1][r] = rr[r][15];
-#define QQQ_SOLVE(J)                                                                                          \
-  {                                                                                                           \
-    if (J > 0) {                                                                                              \
-      _Pragma("unroll") for (int r = 0; r < 4; ++r) m[(J + 1) & 1][r] = rr[r][J > 0 ? J - 1 : 0];             \
-      __builtin_amdgcn_sched_barrier(0);                                                                      \
-    }                                                                                                         \
-    fmac_row<J, true, 4>(y, y[0], m[J & 1]);                                                                  \
+  for (int e = 0; e < 16; ++e) {
+    const int j = 4 * e + wave;
+    if (j < nb) agent_store(f.A + (int64_t)(c0 + j) * f.ld + 64 * i + lane, ys[j * kS + lane]);
   }
-    QQQ_SOLVE(15) QQQ_SOLVE(14) QQQ_SOLVE(13) QQQ_SOLVE(12) QQQ_SOLVE(11) QQQ_SOLVE(10) QQQ_SOLVE(9) QQQ_SOLVE(8)
-    QQQ_SOLVE(7) QQQ_SOLVE(6) QQQ_SOLVE(5) QQQ_SOLVE(4) QQQ_SOLVE(3) QQQ_SOLVE(2) QQQ_SOLVE(1) QQQ_SOLVE(0)
-#undef QQQ_SOLVE
-    const int col = 16 * p + l16;
-    if (row < c0 && col < nb) A[row * K + c0 + col] = y[0] * rcp[col];
-    ys[col * kS + 4 * wave + q] = y[0];  // (nothing reads the block's R D any more)
+}
+
+__global__ __launch_bounds__(256, 1) void factor_kernel(const Factor f) {
+  // two blocks of 64 x 64, or two stages of an update of 128 x 128: each workgroup, the chain above all, has its CU to itself
+  __shared__ __attribute__((aligned(16))) double ys[4 * 32 * 144];
+  static_assert(2 * 64 * kS <= 4 * 32 * 144, "the blocks fit");
+  double* const xs = ys + 64 * kS;
+  __shared__ double rcp[64];
+  __shared__ int s_ticket;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, q = lane >> 4, nb = f.nb;
+  auto draw = [&](int queue) {
+    if (tid == 0) s_ticket = (int)__hip_atomic_fetch_add(f.ticket + queue, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const int t = __builtin_amdgcn_readfirstlane(s_ticket);
+    __syncthreads();
+    return t;
+  };
+  const int number = draw(0);
+  if (number == 0) {  // ---- the chain
+    __builtin_amdgcn_s_setprio(3);
+    for (int k = nb - 1; k >= 0; --k) {
+      const int c0 = 64 * k, cols = min(64, f.K - c0);
+      // the block's upper triangle, a wave's 16 x 16 tiles u = wave, wave + 4, wave + 8 of ten; channels past K are identity
+      await(f.applied + (int64_t)k * nb + k, (uint32_t)max(nb - k - 2, 0), lane == 0);
+      v4d acc[3];
+      int tr[3], tc[3];
 #pragma unroll
-    for (int r = 0; r < 3; ++r) y[r] = y[r + 1];
+      for (int x = 0; x < 3; ++x) {
+        const int u = min(wave + 4 * x, 9);
+        tc[x] = u >= 6 ? 3 : u >= 3 ? 2 : u >= 1 ? 1 : 0;
+        tr[x] = u - tc[x] * (tc[x] + 1) / 2;
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          acc[x][v] = agent_load(f.A + (int64_t)(c0 + min(16 * tr[x] + 4 * v + q, cols - 1)) * f.ld + c0 + min(16 * tc[x] + l16, cols - 1));
+      }
+      if (k + 1 < nb) {
+        publish(f.solved + (int64_t)(k + 1) * nb + k, 1u);  // (the row tile that the last round solved: its stores went out before these loads)
+        double a[2][3], b[2][3];
+        auto read = [&](int s) {
+          const double rd = -rcp[4 * s + q];
+#pragma unroll
+          for (int x = 0; x < 3; ++x) {
+            b[s & 1][x] = ys[(4 * s + q) * kS + 16 * tc[x] + l16];
+            a[s & 1][x] = ys[(4 * s + q) * kS + 16 * tr[x] + l16] * rd;
+          }
+        };
+        read(0);
+#pragma unroll
+        for (int s = 0; s < 16; ++s) {
+          if (s < 15) read(s + 1);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int x = 0; x < 3; ++x) acc[x] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s & 1][x], b[s & 1][x], acc[x], 0, 0, 0);
+        }
+        lds_barrier();
+      }
+#pragma unroll
+      for (int x = 0; x < 3; ++x)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int i = 16 * tr[x] + 4 * v + q, j = 16 * tc[x] + l16;
+          if (wave + 4 * x < 10) ys[i * kS + j] = i <= j && j < cols ? (double)acc[x][v] : i == j ? 1.0 : 0.0;
+        }
+      lds_barrier();
+      factor_diagonal(ys, xs, rcp);
+      // R transposed below the diagonal
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int j = 4 * e + wave;
+        if (lane < j && j < cols) agent_store(f.A + (int64_t)(c0 + j) * f.ld + c0 + lane, xs[lane * kS + j]);
+      }
+      if (tid < cols) agent_store(f.rcp + c0 + tid, rcp[tid]);
+      if (k == 0) return;
+      await(f.applied + (int64_t)(k - 1) * nb + k, (uint32_t)(nb - k - 1), lane == 0);
+      double rows[4][4];
+      load_rows(f, k - 1, c0, rows);
+      publish(f.factored + k, 1u);
+      solve_rows(f, k - 1, c0, rows, ys, xs, rcp);
+    }
+    return;
   }
-  __syncthreads();
+
+  // ---- everything else
+  int queue = number % 3 == 1 ? 1 : 2, base = 0;
+  Tasks step(nb, nb - 1);
+  for (int ticket = draw(queue);; ticket = draw(queue)) {
+    auto count = [&]() { return queue == 1 ? step.n_solve + step.n_near : step.n_next + step.n_far; };
+    while (ticket - base >= count() && step.k > 0) {
+      base += count();
+      step = Tasks(nb, step.k - 1);
+    }
+    if (ticket - base >= count()) {
+      if (queue == 1) return;
+      queue = 1;
+      base = 0;
+      step = Tasks(nb, nb - 1);
+      continue;
+    }
+    const int k = step.k, solve0 = step.n_next + step.n_far, u = ticket - base + (queue == 1 ? solve0 : 0);
+    if (u >= solve0 && u < solve0 + step.n_solve) {
+      const int i = k - 2 - (u - solve0), c0 = 64 * k, cols = min(64, f.K - c0);
+      await(lane == 0 ? f.factored + k : f.applied + (int64_t)i * nb + k, lane == 0 ? 1u : (uint32_t)(nb - k - 1), lane < 2);
+      double rows[4][4];
+      load_rows(f, i, c0, rows);
+      double r[16];
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int j = 16 * e + (tid >> 4), i = tid & 15;
-    const int64_t to = (int64_t)blockIdx.x * 16 + i;
-    if (j < nb && to < c0) A[(int64_t)(c0 + j) * K + to] = ys[j * kS + i];
+      for (int e = 0; e < 16; ++e) {
+        const int j = 4 * e + wave;
+        r[e] = agent_load(f.A + (int64_t)(c0 + min(j, cols - 1)) * f.ld + c0 + lane);
+      }
+      const double rd = agent_load(f.rcp + c0 + min(lane, cols - 1));
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int j = 4 * e + wave;
+        xs[lane * kS + j] = lane < j && j < cols ? r[e] : 0.0;
+      }
+      if (tid < 64) rcp[tid] = tid < cols ? rd : 1.0;
+      lds_barrier();
+      solve_rows(f, i, c0, rows, ys, xs, rcp);
+      publish(f.solved + (int64_t)k * nb + i, 1u);
+    } else if (u >= solve0 || u < step.n_next) {
+      const bool near = u >= solve0;
+      const Tile64 t = near ? tile_from_last(Tasks::triangle(k), u - solve0 - step.n_solve + 1)  // (the first is the chain's)
+                            : tile_from_last(Tasks::triangle(kOuter * step.g), u);
+      const int p0 = near ? k : step.p0, np = near ? 1 : step.np;
+      // lanes 0 .. 3 and 4 .. 7: the panels' tiles i and j; lane 8: the tile itself
+      const uint32_t* flag = lane < 8 ? f.solved + (int64_t)min(p0 + (lane & 3), nb - 1) * nb + (lane < 4 ? t.i : t.j) : f.applied + (int64_t)t.i * nb + t.j;
+      await(flag, lane < 8 ? 1u : (uint32_t)(nb - p0 - np), lane < 8 ? (lane & 3) < np : lane == 8);
+      factor_update<64>(f, t.i, t.j, p0, np, true, ys);
+      publish(f.applied + (int64_t)t.i * nb + t.j, (uint32_t)(nb - p0));
+    } else {
+      const Tile64 t = tile_from_last(Tasks::triangle(kOuter / 2 * (step.g - 1)), u - step.n_next + step.far0);
+      const int i = 2 * t.i, j = 2 * t.j, p0 = step.p0, np = step.np;
+      // lanes 0 .. 15: row tiles i, i + 1, j, j + 1 of the panels; lanes 16 .. 19: the four tiles themselves, the one below the diagonal left out
+      const int ti = i + ((lane >> 1) & 1), tj = j + (lane & 1), tile = lane >> 2;
+      const bool panel = lane < 16;
+      const uint32_t* flag = panel ? f.solved + (int64_t)min(p0 + (lane & 3), nb - 1) * nb + (tile < 2 ? i : j) + (tile & 1) : f.applied + (int64_t)ti * nb + tj;
+      await(flag, panel ? 1u : (uint32_t)(nb - p0 - np), panel ? (lane & 3) < np : lane < 20 && ti <= tj);
+      factor_update<128>(f, i, j, p0, np, i + (wave >> 1) <= j + (wave & 1), ys);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      lds_barrier();
+      if (wave == 0 && lane >= 16 && lane < 20 && ti <= tj) agent_store(f.applied + (int64_t)ti * nb + tj, (uint32_t)(nb - p0));
+    }
   }
 }
 
@@ -500,7 +768,7 @@ __device__ __forceinline__ Tile upper_tile(int u) {
 // all channels solves z R = P over the block's triangle (z = P for its first channel).
 // W64 is overwritten with W_i - q s, the left operand of the update of the channels after.
 template <bool GROUP>
-__global__ __launch_bounds__(256, 2) void sweep_kernel(const _Float16* w, const double* A, const double* keep, int64_t N,
+__global__ __launch_bounds__(256, 2) void sweep_kernel(const _Float16* w, const double* A, int ld, const double* keep, int64_t N,
                                                     int64_t K, int o0, int o1, uint16_t* scales, double* W64,
                                                     uint32_t* w_nat) {
   constexpr int kRows = 16 * (16 * 36 + 8);  // doubles: 16 rows of 129 - 16 r for r = 0 .. 7
@@ -558,13 +826,13 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const _Float16* w, const 
       }
       __syncthreads();
       v4d m[2] = {};
-      const uint32_t right = (uint32_t)(4 * q * K + min((int64_t)c0 + 32 * wave + 2 * l16, K - 2));  // of row k + s: k = 4 q + s
+      const uint32_t right = (uint32_t)(4 * q * ld + min((int64_t)c0 + 32 * wave + 2 * l16, K - 2));  // of row k + s: k = 4 q + s
       // 16 channels of k at a time, requested kAhead sixteens (1.5 thousand clocks of products) before they are multiplied
       constexpr int kAhead = 3;
       double2 rb[8][4];
       auto request = [&](int h, int k) {
 #pragma unroll
-        for (int s = 0; s < 4; ++s) rb[h][s] = *reinterpret_cast<const double2*>(A + (int64_t)(k + s) * K + right);
+        for (int s = 0; s < 4; ++s) rb[h][s] = *reinterpret_cast<const double2*>(A + (int64_t)(k + s) * ld + right);
         __builtin_amdgcn_sched_barrier(0);
       };
 #pragma unroll
@@ -597,7 +865,7 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const _Float16* w, const 
     // tiles on and above the diagonal, nine to a wave; every load is requested before the first value is placed
     double e[9][4];
     {
-      const double* block = A + (int64_t)c0 * K + c0;
+      const double* block = A + (int64_t)c0 * ld + c0;
 #pragma unroll
       for (int x = 0; x < 9; ++x) {
         const Tile g = upper_tile(wave + 4 * x);
@@ -606,7 +874,7 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const _Float16* w, const 
         // the workspace's
 #pragma unroll
         for (int v = 0; v < 4; ++v)
-          e[x][v] = (block + (hi + 4 * v < nb ? hi + 4 * v : 0) * (int)K + (lo < nb ? lo : 0))[q * (int)K + l16];
+          e[x][v] = (block + (hi + 4 * v < nb ? hi + 4 * v : 0) * ld + (lo < nb ? lo : 0))[q * ld + l16];
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -769,7 +1037,9 @@ __global__ __launch_bounds__(256) void group_finish_kernel(const uint32_t* w_nat
 }
 
 // what both sweeps share: argument checks, the working copies, damping and the factorisation
-struct Work { double *A, *W64, *keep; };
+struct Work { double *A, *W64, *keep; int ld; };
+int64_t row_stride(int64_t K) { return ((K + 15) & ~(int64_t)15) + 16; }
+int64_t flag_count(int64_t K) { const int64_t nb = (K + 63) / 64; return 32 + nb + 2 * nb * nb; }
 int begin(const char* who, const void* w_fp16, const double* H, int64_t N, int64_t K, double percdamp,
           const uint32_t* w_nat, void* workspace, size_t workspace_bytes, hipStream_t st, Work* out) {
   if (N < 1 || N > 65535 || K < 8 || K % 8 != 0 || K > 16384 || !(percdamp >= 0.0) || percdamp > 1e6)
@@ -782,54 +1052,38 @@ int begin(const char* who, const void* w_fp16, const double* H, int64_t N, int64
   const size_t need = qqq_gptq_workspace_bytes(N, K);
   if (workspace_bytes < need)
     return set_error(QQQ_ERR_WORKSPACE, "%s: workspace %zu bytes < %zu needed", who, workspace_bytes, need);
-  char* base = (char*)workspace;
+  char* base = (char*)((reinterpret_cast<uintptr_t>(workspace) + 127) & ~(uintptr_t)127);  // (cache lines: see factor_kernel)
+  const int64_t ld = row_stride(K), n_flags = flag_count(K);
   double* A = (double*)base;
-  double* W64 = (double*)(base + align256((size_t)K * K * 8));
+  double* W64 = (double*)(base + align256((size_t)K * ld * 8));
   double* keep = (double*)((char*)W64 + align256((size_t)N * K * 8));
-  double* damp = (double*)((char*)keep + align256((size_t)K * 8));
+  double* rcp = (double*)((char*)keep + align256((size_t)K * 8));
+  uint32_t* flags = (uint32_t*)((char*)rcp + align256((size_t)K * 8));
+  double* damp = (double*)((char*)flags + align256((size_t)n_flags * 4));
   int rc;
   hipLaunchKernelGGL(diagonal_kernel, dim3(1), dim3(1024), 0, st, H, K, percdamp, keep, damp);
   if ((rc = check_launch("gptq diagonal")) != QQQ_OK) return rc;
   hipLaunchKernelGGL(prepare_kernel, dim3((unsigned)(K + N < 4096 ? K + N : 4096)), dim3(256), 0, st, H,
-                     (const _Float16*)w_fp16, keep, damp, N, K, A, W64);
+                     (const _Float16*)w_fp16, keep, damp, N, K, A, ld, W64, flags, (int)n_flags);
   if ((rc = check_launch("gptq prepare")) != QQQ_OK) return rc;
-  // Blocks of 64 from the last; each at once reduces the columns of its own kFO, and all columns before those are
-  // reduced by the whole kFO together (see sweep): the next kFO's columns at once, the rest inside the launches of the next
-  // kFO's blocks, whose chains leave CUs idle.  Two workgroups of that kernel fit a CU, and up to seven for every four CUs what a
-  // launch carries costs less in it than by itself (K = 4096: a launch takes 14.4 us without tiles, 17.7 with 226 workgroups, 23.4 with 436,
-  // 27.7 with 498, 38.8 with 635); what is left then (the first columns) goes at once as well.
-  auto reduce = [&](int64_t c0, int64_t kd, int64_t col0, int64_t cols, int64_t rows) {
-    if (cols <= 0 || rows <= 0) return;
-    hipLaunchKernelGGL((f64_update_kernel<true, true>), dim3((unsigned)((cols + 63) / 64), (unsigned)((rows + 63) / 64)),
-                       dim3(256), 0, st, A + c0, K, A + c0 * K + col0, K, A + col0, K, (int)rows, (int)cols, (int)kd, (int)col0);
-  };
-  Trailing tr = {};
-  int tiles_left = 0;  // of tr
-  for (int64_t o0 = (K - 1) / kFO * kFO; o0 >= 0; o0 -= kFO) {
-    const int64_t o1 = o0 + kFO < K ? o0 + kFO : K;
-    for (int64_t c0 = (o1 - 1) / kFB * kFB; c0 >= o0; c0 -= kFB) {
-      const int solvers = c0 ? (int)(c0 / 16) : 1;
-      const int blocks_left = (int)((c0 - o0) / kFB) + 1;
-      const int carried = (tiles_left + blocks_left - 1) / blocks_left;
-      hipLaunchKernelGGL(factor_panel_kernel, dim3((unsigned)(solvers + carried)), dim3(256), 0, st, A, K, (int)c0, solvers, tr);
-      tr.tile0 += carried;
-      tiles_left -= carried;
-      reduce(c0, K - c0 < kFB ? K - c0 : kFB, o0, c0 - o0, c0);
-    }
-    if (o0 == 0) break;
-    const int64_t p0 = o0 - kFO;
-    reduce(o0, o1 - o0, p0, kFO, o0);
-    const int nt = (int)(p0 / 64), most = (kFO / kFB) * max(num_cus() * 7 / 4 - (int)(p0 / 16), 0);
-    int at_once = 0;  // tile columns
-    while (nt * (nt + 1) / 2 - at_once * (at_once + 1) / 2 > most) ++at_once;
-    reduce(o0, o1 - o0, 0, (int64_t)at_once * 64, (int64_t)at_once * 64);
-    tr = {(int)o0, (int)(o1 - o0), (int)p0, at_once * (at_once + 1) / 2};
-    tiles_left = nt * (nt + 1) / 2 - tr.tile0;
-  }
+  Factor f;
+  f.A = A;
+  f.rcp = rcp;
+  f.K = (int)K;
+  f.ld = (int)ld;
+  f.nb = (int)((K + 63) / 64);
+  f.ticket = flags;
+  f.factored = flags + 32;
+  f.applied = f.factored + f.nb;
+  f.solved = f.applied + (size_t)f.nb * f.nb;
+  // two workgroups of it fit a CU; the chain and a tile for each of the others
+  const int tiles = f.nb * (f.nb - 1) / 2;
+  hipLaunchKernelGGL(factor_kernel, dim3((unsigned)(1 + min(tiles, num_cus() - 1))), dim3(256), 0, st, f);
   if ((rc = check_launch("gptq factorisation")) != QQQ_OK) return rc;
   out->A = A;
   out->W64 = W64;
   out->keep = keep;
+  out->ld = (int)ld;
   return QQQ_OK;
 }
 
@@ -841,11 +1095,11 @@ int sweep(const Work& wk, const void* w_fp16, int64_t N, int64_t K, uint16_t* sc
   for (int64_t o0 = 0; o0 < K; o0 += kSO) {
     const int64_t o1 = o0 + kSO < K ? o0 + kSO : K;
     hipLaunchKernelGGL((sweep_kernel<GROUP>), dim3((unsigned)((N + 15) / 16)), dim3(256), 0, st, (const _Float16*)w_fp16,
-                       wk.A, wk.keep, N, K, (int)o0, (int)o1, scales, wk.W64, w_nat);
+                       wk.A, wk.ld, wk.keep, N, K, (int)o0, (int)o1, scales, wk.W64, w_nat);
     if (o1 < K)
-      hipLaunchKernelGGL((f64_update_kernel<false, false>), dim3((unsigned)((K - o1 + 63) / 64), (unsigned)((N + 63) / 64)),
-                         dim3(256), 0, st, wk.W64 + o0, K, wk.A + o0 * K + o1, K, wk.W64 + o1, K, (int)N, (int)(K - o1),
-                         (int)kSO, 0);
+      hipLaunchKernelGGL(f64_update_kernel, dim3((unsigned)((K - o1 + 63) / 64), (unsigned)((N + 63) / 64)),
+                         dim3(256), 0, st, wk.W64 + o0, K, wk.A + o0 * wk.ld + o1, wk.ld, wk.W64 + o1, K, (int)N, (int)(K - o1),
+                         (int)kSO);
   }
   return check_launch("gptq sweep");
 }
@@ -860,7 +1114,8 @@ extern "C" {
 
 size_t qqq_gptq_workspace_bytes(int64_t N, int64_t K) {
   if (N < 1 || N > 65535 || K < 8 || K % 8 != 0 || K > 16384) return 0;
-  return align256((size_t)K * K * 8) + align256((size_t)N * K * 8) + 2 * align256((size_t)K * 8) + 256;
+  return align256((size_t)K * row_stride(K) * 8) + align256((size_t)N * K * 8) + 2 * align256((size_t)K * 8) +
+         align256((size_t)flag_count(K) * 4) + 256 + 128;
 }
 
 int qqq_gptq_quantize_w4_perchannel(const void* w_fp16, const double* H, int64_t N, int64_t K, double percdamp,

@@ -255,3 +255,25 @@ def test_hessian_of_heavy_channels_is_no_slower_than_fp64(share):
             best = min(best, e0.elapsed_time(e1))
         times.append(best)
     assert times[0] < 1.1 * times[1], times
+
+
+@pytest.mark.parametrize("K,N,shift", [(64, 17, 16), (520, 40, 48), (1032, 33, 0)])
+def test_factorisation_on_a_workspace_in_use(K, N, shift):
+    """The factorisation's flags and the lines that its workgroups share, on a workspace that begins anywhere and holds the last call's
+    Hessian, factor and flags, then bytes that are no numbers: each call gives the oracle's codes."""
+    need = int(qqq.lib().qqq_gptq_workspace_bytes(N, K))
+    buf = torch.full((need + 256,), 0xFF, dtype=torch.uint8, device="cuda")
+    ws = buf[shift:shift + need]
+    for seed in (1, 2, 1):
+        x, w = layer(2 * K + 10, K, N, 700 + K + seed)
+        H = cal.hessian(x)
+        codes, s_bits, _ = cal.gptq_quantize(w, H, 0.01)
+        d_w, d_H = dev16(w), torch.from_numpy(H).cuda()
+        w_nat = torch.empty((N, K // 8), dtype=torch.int32, device="cuda")
+        s_w = torch.empty((N,), dtype=torch.float16, device="cuda")
+        rc = qqq.lib().qqq_gptq_quantize_w4_perchannel(d_w.data_ptr(), d_H.data_ptr(), N, K, 0.01, w_nat.data_ptr(), s_w.data_ptr(),
+                                                       ws.data_ptr(), need, torch.cuda.current_stream().cuda_stream)
+        assert rc == 0, qqq.lib().qqq_last_error()
+        torch.cuda.synchronize()
+        assert np.array_equal(f16_bits(s_w), s_bits) and np.array_equal(codes_of(w_nat, K), codes), seed
+        assert (buf[:shift] == 0xFF).all() and (buf[shift + need:] == 0xFF).all()
