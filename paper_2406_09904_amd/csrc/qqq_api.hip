@@ -101,6 +101,8 @@ static size_t split_bytes(int64_t M, int64_t N) {
 //                 last round that costs its own time whatever T:  x <= 1: fixed + per_round x + T (alone (1 - x) + full x);
 //                 x > 1: fixed + per_round x + T rounds x + [f > 0] rest (1 - f).  5 % rms (7 to 9 % in the other form; with the
 //                 rows of longer K the pick was up to 30 % off there, M = 1264, K = 256, N = 50432 62.6 us for 48.9).
+//   trimmed[]     what a launch of shapes 1 to 4 takes of that where their tiles go without their last 32 rows: medians of 50 launches of each shape and
+//                 conversion on new kernel and old (K = 1024 .. 11008, up to 8 tiles of rows), within 0.02 of each; half as much below short_ksteps.
 //   stream_tbs    what the weight stream of a prefill launch reaches at best; where it is what bounds several tiles, the one with the
 //                 least to do beside it is ahead (behind_stream).
 //   prepass_*     the biased route beyond the K that its rows were fitted to: a part per 1000 of K (K = 37760, M = 66, N = 4496 48.8 us
@@ -222,6 +224,8 @@ static const struct DispatchModel {
           {4, 128, 128, 0.842, 0.843, 0.753, 2.243, 4.8, 2.0},
           {5, 64, 128, 0.727, 0.884, 0.582, 2.031, 3.8, 0.8},
           {kPersistent, 128, 512, 2.503, 1.467, 2.313, 9.922, 7.8, 7.8}}};
+  double trimmed[kCostClasses][4] = {{1.0, 0.868, 0.945, 0.885}, {0.905, 0.868, 0.923, 0.905}, {0.923, 0.912, 0.935, 0.887},
+                                     {0.932, 0.909, 0.955, 0.915}, {0.952, 0.945, 0.947, 0.955}, {1.0, 1.0, 1.0, 1.0}};
   double stream_tbs = 4.6, behind_stream = 0.1;
   double split_us = 2.05, split_part_us = 0.28, split_mint32_us = 1.33;
   double margin_split = 0.97, margin_persistent = 0.965;
@@ -276,6 +280,10 @@ static PrefillPlan plan_prefill(int64_t M, int64_t N, int64_t K, int cost, bool 
       us += short_k || x > 1.0 ? c.per_round * x : c.per_round;
       if (x <= 1.0) us += t * (c.alone * (1.0 - x) + c.full * x);
       else us += t * c.rounds * x + (f > 0.0 ? (short_k ? 1.0 : t) * c.rest * (1.0 - f) : 0.0);
+      if (c.shape >= 1 && c.shape <= 4 && trimmed_rows(M, c.bm) < c.bm) {
+        const double part = kModel.trimmed[cost][c.shape - 1];
+        us *= short_k ? 0.5 * (1.0 + part) : part;
+      }
       if (us < stream_us) us = stream_us - kModel.behind_stream * (stream_us - us);
       if (ks > 1) us += kModel.split_us + ks * (kModel.split_part_us + kModel.split_mint32_us * 1e-6 * (double)M * (double)N);
       double score = us;

@@ -44,18 +44,18 @@ __device__ __forceinline__ v4i convert_b(uint32_t d0, uint32_t d1, int sg) {
 template <int MT, int CT, int NW, int ST = 3>
 struct DmaShape {
   static constexpr int kBM = 32 * MT, kBN = NW * 32 * CT, kBK = 128, kStages = ST;
-  static constexpr int kAStage = kBM * kBK;           // activations of one k-step
+  static constexpr int kARows = (kBM + 8 * NW - 1) / (8 * NW) * (8 * NW);  // (whole DMA pieces for every wave)
+  static constexpr int kAStage = kARows * kBK;        // activations of one k-step
   static constexpr int kWWave = CT * 2048;            // packed codes of one wave and k-step
   static constexpr int kWStage = NW * kWWave;
   static constexpr int kSgStage = NW * 256;           // 256 B of group scales per wave (32*CT used)
   static constexpr int kStage = kAStage + kWStage + kSgStage;
-  static constexpr int kAPieces = kBM / (8 * NW);     // 1 KiB DMA pieces (8 rows) per wave
+  static constexpr int kAPieces = kARows / (8 * NW);    // 1 KiB DMA pieces (8 rows) per wave
   static constexpr int kWChunks = 2 * CT;             // 1 KiB DMA chunks (16 channels) per wave
   static constexpr int kEpRow = 64 * CT + 16;         // fp16 row of the epilogue patch + bank pad
   static constexpr int kEpRows = kBM <= 128 ? kBM : kBM / 2;  // rows of it that are staged at a time
-  static constexpr int kEpWave = kEpRows * kEpRow + kBM * 4;  // and the wave's copy of the token scales
+  static constexpr int kEpWave = kEpRows * kEpRow + (kBM + 63) / 64 * 256;  // and the wave's copy of the token scales
   static constexpr int kLds = kStages * kStage;
-  static_assert(kBM % (8 * NW) == 0, "activation rows must split evenly over the waves");
   static_assert(NW * kEpWave <= kLds, "epilogue staging must fit the ring");
   static_assert(kLds <= 160 * 1024, "ring must fit the 160 KiB LDS");
 };
