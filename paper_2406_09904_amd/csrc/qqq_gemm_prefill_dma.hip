@@ -512,39 +512,45 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_prefill_dma_kernel(const Gemm
 
   if constexpr (LOSS) {
     static_assert(MODE == kPerChannel, "the search quantises per channel");
-    // fp64(acc) * fp64(s_a) * fp64(s_w) - fp64(y_ref), squared and summed in fp64 (acc carries the exact factor 16)
-    // Half a channel's reference values are requested before the first is used, rows past M repeating the last one and counting
-    // nothing (a load under the row's own condition waits for memory every time: M = 512, K = N = 4096, eight grid points
-    // 76 us a launch, 69 so).  The selection of the rows below M compiles to a branch per element with its own LDS read of the
-    // token scale, and the squares are added up only after the last of them: the 128x512 tile holds 128 fp64 differences then,
-    // 256 VGPRs with 90 spilled (188 bytes of scratch a lane); the narrower tiles spill nothing.
+    // fp64(acc) * fp64(s_a) * fp64(s_w) - fp64(y_ref), squared and summed in fp64 (acc carries the exact factor 16).  Reference values are
+    // requested sixteen at a time, ahead of the sixteen (in the smaller tiles 32) before them (M = 512, K = N = 4096, eight grid points 69 us with half a
+    // channel's values requested, waited for and used in turn, and a branch per element, 56 so).  Rows past M repeat the last one's and
+    // channels past N the first's; their token and channel scales and references count as 0, so nothing here is conditional.
     static_assert(S::kLds >= NW * 512 + NW * S::kBM * 4, "the partial sums and every wave's copy of the token scales");
     float* sa = (float*)(lds + NW * 512) + wave * S::kBM;
 #pragma unroll
-    for (int i = 0; i < kSaPerLane; ++i) sa[lane + 64 * i] = sa_own[i];
-    double sum = 0.0;
-#pragma unroll
-    for (int c = 0; c < TC; ++c) {
-      const double sw = nvalid[c] ? (double)(float)p.s_w[col[c]] : 0.0;
+    for (int i = 0; i < kSaPerLane; ++i) sa[lane + 64 * i] = m0 + lane + 64 * i < M ? sa_own[i] : 0.0f;
+    constexpr int kPer = 16 / kRegs, kParts = TM / kPer;  // row tiles of a part, parts of a channel tile
+    constexpr int kAll = TC * kParts, kAheadParts = CT == 2 ? 1 : 2;
+    float y[kAheadParts + 1][kPer][kRegs];
+    auto request = [&](int part) {
+      const int c = part / kParts, first = part % kParts * kPer;
       const float* ref = p.y_ref + (nvalid[c] ? col[c] : 0);
 #pragma unroll
-      for (int half = 0; half < TM; half += TM / 2) {
-        float y[TM / 2][kRegs];
+      for (int mt = 0; mt < kPer; ++mt)
 #pragma unroll
-        for (int mt = 0; mt < TM / 2; ++mt)
+        for (int v = 0; v < kRegs; ++v) y[part % (kAheadParts + 1)][mt][v] = ref[(int64_t)min(m0 + acc_row(first + mt, v), M - 1) * N];
+      __builtin_amdgcn_sched_barrier(0);
+    };
 #pragma unroll
-          for (int v = 0; v < kRegs; ++v) y[mt][v] = ref[(int64_t)min(m0 + acc_row(half + mt, v), M - 1) * N];
+    for (int part = 0; part < (kAheadParts < kAll ? kAheadParts : kAll); ++part) request(part);
+    double sum = 0.0;
 #pragma unroll
-        for (int mt = 0; mt < TM / 2; ++mt)
+    for (int part = 0; part < kAll; ++part) {
+      if (part + kAheadParts < kAll) request(part + kAheadParts);
+      const int c = part / kParts, first = part % kParts * kPer;
+      const double sw = nvalid[c] ? (double)(float)p.s_w[col[c]] : 0.0;
 #pragma unroll
-          for (int v = 0; v < kRegs; ++v) {
-            const int r = acc_row(half + mt, v);
-            const double d = (double)(acc[half + mt][c][v] >> 4) * (double)sa[r] * sw - (double)y[mt][v];
-            const double kept = m0 + r < M && nvalid[c] ? d : 0.0;
-            sum += kept * kept;
-          }
-        __builtin_amdgcn_sched_barrier(0);  // the next half's requests stay behind this one's uses
-      }
+      for (int mt = 0; mt < kPer; ++mt)
+#pragma unroll
+        for (int v = 0; v < kRegs; ++v) {
+          const int r = acc_row(first + mt, v);
+          const float ref = m0 + r < M && nvalid[c] ? y[part % (kAheadParts + 1)][mt][v] : 0.0f;
+          const double d = (double)(acc[first + mt][c][v] >> 4) * (double)sa[r] * sw - (double)ref;
+          sum += d * d;
+          if (v % 4 == 3) asm volatile("" : "+v"(sum));  // (else the squares of all are kept until the end: 149 registers spilled)
+        }
+      __builtin_amdgcn_sched_barrier(0);
     }
     double* part = (double*)lds;
     part[tid] = sum;
