@@ -25,14 +25,16 @@ static int check_launch(const char* what) {
 
 // ------------------------------------------------------------------ small helpers
 
-__global__ __launch_bounds__(256) void fill_u32_kernel(uint32_t* p, size_t n, uint32_t v) {
+__global__ __launch_bounds__(256) void fill_u32_kernel(uint32_t* p, size_t n, uint32_t v, uint32_t* p2, size_t n2) {
   const size_t stride = (size_t)gridDim.x * 256;
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += stride) p[i] = v;
+  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n + n2; i += stride) (i < n ? p[i] : p2[i - n]) = v;
 }
 
-static int fill_u32(void* p, size_t n, uint32_t v, hipStream_t st) {
-  const unsigned blocks = (unsigned)((n + 255) / 256 < 2048 ? (n + 255) / 256 : 2048);
-  hipLaunchKernelGGL(fill_u32_kernel, dim3(blocks ? blocks : 1), dim3(256), 0, st, (uint32_t*)p, n, v);
+// one array, or two
+static int fill_u32(void* p, size_t n, uint32_t v, hipStream_t st, void* p2 = nullptr, size_t n2 = 0) {
+  const size_t want = (n + n2 + 255) / 256;
+  const unsigned blocks = (unsigned)(want < 2048 ? want : 2048);
+  hipLaunchKernelGGL(fill_u32_kernel, dim3(blocks ? blocks : 1), dim3(256), 0, st, (uint32_t*)p, n, v, (uint32_t*)p2, n2);
   return check_launch("fill");
 }
 
@@ -74,8 +76,9 @@ __global__ __launch_bounds__(256) void channel_absmax_kernel(const uint4* x, int
   if (t < kvec * 8) atomicMax(&absmax_bits[t], r);
 }
 
-// in place: fp16 bit patterns -> fp32 values; top[0] = the largest (one workgroup)
-__global__ __launch_bounds__(1024) void absmax_finish_kernel(uint32_t* absmax, int64_t K, float* top) {
+// in place: fp16 bit patterns -> fp32 values (one workgroup); with sigmas, from the largest of them
+// sigma_g = fp32(max|X| * g / G), the product and the quotient in fp64, g = 1..G
+__global__ __launch_bounds__(1024) void absmax_finish_kernel(uint32_t* absmax, int64_t K, float* sigmas, int G) {
   __shared__ uint32_t smax;
   if (threadIdx.x == 0) smax = 0;
   __syncthreads();
@@ -87,23 +90,16 @@ __global__ __launch_bounds__(1024) void absmax_finish_kernel(uint32_t* absmax, i
   }
   atomicMax(&smax, mx);
   __syncthreads();
-  if (threadIdx.x == 0 && top) top[0] = half_bits_to_float(smax);
-}
-
-// sigma_g = fp32(max|X| * g / G) with the product and the quotient in fp64, g = 1..G
-__global__ void sigma_grid_kernel(const float* top, int G, float* sigmas) {
-  const int g = blockIdx.x * blockDim.x + threadIdx.x;
-  if (g < G) sigmas[g] = (float)((double)top[0] * (double)(g + 1) / (double)G);
+  if ((int)threadIdx.x < G) sigmas[threadIdx.x] = (float)((double)half_bits_to_float(smax) * (double)(threadIdx.x + 1) / (double)G);
 }
 
 // s_t = absmax_t / sigma (one fp32 division) where absmax_t > sigma, else 1; grid.y: several sigmas, their vectors
 // stride_bytes apart
 __global__ __launch_bounds__(256) void smoothing_vector_kernel(const float* absmax, const float* sigmas,
-                                                               const int32_t* index, int64_t K, float* s,
-                                                               int64_t stride_bytes) {
+                                                               int64_t K, float* s, int64_t stride_bytes) {
   const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (t >= K) return;
-  const float sigma = sigmas[(index ? index[0] : 0) + blockIdx.y];
+  const float sigma = sigmas[blockIdx.y];
   const float a = absmax[t];
   ((float*)((char*)s + stride_bytes * blockIdx.y))[t] = a > sigma ? a / sigma : 1.0f;
 }
@@ -152,12 +148,12 @@ __global__ __launch_bounds__(256) void smooth_apply_kernel(const uint4* in, cons
 // One token per workgroup (qqq_quant_act on X ./ s).  KEEP: the smoothed row stays in registers (K <= 8192); else it
 // is computed twice.
 template <bool KEEP>
-__global__ __launch_bounds__(256) void point_activations_kernel(const uint4* x, const float* s, int kvec, int64_t point_bytes,
+__global__ __launch_bounds__(256) void point_activations_kernel(const uint4* x, const float* s, int64_t s_bytes, int kvec, int64_t point_bytes,
                                                                 int8_t* a_q, float* s_a) {
   __shared__ uint32_t part[4];
   const int64_t off = point_bytes * blockIdx.y, m = blockIdx.x;
   const uint4* row = x + m * kvec;
-  const float* sv = (const float*)((const char*)s + off);
+  const float* sv = (const float*)((const char*)s + s_bytes * blockIdx.y);
   uint2* out = (uint2*)(a_q + off) + m * kvec;
   constexpr int kVecs = KEEP ? 4 : 1;
   uint4 v[kVecs];
@@ -201,7 +197,7 @@ __global__ __launch_bounds__(256) void point_activations_kernel(const uint4* x, 
 // N = 4096 158, 142 now).  V = 0: any row, 8 at a time, in loops and 108 registers, four workgroups a CU (the channels written out, 142 registers and three
 // workgroups: 5 points at M = 100, K = 8192, N = 3088 277 us, 244 now).
 template <int V>
-__global__ __launch_bounds__(256, V ? 1 : 4) void point_weights_kernel(const uint4* w, const float* s, int64_t N, int kvec,
+__global__ __launch_bounds__(256, V ? 1 : 4) void point_weights_kernel(const uint4* w, const float* s, int64_t s_bytes, int64_t N, int kvec,
                                                             int64_t point_bytes, uint8_t* packed, uint16_t* s_w) {
   constexpr bool ONE = V > 0;
   constexpr int kV = ONE ? V : 8;
@@ -222,7 +218,7 @@ __global__ __launch_bounds__(256, V ? 1 : 4) void point_weights_kernel(const uin
     pt = (int)(lin / groups);
   }
   const int64_t off = point_bytes * pt;
-  const float* sv = (const float*)((const char*)s + off);
+  const float* sv = (const float*)((const char*)s + s_bytes * pt);
   uint32_t* out = (uint32_t*)(packed + off);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   __shared__ float scales[ONE ? 1 : 16];
@@ -402,12 +398,33 @@ __global__ __launch_bounds__(64) void fp16_gemm_nt_wave_kernel(const uint4* x, c
 
 // ------------------------------------------------------------------ the grid's minimum
 
-__global__ void argmin_kernel(const double* losses, int G, int32_t* best) {
-  if (blockIdx.x != 0 || threadIdx.x != 0) return;
+// The first minimum of the losses and, with its sigma, the smoothing vector and both smoothed matrices, in one launch (four of a few microseconds
+// otherwise): every workgroup looks for the minimum itself.  A thread keeps eight channels' s and walks down the rows of X, then of W.
+__global__ __launch_bounds__(256) void best_point_kernel(const double* losses, int G, const float* absmax, const float* sigmas, const uint4* x,
+                                                         const uint4* w, int64_t M, int64_t N, int64_t kvec, uint4* xs, uint4* ws, float* s,
+                                                         int32_t* best) {
+  __shared__ double loss[256];
+  if ((int)threadIdx.x < G) loss[threadIdx.x] = losses[threadIdx.x];
+  __syncthreads();
   int b = 0;
   for (int g = 1; g < G; ++g)
-    if (losses[g] < losses[b]) b = g;  // first minimum
-  best[0] = b;
+    if (loss[g] < loss[b]) b = g;  // first minimum
+  const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) best[0] = b;
+  if (v >= kvec) return;
+  const float sigma = sigmas[b];
+  float4 a[2] = {reinterpret_cast<const float4*>(absmax)[2 * v], reinterpret_cast<const float4*>(absmax)[2 * v + 1]};
+  float* e = reinterpret_cast<float*>(a);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) e[i] = e[i] > sigma ? e[i] / sigma : 1.0f;
+  if (blockIdx.y == 0) {
+    reinterpret_cast<float4*>(s)[2 * v] = a[0];
+    reinterpret_cast<float4*>(s)[2 * v + 1] = a[1];
+  }
+  int64_t r = blockIdx.y;
+  for (; r < M; r += gridDim.y) xs[r * kvec + v] = smooth8<true>(x[r * kvec + v], a[0], a[1]);
+#pragma unroll 4
+  for (r -= M; r < N; r += gridDim.y) ws[r * kvec + v] = smooth8<false>(w[r * kvec + v], a[0], a[1]);
 }
 
 // loss += sum ( fp64(acc) * fp64(s_a[m]) * fp64(s_w[n]) - fp64(y_ref) )^2, fp64 throughout
@@ -447,8 +464,9 @@ static size_t smooth_workspace_bytes(int64_t M, int64_t N, int64_t K) {
   return total;
 }
 
-static int launch_absmax(const void* x, int64_t M, int64_t K, float* absmax, float* top, hipStream_t st) {
-  int rc = fill_u32(absmax, (size_t)K, 0u, st);
+// sigmas: optional, the grid's G thresholds; losses, then, are set to 0 too
+static int launch_absmax(const void* x, int64_t M, int64_t K, float* absmax, float* sigmas, int G, double* losses, hipStream_t st) {
+  int rc = fill_u32(absmax, (size_t)K, 0u, st, losses, (size_t)G * 2);
   if (rc != QQQ_OK) return rc;
   const int64_t kvec = K / 8;
   int64_t row_blocks = (M + 31) / 32;
@@ -458,14 +476,12 @@ static int launch_absmax(const void* x, int64_t M, int64_t K, float* absmax, flo
                      st, (const uint4*)x, M, kvec, rows_per_block, (uint32_t*)absmax);
   rc = check_launch("channel_absmax");
   if (rc != QQQ_OK) return rc;
-  hipLaunchKernelGGL(absmax_finish_kernel, dim3(1), dim3(1024), 0, st, (uint32_t*)absmax, K, top);
+  hipLaunchKernelGGL(absmax_finish_kernel, dim3(1), dim3(1024), 0, st, (uint32_t*)absmax, K, sigmas, G);
   return check_launch("channel_absmax (finish)");
 }
 
-static int launch_smooth(const void* x, const void* w, const float* absmax, const float* sigmas, const int32_t* index,
-                         int64_t M, int64_t N, int64_t K, void* xs, void* ws, float* s, hipStream_t st) {
-  hipLaunchKernelGGL(smoothing_vector_kernel, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, absmax, sigmas, index,
-                     K, s, (int64_t)0);
+static int launch_smooth(const void* x, const void* w, const float* absmax, const float* sigmas, int64_t M, int64_t N, int64_t K, void* xs, void* ws, float* s, hipStream_t st) {
+  hipLaunchKernelGGL(smoothing_vector_kernel, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, absmax, sigmas, K, s, (int64_t)0);
   int rc = check_launch("smoothing_vector");
   if (rc != QQQ_OK) return rc;
   const int64_t kvec = K / 8;
@@ -523,7 +539,7 @@ int qqq_channel_absmax(const void* x_fp16, int64_t M, int64_t K, float* absmax, 
   if (!x_fp16 || !absmax) return set_error(QQQ_ERR_NULL, "channel_absmax: null pointer argument");
   if (!aligned16c(x_fp16) || (reinterpret_cast<uintptr_t>(absmax) & 3u))
     return set_error(QQQ_ERR_SHAPE, "channel_absmax: x must be 16-byte, absmax 4-byte aligned");
-  return launch_absmax(x_fp16, M, K, absmax, nullptr, (hipStream_t)stream);
+  return launch_absmax(x_fp16, M, K, absmax, nullptr, 0, nullptr, (hipStream_t)stream);
 }
 
 int qqq_smooth_apply(const void* x_fp16, const void* w_fp16, const float* absmax, const float* sigma, int64_t M,
@@ -536,7 +552,7 @@ int qqq_smooth_apply(const void* x_fp16, const void* w_fp16, const float* absmax
   if (!aligned16c(x_fp16) || !aligned16c(w_fp16) || !aligned16c(xs_fp16) || !aligned16c(ws_fp16) || !aligned16c(s) ||
       (reinterpret_cast<uintptr_t>(absmax) & 3u) || (reinterpret_cast<uintptr_t>(sigma) & 3u))
     return set_error(QQQ_ERR_SHAPE, "smooth_apply: matrices and s must be 16-byte, absmax and sigma 4-byte aligned");
-  return launch_smooth(x_fp16, w_fp16, absmax, sigma, nullptr, M, N, K, xs_fp16, ws_fp16, s, (hipStream_t)stream);
+  return launch_smooth(x_fp16, w_fp16, absmax, sigma, M, N, K, xs_fp16, ws_fp16, s, (hipStream_t)stream);
 }
 
 int qqq_fp16_gemm_nt(const void* x_fp16, const void* w_fp16, int64_t M, int64_t N, int64_t K, float* y, void* stream) {
@@ -580,7 +596,6 @@ int qqq_adaptive_smoothing(const void* x_fp16, const void* w_fp16, int64_t M, in
   size_t at = 0;
   auto take = [&](size_t bytes) { char* p = base + at; at += align256c(bytes); return p; };
   float* absmax = (float*)take((size_t)K * 4);
-  float* top = (float*)take(256);
   float* y_ref = (float*)take((size_t)M * N * 4);
   // a grid point's smoothing vector and quantised operands; as many points at a time as the workspace holds
   const size_t first = at;
@@ -593,12 +608,16 @@ int qqq_adaptive_smoothing(const void* x_fp16, const void* w_fp16, int64_t M, in
   const int64_t room = (int64_t)(total - first) / point_bytes;  // at least two: see smooth_workspace_bytes
   const int at_once = room < grid_points ? (int)room : grid_points;
 
-  int rc = launch_absmax(x_fp16, M, K, absmax, top, st);
+  int rc = launch_absmax(x_fp16, M, K, absmax, sigmas, grid_points, losses, st);
   if (rc != QQQ_OK) return rc;
-  hipLaunchKernelGGL(sigma_grid_kernel, dim3(1), dim3(256), 0, st, top, grid_points, sigmas);
-  if ((rc = check_launch("sigma_grid")) != QQQ_OK) return rc;
   if ((rc = launch_fp16_gemm(x_fp16, w_fp16, M, N, K, y_ref, st)) != QQQ_OK) return rc;
-  if ((rc = fill_u32(losses, (size_t)grid_points * 2, 0u, st)) != QQQ_OK) return rc;
+  const int64_t column_blocks = (K / 8 + 255) / 256;
+  auto finish = [&]() {  // (two rounds of workgroups: a thread's rows are requested four at a time)
+    const int64_t rows = 8 * num_cus() / column_blocks;
+    hipLaunchKernelGGL(best_point_kernel, dim3((unsigned)column_blocks, (unsigned)(rows < 1 ? 1 : rows < M + N ? rows : M + N)), dim3(256), 0, st, losses,
+                       grid_points, absmax, sigmas, (const uint4*)x_fp16, (const uint4*)w_fp16, M, N, K / 8, (uint4*)xs_fp16, (uint4*)ws_fp16, s, best);
+    return check_launch("best point");
+  };
   if (steps_ahead(M, N, K, grid_points, at_once)) {
     // a point at a time through the hot path's own calls, the smoothed layer, its codes and their product in the workspace
     at = first;
@@ -618,7 +637,7 @@ int qqq_adaptive_smoothing(const void* x_fp16, const void* w_fp16, int64_t M, in
     const int64_t elements = M * N;
     const unsigned blocks = (unsigned)((elements + 255) / 256 < 2048 ? (elements + 255) / 256 : 2048);
     for (int g = 0; g < grid_points; ++g) {
-      if ((rc = launch_smooth(x_fp16, w_fp16, absmax, sigmas + g, nullptr, M, N, K, xs, ws, s_point, st)) != QQQ_OK) return rc;
+      if ((rc = launch_smooth(x_fp16, w_fp16, absmax, sigmas + g, M, N, K, xs, ws, s_point, st)) != QQQ_OK) return rc;
       if ((rc = qqq_quant_act(xs, M, K, K, a_q, s_a, stream)) != QQQ_OK) return rc;
       if ((rc = qqq_quantize_w4_perchannel(ws, N, K, K, w_nat, s_w, stream)) != QQQ_OK) return rc;
       if ((rc = qqq_pack_w4(w_nat, N, K, packed, stream)) != QQQ_OK) return rc;
@@ -627,9 +646,7 @@ int qqq_adaptive_smoothing(const void* x_fp16, const void* w_fp16, int64_t M, in
       if ((rc = check_launch("smooth_loss")) != QQQ_OK) return rc;
     }
     route_note("loss");
-    hipLaunchKernelGGL(argmin_kernel, dim3(1), dim3(64), 0, st, losses, grid_points, best);
-    if ((rc = check_launch("argmin")) != QQQ_OK) return rc;
-    return launch_smooth(x_fp16, w_fp16, absmax, sigmas, best, M, N, K, xs_fp16, ws_fp16, s, st);
+    return finish();
   }
   GemmParams p = {};
   p.a_q = a_q;
@@ -644,27 +661,33 @@ int qqq_adaptive_smoothing(const void* x_fp16, const void* w_fp16, int64_t M, in
   p.y_ref = y_ref;
   p.point_bytes = point_bytes;
   const int kvec = (int)(K / 8);
+  // all points' smoothing vectors at once where the smoothed weights' place, which is written last, holds them
+  float* vectors = 2 * grid_points <= N ? (float*)ws_fp16 : nullptr;
+  if (vectors)
+    hipLaunchKernelGGL(smoothing_vector_kernel, dim3((unsigned)((K + 255) / 256), (unsigned)grid_points), dim3(256), 0, st, absmax,
+                       sigmas, K, vectors, K * 4);
   for (int g = 0; g < grid_points; g += at_once) {
     // the candidates' smoothed layers, quantised as the hot path quantises them, and their losses
     const unsigned points = (unsigned)(grid_points - g < at_once ? grid_points - g : at_once);
-    hipLaunchKernelGGL(smoothing_vector_kernel, dim3((unsigned)((K + 255) / 256), points), dim3(256), 0, st, absmax,
-                       sigmas + g, (const int32_t*)nullptr, K, s_point, point_bytes);
+    if (vectors == nullptr)
+      hipLaunchKernelGGL(smoothing_vector_kernel, dim3((unsigned)((K + 255) / 256), points), dim3(256), 0, st, absmax,
+                         sigmas + g, K, s_point, point_bytes);
+    const float* s_of = vectors ? vectors + g * K : s_point;
+    const int64_t s_bytes = vectors ? K * 4 : point_bytes;
     auto activations = K <= 8192 ? point_activations_kernel<true> : point_activations_kernel<false>;
-    hipLaunchKernelGGL(activations, dim3((unsigned)M, points), dim3(256), 0, st, (const uint4*)x_fp16, s_point, kvec,
+    hipLaunchKernelGGL(activations, dim3((unsigned)M, points), dim3(256), 0, st, (const uint4*)x_fp16, s_of, s_bytes, kvec,
                        point_bytes, a_q, s_a);
     static constexpr decltype(&point_weights_kernel<0>) kWeights[9] = {
         point_weights_kernel<0>, point_weights_kernel<1>, point_weights_kernel<2>, point_weights_kernel<3>, point_weights_kernel<4>,
         point_weights_kernel<5>, point_weights_kernel<6>, point_weights_kernel<7>, point_weights_kernel<8>};
     const auto weights = kWeights[K <= 4096 ? (K + 511) / 512 : 0];
-    hipLaunchKernelGGL(weights, dim3((unsigned)(N / 16), points), dim3(256), 0, st, (const uint4*)w_fp16, s_point, N, kvec,
+    hipLaunchKernelGGL(weights, dim3((unsigned)(N / 16), points), dim3(256), 0, st, (const uint4*)w_fp16, s_of, s_bytes, N, kvec,
                        point_bytes, packed, s_w);
     if ((rc = check_launch("smoothing grid point")) != QQQ_OK) return rc;
     p.loss = losses + g;
     if ((rc = launch_gemm_loss(p, (int)points, st)) != QQQ_OK) return rc;
   }
-  hipLaunchKernelGGL(argmin_kernel, dim3(1), dim3(64), 0, st, losses, grid_points, best);
-  if ((rc = check_launch("argmin")) != QQQ_OK) return rc;
-  return launch_smooth(x_fp16, w_fp16, absmax, sigmas, best, M, N, K, xs_fp16, ws_fp16, s, st);
+  return finish();
 }
 
 }  // extern "C"
