@@ -10,6 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libqqq.so")
+CALL = os.path.join(HERE, "_qqq_call.so")  # the linear calls' native marshalling (Python extension)
 SOURCES = ["qqq_api.hip", "qqq_pack.hip", "qqq_quant_act.hip", "qqq_gemm_skinny.hip",
            "qqq_gemm_prefill_dma.hip", "qqq_gemm_prefill_ring.hip", "qqq_group_bias.hip", "qqq_quant_weight.hip", "qqq_probes.hip", "qqq_calib.hip",
            "qqq_hessian.hip", "qqq_compensate.hip"]
@@ -23,6 +24,25 @@ def hipcc() -> str:
         if c and (os.path.sep not in c or os.path.exists(c)):
             return c
     raise RuntimeError("hipcc not found")
+
+
+def build_call() -> str:
+    """Compiles the Python extension against this interpreter and torch; returns its path."""
+    import sysconfig
+
+    import torch
+    base = os.path.join(os.path.dirname(torch.__file__))
+    inc = os.path.join(base, "include")
+    tmp = CALL + ".tmp.%d" % os.getpid()
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", sysconfig.get_paths()["include"], "-isystem", inc,
+           "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), os.path.join(CSRC, "qqq_torch_call.cpp"), "-o", tmp,
+           "-L", os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed for qqq_torch_call.cpp:\n" + r.stdout + r.stderr)
+    os.replace(tmp, CALL)
+    return CALL
 
 
 def build(verbose: bool = False, extra_flags=(), out_dir: str = None) -> str:
@@ -45,8 +65,11 @@ def build(verbose: bool = False, extra_flags=(), out_dir: str = None) -> str:
             print(out, file=sys.stderr)
         return obj
 
-    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
+        call = ex.submit(build_call) if out_dir is None else None
         objs = list(ex.map(one, SOURCES))
+        if call is not None:
+            call.result()
     tmp = lib_path + ".tmp.%d" % os.getpid()
     r = subprocess.run([cc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs],
                        capture_output=True, text=True)

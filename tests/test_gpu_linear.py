@@ -198,3 +198,52 @@ def test_linear_argument_errors():
         qqq.qqq_linear_w4a8_perchannel(a, w, s_w, small)
     assert e.value.code == 3
     assert qqq.qqq_linear_workspace_bytes(M, N, K + 1) == 0
+
+
+class _Marked(torch.Tensor):
+    pass
+
+
+class _Through(torch.overrides.TorchFunctionMode):
+    def __torch_function__(self, func, types, args=(), kwargs=None):
+        return func(*args, **(kwargs or {}))
+
+
+@pytest.mark.parametrize("M,K,N,hi", [(1, 4096, 1024, 0), (3, 1024, 272, 16), (70, 512, 256, 16)])
+def test_linear_marshalled_natively_and_in_python(M, K, N, hi, monkeypatch):
+    """The extension takes plain calls, row strides and given outputs among them; it declines subclasses, function modes and wrong arguments, which
+    then go the way of the binding's own path: same results, same errors."""
+    a = synth.activations_fp16(M, 2 * K, 3 + M)
+    d_a = to_dev(a.view(np.uint16), torch)[:, :K]
+    d_w = qqq.qqq_pack_w4(to_dev(synth.random_w_nat(N, K, 5), torch), K)
+    d_sw = to_dev(synth.weight_scales_fp16(N, 6, 0.001, 0.005).view(np.uint16), torch)
+    d_sg = to_dev(synth.group_scales(K, N, 8, 1, hi), torch) if hi else None
+    ws = qqq.new_linear_workspace(M, N, K)
+    native = qqq._native_linear
+
+    def call(x, w=d_w, **kw):
+        return qqq.qqq_linear_w4a8_pergroup(x, w, d_sg, d_sw, ws, sg_max=16, **kw) if hi else qqq.qqq_linear_w4a8_perchannel(x, w, d_sw, ws, **kw)
+
+    assert native(d_a, d_w, d_sg, d_sw, ws, None, None, 128, 16, torch.cuda.current_stream().cuda_stream).shape == (M, N)
+    y0 = call(d_a)
+    out, acc = torch.empty_like(y0), torch.empty((M, N), dtype=torch.int32, device="cuda")
+    assert call(d_a, y=out, acc_out=acc) is out and torch.equal(out, y0)
+    assert y0.dtype == torch.float16 and not y0.requires_grad and y0.is_contiguous()
+    with torch.cuda.stream(torch.cuda.Stream()):
+        y1 = call(d_a)
+    torch.cuda.synchronize()
+    declined = []
+    monkeypatch.setattr(qqq, "_native_linear", lambda *args: declined.append(native(*args)) or declined[-1])
+    assert torch.equal(call(d_a.as_subclass(_Marked)), y0) and declined[-1] is None
+    with _Through():
+        y2 = call(d_a)
+    assert declined[-1] is None and torch.equal(y1, y0) and torch.equal(y2, y0)
+    for bad in (d_a.float(), d_a.t(), d_a[0]):
+        with pytest.raises(ValueError):
+            call(bad)
+        assert declined[-1] is None
+    with pytest.raises(ValueError):
+        call(d_a, w=d_w.cpu())
+    with pytest.raises(qqq.QQQError) as e:
+        call(d_a, w=d_w[1:])                             # not 16-byte aligned: the library's own check
+    assert e.value.code == 2 and declined[-1] == 2
