@@ -31,6 +31,7 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 
 constexpr int kFB = 64;    // channels per factorisation block
 constexpr int kSB = 128;   // channels per sweep block (= a group of the per-group quantiser)
+constexpr int kCarried = 4;  // update tiles that go with a sweep, for each workgroup that fits beside it
 constexpr int kSO = 512;  // channels after which the rest of the weights is updated
 static_assert(kSB == QQQ_GROUP && kSB == 128, "a sweep block is one group");
 
@@ -767,15 +768,25 @@ __device__ __forceinline__ Tile upper_tile(int u) {
 // its move once the block's earlier channels have had theirs; with none of them quantised yet, the move z of
 // all channels solves z R = P over the block's triangle (z = P for its first channel).
 // W64 is overwritten with W_i - q s, the left operand of the update of the channels after.
+// The first `sweepers` workgroups do that; the others, one to a CU beside them, take 64 x 64 tiles of what the 512 channels before these owe to
+// columns that neither they nor these touch (Carried): products for matrix cores that the chains leave idle most of the time, though a chain's fp64
+// steps wait for them (wave priorities change nothing), so most tiles stay with f64_update_kernel, three workgroups a CU.  us with none / 2 / 4 / 8 for each
+// workgroup that fits beside the sweep: K = N = 4096 3327 / 3290 / 3262 / 3299, K = 2048, N = 5632 with group scales 1537 / 1499 / 1473 / 1471 (whole calls).
+struct Carried { const double *A, *B; double* C; int N, cols, rows_of_tiles; };  // as f64_update_kernel's operands, kSO deep
 template <bool GROUP>
 __global__ __launch_bounds__(256, 2) void sweep_kernel(const _Float16* w, const double* A, int ld, const double* keep, int64_t N,
                                                     int64_t K, int o0, int o1, uint16_t* scales, double* W64,
-                                                    uint32_t* w_nat) {
+                                                    uint32_t* w_nat, int sweepers, const Carried cr) {
   constexpr int kRows = 16 * (16 * 36 + 8);  // doubles: 16 rows of 129 - 16 r for r = 0 .. 7
   // in the same place before R is: the product's 16 rows of the left operand and of the result
   constexpr int kLs = kSO - kSB + 2, kXs = kSB + 2;
   static_assert(16 * (kLs + kXs) <= kRows, "the product's operand and result fit");
   __shared__ __attribute__((aligned(16))) double rl[kRows + 64];  // (a step reads up to three vectors of 16 past its row)
+  if ((int)blockIdx.x >= sweepers) {
+    const int u = (int)blockIdx.x - sweepers;
+    update_tile(cr.A, K, cr.B, ld, cr.C, K, cr.N, cr.cols, kSO, u % cr.rows_of_tiles, u / cr.rows_of_tiles, rl, rl + 64 * kAs);
+    return;
+  }
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, q = lane >> 4;
   const int64_t n0 = (int64_t)blockIdx.x * 16;
@@ -1091,15 +1102,21 @@ int begin(const char* who, const void* w_fp16, const double* H, int64_t N, int64
 template <bool GROUP>
 int sweep(const Work& wk, const void* w_fp16, int64_t N, int64_t K, uint16_t* scales, uint32_t* w_nat, hipStream_t st) {
   // kSO channels at a time; all channels after those are moved by them together: passes over the running weights kept few,
-  // and products deep enough for the matrix cores
+  // and products deep enough for the matrix cores.  The next kSO channels need that at once; of the others the last ones go along with the next kSO's
+  // sweep, whose chains leave the matrix cores idle: as many tiles as the workgroups that fit beside it get done in its time.
+  const int sweepers = (int)((N + 15) / 16), row_tiles = (int)((N + 63) / 64), beside = 2 * num_cus() - sweepers;
+  const int64_t carry = (int64_t)(beside > 0 ? beside * kCarried / row_tiles : 0) * 64;
+  Carried cr = {};
   for (int64_t o0 = 0; o0 < K; o0 += kSO) {
-    const int64_t o1 = o0 + kSO < K ? o0 + kSO : K;
-    hipLaunchKernelGGL((sweep_kernel<GROUP>), dim3((unsigned)((N + 15) / 16)), dim3(256), 0, st, (const _Float16*)w_fp16,
-                       wk.A, wk.ld, wk.keep, N, K, (int)o0, (int)o1, scales, wk.W64, w_nat);
-    if (o1 < K)
-      hipLaunchKernelGGL(f64_update_kernel, dim3((unsigned)((K - o1 + 63) / 64), (unsigned)((N + 63) / 64)),
-                         dim3(256), 0, st, wk.W64 + o0, K, wk.A + o0 * wk.ld + o1, wk.ld, wk.W64 + o1, K, (int)N, (int)(K - o1),
-                         (int)kSO);
+    const int64_t o1 = o0 + kSO < K ? o0 + kSO : K, o2 = o1 + kSO < K ? o1 + kSO : K;
+    const int tiles = cr.cols ? row_tiles * ((cr.cols + 63) / 64) : 0;
+    hipLaunchKernelGGL((sweep_kernel<GROUP>), dim3((unsigned)(sweepers + tiles)), dim3(256), 0, st, (const _Float16*)w_fp16,
+                       wk.A, wk.ld, wk.keep, N, K, (int)o0, (int)o1, scales, wk.W64, w_nat, sweepers, cr);
+    if (o1 == K) break;
+    const int64_t from = K - o2 > carry ? K - carry : o2;  // columns from here on go with the next sweep
+    hipLaunchKernelGGL(f64_update_kernel, dim3((unsigned)((from - o1 + 63) / 64), (unsigned)row_tiles), dim3(256), 0, st,
+                       wk.W64 + o0, K, wk.A + o0 * wk.ld + o1, (int64_t)wk.ld, wk.W64 + o1, K, (int)N, (int)(from - o1), kSO);
+    cr = {wk.W64 + o0, wk.A + o0 * wk.ld + from, wk.W64 + from, (int)N, (int)(K - from), row_tiles};
   }
   return check_launch("gptq sweep");
 }

@@ -277,3 +277,25 @@ def test_factorisation_on_a_workspace_in_use(K, N, shift):
         torch.cuda.synchronize()
         assert np.array_equal(f16_bits(s_w), s_bits) and np.array_equal(codes_of(w_nat, K), codes), seed
         assert (buf[:shift] == 0xFF).all() and (buf[shift + need:] == 0xFF).all()
+
+
+@pytest.mark.parametrize("K,N", [(2176, 33), (1800, 1040)])
+def test_updates_that_go_with_the_next_sweep(K, N):
+    """More than three sweeps: the last columns receive a sweep's moves beside the next one, in one row of tiles and in several, a ragged last
+    tile of columns among them.  Against a 64-bit torch sweep by the explicit inverse; the bar as above."""
+    g = torch.Generator(device="cuda").manual_seed(78)
+    x = torch.randn((900, 48), generator=g, device="cuda") @ torch.randn((48, K), generator=g, device="cuda") * 0.2
+    x = (x + torch.randn(x.shape, generator=g, device="cuda")).to(torch.float16).to(torch.float64)
+    H = 2.0 * (x.t().contiguous() @ x)
+    w = (torch.randn((N, K), generator=g, device="cuda") * 0.03).to(torch.float16)
+    w_nat, s_w = qqq.qqq_gptq_quantize_w4_perchannel(w, H, 0.01)
+    damped = H + 0.01 * H.diagonal().mean() * torch.eye(K, dtype=torch.float64, device="cuda")
+    U = torch.linalg.cholesky(torch.cholesky_inverse(torch.linalg.cholesky(damped)), upper=True)
+    U = U / U.diagonal()[:, None]
+    run, s = w.to(torch.float64), s_w.to(torch.float64)
+    codes = torch.zeros_like(run)
+    for i in range(K):
+        codes[:, i] = torch.round((run[:, i] / s).to(torch.float32)).clamp_(-7, 7)
+        run[:, i + 1:] -= (run[:, i] - codes[:, i] * s)[:, None] * U[i, i + 1:]
+    got = orc.w8_perchannel(w_nat.cpu().numpy().view(np.uint32), K)
+    assert np.array_equal(got, codes.cpu().numpy().astype(got.dtype))
