@@ -285,8 +285,8 @@ __global__ __launch_bounds__(256, 3) void f64_update_kernel(const double* A, int
 // task needs only earlier ones and the chain's earlier blocks, so that a drawn task's waits end however few workgroups run beside it.  There are two
 // queues, a workgroup in three on the one that the chain waits for (solves, updates by one panel), the others on the updates by four panels at once, whose
 // tasks are long; three workgroups keep chain and queues going.  What a task needs is told by flags: a block factored, a tile solved, the number of panels that a tile has received.
-// Tiles receive the panels of their own four blocks (kOuter) and of the next four one by one, and those of later blocks four at a time, during the steps of
-// the four blocks after them; the columns that turn to single panels next come first, in 64 x 64 tiles, the others in 128 x 128.
+// Tiles receive the panels of their own four blocks (kOuter) one by one, those of the next four two at a time, and those of later blocks four at a time, during the
+// steps of the four blocks after them; the columns whose turn to factor comes next first, in 64 x 64 tiles, the others in 128 x 128.
 // Between XCDs caches are coherent at kernel boundaries only, so what one workgroup writes for another goes through to memory (agent-scope
 // stores, a wait, then the flag).  R D is kept transposed below the diagonal, each line written once and read only after its flag, so updates read it
 // with plain loads, and take R from it too (x = y / d, the same bits); tiles that change are read at agent scope.
@@ -325,23 +325,24 @@ __device__ __forceinline__ void publish(uint32_t* flag, uint32_t v) {
   if (threadIdx.x == 0) agent_store(flag, v);
 }
 
-// The tasks of one step (block k) in order: far updates of the four blocks before last by the last four (those columns get block k's panel
-// next), a quarter of the other far updates, the solves of panel k, its near updates.
+// The tasks of one step (block k).  In order, one queue: far updates, i.e. by the four panels after block k's four, of the four blocks before
+// these (whose turn comes next), then a quarter of the others.  The other queue: the solves of panel k, its updates of its own four blocks and, every
+// second step, those of the four before by two panels.
 struct Tasks {
   int k, g, nb, p0, np;  // g: block k's four; panels [p0, p0 + np) of the four after
-  int n_next, far0, n_far, n_solve, n_near;
+  int n_next, far0, n_far, n_solve, n_near, n_pair;
   __device__ __forceinline__ Tasks(int nb_, int k_) : k(k_), g(k_ / kOuter), nb(nb_) {
     p0 = kOuter * (g + 1);
     np = p0 < nb ? min(kOuter, nb - p0) : 0;
-    const int n = max(kOuter * (g - 1), 0), wide = triangle(n / 2), quarter = p0 - 1 - k;
-    n_next = np && k == p0 - 1 && g > 0 ? triangle(kOuter * g) - triangle(n) : 0;
+    const int own = kOuter * g, n = max(own - kOuter, 0), wide = triangle(n / 2), quarter = p0 - 1 - k;
+    n_next = np && k == p0 - 1 && g > 0 ? triangle(own) - triangle(n) : 0;
     far0 = np ? wide * quarter / kOuter : 0;
     n_far = np ? wide * (quarter + 1) / kOuter - far0 : 0;
     n_solve = max(k - 1, 0);
-    n_near = k > 0 ? triangle(k) - triangle(n) - 1 : 0;
+    n_near = k > own ? triangle(k) - triangle(own) - 1 : 0;
+    n_pair = g > 0 && (k == own || (k == own + 1 && own + 2 < nb)) ? triangle(own) - triangle(n) : 0;
   }
   static __device__ __forceinline__ int triangle(int n) { return n * (n + 1) / 2; }
-  __device__ __forceinline__ int count() const { return n_next + n_far + n_solve + n_near; }
 };
 struct Tile64 { int i, j; };
 // tile number u of a triangle counted from its last: columns from the last, rows from the diagonal up
@@ -675,7 +676,7 @@ __global__ __launch_bounds__(256, 1) void factor_kernel(const Factor f) {
   int queue = number % 3 == 1 ? 1 : 2, base = 0;
   Tasks step(nb, nb - 1);
   for (int ticket = draw(queue);; ticket = draw(queue)) {
-    auto count = [&]() { return queue == 1 ? step.n_solve + step.n_near : step.n_next + step.n_far; };
+    auto count = [&]() { return queue == 1 ? step.n_solve + step.n_near + step.n_pair : step.n_next + step.n_far; };
     while (ticket - base >= count() && step.k > 0) {
       base += count();
       step = Tasks(nb, step.k - 1);
@@ -710,10 +711,24 @@ __global__ __launch_bounds__(256, 1) void factor_kernel(const Factor f) {
       solve_rows(f, i, c0, rows, ys, xs, rcp);
       publish(f.solved + (int64_t)k * nb + i, 1u);
     } else if (u >= solve0 || u < step.n_next) {
-      const bool near = u >= solve0;
-      const Tile64 t = near ? tile_from_last(Tasks::triangle(k), u - solve0 - step.n_solve + 1)  // (the first is the chain's)
-                            : tile_from_last(Tasks::triangle(kOuter * step.g), u);
-      const int p0 = near ? k : step.p0, np = near ? 1 : step.np;
+      const int near = u - solve0 - step.n_solve, pair = near - step.n_near;
+      Tile64 t;
+      int p0 = step.p0, np = step.np;
+      if (near < 0) {
+        t = tile_from_last(Tasks::triangle(kOuter * step.g), u);
+      } else if (pair < 0) {
+        t = tile_from_last(Tasks::triangle(k), near + 1);  // (the first is the chain's)
+        p0 = k;
+        np = 1;
+      } else {
+        t = tile_from_last(Tasks::triangle(kOuter * step.g), pair);
+        p0 = kOuter * step.g + (k == kOuter * step.g ? 0 : 2);
+        np = min(2, nb - p0);
+        if (k == kOuter * step.g && pair == 0) {  // (the chain takes panel k off the tile that it factors next)
+          ++p0;
+          if (--np == 0) continue;
+        }
+      }
       // lanes 0 .. 3 and 4 .. 7: the panels' tiles i and j; lane 8: the tile itself
       const uint32_t* flag = lane < 8 ? f.solved + (int64_t)min(p0 + (lane & 3), nb - 1) * nb + (lane < 4 ? t.i : t.j) : f.applied + (int64_t)t.i * nb + t.j;
       await(flag, lane < 8 ? 1u : (uint32_t)(nb - p0 - np), lane < 8 ? (lane & 3) < np : lane == 8);
