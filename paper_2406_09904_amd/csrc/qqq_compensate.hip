@@ -15,9 +15,9 @@
 //   sweep          per 512 channels, from the first: sweep_kernel, then the update of the channels after
 // What is left serial is one dependent step per channel, in registers.
 // Bound, without the Hessian: K = N = 4096 holds 2.3e10 + 6.9e10 fp64 operations, 1.2 ms at the nominal 78.6 TFLOP/s of the
-// fp64 matrix cores (1.7 ms at the 54 that f64_update_kernel reaches).  Measured, K = N = 4096: 3.0 ms, and 3.3 ms with the
+// fp64 matrix cores (1.7 ms at the 54 that f64_update_kernel reaches).  Measured, K = N = 4096: 2.9 ms, and 3.2 ms with the
 // Hessian of 2048 tokens (an inverse by K rank-1 sweeps and a rank-1 update of both matrices per channel: 360 ms); K = 2048,
-// N = 5632 with group scales: 1.5 ms, 1.55 ms with the Hessian of 1111 tokens (81 ms).
+// N = 5632 with group scales: 1.4 ms, 1.47 ms with the Hessian of 1111 tokens (81 ms).
 #include "qqq_calib.h"
 #include "qqq_internal.h"
 
@@ -291,9 +291,9 @@ __global__ __launch_bounds__(256, 3) void f64_update_kernel(const double* A, int
 // stores, a wait, then the flag).  R D is kept transposed below the diagonal, each line written once and read only after its flag, so updates read it
 // with plain loads, and take R from it too (x = y / d, the same bits); tiles that change are read at agent scope.
 // One workgroup a CU: with two, solves and updates on a CU held each other up and the chain with them (K = 4096, 64 x 64 tiles only: 2530 us, 1660 with one).
-// us, K = 1024 / 2048 / 4096: about 270 / 570 / 1470 (a launch per block, its workgroups all factoring the tile again, with the updates carried in or between:
-// 385 / 800 / 1960).  A block of the chain takes 16.5 us of waiting for nobody: the tile 7.7, the row tile 3.6, off the next tile 2.1, flags and loads 3.
-// At K = 4096 the first half of the blocks waits for updates: a 64 x 64 tile takes 5 us for one panel, 15 for four, a 128 x 128 tile 45 for four.
+// us, K = 2048 / 4096: 536 / 1220 (a launch per block, its workgroups all factoring the tile again, with the updates carried in or between: 800 / 1960).
+// A block of the chain takes 16.5 us of waiting for nobody: the tile 7.7, the row tile 3.6, off the next tile 2.1, flags and loads 3.
+// At K = 4096 the first half of the blocks waits for updates: a 64 x 64 tile takes 5 us for one panel, 7 for two, 15 for four, a 128 x 128 tile 44 for four.
 constexpr int kOuter = 4;
 constexpr int kS = 66;  // row stride of a 64 x 64 block in LDS
 
