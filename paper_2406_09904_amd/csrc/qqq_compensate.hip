@@ -284,7 +284,7 @@ __global__ __launch_bounds__(256, 3) void f64_update_kernel(const double* A, int
 // next to it and takes that off the next tile, without leaving its CU.  All other workgroups draw tickets for the rest (Tasks), in a fixed order in which a
 // task needs only earlier ones and the chain's earlier blocks, so that a drawn task's waits end however few workgroups run beside it.  There are two
 // queues, a workgroup in three on the one that the chain waits for (solves, updates by one panel), the others on the updates by four panels at once, whose
-// tasks are long; three workgroups keep chain and queues going.  What a task needs is told by flags: a block factored, a tile solved, the number of panels that a tile has received.
+// tasks are long; three workgroups keep chain and queues going (a stream's CU mask leaves it a CU of each XCD at least, eight workgroups).  What a task needs is told by flags: a block factored, a tile solved, the number of panels that a tile has received.
 // Tiles receive the panels of their own four blocks (kOuter) one by one, those of the next four two at a time, and those of later blocks four at a time, during the
 // steps of the four blocks after them; the columns whose turn to factor comes next first, in 64 x 64 tiles, the others in 128 x 128.
 // Between XCDs caches are coherent at kernel boundaries only, so what one workgroup writes for another goes through to memory (agent-scope
@@ -1102,7 +1102,7 @@ int begin(const char* who, const void* w_fp16, const double* H, int64_t N, int64
   f.factored = flags + 32;
   f.applied = f.factored + f.nb;
   f.solved = f.applied + (size_t)f.nb * f.nb;
-  // two workgroups of it fit a CU; the chain and a tile for each of the others
+  // one workgroup of it fits a CU: the chain, and a tile for each of the others
   const int tiles = f.nb * (f.nb - 1) / 2;
   hipLaunchKernelGGL(factor_kernel, dim3((unsigned)(1 + min(tiles, num_cus() - 1))), dim3(256), 0, st, f);
   if ((rc = check_launch("gptq factorisation")) != QQQ_OK) return rc;

@@ -299,3 +299,49 @@ def test_updates_that_go_with_the_next_sweep(K, N):
         run[:, i + 1:] -= (run[:, i] - codes[:, i] * s)[:, None] * U[i, i + 1:]
     got = orc.w8_perchannel(w_nat.cpu().numpy().view(np.uint32), K)
     assert np.array_equal(got, codes.cpu().numpy().astype(got.dtype))
+
+
+def _compensate(w, H):
+    return qqq.qqq_gptq_quantize_w4_perchannel(w, H, 0.01)
+
+
+@pytest.mark.parametrize("K,N,cus", [(200, 20, 8), (1032, 33, 8), (1288, 33, 16)])
+def test_compensation_on_a_stream_confined_to_a_few_cus(K, N, cus):
+    """The narrowest CU masks that a stream takes, a CU or two of each XCD: most of the factorisation's workgroups start when others are through."""
+    import ctypes
+
+    x, w = layer(2 * K + 10, K, N, 800 + K)
+    d_w, H = dev16(w), torch.from_numpy(cal.hessian(x)).cuda()
+    want = _compensate(d_w, H)
+    torch.cuda.synchronize()
+    hip = ctypes.CDLL("libamdhip64.so")
+    handle, mask = ctypes.c_void_p(), (ctypes.c_uint32 * 8)((1 << cus) - 1)
+    assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(handle), 8, mask) == 0
+    with torch.cuda.stream(torch.cuda.ExternalStream(handle.value)):
+        got = _compensate(d_w, H)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(want, got))
+    hip.hipStreamDestroy(handle)
+
+
+def test_compensation_captured_and_replayed():
+    """Flags and tickets start anew in every replay, also with other inputs and eager calls in between."""
+    K, N = 712, 48
+    layers = []
+    for seed in (5, 6):
+        x, w = layer(2 * K + 10, K, N, 810 + seed)
+        layers.append((dev16(w), torch.from_numpy(cal.hessian(x)).cuda()))
+    want = [_compensate(*one) for one in layers]
+    d_w, H = (t.clone() for t in layers[0])
+    _compensate(d_w, H)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        got = _compensate(d_w, H)
+    for i in (0, 1, 1, 0):
+        d_w.copy_(layers[i][0])
+        H.copy_(layers[i][1])
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(want[i], got)), i
+        _compensate(*layers[1 - i])
