@@ -30,7 +30,7 @@ extern "C" {
  *   Q(X') = qqq_quant_act, Q(W') = qqq_quantize_w4_perchannel, their product the exact int32
  *   accumulator of qqq_gemm_w4a8_perchannel times s_a[m] s_w[n] in fp64; X W^T by an fp16 MFMA
  *   GEMM with fp32 accumulation; the loss summed in fp64; the first minimum over the grid wins.
- * Outputs: xs_fp16 [M,K] and ws_fp16 [N,K], the smoothed layer for the winning threshold;
+ * Outputs: xs_fp16 [M,K] and ws_fp16 [N,K], the smoothed layer for the winning threshold (each may be its input's own place);
  *   s [K] fp32 its smoothing vector; sigmas [G] fp32; losses [G] fp64; best [1] int32 (0-based
  *   grid index).  1 <= grid_points <= 256.
  * workspace: qqq_smoothing_workspace_bytes(M,N,K) bytes, contents irrelevant on entry.

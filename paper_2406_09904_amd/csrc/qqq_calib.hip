@@ -661,8 +661,13 @@ int qqq_adaptive_smoothing(const void* x_fp16, const void* w_fp16, int64_t M, in
   p.y_ref = y_ref;
   p.point_bytes = point_bytes;
   const int kvec = (int)(K / 8);
-  // all points' smoothing vectors at once where the smoothed weights' place, which is written last, holds them
-  float* vectors = 2 * grid_points <= N ? (float*)ws_fp16 : nullptr;
+  // all points' smoothing vectors at once where the smoothed weights' place, which is written last, holds them and no input lies in it (a layer may be
+  // smoothed in place)
+  const auto holds = [&](const void* in, int64_t rows) {
+    const uintptr_t at_in = reinterpret_cast<uintptr_t>(in), at_ws = reinterpret_cast<uintptr_t>(ws_fp16);
+    return at_in < at_ws + (uintptr_t)N * K * 2 && at_ws < at_in + (uintptr_t)rows * K * 2;
+  };
+  float* vectors = 2 * grid_points <= N && !holds(w_fp16, N) && !holds(x_fp16, M) ? (float*)ws_fp16 : nullptr;
   if (vectors)
     hipLaunchKernelGGL(smoothing_vector_kernel, dim3((unsigned)((K + 255) / 256), (unsigned)grid_points), dim3(256), 0, st, absmax,
                        sigmas, K, vectors, K * 4);

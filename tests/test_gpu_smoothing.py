@@ -54,6 +54,30 @@ def test_grid_points_equal_their_steps(M, K, N, G, route):
     assert torch.equal(got["xs"], xs) and torch.equal(got["ws"], ws) and torch.equal(got["s"], s)
 
 
+def _search(x, w, G, xs, ws):
+    """The C entry point with the caller's outputs."""
+    (M, K), N = x.shape, w.shape[0]
+    s, sigmas = torch.empty(K, device="cuda"), torch.empty(G, device="cuda")
+    losses, best = torch.empty(G, dtype=torch.float64, device="cuda"), torch.empty(1, dtype=torch.int32, device="cuda")
+    work = torch.empty(int(qqq.lib().qqq_smoothing_workspace_bytes(M, N, K)), dtype=torch.uint8, device="cuda")
+    rc = qqq.lib().qqq_adaptive_smoothing(x.data_ptr(), w.data_ptr(), M, N, K, G, xs.data_ptr(), ws.data_ptr(), s.data_ptr(), sigmas.data_ptr(),
+                                          losses.data_ptr(), best.data_ptr(), work.data_ptr(), work.numel(), torch.cuda.current_stream().cuda_stream)
+    assert rc == 0, qqq.lib().qqq_last_error()
+    return s, sigmas, best, losses
+
+
+@pytest.mark.parametrize("M,K,N,G", [(20, 256, 64, 9), (70, 4096, 144, 9), (300, 512, 2064, 9), (40, 6144, 256, 1)])
+def test_search_in_place(M, K, N, G):
+    """The smoothed layer may take the layer's own place: bit for bit what it is elsewhere (the losses but for the order of fp64 sums)."""
+    x = torch.from_numpy(synth.activations_fp16(M, K, 730 + M, "normal", 4 / K, 40.0)).cuda()
+    w = torch.from_numpy(synth.weights_fp16(N, K, 731 + M)).cuda()
+    xs, ws = torch.empty_like(x), torch.empty_like(w)
+    want = _search(x, w, G, xs, ws)
+    got = _search(x, w, G, x, w)
+    assert torch.equal(x, xs) and torch.equal(w, ws)
+    assert all(torch.equal(a, b) for a, b in zip(want[:3], got[:3])) and torch.allclose(want[3], got[3], rtol=1e-12, atol=0.0)
+
+
 @pytest.mark.parametrize("M,K,N,tile", [
     (1, 16, 1, "32x32"), (65, 48, 129, "32x32"), (64, 64, 128, "32x32"), (130, 80, 255, "32x32"), (257, 16, 9000, "32x32"),
     (33, 256, 7000, "32x32"), (33, 1040, 300, "64x128"), (65, 1296, 129, "64x128"), (64, 320, 128, "64x128"), (130, 336, 255, "64x128"),
