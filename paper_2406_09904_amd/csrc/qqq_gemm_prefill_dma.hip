@@ -515,11 +515,12 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_prefill_dma_kernel(const Gemm
     // fp64(acc) * fp64(s_a) * fp64(s_w) - fp64(y_ref), squared and summed in fp64 (acc carries the exact factor 16).  Reference values are
     // requested sixteen at a time, ahead of the sixteen (in the smaller tiles 32) before them (M = 512, K = N = 4096, eight grid points 69 us with half a
     // channel's values requested, waited for and used in turn, and a branch per element, 56 so).  Rows past M repeat the last one's and
-    // channels past N the first's; their token and channel scales and references count as 0, so nothing here is conditional.
+    // channels past N the first's; their differences lose their upper halves, whatever they are (an infinite channel scale times a token scale of 0 would
+    // be NaN): what is left is below 2^-1042, its square 0.  A selection: through an asm statement, or the compiler makes a branch per element of it.
     static_assert(S::kLds >= NW * 512 + NW * S::kBM * 4, "the partial sums and every wave's copy of the token scales");
     float* sa = (float*)(lds + NW * 512) + wave * S::kBM;
 #pragma unroll
-    for (int i = 0; i < kSaPerLane; ++i) sa[lane + 64 * i] = m0 + lane + 64 * i < M ? sa_own[i] : 0.0f;
+    for (int i = 0; i < kSaPerLane; ++i) sa[lane + 64 * i] = sa_own[i];
     constexpr int kPer = 16 / kRegs, kParts = TM / kPer;  // row tiles of a part, parts of a channel tile
     constexpr int kAll = TC * kParts, kAheadParts = CT == 2 ? 1 : 2;
     float y[kAheadParts + 1][kPer][kRegs];
@@ -545,8 +546,11 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_prefill_dma_kernel(const Gemm
 #pragma unroll
         for (int v = 0; v < kRegs; ++v) {
           const int r = acc_row(first + mt, v);
-          const float ref = m0 + r < M && nvalid[c] ? y[part % (kAheadParts + 1)][mt][v] : 0.0f;
-          const double d = (double)(acc[first + mt][c][v] >> 4) * (double)sa[r] * sw - (double)ref;
+          const double t = (double)(acc[first + mt][c][v] >> 4) * (double)sa[r] * sw - (double)y[part % (kAheadParts + 1)][mt][v];
+          uint2 bits = __builtin_bit_cast(uint2, t);
+          asm("" : "+v"(bits.y));
+          bits.y = m0 + r < M && nvalid[c] ? bits.y : 0u;
+          const double d = __builtin_bit_cast(double, bits);
           sum += d * d;
           if (v % 4 == 3) asm volatile("" : "+v"(sum));  // (else the squares of all are kept until the end: 149 registers spilled)
         }

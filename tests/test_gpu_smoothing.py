@@ -78,6 +78,34 @@ def test_search_in_place(M, K, N, G):
     assert all(torch.equal(a, b) for a, b in zip(want[:3], got[:3])) and torch.allclose(want[3], got[3], rtol=1e-12, atol=0.0)
 
 
+@pytest.mark.parametrize("M,K,N,G,tile", [(20, 256, 144, 8, "64x128"), (87, 128, 2832, 23, "128x128"), (300, 512, 2064, 9, "128x256"),
+                                          (500, 2944, 4080, 8, "128x512")])
+def test_overflowing_points_lose(M, K, N, G, tile):
+    """Points at which a weight overflows, in tiles with rows past M and channels past N: their loss is infinite, as its terms are, and a later,
+    finite one wins.  (One heavy input channel, so that every row's code in it is not 0.)"""
+    g = torch.Generator(device="cuda").manual_seed(740 + M)
+    x = torch.randn((M, K), generator=g, device="cuda") * 0.05
+    x[:, 7] = torch.rand(M, generator=g, device="cuda") + 7.0
+    w = torch.randn((N, K), generator=g, device="cuda") * 0.02
+    w[N // 3, 7] = 12000.0                               # 8 times that is past fp16's 65504
+    x, w = x.to(torch.float16), w.to(torch.float16)
+    got = qqq.qqq_adaptive_smoothing(x, w, G)
+    assert "loss tile=%s" % tile in qqq.last_route(), qqq.last_route()
+    amax, ref = qqq.qqq_channel_absmax(x), qqq.qqq_fp16_gemm_nt(x, w).double()
+    losses = []
+    for i in range(G):
+        xs, ws, _ = qqq.qqq_smooth_apply(x, w, amax, got["sigmas"][i:i + 1].clone())
+        a_q, s_a = qqq.qqq_quant_act(xs)
+        w_nat, s_w = qqq.qqq_quantize_w4_perchannel(ws)
+        acc = torch.empty((M, N), dtype=torch.int32, device="cuda")
+        qqq.qqq_gemm_w4a8_perchannel(a_q, s_a, qqq.qqq_pack_w4(w_nat, K), s_w, qqq.new_workspace(M, N, K), acc_out=acc)
+        losses.append((acc.double() * s_a.double()[:, None] * s_w.double()[None, :] - ref).square().sum())
+    losses = torch.stack(losses)
+    assert torch.isinf(losses[0]) and torch.isfinite(losses[-1])
+    assert torch.allclose(got["losses"], losses, rtol=1e-12, atol=0.0), (got["losses"], losses)
+    assert int(got["best"].item()) == int(torch.argmin(losses).item())
+
+
 @pytest.mark.parametrize("M,K,N,tile", [
     (1, 16, 1, "32x32"), (65, 48, 129, "32x32"), (64, 64, 128, "32x32"), (130, 80, 255, "32x32"), (257, 16, 9000, "32x32"),
     (33, 256, 7000, "32x32"), (33, 1040, 300, "64x128"), (65, 1296, 129, "64x128"), (64, 320, 128, "64x128"), (130, 336, 255, "64x128"),
