@@ -131,6 +131,13 @@ int qqq_set_prefill_tuning(int tune);
  */
 int qqq_set_prefill_ksplit(int k_splits);
 
+/*
+ * Diagnostic knob (host state, not thread-safe): the most workgroups that the factorisation of the qqq_gptq_* calls is launched
+ * with, 0 = automatic (about one per CU).  Any number gives the same bits; with one or two the chain of pivots does the other
+ * work too, as where a launch gets no more CUs than that.  Negative values only query.  Returns the previous value.
+ */
+int qqq_set_factor_workgroups(int most);
+
 #ifdef __cplusplus
 }
 #endif

@@ -29,7 +29,7 @@ SYMBOLS = [
     "qqq_debug_count_sg_violations", "qqq_probe_stream_read", "qqq_probe_mfma_i8", "qqq_probe_prefill_loop",
     "qqq_smoothing_workspace_bytes", "qqq_adaptive_smoothing", "qqq_channel_absmax", "qqq_smooth_apply",
     "qqq_fp16_gemm_nt", "qqq_hessian", "qqq_gptq_workspace_bytes", "qqq_gptq_quantize_w4_perchannel",
-    "qqq_gptq_quantize_w4_pergroup",
+    "qqq_gptq_quantize_w4_pergroup", "qqq_set_factor_workgroups",
 ]
 
 _CALL_PATH = os.path.join(_HERE, "_qqq_call.so")
@@ -114,6 +114,7 @@ def lib():
         L.qqq_set_skinny_tuning.argtypes = [ci, ci, ci, ci]
         L.qqq_set_prefill_tuning.argtypes = [ci]
         L.qqq_set_prefill_ksplit.argtypes = [ci]
+        L.qqq_set_factor_workgroups.argtypes = [ci]
         if os.path.exists(_CALL_PATH):
             _native().bind(*(ctypes.cast(f, vp).value for f in (L.qqq_linear_w4a8_perchannel, L.qqq_linear_w4a8_pergroup)))
         elif torch.cuda.is_available():
@@ -525,3 +526,8 @@ def set_prefill_tuning(waves: int) -> int:
 def set_prefill_ksplit(k_splits: int) -> int:
     """Diagnostic: K splits of the per-tile prefill kernel for 64 < M <= 512 (0 = automatic)."""
     return lib().qqq_set_prefill_ksplit(k_splits)
+
+
+def set_factor_workgroups(most: int) -> int:
+    """Diagnostic: the most workgroups of the compensation's factorisation (0 = automatic)."""
+    return lib().qqq_set_factor_workgroups(most)

@@ -19,7 +19,9 @@
 // Hessian of 2048 tokens (an inverse by K rank-1 sweeps and a rank-1 update of both matrices per channel: 360 ms); K = 2048,
 // N = 5632 with group scales: 1.4 ms, 1.47 ms with the Hessian of 1111 tokens (81 ms).
 #include "qqq_calib.h"
+#include "qqq_factor_schedule.h"
 #include "qqq_internal.h"
+#include "qqq_tuning.h"
 
 #include <type_traits>
 
@@ -281,29 +283,36 @@ __global__ __launch_bounds__(256, 3) void f64_update_kernel(const double* A, int
 // Blocks of 64 channels from the last: block k's diagonal tile is factored (64 dependent pivots), the row tiles i < k above it are solved
 // (y_j = a_j - sum_{k' > j} y_k' R[j,k'], x_j = y_j / d_j: R = x and R D = y there), and every tile (i, j), i <= j < k, gets A -= R[i,k] (R D)[j,k]^T.
 // What bounds it is the chain of all pivots, so one workgroup does nothing else: block after block it factors the tile, solves the row tile
-// next to it and takes that off the next tile, without leaving its CU.  All other workgroups draw tickets for the rest (Tasks), in a fixed order in which a
-// task needs only earlier ones and the chain's earlier blocks, so that a drawn task's waits end however few workgroups run beside it.  There are two
-// queues, a workgroup in three on the one that the chain waits for (solves, updates by one panel), the others on the updates by four panels at once, whose
-// tasks are long; three workgroups keep chain and queues going (a stream's CU mask leaves it a CU of each XCD at least, eight workgroups).  What a task needs is told by flags: a block factored, a tile solved, the number of panels that a tile has received.
+// next to it and takes that off the next tile, without leaving its CU.  All other workgroups draw tickets for the rest (qqq_factor_schedule.h), in a fixed order in
+// which a task needs only earlier ones and the chain's earlier blocks.  There are two queues, a workgroup in three on the one that the chain waits for (solves,
+// updates by one panel), the others on the updates by four panels at once, whose tasks are long.  Three resident workgroups keep chain and queues going.  Where
+// fewer have come (a launch beside others on streams that share a few CUs, a small partition of the chip) the chain does tasks itself when it would
+// wait, in the same order: so the waits end however few workgroups run, one included, and the results have the same bits.  (That costs the launch that has its
+// CUs 0.4 %: K = N = 4096 3197 -> 3211 us a call, K = 2048, N = 5632 with group scales 1465 -> 1469.)  What a task needs is told by flags: a block
+// factored, a tile solved, the number of panels that a tile has received.
 // Tiles receive the panels of their own four blocks (kOuter) one by one, those of the next four two at a time, and those of later blocks four at a time, during the
 // steps of the four blocks after them; the columns whose turn to factor comes next first, in 64 x 64 tiles, the others in 128 x 128.
 // Between XCDs caches are coherent at kernel boundaries only, so what one workgroup writes for another goes through to memory (agent-scope
 // stores, a wait, then the flag).  R D is kept transposed below the diagonal, each line written once and read only after its flag, so updates read it
 // with plain loads, and take R from it too (x = y / d, the same bits); tiles that change are read at agent scope.
 // One workgroup a CU: with two, solves and updates on a CU held each other up and the chain with them (K = 4096, 64 x 64 tiles only: 2530 us, 1660 with one).
-// us, K = 2048 / 4096: 536 / 1220 (a launch per block, its workgroups all factoring the tile again, with the updates carried in or between: 800 / 1960).
+// K = 2048 / 4096: 536 / 1220 us (a launch per block, its workgroups all factoring the tile again, with the updates carried in or between: 800 / 1960).
 // A block of the chain takes 16.5 us of waiting for nobody: the tile 7.7, the row tile 3.6, off the next tile 2.1, flags and loads 3.
 // At K = 4096 the first half of the blocks waits for updates: a 64 x 64 tile takes 5 us for one panel, 7 for two, 15 for four, a 128 x 128 tile 44 for four.
-constexpr int kOuter = 4;
+// A thread's number, new to the compiler: what follows from it is computed where it is used.  (Where the chain does tasks, the compiler would otherwise
+// keep the addresses of all their parts in registers while it factors, 47 to 80 more than there are.)
+__device__ __forceinline__ int thread_id() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
 constexpr int kS = 66;  // row stride of a 64 x 64 block in LDS
 
 struct Factor {
   double* A;        // [K][ld], ld a multiple of 16: a tile's rows are whole cache lines
   double* rcp;      // [K] 1 / d_j
-  uint32_t* ticket;
-  uint32_t* factored;  // [nb]
-  uint32_t* applied;   // [nb][nb]: panels tile (i, j) has received
-  uint32_t* solved;    // [nb][nb]: tile i of panel k, at [k][i]
+  uint32_t* ticket;  // [0]: workgroups that have come; [1], [2]: tasks drawn from the queues
+  uint32_t* flags;   // see Flags
   int K, ld, nb;
 };
 
@@ -325,43 +334,14 @@ __device__ __forceinline__ void publish(uint32_t* flag, uint32_t v) {
   if (threadIdx.x == 0) agent_store(flag, v);
 }
 
-// The tasks of one step (block k).  In order, one queue: far updates, i.e. by the four panels after block k's four, of the four blocks before
-// these (whose turn comes next), then a quarter of the others.  The other queue: the solves of panel k, its updates of its own four blocks and, every
-// second step, those of the four before by two panels.
-struct Tasks {
-  int k, g, nb, p0, np;  // g: block k's four; panels [p0, p0 + np) of the four after
-  int n_next, far0, n_far, n_solve, n_near, n_pair;
-  __device__ __forceinline__ Tasks(int nb_, int k_) : k(k_), g(k_ / kOuter), nb(nb_) {
-    p0 = kOuter * (g + 1);
-    np = p0 < nb ? min(kOuter, nb - p0) : 0;
-    const int own = kOuter * g, n = max(own - kOuter, 0), wide = triangle(n / 2), quarter = p0 - 1 - k;
-    n_next = np && k == p0 - 1 && g > 0 ? triangle(own) - triangle(n) : 0;
-    far0 = np ? wide * quarter / kOuter : 0;
-    n_far = np ? wide * (quarter + 1) / kOuter - far0 : 0;
-    n_solve = max(k - 1, 0);
-    n_near = k > own ? triangle(k) - triangle(own) - 1 : 0;
-    n_pair = g > 0 && (k == own || (k == own + 1 && own + 2 < nb)) ? triangle(own) - triangle(n) : 0;
-  }
-  static __device__ __forceinline__ int triangle(int n) { return n * (n + 1) / 2; }
-};
-struct Tile64 { int i, j; };
-// tile number u of a triangle counted from its last: columns from the last, rows from the diagonal up
-__device__ __forceinline__ Tile64 tile_from_last(int total, int u) {
-  const int v = total - 1 - u;
-  int j = (int)((__builtin_sqrtf(8.0f * (float)v + 1.0f) - 1.0f) * 0.5f);  // column j starts at j (j + 1) / 2
-  while (j * (j + 1) / 2 > v) --j;
-  while ((j + 1) * (j + 2) / 2 <= v) ++j;
-  return {v - j * (j + 1) / 2, j};
-}
-
 // What a tile of EDGE x EDGE at rows 64 i, columns 64 j receives from panels [p0, p0 + np): -= R[rows, panels] (R D)[columns, panels]^T, a wave per
 // quarter of it, 32 channels at a time through two LDS stages: the next one is placed, and the one after it requested, behind half of a
 // stage's products.  Both operands are k-major, R = R D / d is formed on the way.  MFMA layout and row strides as in update_tile.  `mine`: this wave's
 // quarter is wanted (of a 128 x 128 tile on the diagonal three are).
 template <int EDGE>
-__device__ __forceinline__ void factor_update(const Factor& f, int i, int j, int p0, int np, bool mine, double* stages) {
+__device__ __forceinline__ void factor_update(const Factor& f, int tid, int i, int j, int p0, int np, bool mine, double* stages) {
   constexpr int kStride = EDGE + 16, kQ = EDGE / 32, kRows = 512 / EDGE, kLoads = 32 / kRows;  // 16 x 16 tiles a side of a quarter; rows of a load
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, q = lane >> 4;
+  const int lane = tid & 63, wave = tid >> 6, l16 = lane & 15, q = lane >> 4;
   const int wr = (wave >> 1) * (EDGE / 2), wc = (wave & 1) * (EDGE / 2);
   const int k1 = min((p0 + np) * 64, f.K), row0 = tid / (EDGE / 2), col0 = 2 * (tid % (EDGE / 2));
   const double* pa = f.A + 64 * i + col0;
@@ -550,16 +530,16 @@ __device__ __forceinline__ void factor_diagonal(double* ys, double* xs, double* 
 // after them owe (fp64 MFMA), then the 16 one after the other, 16 lanes a row.  u[p][v]: row 16 wave + 4 v + q, column 16 p + l16.  R goes to
 // its place, R D to ys, [column][row].  (All columns after each column in vector multiply-adds: 4.8 us,
 // 2.7 so.)
-__device__ __forceinline__ void load_rows(const Factor& f, int i, int c0, double (&u)[4][4]) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, q = lane >> 4, nb = min(64, f.K - c0);
+__device__ __forceinline__ void load_rows(const Factor& f, int tid, int i, int c0, double (&u)[4][4]) {
+  const int lane = tid & 63, wave = tid >> 6, l16 = lane & 15, q = lane >> 4, nb = min(64, f.K - c0);
 #pragma unroll
   for (int p = 3; p >= 0; --p)
 #pragma unroll
     for (int v = 0; v < 4; ++v)
       u[p][v] = agent_load(f.A + (int64_t)(64 * i + 16 * wave + 4 * v + q) * f.ld + c0 + min(16 * p + l16, nb - 1));
 }
-__device__ __forceinline__ void solve_rows(const Factor& f, int i, int c0, double (&u)[4][4], double* ys, const double* xs, const double* rcp) {
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, q = lane >> 4, nb = min(64, f.K - c0);
+__device__ __forceinline__ void solve_rows(const Factor& f, int tid, int i, int c0, double (&u)[4][4], double* ys, const double* xs, const double* rcp) {
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, q = lane >> 4, nb = min(64, f.K - c0);
 #pragma unroll
   for (int p = 3; p >= 0; --p) {
     v4d acc = {u[p][0], u[p][1], u[p][2], u[p][3]};
@@ -591,162 +571,229 @@ __device__ __forceinline__ void solve_rows(const Factor& f, int i, int c0, doubl
   }
 }
 
-__global__ __launch_bounds__(256, 1) void factor_kernel(const Factor f) {
-  // two blocks of 64 x 64, or two stages of an update of 128 x 128: each workgroup, the chain above all, has its CU to itself
-  __shared__ __attribute__((aligned(16))) double ys[4 * 32 * 144];
-  static_assert(2 * 64 * kS <= 4 * 32 * 144, "the blocks fit");
+// Two blocks of 64 x 64, or two stages of an update of 128 x 128: each workgroup, the chain above all, has its CU to itself
+struct FactorLds {
+  __attribute__((aligned(16))) double ys[4 * 32 * 144];
+  double rcp[64];
+  int ticket, queue;
+};
+static_assert(2 * 64 * kS <= 4 * 32 * 144, "the blocks fit");
+typedef __attribute__((address_space(3))) FactorLds* FactorLdsPtr;
+
+// R of the block at c0 and its 1 / d, as factor_diagonal left them; channels past K are identity.  load() places what the constructor requests
+struct BlockOfR {
+  double r[16], rd;
+  int tid, cols;
+  __device__ __forceinline__ BlockOfR(const Factor& f, int tid_, int c0) : tid(tid_), cols(min(64, f.K - c0)) {
+    const int lane = tid & 63, wave = tid >> 6;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) r[e] = agent_load(f.A + (int64_t)(c0 + min(4 * e + wave, cols - 1)) * f.ld + c0 + lane);
+    rd = agent_load(f.rcp + c0 + min(lane, cols - 1));
+  }
+  __device__ __forceinline__ void place(double* xs, double* rcp) const {
+    const int lane = tid & 63, wave = tid >> 6;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int j = 4 * e + wave;
+      xs[lane * kS + j] = lane < j && j < cols ? r[e] : 0.0;
+    }
+    if (tid < 64) rcp[tid] = tid < cols ? rd : 1.0;
+    lds_barrier();
+  }
+};
+
+// WIDE: a tile of 128 x 128 as one, else as its four of 64 x 64 (the same bits, half the registers)
+template <bool WIDE>
+__device__ __forceinline__ void do_task(const Factor& f, int tid, const Task& t, double* ys, double* rcp) {
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const Flags told = {f.nb};
+  const Need need = need_of(told, t, lane);
+  await(f.flags + need.flag, (uint32_t)need.least, need.asks);
+  if (t.kind == kSolve) {
+    double rows[4][4];
+    load_rows(f, tid, t.i, 64 * t.j, rows);
+    const BlockOfR block(f, tid, 64 * t.j);
+    block.place(ys + 64 * kS, rcp);
+    solve_rows(f, tid, t.i, 64 * t.j, rows, ys, ys + 64 * kS, rcp);
+  } else if (t.kind == kUpdate64) {
+    factor_update<64>(f, tid, t.i, t.j, t.p0, t.np, true, ys);
+  } else if constexpr (!WIDE) {
+#pragma nounroll
+    for (int x = 0; x < 4; ++x)
+      if (t.i + x / 2 <= t.j + x % 2) factor_update<64>(f, tid, t.i + x / 2, t.j + x % 2, t.p0, t.np, true, ys);
+  } else {
+    factor_update<128>(f, tid, t.i, t.j, t.p0, t.np, t.i + (wave >> 1) <= t.j + (wave & 1), ys);
+  }
+  const Done done = done_of(told, t, lane);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  lds_barrier();
+  if (wave == 0 && done.tells) agent_store(f.flags + done.flag, (uint32_t)done.value);
+}
+
+// Where the chain would wait (block k, its tile factored or not yet) and no crew has been seen: 0 if the wait is over, 2 if there is a crew by now; 1 after
+// a task done or looked for, to be asked again.  `away`: its blocks are not in LDS any more.  A task that it does not find is in the hands of a workgroup
+// whose own waits end (see queue_for_chain).
+__device__ __forceinline__ int instead_of_waiting(const Factor& f, FactorLds& lds, int k, bool factored, bool& away) {
+  const int id = thread_id(), nb = f.nb;
+  const Flags told = {nb};
+  const Need need = need_of_chain(told, k, factored);
+  if (id == 0) lds.ticket = agent_load(f.ticket) >= (uint32_t)kFactorCrew ? 2 : agent_load(f.flags + need.flag) < (uint32_t)need.least;
+  __syncthreads();
+  const int found = __builtin_amdgcn_readfirstlane(lds.ticket);
+  __syncthreads();
+  if (found != 1) return found;
+  if (!away) publish(f.flags + (factored ? told.factored(k) : told.solved(k + 1, k)), 1u);  // (what it owes the others)
+  away = true;
+  if (id == 0) {
+    Queue head(1, nb);
+    const uint32_t drawn1 = agent_load(f.ticket + 1), drawn2 = agent_load(f.ticket + 2);
+    const int queue = queue_for_chain(nb, k, (int)drawn1, (int)drawn2, &head);
+    uint32_t drawn = queue == 2 ? drawn2 : drawn1;
+    const bool mine = queue != 0 && __hip_atomic_compare_exchange_strong(f.ticket + queue, &drawn, drawn + 1, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                                         __HIP_MEMORY_SCOPE_AGENT);
+    lds.ticket = mine ? (int)drawn : -1;
+    lds.queue = queue;
+  }
+  __syncthreads();
+  const int ticket = __builtin_amdgcn_readfirstlane(lds.ticket);
+  Queue from(__builtin_amdgcn_readfirstlane(lds.queue), nb);
+  __syncthreads();
+  if (ticket < 0) return 1;
+  from.reach(ticket);
+  const Task t = task_of(from.step, from.queue, ticket - from.base);
+  if (t.kind != kNothing) do_task<false>(f, id, t, lds.ys, lds.rcp);
+  return 1;
+}
+
+// The chain from block k on.  FEW: until a crew has been seen; returns the block to go on with, or -1 after the last.  (Two bodies: the one that nearly
+// all blocks go through waits, and holds no registers for tasks: K = 1024 .. 4096 1 to 2 % slower with one.)
+template <bool FEW>
+__device__ __forceinline__ int chain(const Factor& f, FactorLds& lds, int k) {
+  double* const ys = lds.ys;
   double* const xs = ys + 64 * kS;
-  __shared__ double rcp[64];
-  __shared__ int s_ticket;
+  double* const rcp = lds.rcp;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, q = lane >> 4, nb = f.nb;
+  const Flags told = {nb};
+  bool few = FEW, away = false;
+  int found = 1;
+  for (;; --k) {
+    const int c0 = 64 * k, cols = min(64, f.K - c0);
+    if constexpr (FEW) {
+      if (!few) return k;
+      while ((found = instead_of_waiting(f, lds, k, false, away)) == 1) {}
+      few = found != 2;
+    }
+    await(f.flags + told.applied(k, k), (uint32_t)need_of_chain(told, k, false).least, lane == 0);
+    if constexpr (FEW) {
+      if (away) {  // R D of the row tile that was solved last, and 1 / d of its block
+        const int before = min(64, f.K - c0 - 64);
+        for (int j = wave; j < 64; j += 4) ys[j * kS + lane] = j < before ? agent_load(f.A + (int64_t)(c0 + 64 + j) * f.ld + c0 + lane) : 0.0;
+        if (tid < 64) rcp[tid] = tid < before ? agent_load(f.rcp + c0 + 64 + tid) : 1.0;
+        lds_barrier();
+      }
+      away = false;
+    }
+    // the block's upper triangle, a wave's 16 x 16 tiles u = wave, wave + 4, wave + 8 of ten; channels past K are identity
+    v4d acc[3];
+    int tr[3], tc[3];
+#pragma unroll
+    for (int x = 0; x < 3; ++x) {
+      const int u = min(wave + 4 * x, 9);
+      tc[x] = u >= 6 ? 3 : u >= 3 ? 2 : u >= 1 ? 1 : 0;
+      tr[x] = u - tc[x] * (tc[x] + 1) / 2;
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        acc[x][v] = agent_load(f.A + (int64_t)(c0 + min(16 * tr[x] + 4 * v + q, cols - 1)) * f.ld + c0 + min(16 * tc[x] + l16, cols - 1));
+    }
+    if (k + 1 < nb) {
+      publish(f.flags + told.solved(k + 1, k), 1u);  // (the row tile that the last round solved: its stores went out before these loads)
+      double a[2][3], b[2][3];
+      auto read = [&](int s) {
+        const double rd = -rcp[4 * s + q];
+#pragma unroll
+        for (int x = 0; x < 3; ++x) {
+          b[s & 1][x] = ys[(4 * s + q) * kS + 16 * tc[x] + l16];
+          a[s & 1][x] = ys[(4 * s + q) * kS + 16 * tr[x] + l16] * rd;
+        }
+      };
+      read(0);
+#pragma unroll
+      for (int s = 0; s < 16; ++s) {
+        if (s < 15) read(s + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int x = 0; x < 3; ++x) acc[x] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s & 1][x], b[s & 1][x], acc[x], 0, 0, 0);
+      }
+      lds_barrier();
+    }
+#pragma unroll
+    for (int x = 0; x < 3; ++x)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int i = 16 * tr[x] + 4 * v + q, j = 16 * tc[x] + l16;
+        if (wave + 4 * x < 10) ys[i * kS + j] = i <= j && j < cols ? (double)acc[x][v] : i == j ? 1.0 : 0.0;
+      }
+    lds_barrier();
+    factor_diagonal(ys, xs, rcp);
+    // R transposed below the diagonal
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int j = 4 * e + wave;
+      if (lane < j && j < cols) agent_store(f.A + (int64_t)(c0 + j) * f.ld + c0 + lane, xs[lane * kS + j]);
+    }
+    if (tid < cols) agent_store(f.rcp + c0 + tid, rcp[tid]);
+    if (k == 0) return -1;
+    if constexpr (FEW) {
+      while (few && (found = instead_of_waiting(f, lds, k, true, away)) == 1) {}
+      few = found != 2;
+    }
+    await(f.flags + told.applied(k - 1, k), (uint32_t)need_of_chain(told, k, true).least, lane == 0);
+    if constexpr (FEW) {
+      if (away) {
+        const BlockOfR block(f, tid, c0);
+        block.place(xs, rcp);
+      }
+      away = false;
+    }
+    double rows[4][4];
+    load_rows(f, tid, k - 1, c0, rows);
+    publish(f.flags + told.factored(k), 1u);
+    solve_rows(f, tid, k - 1, c0, rows, ys, xs, rcp);
+  }
+}
+
+__global__ __launch_bounds__(256, 1) void factor_kernel(const Factor f) {
+  __shared__ FactorLds lds;
+  double* const ys = lds.ys;
+  double* const rcp = lds.rcp;
+  const int tid = threadIdx.x, nb = f.nb;
   auto draw = [&](int queue) {
-    if (tid == 0) s_ticket = (int)__hip_atomic_fetch_add(f.ticket + queue, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) lds.ticket = (int)__hip_atomic_fetch_add(f.ticket + queue, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
-    const int t = __builtin_amdgcn_readfirstlane(s_ticket);
+    const int t = __builtin_amdgcn_readfirstlane(lds.ticket);
     __syncthreads();
     return t;
   };
   const int number = draw(0);
-  if (number == 0) {  // ---- the chain
+  if (number == 0) {
     __builtin_amdgcn_s_setprio(3);
-    for (int k = nb - 1; k >= 0; --k) {
-      const int c0 = 64 * k, cols = min(64, f.K - c0);
-      // the block's upper triangle, a wave's 16 x 16 tiles u = wave, wave + 4, wave + 8 of ten; channels past K are identity
-      await(f.applied + (int64_t)k * nb + k, (uint32_t)max(nb - k - 2, 0), lane == 0);
-      v4d acc[3];
-      int tr[3], tc[3];
-#pragma unroll
-      for (int x = 0; x < 3; ++x) {
-        const int u = min(wave + 4 * x, 9);
-        tc[x] = u >= 6 ? 3 : u >= 3 ? 2 : u >= 1 ? 1 : 0;
-        tr[x] = u - tc[x] * (tc[x] + 1) / 2;
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-          acc[x][v] = agent_load(f.A + (int64_t)(c0 + min(16 * tr[x] + 4 * v + q, cols - 1)) * f.ld + c0 + min(16 * tc[x] + l16, cols - 1));
-      }
-      if (k + 1 < nb) {
-        publish(f.solved + (int64_t)(k + 1) * nb + k, 1u);  // (the row tile that the last round solved: its stores went out before these loads)
-        double a[2][3], b[2][3];
-        auto read = [&](int s) {
-          const double rd = -rcp[4 * s + q];
-#pragma unroll
-          for (int x = 0; x < 3; ++x) {
-            b[s & 1][x] = ys[(4 * s + q) * kS + 16 * tc[x] + l16];
-            a[s & 1][x] = ys[(4 * s + q) * kS + 16 * tr[x] + l16] * rd;
-          }
-        };
-        read(0);
-#pragma unroll
-        for (int s = 0; s < 16; ++s) {
-          if (s < 15) read(s + 1);
-          __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int x = 0; x < 3; ++x) acc[x] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s & 1][x], b[s & 1][x], acc[x], 0, 0, 0);
-        }
-        lds_barrier();
-      }
-#pragma unroll
-      for (int x = 0; x < 3; ++x)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int i = 16 * tr[x] + 4 * v + q, j = 16 * tc[x] + l16;
-          if (wave + 4 * x < 10) ys[i * kS + j] = i <= j && j < cols ? (double)acc[x][v] : i == j ? 1.0 : 0.0;
-        }
-      lds_barrier();
-      factor_diagonal(ys, xs, rcp);
-      // R transposed below the diagonal
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int j = 4 * e + wave;
-        if (lane < j && j < cols) agent_store(f.A + (int64_t)(c0 + j) * f.ld + c0 + lane, xs[lane * kS + j]);
-      }
-      if (tid < cols) agent_store(f.rcp + c0 + tid, rcp[tid]);
-      if (k == 0) return;
-      await(f.applied + (int64_t)(k - 1) * nb + k, (uint32_t)(nb - k - 1), lane == 0);
-      double rows[4][4];
-      load_rows(f, k - 1, c0, rows);
-      publish(f.factored + k, 1u);
-      solve_rows(f, k - 1, c0, rows, ys, xs, rcp);
-    }
+    const int k = chain<true>(f, lds, nb - 1);
+    if (k >= 0) chain<false>(f, lds, k);
     return;
   }
 
   // ---- everything else
-  int queue = number % 3 == 1 ? 1 : 2, base = 0;
-  Tasks step(nb, nb - 1);
-  for (int ticket = draw(queue);; ticket = draw(queue)) {
-    auto count = [&]() { return queue == 1 ? step.n_solve + step.n_near + step.n_pair : step.n_next + step.n_far; };
-    while (ticket - base >= count() && step.k > 0) {
-      base += count();
-      step = Tasks(nb, step.k - 1);
-    }
-    if (ticket - base >= count()) {
-      if (queue == 1) return;
-      queue = 1;
-      base = 0;
-      step = Tasks(nb, nb - 1);
+  Queue from(number % 3 == 1 ? 1 : 2, nb);
+  for (;;) {
+    const int ticket = draw(from.queue);
+    if (!from.reach(ticket)) {
+      if (from.queue == 1) return;
+      from = Queue(1, nb);
       continue;
     }
-    const int k = step.k, solve0 = step.n_next + step.n_far, u = ticket - base + (queue == 1 ? solve0 : 0);
-    if (u >= solve0 && u < solve0 + step.n_solve) {
-      const int i = k - 2 - (u - solve0), c0 = 64 * k, cols = min(64, f.K - c0);
-      await(lane == 0 ? f.factored + k : f.applied + (int64_t)i * nb + k, lane == 0 ? 1u : (uint32_t)(nb - k - 1), lane < 2);
-      double rows[4][4];
-      load_rows(f, i, c0, rows);
-      double r[16];
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int j = 4 * e + wave;
-        r[e] = agent_load(f.A + (int64_t)(c0 + min(j, cols - 1)) * f.ld + c0 + lane);
-      }
-      const double rd = agent_load(f.rcp + c0 + min(lane, cols - 1));
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int j = 4 * e + wave;
-        xs[lane * kS + j] = lane < j && j < cols ? r[e] : 0.0;
-      }
-      if (tid < 64) rcp[tid] = tid < cols ? rd : 1.0;
-      lds_barrier();
-      solve_rows(f, i, c0, rows, ys, xs, rcp);
-      publish(f.solved + (int64_t)k * nb + i, 1u);
-    } else if (u >= solve0 || u < step.n_next) {
-      const int near = u - solve0 - step.n_solve, pair = near - step.n_near;
-      Tile64 t;
-      int p0 = step.p0, np = step.np;
-      if (near < 0) {
-        t = tile_from_last(Tasks::triangle(kOuter * step.g), u);
-      } else if (pair < 0) {
-        t = tile_from_last(Tasks::triangle(k), near + 1);  // (the first is the chain's)
-        p0 = k;
-        np = 1;
-      } else {
-        t = tile_from_last(Tasks::triangle(kOuter * step.g), pair);
-        p0 = kOuter * step.g + (k == kOuter * step.g ? 0 : 2);
-        np = min(2, nb - p0);
-        if (k == kOuter * step.g && pair == 0) {  // (the chain takes panel k off the tile that it factors next)
-          ++p0;
-          if (--np == 0) continue;
-        }
-      }
-      // lanes 0 .. 3 and 4 .. 7: the panels' tiles i and j; lane 8: the tile itself
-      const uint32_t* flag = lane < 8 ? f.solved + (int64_t)min(p0 + (lane & 3), nb - 1) * nb + (lane < 4 ? t.i : t.j) : f.applied + (int64_t)t.i * nb + t.j;
-      await(flag, lane < 8 ? 1u : (uint32_t)(nb - p0 - np), lane < 8 ? (lane & 3) < np : lane == 8);
-      factor_update<64>(f, t.i, t.j, p0, np, true, ys);
-      publish(f.applied + (int64_t)t.i * nb + t.j, (uint32_t)(nb - p0));
-    } else {
-      const Tile64 t = tile_from_last(Tasks::triangle(kOuter / 2 * (step.g - 1)), u - step.n_next + step.far0);
-      const int i = 2 * t.i, j = 2 * t.j, p0 = step.p0, np = step.np;
-      // lanes 0 .. 15: row tiles i, i + 1, j, j + 1 of the panels; lanes 16 .. 19: the four tiles themselves, the one below the diagonal left out
-      const int ti = i + ((lane >> 1) & 1), tj = j + (lane & 1), tile = lane >> 2;
-      const bool panel = lane < 16;
-      const uint32_t* flag = panel ? f.solved + (int64_t)min(p0 + (lane & 3), nb - 1) * nb + (tile < 2 ? i : j) + (tile & 1) : f.applied + (int64_t)ti * nb + tj;
-      await(flag, panel ? 1u : (uint32_t)(nb - p0 - np), panel ? (lane & 3) < np : lane < 20 && ti <= tj);
-      factor_update<128>(f, i, j, p0, np, i + (wave >> 1) <= j + (wave & 1), ys);
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      lds_barrier();
-      if (wave == 0 && lane >= 16 && lane < 20 && ti <= tj) agent_store(f.applied + (int64_t)ti * nb + tj, (uint32_t)(nb - p0));
-    }
+    const Task t = task_of(from.step, from.queue, ticket - from.base);
+    if (t.kind != kNothing) do_task<true>(f, tid, t, ys, rcp);
   }
 }
 
@@ -1062,6 +1109,8 @@ __global__ __launch_bounds__(256) void group_finish_kernel(const uint32_t* w_nat
   }
 }
 
+int g_factor_workgroups = 0;  // qqq_set_factor_workgroups
+
 // what both sweeps share: argument checks, the working copies, damping and the factorisation
 struct Work { double *A, *W64, *keep; int ld; };
 int64_t row_stride(int64_t K) { return ((K + 15) & ~(int64_t)15) + 16; }
@@ -1099,12 +1148,10 @@ int begin(const char* who, const void* w_fp16, const double* H, int64_t N, int64
   f.ld = (int)ld;
   f.nb = (int)((K + 63) / 64);
   f.ticket = flags;
-  f.factored = flags + 32;
-  f.applied = f.factored + f.nb;
-  f.solved = f.applied + (size_t)f.nb * f.nb;
+  f.flags = flags + 32;
   // one workgroup of it fits a CU: the chain, and a tile for each of the others
-  const int tiles = f.nb * (f.nb - 1) / 2;
-  hipLaunchKernelGGL(factor_kernel, dim3((unsigned)(1 + min(tiles, num_cus() - 1))), dim3(256), 0, st, f);
+  const int tiles = f.nb * (f.nb - 1) / 2, groups = 1 + min(tiles, num_cus() - 1), most = g_factor_workgroups;
+  hipLaunchKernelGGL(factor_kernel, dim3((unsigned)(most > 0 && most < groups ? most : groups)), dim3(256), 0, st, f);
   if ((rc = check_launch("gptq factorisation")) != QQQ_OK) return rc;
   out->A = A;
   out->W64 = W64;
@@ -1143,6 +1190,12 @@ int sweep(const Work& wk, const void* w_fp16, int64_t N, int64_t K, uint16_t* sc
 using namespace qqq;
 
 extern "C" {
+
+int qqq_set_factor_workgroups(int most) {
+  const int before = g_factor_workgroups;
+  if (most >= 0) g_factor_workgroups = most;
+  return before;
+}
 
 size_t qqq_gptq_workspace_bytes(int64_t N, int64_t K) {
   if (N < 1 || N > 65535 || K < 8 || K % 8 != 0 || K > 16384) return 0;

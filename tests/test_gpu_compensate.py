@@ -345,3 +345,18 @@ def test_compensation_captured_and_replayed():
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(want[i], got)), i
         _compensate(*layers[1 - i])
+
+
+@pytest.mark.parametrize("K,N", [(64, 17), (200, 20), (576, 48), (1032, 33), (1344, 16)])
+@pytest.mark.parametrize("most", [1, 2, 3, 5])
+def test_factorisation_by_a_few_workgroups(K, N, most):
+    """One workgroup does all of it, two and more share it: the same bits."""
+    x, w = layer(2 * K + 10, K, N, 820 + K)
+    d_w, H = dev16(w), torch.from_numpy(cal.hessian(x)).cuda()
+    want = _compensate(d_w, H)
+    before = qqq.set_factor_workgroups(most)
+    try:
+        got = [_compensate(d_w, H) for _ in range(3)]
+    finally:
+        qqq.set_factor_workgroups(before)
+    assert all(torch.equal(a, b) for one in got for a, b in zip(want, one))
