@@ -8,7 +8,9 @@ tensor is not on the GPU the call raises.
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
+import warnings
 
 import torch
 
@@ -32,7 +34,6 @@ SYMBOLS = [
     "qqq_gptq_quantize_w4_pergroup", "qqq_set_factor_workgroups",
 ]
 
-_CALL_PATH = os.path.join(_HERE, "_qqq_call.so")
 _lib = None
 _F16, _I8, _U8, _I32 = torch.float16, torch.int8, torch.uint8, torch.int32
 
@@ -50,12 +51,25 @@ def _no_native(*args):
 _native_linear = _no_native
 
 
-def _native():
-    """The extension that takes the linear calls from tensors to the library (csrc/qqq_torch_call.cpp)."""
+def _call_path():
+    from .build import call_path
+    return call_path()
+
+
+def _load_native(library):
+    """The extension that takes the linear calls from tensors to the library (csrc/qqq_torch_call.cpp).  Without it they are marshalled here."""
     global _native_linear
-    from . import _qqq_call
-    _native_linear = _qqq_call.linear
-    return _qqq_call
+    path = _call_path()
+    try:
+        spec = importlib.util.spec_from_file_location("_qqq_call", path)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+    except ImportError as e:
+        warnings.warn("linear calls are marshalled in Python, a microsecond slower each: build.py has not built %s for this torch and interpreter (%s)"
+                      % (os.path.basename(path), e), RuntimeWarning, stacklevel=3)
+        return
+    module.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (library.qqq_linear_w4a8_perchannel, library.qqq_linear_w4a8_pergroup)))
+    _native_linear = module.linear
 
 
 def lib():
@@ -115,10 +129,7 @@ def lib():
         L.qqq_set_prefill_tuning.argtypes = [ci]
         L.qqq_set_prefill_ksplit.argtypes = [ci]
         L.qqq_set_factor_workgroups.argtypes = [ci]
-        if os.path.exists(_CALL_PATH):
-            _native().bind(*(ctypes.cast(f, vp).value for f in (L.qqq_linear_w4a8_perchannel, L.qqq_linear_w4a8_pergroup)))
-        elif torch.cuda.is_available():
-            raise RuntimeError("_qqq_call.so is not built: build the package first (build.py)")
+        _load_native(L)
         _lib = L
     return _lib
 

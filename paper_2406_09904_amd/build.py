@@ -10,7 +10,6 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libqqq.so")
-CALL = os.path.join(HERE, "_qqq_call.so")  # the linear calls' native marshalling (Python extension)
 SOURCES = ["qqq_api.hip", "qqq_pack.hip", "qqq_quant_act.hip", "qqq_gemm_skinny.hip",
            "qqq_gemm_prefill_dma.hip", "qqq_gemm_prefill_ring.hip", "qqq_group_bias.hip", "qqq_quant_weight.hip", "qqq_probes.hip", "qqq_calib.hip",
            "qqq_hessian.hip", "qqq_compensate.hip"]
@@ -26,14 +25,23 @@ def hipcc() -> str:
     raise RuntimeError("hipcc not found")
 
 
+def call_path() -> str:
+    """The linear calls' native marshalling (a Python extension), by the interpreter and the torch that it is built against: another's is never loaded."""
+    import sysconfig
+
+    import torch
+    return os.path.join(HERE, "_qqq_call.torch-%s.%s.so" % (torch.__version__, sysconfig.get_config_var("SOABI")))
+
+
 def build_call() -> str:
     """Compiles the Python extension against this interpreter and torch; returns its path."""
     import sysconfig
 
     import torch
+    target = call_path()
     base = os.path.join(os.path.dirname(torch.__file__))
     inc = os.path.join(base, "include")
-    tmp = CALL + ".tmp.%d" % os.getpid()
+    tmp = target + ".tmp.%d" % os.getpid()
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", sysconfig.get_paths()["include"], "-isystem", inc,
            "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), os.path.join(CSRC, "qqq_torch_call.cpp"), "-o", tmp,
@@ -41,8 +49,8 @@ def build_call() -> str:
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("g++ failed for qqq_torch_call.cpp:\n" + r.stdout + r.stderr)
-    os.replace(tmp, CALL)
-    return CALL
+    os.replace(tmp, target)
+    return target
 
 
 def build(verbose: bool = False, extra_flags=(), out_dir: str = None) -> str:

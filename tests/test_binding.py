@@ -1,5 +1,6 @@
 """CPU-only checks of the binding itself."""
 import importlib.util
+import os
 
 import pytest
 import torch
@@ -21,3 +22,33 @@ def test_stream_handle_without_torchs_private_names(monkeypatch, missing):
     spec.loader.exec_module(module)
     assert module._stream() == 0x1234
     assert module._raw_stream(module._device()) == 0x1234
+
+
+@pytest.mark.parametrize("kind", ["missing", "damaged", "another module's"])
+def test_library_without_a_fitting_extension(monkeypatch, tmp_path, kind):
+    """Only the linear calls' marshalling is in the extension: without one that can be loaded the library is still whole, on a GPU machine too."""
+    path = tmp_path / "_qqq_call.so"
+    if kind == "damaged":
+        path.write_bytes(b"\x7fELF nothing")
+    elif kind == "another module's":
+        import _struct
+        path.write_bytes(open(_struct.__file__, "rb").read() if getattr(_struct, "__file__", None) else open(binding.LIB_PATH, "rb").read())
+    spec = importlib.util.spec_from_file_location("paper_2406_09904_amd.binding_alone", binding.__file__)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    monkeypatch.setattr(torch.cuda, "is_available", lambda: True)
+    monkeypatch.setattr(module, "_call_path", lambda: str(path))
+    with pytest.warns(RuntimeWarning, match="marshalled in Python"):
+        module.lib()
+    assert module._native_linear is module._no_native
+    assert module.qqq_packed_w4_bytes(4096, 4096) == 4096 * 4096 // 2
+
+
+def test_extension_is_the_present_torchs():
+    """The file's name carries the torch and the interpreter that it was built against."""
+    from paper_2406_09904_amd import build
+    import sysconfig
+    name = os.path.basename(build.call_path())
+    assert torch.__version__ in name and sysconfig.get_config_var("SOABI") in name
+    binding.lib()
+    assert binding._native_linear is not binding._no_native
