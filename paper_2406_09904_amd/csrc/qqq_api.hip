@@ -101,8 +101,9 @@ static size_t split_bytes(int64_t M, int64_t N) {
 //                 last round that costs its own time whatever T:  x <= 1: fixed + per_round x + T (alone (1 - x) + full x);
 //                 x > 1: fixed + per_round x + T rounds x + [f > 0] rest (1 - f).  5 % rms (7 to 9 % in the other form; with the
 //                 rows of longer K the pick was up to 30 % off there, M = 1264, K = 256, N = 50432 62.6 us for 48.9).
-//   trimmed[]     what a launch of shapes 1 to 4 takes of that where their tiles go without their last 32 rows: medians of 50 launches of each shape and
-//                 conversion on new kernel and old (K = 1024 .. 11008, up to 8 tiles of rows), within 0.02 of each; half as much below short_ksteps.
+//   trimmed[]     what a launch of shapes 1 to 4 takes of that where their tiles go without their last 32 rows: fitted to 32000 launches of 2485 shapes on
+//                 kernels with and without (K = 1024 .. 11008, M = 33 .. 2000, also with a K split), 1 to 2 % rms, no bias; half as much below
+//                 short_ksteps.  (Medians of 50 launches each were up to 0.04 lower, and 3 to 9 % were lost where they decided.)
 //   stream_tbs    what the weight stream of a prefill launch reaches at best; where it is what bounds several tiles, the one with the
 //                 least to do beside it is ahead (behind_stream).
 //   prepass_*     the biased route beyond the K that its rows were fitted to: a part per 1000 of K (K = 37760, M = 66, N = 4496 48.8 us
@@ -110,6 +111,9 @@ static size_t split_bytes(int64_t M, int64_t N) {
 //   split_*       the K-split's slabs and its second kernel: a launch, a part per split (they are read one after the other), and a
 //                 part per million raw int32 of the slabs (6 TB/s written and read).
 //   margin_split, min_ksteps_per_split  a split must be 3 % cheaper (modelled), its parts four k-steps long.
+//   margin_trimmed_split  a split 128 x 128 tile without its last 32 rows is modelled 4 % too cheap beside the 64 x 128 tile with its deep ring (scales
+//                 <= 15, M = 148, K = 4352, N = 7376 22.4 us, 20.9 on 64 x 128): on 2000 shapes of M = 65 .. 1500 four picks are 3 % or more slower than
+//                 those of untrimmed kernels with it, none 5 %; without it nine and three.
 //   margin_persistent  per-channel, the persistent kernel and the same tile one by one are as close as the model's error up to
 //                 40 k-steps (K = 5120, M = 2048, N = 13824: 118.8 and 119.0 us): there the persistent one keeps what is within
 //                 3.5 %; from 64 on it is 5 % behind on average.
@@ -224,11 +228,11 @@ static const struct DispatchModel {
           {4, 128, 128, 0.842, 0.843, 0.753, 2.243, 4.8, 2.0},
           {5, 64, 128, 0.727, 0.884, 0.582, 2.031, 3.8, 0.8},
           {kPersistent, 128, 512, 2.503, 1.467, 2.313, 9.922, 7.8, 7.8}}};
-  double trimmed[kCostClasses][4] = {{1.0, 0.868, 0.945, 0.885}, {0.905, 0.868, 0.923, 0.905}, {0.923, 0.912, 0.935, 0.887},
-                                     {0.932, 0.909, 0.955, 0.915}, {0.952, 0.945, 0.947, 0.955}, {1.0, 1.0, 1.0, 1.0}};
+  double trimmed[kCostClasses][4] = {{1.0, 0.887, 0.930, 0.911}, {0.923, 0.905, 0.934, 0.911}, {0.928, 0.920, 0.938, 0.905},
+                                     {0.931, 0.916, 0.949, 0.913}, {0.951, 0.949, 0.942, 0.951}, {1.0, 1.0, 1.0, 1.0}};
   double stream_tbs = 4.6, behind_stream = 0.1;
   double split_us = 2.05, split_part_us = 0.28, split_mint32_us = 1.33;
-  double margin_split = 0.97, margin_persistent = 0.965;
+  double margin_split = 0.97, margin_persistent = 0.965, margin_trimmed_split = 1.04;
   int margin_persistent_ksteps = 40;
   int min_ksteps_per_split = 4, short_ksteps = 8;
   int prepass_k = 11800;
@@ -280,7 +284,8 @@ static PrefillPlan plan_prefill(int64_t M, int64_t N, int64_t K, int cost, bool 
       us += short_k || x > 1.0 ? c.per_round * x : c.per_round;
       if (x <= 1.0) us += t * (c.alone * (1.0 - x) + c.full * x);
       else us += t * c.rounds * x + (f > 0.0 ? (short_k ? 1.0 : t) * c.rest * (1.0 - f) : 0.0);
-      if (c.shape >= 1 && c.shape <= 4 && trimmed_rows(M, c.bm) < c.bm) {
+      const bool trimmed = c.shape >= 1 && c.shape <= 4 && trimmed_rows(M, c.bm) < c.bm;
+      if (trimmed) {
         const double part = kModel.trimmed[cost][c.shape - 1];
         us *= short_k ? 0.5 * (1.0 + part) : part;
       }
@@ -288,6 +293,7 @@ static PrefillPlan plan_prefill(int64_t M, int64_t N, int64_t K, int cost, bool 
       if (ks > 1) us += kModel.split_us + ks * (kModel.split_part_us + kModel.split_mint32_us * 1e-6 * (double)M * (double)N);
       double score = us;
       if (ks > 1) score /= kModel.margin_split;
+      if (ks > 1 && trimmed && c.shape == 4) score *= kModel.margin_trimmed_split;
       if (c.shape == kPersistent && cost == kCostChannel && T <= kModel.margin_persistent_ksteps) score *= kModel.margin_persistent;
       if (best_score == 0.0 || score < best_score) best = {c.shape, ks, us}, best_score = score;
     }

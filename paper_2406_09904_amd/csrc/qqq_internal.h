@@ -90,7 +90,7 @@ void set_prefill_tuning(int tune);
 int get_prefill_tuning();
 int get_prefill_ring_depth();
 int launch_gemm_prefill_dma(const GemmParams& p, int mode, int shape, hipStream_t st);
-int trimmed_rows(int64_t M, int rows);  // rows of a 192- or 256-row tile for M rows
+int trimmed_rows(int64_t M, int rows);  // rows that a tile of 128 (not 128 x 512), 192 or 256 goes with for M rows
 int launch_gemm_prefill_ring(const GemmParams& p, int mode, hipStream_t st);
 int launch_gemm_loss(const GemmParams& p, int points, hipStream_t st);
 int loss_shape(int64_t M, int64_t N, int64_t K, int points);  // tile the cost model picks for launch_gemm_loss

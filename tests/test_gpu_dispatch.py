@@ -122,6 +122,17 @@ def test_automatic_pick_takes_the_192_row_tile(variant):
     assert "tile=192x256" in qqq.last_route(), qqq.last_route()
 
 
+# a tile without its last rows is not taken for more than it gains: 6 to 8 % behind on the 128 x 128 tile with a K split, or with the pre-pass
+@pytest.mark.parametrize("M,K,N,route", [(148, 4352, 7376, "prefill per-tile tile=64x128 waves=4 ring=6"), (75, 3712, 11920, "prefill per-tile tile=64x128 waves=4 ring=6"),
+                                         (156, 9088, 14736, "prefill per-tile tile=192x256 less 32 rows")])
+def test_automatic_pick_beside_tiles_without_their_last_rows(M, K, N, route):
+    a_q, s_a = qqq.qqq_quant_act(torch.ones((M, K), dtype=torch.float16, device="cuda"))
+    w = qqq.qqq_pack_w4(torch.zeros((N, K // 8), dtype=torch.int32, device="cuda"), K)
+    s_g, s_w = torch.ones((K // 128, N), dtype=torch.int8, device="cuda"), torch.ones((N,), dtype=torch.float16, device="cuda")
+    qqq.qqq_gemm_w4a8_pergroup(a_q, s_a, w, s_g, s_w, qqq.new_workspace(M, N, K), sg_max=15)
+    assert qqq.last_route().startswith(route), qqq.last_route()
+
+
 # the ends of the range of K and N: long K on a narrow layer, where the decode kernel slices K (a model that does not know of the
 # slices is up to 5 times off), and a few k-steps on a wide one, where what a tile costs beside its k-steps decides (30 %)
 ENDS = [(30, 58240, 16, "any"), (44, 60288, 64, "pg"), (48, 56704, 32, "pc"), (50, 57216, 48, "real"), (180, 128, 34880, "pc"),
