@@ -54,6 +54,16 @@ def test_grid_points_equal_their_steps(M, K, N, G, route):
     assert torch.equal(got["xs"], xs) and torch.equal(got["ws"], ws) and torch.equal(got["s"], s)
 
 
+@pytest.mark.parametrize("M,K,N,G,route", [
+    (20, 128, 16, 9, "loss tile=64x128 points=9"), (20, 1024, 16, 9, "loss tile=64x128 points=5 + loss tile=64x128 points=4"),
+    (70, 4096, 32, 17, " + loss tile=64x128 points=3 + loss tile=64x128 points=2"), (33, 4224, 16, 12, " + loss tile=64x128 points=3"),
+    (500, 128, 16, 9, "loss tile=64x128 points=5 + loss tile=64x128 points=4"), (20, 128, 32, 16, "loss tile=64x128 points=16"),
+    (20, 128, 32, 17, "loss tile=64x128 points=17")])
+def test_more_points_than_the_smoothed_weights_have_room_for(M, K, N, G, route):
+    """From more than N / 2 points on, smoothing vectors are made batch by batch in the workspace (the sixteen of N = 32 just fit)."""
+    test_grid_points_equal_their_steps(M, K, N, G, route)
+
+
 def _search(x, w, G, xs, ws):
     """The C entry point with the caller's outputs."""
     (M, K), N = x.shape, w.shape[0]
