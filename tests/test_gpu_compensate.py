@@ -360,3 +360,28 @@ def test_factorisation_by_a_few_workgroups(K, N, most):
     finally:
         qqq.set_factor_workgroups(before)
     assert all(torch.equal(a, b) for one in got for a, b in zip(want, one))
+
+
+def test_compensations_that_share_eight_cus():
+    """Four calls at once on streams of the same eight CUs: none has its CUs to itself, each goes on with what it gets."""
+    import ctypes
+
+    K, N = 576, 24
+    x, w = layer(2 * K + 10, K, N, 830)
+    d_w, H = dev16(w), torch.from_numpy(cal.hessian(x)).cuda()
+    want = _compensate(d_w, H)
+    torch.cuda.synchronize()
+    hip = ctypes.CDLL("libamdhip64.so")
+    handles, got, mask = [], [], (ctypes.c_uint32 * 8)(0xFF)
+    for _ in range(4):
+        handles.append(ctypes.c_void_p())
+        assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(handles[-1]), 8, mask) == 0
+    for _ in range(2):
+        for handle in handles:
+            with torch.cuda.stream(torch.cuda.ExternalStream(handle.value)):
+                got.append(_compensate(d_w, H))
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for one in got for a, b in zip(want, one))
+    del got
+    for handle in handles:
+        hip.hipStreamDestroy(handle)
