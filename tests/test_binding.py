@@ -1,6 +1,7 @@
 """CPU-only checks of the binding itself."""
 import importlib.util
 import os
+import struct
 
 import pytest
 import torch
@@ -52,3 +53,14 @@ def test_extension_is_the_present_torchs():
     assert torch.__version__ in name and sysconfig.get_config_var("SOABI") in name
     binding.lib()
     assert binding._native_linear is not binding._no_native
+
+
+def test_extension_has_no_thread_local_variables():
+    """One that nothing reads would slow down every access to torch's and HIP's (glibc 2.35: the thread's table of modules counts as out of date until
+    the newest module's entry is asked for), a microsecond for each of the library's calls."""
+    from paper_2406_09904_amd import build
+    image = open(build.call_path(), "rb").read()
+    at, size, count = struct.unpack_from("<Q", image, 32)[0], *struct.unpack_from("<HH", image, 54)
+    kinds = [struct.unpack_from("<I", image, at + size * i)[0] for i in range(count)]
+    assert image[:5] == b"\x7fELF\x02" and 1 in kinds           # PT_LOAD
+    assert 7 not in kinds                                         # PT_TLS
