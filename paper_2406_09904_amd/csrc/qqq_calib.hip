@@ -612,11 +612,21 @@ int qqq_adaptive_smoothing(const void* x_fp16, const void* w_fp16, int64_t M, in
   if (rc != QQQ_OK) return rc;
   if ((rc = launch_fp16_gemm(x_fp16, w_fp16, M, N, K, y_ref, st)) != QQQ_OK) return rc;
   const int64_t column_blocks = (K / 8 + 255) / 256;
-  auto finish = [&]() {  // (two rounds of workgroups: a thread's rows are requested four at a time)
+  // an input lies in the smoothed weights' place (a layer may be smoothed in place)
+  const auto holds = [&](const void* in, int64_t rows) {
+    const uintptr_t at_in = reinterpret_cast<uintptr_t>(in), at_ws = reinterpret_cast<uintptr_t>(ws_fp16);
+    return at_in < at_ws + (uintptr_t)N * K * 2 && at_ws < at_in + (uintptr_t)rows * K * 2;
+  };
+  auto apply_best = [&](int64_t m, int64_t n) {  // (two rounds of workgroups: a thread's rows are requested four at a time)
     const int64_t rows = 8 * num_cus() / column_blocks;
-    hipLaunchKernelGGL(best_point_kernel, dim3((unsigned)column_blocks, (unsigned)(rows < 1 ? 1 : rows < M + N ? rows : M + N)), dim3(256), 0, st, losses,
-                       grid_points, absmax, sigmas, (const uint4*)x_fp16, (const uint4*)w_fp16, M, N, K / 8, (uint4*)xs_fp16, (uint4*)ws_fp16, s, best);
+    hipLaunchKernelGGL(best_point_kernel, dim3((unsigned)column_blocks, (unsigned)(rows < 1 ? 1 : rows < m + n ? rows : m + n)), dim3(256), 0, st, losses,
+                       grid_points, absmax, sigmas, (const uint4*)x_fp16, (const uint4*)w_fp16, m, n, K / 8, (uint4*)xs_fp16, (uint4*)ws_fp16, s, best);
     return check_launch("best point");
+  };
+  auto finish = [&]() {
+    if (!holds(x_fp16, M)) return apply_best(M, N);
+    const int done = apply_best(M, 0);  // the smoothed weights go where X is read: X first
+    return done != QQQ_OK ? done : apply_best(0, N);
   };
   if (steps_ahead(M, N, K, grid_points, at_once)) {
     // a point at a time through the hot path's own calls, the smoothed layer, its codes and their product in the workspace
@@ -661,12 +671,7 @@ int qqq_adaptive_smoothing(const void* x_fp16, const void* w_fp16, int64_t M, in
   p.y_ref = y_ref;
   p.point_bytes = point_bytes;
   const int kvec = (int)(K / 8);
-  // all points' smoothing vectors at once where the smoothed weights' place, which is written last, holds them and no input lies in it (a layer may be
-  // smoothed in place)
-  const auto holds = [&](const void* in, int64_t rows) {
-    const uintptr_t at_in = reinterpret_cast<uintptr_t>(in), at_ws = reinterpret_cast<uintptr_t>(ws_fp16);
-    return at_in < at_ws + (uintptr_t)N * K * 2 && at_ws < at_in + (uintptr_t)rows * K * 2;
-  };
+  // all points' smoothing vectors at once where the smoothed weights' place, which is written last, holds them and no input
   float* vectors = 2 * grid_points <= N && !holds(w_fp16, N) && !holds(x_fp16, M) ? (float*)ws_fp16 : nullptr;
   if (vectors)
     hipLaunchKernelGGL(smoothing_vector_kernel, dim3((unsigned)((K + 255) / 256), (unsigned)grid_points), dim3(256), 0, st, absmax,

@@ -88,6 +88,20 @@ def test_search_in_place(M, K, N, G):
     assert all(torch.equal(a, b) for a, b in zip(want[:3], got[:3])) and torch.allclose(want[3], got[3], rtol=1e-12, atol=0.0)
 
 
+@pytest.mark.parametrize("M,K,N,G,at", [(20, 256, 64, 9, 0), (2100, 1024, 2064, 9, 1), (300, 512, 320, 5, 37), (40, 6144, 256, 1, 0)])
+def test_search_with_the_smoothed_weights_in_the_activations_place(M, K, N, G, at):
+    """Smoothed weights in the buffer of X, from its row `at` on: X is smoothed before they are written."""
+    buf = torch.empty((max(M, at + N), K), dtype=torch.float16, device="cuda")
+    x, ws = buf[:M], buf[at:at + N]
+    x.copy_(torch.from_numpy(synth.activations_fp16(M, K, 735 + M, "normal", 4 / K, 40.0)))
+    w = torch.from_numpy(synth.weights_fp16(N, K, 736 + M)).cuda()
+    xs, want_xs, want_ws = torch.empty_like(x), torch.empty_like(x), torch.empty_like(w)
+    want = _search(x, w, G, want_xs, want_ws)
+    got = _search(x, w, G, xs, ws)
+    assert torch.equal(xs, want_xs) and torch.equal(ws, want_ws)
+    assert all(torch.equal(a, b) for a, b in zip(want[:3], got[:3])) and torch.allclose(want[3], got[3], rtol=1e-12, atol=0.0)
+
+
 @pytest.mark.parametrize("M,K,N,G,tile", [(20, 256, 144, 8, "64x128"), (87, 128, 2832, 23, "128x128"), (300, 512, 2064, 9, "128x256"),
                                           (500, 2944, 4080, 8, "128x512")])
 def test_overflowing_points_lose(M, K, N, G, tile):
