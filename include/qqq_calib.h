@@ -70,9 +70,10 @@ int qqq_hessian(const void* x_fp16, int64_t M, int64_t K, double* H, void* strea
  * in fp64.  Scale: s_w[n] = fp16_rne(fp32(max_k |W[n,k]|) / 7) from the original weights;
  * code = clamp(rne(fp32(w / s_w)), -7, 7) on the running fp64 weight.
  *   H [K,K] fp64 (read only); w_nat [N,K/8] natural nibble words (for qqq_pack_w4); s_w_fp16 [N].
- *   workspace: qqq_gptq_workspace_bytes(N,K) bytes, contents irrelevant on entry.
+ *   workspace: qqq_gptq_workspace_bytes(N,K) bytes, asked of the library in use (the size is each version's own),
+ *   contents irrelevant on entry.
  * Only the upper triangle of H is read (H is symmetric).
- * Cost: K^3/3 + N K^2 fp64 operations, about 2.2 K / 64 launches.
+ * Cost: K^3/3 + N K^2 fp64 operations, 2 ceil(K / 512) + 3 launches.
  */
 size_t qqq_gptq_workspace_bytes(int64_t N, int64_t K);
 int qqq_gptq_quantize_w4_perchannel(const void* w_fp16, const double* H, int64_t N, int64_t K,
