@@ -287,8 +287,9 @@ __global__ __launch_bounds__(256, 3) void f64_update_kernel(const double* A, int
 // which a task needs only earlier ones and the chain's earlier blocks.  There are two queues, a workgroup in three on the one that the chain waits for (solves,
 // updates by one panel), the others on the updates by four panels at once, whose tasks are long.  Three resident workgroups keep chain and queues going.  Where
 // fewer have come (a launch beside others on streams that share a few CUs, a small partition of the chip) the chain does tasks itself when it would
-// wait, in the same order: so the waits end however few workgroups run, one included, and the results have the same bits.  (That costs the launch that has its
-// CUs 0.4 %: K = N = 4096 3197 -> 3211 us a call, K = 2048, N = 5632 with group scales 1465 -> 1469.)  What a task needs is told by flags: a block
+// wait, in the same order: so the waits end however few workgroups run, one included, and the results have the same bits.  (A launch that has its
+// CUs pays nothing: K = N = 4096 3209 us a call with a chain that only waits, 3198 so; K = 2048, N = 5632 with group scales 1479 and 1474; with the
+// chain's first block always in the body that looks for tasks 3204 and 1478, K = 1024 .. 3072 0.4 to 0.8 % slower than one that only waits.)  What a task needs is told by flags: a block
 // factored, a tile solved, the number of panels that a tile has received.
 // Tiles receive the panels of their own four blocks (kOuter) one by one, those of the next four two at a time, and those of later blocks four at a time, during the
 // steps of the four blocks after them; the columns whose turn to factor comes next first, in 64 x 64 tiles, the others in 128 x 128.
@@ -778,7 +779,18 @@ __global__ __launch_bounds__(256, 1) void factor_kernel(const Factor f) {
   const int number = draw(0);
   if (number == 0) {
     __builtin_amdgcn_s_setprio(3);
-    const int k = chain<true>(f, lds, nb - 1);
+    // Two blocks have no waits in them.  Otherwise a launch that has its CUs has a crew in a microsecond: worth a few looks, since a block in the body that does
+    // tasks costs that body's instructions from memory, then the other's (5 to 7 us).
+    if (tid == 0) {
+      uint32_t come = kFactorCrew;
+      if (nb > 2)
+        for (int i = 0; i < 8 && (come = agent_load(f.ticket)) < (uint32_t)kFactorCrew; ++i) __builtin_amdgcn_s_sleep(1);
+      lds.ticket = come >= (uint32_t)kFactorCrew;
+    }
+    __syncthreads();
+    const bool crew = __builtin_amdgcn_readfirstlane(lds.ticket) != 0;
+    __syncthreads();
+    const int k = crew ? nb - 1 : chain<true>(f, lds, nb - 1);
     if (k >= 0) chain<false>(f, lds, k);
     return;
   }

@@ -41,3 +41,9 @@ def test_a_chain_that_only_waits_needs_three(replay, slots, nb):
     """What the chain's own tasks are for."""
     assert replay(nb, _grid(nb), slots, 0, 1).returncode == 1
     assert replay(nb, _grid(nb), 3, 0, 1).returncode == 0
+
+
+@pytest.mark.parametrize("nb", [1, 2])
+def test_two_blocks_need_nobody(replay, nb):
+    """Why the kernel's chain looks for no crew there."""
+    assert replay(nb, _grid(nb), 1, 0, 1).returncode == 0
