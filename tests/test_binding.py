@@ -27,7 +27,7 @@ def test_stream_handle_without_torchs_private_names(monkeypatch, missing):
 
 @pytest.mark.parametrize("kind", ["missing", "damaged", "another module's"])
 def test_library_without_a_fitting_extension(monkeypatch, tmp_path, kind):
-    """Only the linear calls' marshalling is in the extension: without one that can be loaded the library is still whole, on a GPU machine too."""
+    """Only the linear calls' marshalling is in the extension: without one that can be loaded the library is still whole, beside a GPU too."""
     path = tmp_path / "_qqq_call.so"
     if kind == "damaged":
         path.write_bytes(b"\x7fELF nothing")
